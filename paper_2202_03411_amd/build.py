@@ -20,9 +20,9 @@ HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-Wno-unused-parameter"]
 
-SOURCES_HOST = ["geometry.cpp", "abi.cpp"]
+SOURCES_HOST = ["geometry.cpp", "ewald.cpp", "abi.cpp"]
 SOURCES_HIP = ["kernels.hip", "gauss.hip", "backward.hip", "render.hip", "detector.hip",
-               "noalloc.hip", "sepg.hip", "peaks.hip"]
+               "noalloc.hip", "sepg.hip", "peaks.hip", "ewald.hip", "ewald_adj.hip"]
 
 
 def _run(cmd, verbose):

@@ -63,9 +63,11 @@ void free_device(msft_plan_s* p)
     if (p->device < 0) return;
     DeviceScope ds(p->device);
     void* ptrs[] = {p->q_dev, p->xs_dev, p->ys_dev, p->zs_dev, p->txa, p->ty, p->tz, p->txa2,
-                    p->txT, p->tyT};
+                    p->txT, p->tyT, p->ew_dev, p->ew_tables};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
+    p->ew_dev = nullptr;
+    p->ew_tables = nullptr;
     p->q_dev = p->xs_dev = p->ys_dev = p->zs_dev = nullptr;
     p->txa = p->txa2 = p->txT = p->tyT = nullptr;
     p->ty = p->tz = nullptr;
@@ -81,6 +83,70 @@ hipError_t dev_alloc(T** out, size_t bytes, size_t* total)
         *total += bytes;
     }
     return e;
+}
+
+// Resident tables of a plan in the spherical-coordinate form: the host's tables and
+// those generated from them in one allocation, and the descriptor that points to them.
+msft_status build_ew_tables(msft_plan_s* p)
+{
+    DeviceScope ds(p->device);
+    if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
+    EwHost& h = p->ew;
+    EwDesc& d = h.d;
+    struct Part {
+        const std::vector<double>* src;   // or null: generated, `count` doubles of zeros
+        size_t count, off;
+    };
+    auto of = [](const std::vector<double>& v) { return Part{&v, v.size(), 0}; };
+    auto zeros = [](size_t n) { return Part{nullptr, n, 0}; };
+    Part parts[] = {of(h.rot), of(h.phiz), of(h.phie), of(h.phio), of(h.dcte), of(h.dcto), of(h.tq),
+                    zeros((size_t)d.nhNp * d.nap), zeros((size_t)d.nhNp * d.nap),
+                    zeros((size_t)d.na * d.km * d.nbp), zeros((size_t)d.na * d.nbp * d.kzp),
+                    of(h.ang_a), of(h.ang_b), of(h.phize), of(h.phizo)};
+    size_t bytes = 0, total = 0;
+    for (Part& q : parts) {
+        q.off = bytes;
+        bytes += align256(sizeof(double) * q.count);
+    }
+    hipStream_t s = nullptr;
+    hipError_t e = dev_alloc((uint8_t**)&p->ew_tables, bytes, &total);
+    if (e == hipSuccess) e = dev_alloc(&p->ew_dev, sizeof(EwDesc), &total);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    auto at = [&](int k) { return (double*)((uint8_t*)p->ew_tables + parts[k].off); };
+    for (int k = 0; k < (int)(sizeof(parts) / sizeof(parts[0])) && e == hipSuccess; ++k)
+        e = parts[k].src ? hipMemcpyAsync(at(k), parts[k].src->data(), sizeof(double) * parts[k].count,
+                                          hipMemcpyHostToDevice, s)
+                         : hipMemsetAsync(at(k), 0, sizeof(double) * parts[k].count, s);
+    if (e == hipSuccess) {
+        d.rot = at(0);
+        d.phiz = at(1);
+        d.phie = at(2);
+        d.phio = at(3);
+        d.dcte = at(4);
+        d.dcto = at(5);
+        d.tq = at(6);
+        d.cosN = at(7);
+        d.sinN = at(8);
+        d.cm = at(9);
+        d.cz = at(10);
+        const EwTables t = {at(11), at(12), at(13), at(14), at(7), at(8), at(9), at(10)};
+        e = hipMemcpyAsync(p->ew_dev, &d, sizeof d, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = (hipError_t)launch_ew_tables(h, d, t, s);
+    }
+    if (s) {
+        const hipError_t e2 = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = e2;
+        (void)hipStreamDestroy(s);
+    }
+    if (e != hipSuccess) {
+        free_device(p);
+        return hip_fail(e, "plan tables");
+    }
+    for (auto* v : {&h.rot, &h.phiz, &h.phie, &h.phio, &h.dcte, &h.dcto, &h.tq, &h.ang_a, &h.ang_b,
+                    &h.phize, &h.phizo})
+        std::vector<double>().swap(*v);
+    p->resident_bytes = total;
+    return MSFT_OK;
 }
 
 // Resident tables of a plan on its device: FP64 q and coordinates, then the
@@ -209,6 +275,17 @@ size_t sep_adj_layout(const msft_plan_s* p, size_t* k_off, size_t* r_off)
     return hb + kb + rb;
 }
 
+// Whether a plan is one for the spherical-coordinate form: the flat detector (its rows are
+// curves in one angle), in a precision whose outputs it does not change beyond their
+// rounding (plain BF16's are defined by it), and work enough that five launches beat the
+// direct form's two (32^3 voxels, 64^2 pixels, 1.3e8 terms: 28 us against 68).
+bool ew_applies(const msft_plan_s* p)
+{
+    const msft_geometry& g = p->geo.g;
+    const double terms = (double)p->geo.npix * g.nx * g.ny * g.nz;
+    return !p->qlist && !p->separable && g.precision != MSFT_BF16 && terms >= EW_MIN_TERMS;
+}
+
 msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix, int device,
                       msft_plan_t* out)
 {
@@ -283,6 +360,21 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
         fwd_ws += align256(p->sep.gauss ? p->sep.hg_bytes(p->dims.nzb) : p->sep.h_bytes(p->dims.nzb));
         adj_ws = sep_adj_layout(p, nullptr, nullptr);
     }
+    if (ew_applies(p)) {
+        try {
+            ew_plan(*g, &p->ew);
+        } catch (const std::bad_alloc&) {
+            delete p;
+            return fail(MSFT_ERR_NOMEM, "host tables");
+        }
+        // what the fixed scratch of msft_simulate_noalloc holds in the direct form stays within it
+        if (p->ew.use && fwd_ws <= MSFT_NOALLOC_MAX_BYTES && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES)
+            p->ew.use = false;
+        if (p->ew.use) {
+            fwd_ws = std::max(fwd_ws, align256(p->ew.workspace));
+            adj_ws = align256(p->ew.workspace);
+        }
+    }
     p->fwd_workspace = fwd_ws;
     p->adj_workspace = adj_ws;
     p->workspace_bytes = std::max(fwd_ws, adj_ws);
@@ -299,7 +391,7 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
             delete p;
             return fail(MSFT_ERR_DEVICE, "no such HIP device");
         }
-        st = build_device_tables(p);
+        st = p->ew.use ? build_ew_tables(p) : build_device_tables(p);
         if (st != MSFT_OK) {
             p->device = -1;
             delete p;
@@ -404,11 +496,31 @@ Stage1Args sep_stage1_args(const msft_plan_s* p, const void* workspace)
     return a;
 }
 
+// One target in the spherical-coordinate form.
+EwReq ew_request(const msft_plan_s* p, const float* delta, const float* beta, float* intensity,
+                 float* amplitude, const void* workspace, int64_t p0, int64_t p1)
+{
+    return EwReq{p->ew_dev, delta, beta, intensity, amplitude, (double*)workspace, p0, p1};
+}
+
+EwBatch ew_single(const EwReq& r)
+{
+    EwBatch b;
+    b.req[0] = r;
+    b.n = 1;
+    return b;
+}
+
 // The contraction of a plan after the scan: one launch for the flat detector,
 // the two stages for the separable one.
 int launch_contraction(const msft_plan_s* p, const void* workspace, float* intensity,
                        float* amplitude, void* stream)
 {
+    if (p->ew.use) {
+        const EwDesc* dims = &p->ew.d;
+        return launch_ew_contract(ew_single(ew_request(p, nullptr, nullptr, intensity, amplitude, workspace,
+                                                       0, p->dims.npix)), &dims, stream);
+    }
     const int prec = p->geo.g.precision;
     if (p->separable && p->sep.gauss) return launch_sepg(sepg_args(p, workspace, intensity, amplitude), stream);
     if (p->dims.g3)
@@ -441,6 +553,15 @@ ScanArgs scan_args(const msft_plan_s* p, const float* delta, const float* beta, 
     s.k0dz = (float)(k0 * g.dz);
     s.dV = (float)(g.dx * g.dy * g.dz);
     return s;
+}
+
+// The column scan of one target into its workspace.
+int launch_target_scan(const msft_plan_s* p, const float* delta, const float* beta, void* workspace,
+                       void* stream)
+{
+    if (!p->ew.use) return launch_scan(p->geo.g.precision, scan_args(p, delta, beta, workspace), stream);
+    const EwDesc* dims = &p->ew.d;
+    return launch_ew_scan(ew_single(ew_request(p, delta, beta, nullptr, nullptr, workspace, 0, 0)), &dims, stream);
 }
 
 msft_status check_runnable(const msft_plan_s* p)
@@ -694,8 +815,7 @@ msft_status msft_plan_grid(msft_plan_t plan, double* x, double* y, double* z)
 static msft_status simulate_launch(msft_plan_t plan, const float* delta, const float* beta,
                                    float* intensity, float* amplitude, void* workspace, void* stream)
 {
-    const ScanArgs sa = scan_args(plan, delta, beta, workspace);
-    int e = launch_scan(plan->geo.g.precision, sa, stream);
+    int e = launch_target_scan(plan, delta, beta, workspace, stream);
     if (e) return hip_fail((hipError_t)e, "scan launch");
     e = launch_contraction(plan, workspace, intensity, amplitude, stream);
     if (e) return hip_fail((hipError_t)e, "forward launch");
@@ -749,7 +869,7 @@ msft_status msft_simulate_scan(msft_plan_t plan, const float* delta, const float
     if (st != MSFT_OK) return st;
     DeviceScope ds(plan->device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
-    int e = launch_scan(plan->geo.g.precision, scan_args(plan, delta, beta, workspace), stream);
+    int e = launch_target_scan(plan, delta, beta, workspace, stream);
     if (e) return hip_fail((hipError_t)e, "scan launch");
     return ok();
 }
@@ -783,7 +903,7 @@ static msft_status batch_layout(const msft_request* reqs, int32_t n, std::vector
         if (reqs[r].plan->separable)
             return fail(MSFT_ERR_UNSUPPORTED, "batches take flat-detector plans only");
         if (offs) (*offs)[r] = off;
-        off += align256(reqs[r].plan->dims.wtile_bytes());
+        off += reqs[r].plan->fwd_workspace;
     }
     *total = off;
     return MSFT_OK;
@@ -829,8 +949,26 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
     DeviceScope ds(device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
     uint8_t* ws = (uint8_t*)workspace;
+    // Requests in the spherical-coordinate form: each stage one launch over up to
+    // EW_MAX_REQ requests, which evaluates the pixels of their ranges only.
+    for (int32_t r = 0; r < n;) {
+        EwBatch b;
+        const EwDesc* dims[EW_MAX_REQ];
+        b.n = 0;
+        for (; r < n && b.n < EW_MAX_REQ; ++r) {
+            const msft_request& q = reqs[r];
+            if (!q.plan->ew.use || b1[r] == b0[r]) continue;
+            dims[b.n] = &q.plan->ew.d;
+            b.req[b.n++] = ew_request(q.plan, q.delta, q.beta, q.intensity, q.amplitude, ws + offs[r],
+                                      (int64_t)b0[r] * BLOCK_PIX, (int64_t)b1[r] * BLOCK_PIX);
+        }
+        if (b.n == 0) continue;
+        int e = launch_ew_scan(b, dims, stream);
+        if (!e) e = launch_ew_contract(b, dims, stream);
+        if (e) return hip_fail((hipError_t)e, "batch launch");
+    }
     for (int32_t r = 0; r < n; ++r) {
-        if (b1[r] == b0[r]) continue;
+        if (b1[r] == b0[r] || reqs[r].plan->ew.use) continue;
         const ScanArgs sa = scan_args(reqs[r].plan, reqs[r].delta, reqs[r].beta, ws + offs[r]);
         int e = launch_scan(precision, sa, stream);
         if (e) return hip_fail((hipError_t)e, "scan launch");
@@ -850,7 +988,7 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
         int32_t nr = 0;
         for (size_t k = k0; k < order.size() && k < k0 + MAX_BATCH; ++k) {
             const int32_t r = order[k];
-            if (b1[r] == b0[r]) continue;
+            if (b1[r] == b0[r] || reqs[r].plan->ew.use) continue;
             b.req[nr] = forward_args(reqs[r].plan, ws + offs[r], reqs[r].intensity, reqs[r].amplitude);
             b.block_begin[nr] = b0[r];
             b.item_begin[nr] = items;
@@ -861,7 +999,7 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
         b.item_begin[nr] = items;
         if (items == 0) continue;
         // every plan of one precision is flat here, so all or none use the Gauss tiles
-        int e = reqs[0].plan->dims.g3 ? launch_forward_batch_g3(b, stream)
+        int e = precision == MSFT_FP32 ? launch_forward_batch_g3(b, stream)
                                       : launch_forward_batch(precision, b, stream);
         if (e) return hip_fail((hipError_t)e, "batch launch");
     }
@@ -878,6 +1016,15 @@ msft_status msft_backward(msft_plan_t plan, const float* delta, const float* bet
         return fail(MSFT_ERR_INVALID, "NULL argument");
     st = check_workspace(workspace, ws_bytes, plan->adj_workspace);
     if (st != MSFT_OK) return st;
+    if (plan->ew.use) {
+        DeviceScope ds(plan->device);
+        if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
+        const EwAdj a = {plan->ew_dev, delta, beta, amplitude, grad_intensity, grad_delta, grad_beta,
+                         (double*)workspace};
+        const int e = launch_ew_adjoint(a, plan->ew.d, stream);
+        if (e) return hip_fail((hipError_t)e, "backward launch");
+        return ok();
+    }
     const Dims& d = plan->dims;
     const msft_geometry& g = plan->geo.g;
     const AdjDims ad = make_adj_dims(d);

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "msft_internal.h"
+#include "wave_f64.h"
 
 namespace msft {
 
@@ -305,17 +306,6 @@ __global__ __launch_bounds__(256) void adj_finalize(FinArgs a)
         carry_b += __shfl(sufb, 0, 64);
         carry_d += __shfl(sufd, 0, 64);
     }
-}
-
-// One DPP step on an FP64 value (both 32-bit halves moved by the same lane pattern;
-// lanes outside the row mask, or whose source lies outside their row, read 0).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROW_MASK, 0xF, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROW_MASK, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | (unsigned long long)lo));
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave in FP64, in registers: doubling

@@ -1,0 +1,378 @@
+// Host side of the spherical-coordinate form (ewald.h): the prolate bases of the axes,
+// the number of Chebyshev nodes a detector needs, and the tables made from them.
+#include "ewald.h"
+
+#include <algorithm>
+#include <cmath>
+
+#include "msft_internal.h"
+
+namespace msft {
+
+namespace {
+
+constexpr double kPi = 3.14159265358979323846;
+
+// What the truncated bases and series may leave out, relative to the norm of exp(-i q r)
+// (basis) or to 1 (series).  The sums run in FP64; 3e-11 of the strength's norm is some
+// ten times below the FP32 strength's own rounding in the darkest pixels of a pattern.
+constexpr double EW_TOL = 3e-11;
+
+int pad(int n, int m) { return (n + m - 1) / m * m; }
+
+// Eigenvalues below x of the symmetric tridiagonal matrix (d, e), by the signs of its
+// Sturm sequence.
+int sturm_count(const std::vector<double>& d, const std::vector<double>& e, double x)
+{
+    int c = 0;
+    double q = d[0] - x;
+    for (size_t k = 0;; ++k) {
+        if (q < 0.0) ++c;
+        if (k + 1 == d.size()) break;
+        if (q == 0.0) q = 1e-300;
+        q = d[k + 1] - x - e[k] * e[k] / q;
+    }
+    return c;
+}
+
+// Eigenvector of (d, e) at the eigenvalue lam: inverse iteration with a pivoted LU.
+std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<double>& e, double lam,
+                               double scale)
+{
+    const int n = (int)d.size();
+    std::vector<double> a(n), b(n, 0.0), c(n, 0.0), l(n, 0.0), x(n);
+    std::vector<char> swapped(n, 0);
+    // rows hold (diagonal, first, second superdiagonal) after elimination
+    double p = d[0] - lam, q = n > 1 ? e[0] : 0.0;
+    for (int k = 0; k + 1 < n; ++k) {
+        const double s = e[k], dn = d[k + 1] - lam, un = k + 2 < n ? e[k + 1] : 0.0;
+        if (std::fabs(p) >= std::fabs(s)) {
+            if (p == 0.0) p = 1e-300;
+            a[k] = p;
+            b[k] = q;
+            l[k] = s / p;
+            p = dn - l[k] * q;
+            q = un;
+        } else {
+            swapped[k] = 1;
+            a[k] = s;
+            b[k] = dn;
+            c[k] = un;
+            l[k] = p / s;
+            p = q - l[k] * dn;
+            q = -l[k] * un;
+        }
+    }
+    a[n - 1] = std::fabs(p) > 1e-16 * scale ? p : 1e-16 * scale;
+    for (int k = 0; k < n; ++k) x[k] = 1.0 + 0.37 * std::sin(1.7 * k + 0.3);
+    for (int it = 0; it < 4; ++it) {
+        for (int k = 0; k + 1 < n; ++k) {
+            if (swapped[k]) std::swap(x[k], x[k + 1]);
+            x[k + 1] -= l[k] * x[k];
+        }
+        for (int k = n - 1; k >= 0; --k) {
+            double v = x[k];
+            if (k + 1 < n) v -= b[k] * x[k + 1];
+            if (k + 2 < n) v -= c[k] * x[k + 2];
+            x[k] = v / a[k];
+        }
+        double big = 0.0, s = 0.0;
+        for (double v : x) big = std::max(big, std::fabs(v));
+        for (double& v : x) {
+            v /= big;
+            s += v * v;
+        }
+        s = 1.0 / std::sqrt(s);
+        for (double& v : x) v *= s;
+    }
+    return x;
+}
+
+// The `count` eigenvectors of largest eigenvalue.
+void tri_top(const std::vector<double>& d, const std::vector<double>& e, int count,
+             std::vector<std::vector<double>>* out)
+{
+    const int n = (int)d.size();
+    double lo = d[0], hi = d[0];
+    for (int k = 0; k < n; ++k) {
+        const double r = (k ? std::fabs(e[k - 1]) : 0.0) + (k + 1 < n ? std::fabs(e[k]) : 0.0);
+        lo = std::min(lo, d[k] - r);
+        hi = std::max(hi, d[k] + r);
+    }
+    const double scale = std::max({std::fabs(lo), std::fabs(hi), 1e-300});
+    double top = hi + 1e-14 * scale;
+    for (int k = 0; k < count; ++k) {
+        double a = lo - 1e-14 * scale, b = top;   // eigenvalue n - 1 - k lies in [a, b]
+        for (int it = 0; it < 200 && b - a > 2e-16 * scale; ++it) {
+            const double m = 0.5 * (a + b);
+            if (m <= a || m >= b) break;
+            if (sturm_count(d, e, m) >= n - k) b = m;
+            else a = m;
+        }
+        top = b;
+        out->push_back(tri_vector(d, e, 0.5 * (a + b), scale));
+    }
+}
+
+// Terms after which the Chebyshev series of exp(i k (x sin(w t) + s r cos(w t))) over
+// |t| <= 1 is below EW_TOL, the largest of three shares s of r; 0: more than `most`.
+int series_terms(double kx, double kr, double w, int most)
+{
+    const double c = (kx + kr) * w;
+    const int guess = (int)std::min(c + 14.0 * std::cbrt(c) + 40.0, 4.0e6);
+    if (guess > 3 * most) return 0;
+    const int M = pad(guess, 8) + 64;
+    std::vector<double> cs(4 * M);
+    for (int k = 0; k < 4 * M; ++k) cs[k] = std::cos(kPi * k / (2.0 * M));
+    int worst = 1;
+    std::vector<double> fr(M), fi(M), mag(M);
+    for (double s : {0.0, 0.5, 1.0}) {
+        for (int j = 0; j < M; ++j) {
+            const double t = std::cos((j + 0.5) * kPi / M);
+            const double ph = kx * std::sin(w * t) + s * kr * std::cos(w * t);
+            fr[j] = std::cos(ph);
+            fi[j] = std::sin(ph);
+        }
+        for (int k = 0; k < M; ++k) {
+            double re = 0.0, im = 0.0;
+            int64_t at = k;
+            for (int j = 0; j < M; ++j, at += 2 * k) {
+                const double v = cs[at % (4 * M)];
+                re += fr[j] * v;
+                im += fi[j] * v;
+            }
+            mag[k] = 2.0 / M * std::sqrt(re * re + im * im);
+        }
+        double tail = 0.0;
+        int need = M;
+        while (need > 1 && tail + mag[need - 1] < EW_TOL) tail += mag[--need];
+        worst = std::max(worst, need);
+    }
+    return worst;
+}
+
+}  // namespace
+
+bool ew_basis(int n, double d, double qh, int limit, int* ke, int* ko, std::vector<double>* even,
+              std::vector<double>* odd)
+{
+    const int nh = (n + 1) / 2, m = n / 2;
+    const double W = std::min(qh * d / (2.0 * kPi), 0.5);
+    if (2.0 * n * W > (double)limit) return false;
+    // the tridiagonal matrix that commutes with the band limit of [-W, W] (Slepian 1978)
+    const double cw = std::cos(2.0 * kPi * W);
+    auto diag = [&](int k) { return 0.25 * (n - 1.0 - 2.0 * k) * (n - 1.0 - 2.0 * k) * cw; };
+    auto off = [&](int k) { return 0.5 * k * (double)(n - k); };   // couples k - 1 and k
+    const double share[] = {0.0, 0.25, 0.5, 0.7, 0.85, 0.93, 0.97, 0.99, 1.0};
+    for (int par = 0; par < 2; ++par) {
+        std::vector<double>& out = par ? *odd : *even;
+        int& kept = par ? *ko : *ke;
+        kept = 0;
+        out.clear();
+        // even or odd half of the matrix (an odd n's centre enters the even half with sqrt 2)
+        const int size = (n % 2 && par == 0) ? m + 1 : m;
+        if (size == 0) continue;
+        std::vector<double> td(size), te(std::max(size - 1, 0));
+        for (int k = 0; k < size; ++k) td[k] = diag(k);
+        for (int k = 0; k + 1 < size; ++k) te[k] = off(k + 1);
+        if (n % 2 == 0) td[size - 1] += par ? -off(m) : off(m);
+        else if (par == 0 && size > 1) te[size - 2] *= std::sqrt(2.0);
+        int count = std::min(size, (int)std::ceil(n * W) + 16 + (int)std::log2((double)n));
+        for (;;) {
+            std::vector<std::vector<double>> v;
+            tri_top(td, te, count, &v);
+            for (auto& x : v) {
+                for (int k = 0; k < size; ++k)
+                    if (!(n % 2 && k == m)) x[k] *= std::sqrt(0.5);
+                x.resize(nh, 0.0);
+            }
+            // residual of cos or sin(q r) after the first K modes, over sample momenta
+            std::vector<std::vector<double>> res;
+            for (double s : share) {
+                std::vector<double> r(nh);
+                for (int h = 0; h < nh; ++h) {
+                    const double ph = s * qh * (n - 1.0 - 2.0 * h) * d / 2.0;
+                    r[h] = par ? std::sin(ph) : std::cos(ph);
+                }
+                res.push_back(r);
+            }
+            int K = 0;
+            bool fits = false;
+            for (;; ++K) {
+                double worst = 0.0;
+                for (auto& r : res) {
+                    double s = 0.0;
+                    for (int h = 0; h < nh; ++h) s += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * r[h];
+                    worst = std::max(worst, s);
+                }
+                fits = std::sqrt(worst / n) < EW_TOL;
+                if (fits || K == count) break;
+                for (auto& r : res) {
+                    double c = 0.0;
+                    for (int h = 0; h < nh; ++h) c += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * v[K][h];
+                    for (int h = 0; h < nh; ++h) r[h] -= c * v[K][h];
+                }
+            }
+            if (!fits && count < size) {
+                count = size;   // a wide band: every mode
+                continue;
+            }
+            kept = K;
+            out.assign((size_t)nh * K, 0.0);
+            for (int k = 0; k < K; ++k)
+                for (int h = 0; h < nh; ++h) out[(size_t)h * K + k] = v[k][h];
+            break;
+        }
+    }
+    return *ke + *ko <= limit;
+}
+
+void ew_plan(const msft_geometry& g, EwHost* hp)
+{
+    EwHost& H = *hp;
+    EwDesc& d = H.d;
+    d = EwDesc{};
+    H.use = false;
+    const int N = g.det_n, half = (N + 1) / 2;
+    const double k0 = (2.0 * kPi) / g.wavelength, theta = (g.theta_max_deg * kPi) / 180.0;
+    const double hx = 0.5 * (g.nx - 1) * g.dx, hy = 0.5 * (g.ny - 1) * g.dy, hz = 0.5 * (g.nz - 1) * g.dz;
+    const bool uni = g.flags & MSFT_DETECTOR_UNIFORM_Q;
+    d.uniform = uni;
+    d.det_n = N;
+    d.rows = half;
+    H.k0 = k0;
+    // row and column angles of the pixels at non-negative coordinates (index N - 1 - h)
+    H.tq.assign((size_t)half * half, 0.0);
+    std::vector<double> pos(half);
+    double range;
+    int terms;
+    if (!uni) {
+        const double t = std::tan(theta);
+        for (int h = 0; h < half; ++h) pos[h] = ((double)(N - 1 - 2 * h) * t) / (double)N;
+        range = std::atan(pos[0]);
+        double r = 0.0;
+        for (int h = 0; h < half; ++h) {
+            const double b = std::atan(pos[h]);
+            r = std::max(r, hy * std::sin(b) + hz * std::cos(b));
+            H.ang_b.push_back(b);
+        }
+        terms = range > 0.0 ? series_terms(k0 * hx, k0 * r, range, 2 * EW_MAX_NODES) : 1;
+    } else {
+        const double qm = k0 * std::sin(theta);
+        for (int h = 0; h < half; ++h) pos[h] = ((double)(N - 1 - 2 * h) * qm) / (double)N;
+        range = 0.0;
+        for (int j = 0; j < half; ++j) {
+            H.ang_a.push_back(std::asin(std::min(1.0, pos[j] / k0)));
+            for (int i = 0; i < half; ++i) {
+                const double s = pos[i] * pos[i] + pos[j] * pos[j], kk = k0 * k0;
+                double& t = H.tq[(size_t)j * half + i];
+                t = s < kk ? std::atan2(pos[i], std::sqrt(kk - s)) : std::nan("");
+                if (s < kk) range = std::max(range, t);
+            }
+        }
+        terms = range > 0.0 ? series_terms(k0 * hx, k0 * hz, range, 2 * EW_MAX_NODES) : 1;
+    }
+    if (terms == 0 || (terms + 1) / 2 > EW_MAX_NODES) return;
+    const int n = (terms + 1) / 2;
+    const double scale = range > 0.0 ? 1.0 / range : 0.0;
+    d.n = n;
+    std::vector<double>& node = uni ? H.ang_b : H.ang_a;
+    for (int k = 0; k < n; ++k) node.push_back(range * std::cos((k + 0.5) * kPi / (2.0 * n)));
+    if (!uni)
+        for (int j = 0; j < half; ++j)
+            for (int i = 0; i < half; ++i)
+                H.tq[(size_t)j * half + i] = std::atan(pos[i] * std::cos(H.ang_b[j])) * scale;
+    else
+        for (double& t : H.tq) t *= scale;
+    d.na = (int)H.ang_a.size();
+    d.nb = (int)H.ang_b.size();
+    d.nap = pad(d.na, 16);
+    d.nbp = pad(d.nb, 16);
+    // momentum ranges over all (a, b)
+    double qm = 0.0, zlo = 0.0, zhi = -2.0 * k0;
+    for (double a : H.ang_a)
+        for (double b : H.ang_b) {
+            const double sa = std::sin(0.5 * a), sb = std::sin(0.5 * b);
+            const double qz = -2.0 * k0 * (sa * sa + std::cos(a) * sb * sb);
+            qm = std::max(qm, std::fabs(k0 * std::cos(a) * std::sin(b)));
+            zlo = std::min(zlo, qz);
+            zhi = std::max(zhi, qz);
+        }
+    H.qc = 0.5 * (zlo + zhi);
+    H.pitchN = uni ? g.dy : g.dx;
+    H.pitchM = uni ? g.dx : g.dy;
+    H.pitchZ = g.dz;
+    d.nx = g.nx;
+    d.ny = g.ny;
+    d.nz = g.nz;
+    d.strength = g.strength;
+    d.k0dz64 = k0 * g.dz;
+    d.dV64 = g.dx * g.dy * g.dz;
+    d.k0dz = (float)d.k0dz64;
+    d.dV = (float)d.dV64;
+    d.nN = uni ? g.ny : g.nx;
+    d.nM = uni ? g.nx : g.ny;
+    d.zsN = uni ? 1 : g.ny;
+    d.zsM = uni ? g.ny : 1;
+    d.nhN = (d.nN + 1) / 2;
+    d.nhM = (d.nM + 1) / 2;
+    d.nhNp = pad(d.nhN, 16);
+    d.nhMp = pad(d.nhM, 16);
+    std::vector<double> ze, zo, me, mo;
+    int kze, kzo, ke, ko;
+    if (!ew_basis(g.nz, g.dz, 0.5 * (zhi - zlo), EW_MAX_KZ, &kze, &kzo, &ze, &zo)) return;
+    if (!ew_basis(d.nM, H.pitchM, qm, EW_MAX_KM, &ke, &ko, &me, &mo)) return;
+    d.kze = kze;
+    d.kz = kze + kzo;
+    d.kzp = pad(d.kz, 4);
+    d.kzt = pad(d.kz, 16);
+    d.ld = 2 * d.kzp;
+    d.kep = pad(ke, 4);
+    d.kop = pad(ko, 4);
+    d.km = d.kep + d.kop;
+    d.ket = pad(ke, 16);
+    d.kot = pad(std::max(ko, 1), 16);
+    // tables
+    const int nzp = pad(g.nz, EW_ZC), nhz = (g.nz + 1) / 2;
+    H.rot.assign(2 * (size_t)nzp, 0.0);
+    H.phiz.assign((size_t)nzp * d.kzt, 0.0);
+    for (int z = 0; z < g.nz; ++z) {
+        const double ph = H.qc * (((double)(2 * z + 1 - g.nz) * g.dz) / 2.0);
+        H.rot[2 * z] = std::cos(ph);
+        H.rot[2 * z + 1] = -std::sin(ph);
+        const int h = std::min(z, g.nz - 1 - z);
+        const double sign = 2 * z + 1 >= g.nz ? 1.0 : -1.0;
+        for (int l = 0; l < kze; ++l) H.phiz[(size_t)z * d.kzt + l] = ze[(size_t)h * kze + l];
+        for (int l = 0; l < kzo; ++l) H.phiz[(size_t)z * d.kzt + kze + l] = sign * zo[(size_t)h * kzo + l];
+    }
+    const int nhzp = pad(nhz, 16);
+    H.phize = ze;
+    H.phize.resize((size_t)nhzp * kze, 0.0);
+    H.phizo = zo;
+    H.phizo.resize((size_t)nhzp * std::max(kzo, 1), 0.0);
+    H.phie.assign((size_t)d.nhMp * d.ket, 0.0);
+    H.phio.assign((size_t)d.nhMp * d.kot, 0.0);
+    for (int h = 0; h < d.nhM; ++h) {
+        for (int m = 0; m < ke; ++m) H.phie[(size_t)h * d.ket + m] = me[(size_t)h * ke + m];
+        for (int m = 0; m < ko; ++m) H.phio[(size_t)h * d.kot + m] = mo[(size_t)h * ko + m];
+    }
+    H.dcte.resize((size_t)n * n);
+    H.dcto.resize((size_t)n * n);
+    for (int a = 0; a < n; ++a)
+        for (int k = 0; k < n; ++k) {
+            const double w = (a + 0.5) * kPi / (2.0 * n);
+            H.dcte[(size_t)a * n + k] = (k ? 2.0 : 1.0) / n * std::cos(2.0 * k * w);
+            H.dcto[(size_t)a * n + k] = 2.0 / n * std::cos((2.0 * k + 1.0) * w);
+        }
+    // workspace: Z is kept for a second contraction, so nothing shares its place
+    const int64_t z = (int64_t)g.nx * g.ny * d.ld, y = (int64_t)d.nN * d.km * d.ld;
+    const int64_t gg = (int64_t)d.na * 2 * d.km * d.ld, a = (int64_t)d.rows * n * 8;
+    auto up = [](int64_t v) { return (v + 31) / 32 * 32; };
+    d.offY = up(z);
+    d.offG = d.offY + up(y);
+    d.offA = d.offG + up(gg);
+    H.workspace = (size_t)(d.offA + up(a)) * 8;
+    H.use = true;
+}
+
+}  // namespace msft

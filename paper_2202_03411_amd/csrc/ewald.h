@@ -1,0 +1,135 @@
+// The forward model and its adjoint in spherical coordinates about a detector axis
+// (internal; shared by the host plan code and the gfx950 kernels).
+//
+// Every pixel of either detector looks at a point of the Ewald sphere,
+//   q + k0 zhat = k0 (sin a, cos a sin b, cos a cos b)   along (N, M, z),
+// so q_N depends on a alone.  The flat detector takes N = x, M = y: tan b = v, so a
+// pixel row j is one value of b, and tan a = u cos b.  The uniform-q detector takes
+// N = y, M = x: a pixel row j is one value of a (sin a = q_y / k0).  Either way a row
+// of pixels is a curve in one angle (a or b), and A along it is an entire function of
+// that angle whose Chebyshev series over the detector's range ends, to rounding, after
+// about k0 |r|_max range terms, however many pixels the row has.  So
+//   scan    Z_l(x, y)   = sum_z phi_l(z) exp(-i qc z) w            (modes l of q_z)
+//   modal   Y_ml(N)     = sum_M phi_m(M) Z_l                       (modes m of q_M)
+//   nodes   G_ml(a)     = sum_N {cos, sin}(q_N(a) N) Y_ml          (per value of a)
+//   yz      S(a, b)     = sum_m c_m(q_M) sum_l c_l(q_z) G_ml(a)    (per pair a, b)
+//   eval    A(pixel)    = sum_k T_k(t) [Chebyshev coefficients of S along the row]
+// in FP64 throughout (w itself is the FP32 scan's).  phi are the discrete prolate
+// sequences of each axis's momentum range: the smallest basis that holds exp(-i q r)
+// of every q in the range on the axis's voxel centres.  They are even or odd, as are
+// cos and sin, so the sums run over half an axis of folded values, and the four
+// even/odd parts of S give the four mirror pixels (+-u, +-v) at once.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+#include "msft.h"
+
+namespace msft {
+
+constexpr double EW_MIN_TERMS = 2e7;  // least pixels x voxels
+constexpr int EW_COLS = 16;       // columns (x, y) of one scan workgroup: the MFMA rows
+constexpr int EW_ZC = 64;         // slices of one scan round
+constexpr int EW_MAX_KZ = 256;    // most modes of z: a scan wave keeps them in registers
+constexpr int EW_MAX_KM = 1024;   // most modes of the M axis
+constexpr int EW_MAX_NODES = 512;  // most Chebyshev nodes: a row's values and coefficients fill 64 KB of LDS
+
+// One plan's sizes and resident tables, as the kernels see them (device memory).
+// Modes are ordered even, then odd; counts ending in p are padded (tables hold zeros there).
+struct EwDesc {
+    int32_t nx, ny, nz, strength;
+    float k0dz, dV;
+    double k0dz64, dV64;
+    int32_t uniform;            // N = y and M = x (else N = x, M = y)
+    int32_t nN, nM, nhN, nhM;   // voxels along N and M, and half of them rounded up
+    int32_t zsN, zsM;           // column strides of N and M in Z (columns x * ny + y)
+    int32_t kze, kz, kzp, kzt;  // even z modes, all, padded to 4, padded to 16
+    int32_t kep, kop, km;       // M modes: even and odd padded to 4, their sum
+    int32_t ket, kot;           // row lengths of phi_e, phi_o (padded to 16)
+    int32_t ld;                 // 2 kzp: doubles of one complex mode vector
+    int32_t na, nap, nb, nbp;   // values of a and b, padded to 16
+    int32_t nhNp, nhMp;         // half axes padded to 16
+    int32_t n, rows;            // Chebyshev nodes, pixel rows (half the detector, rounded up)
+    int32_t det_n;
+    const double* rot;          // [nz padded to EW_ZC] (cos, -sin)(qc z)
+    const double* phiz;         // [nz padded to EW_ZC][kzt]
+    const double* phie;         // [nhMp][ket]
+    const double* phio;         // [nhMp][kot]
+    const double* cosN;         // [nhNp][nap]
+    const double* sinN;
+    const double* cm;           // [na][km][nbp]
+    const double* cz;           // [na][nbp][kzp]
+    const double* dcte;         // [n node][n k]: coefficient k of the even series from node values
+    const double* dcto;
+    const double* tq;           // [row][column] Chebyshev argument, NaN beyond the rim
+    int64_t offY, offG, offA;   // workspace offsets in doubles (Z at 0)
+};
+
+// Host side of a plan: the sizes, and what the device tables are made from.
+struct EwHost {
+    bool use = false;
+    EwDesc d;                                   // pointers unset
+    size_t workspace = 0;                       // bytes, forward and adjoint alike
+    double qc = 0.0, k0 = 0.0;
+    double pitchN = 0.0, pitchM = 0.0, pitchZ = 0.0;
+    std::vector<double> ang_a, ang_b;           // the values of a and b
+    std::vector<double> phiz, phie, phio;       // as in EwDesc
+    std::vector<double> phize, phizo;           // half-axis z modes [nhzp][kze], [nhzp][kz - kze]
+    std::vector<double> rot, dcte, dcto, tq;
+};
+
+// Fill h for the geometry (detector plans only); h->use says whether the form applies:
+// its sizes lie within the limits above.
+void ew_plan(const msft_geometry& g, EwHost* h);
+
+// Even and odd orthonormal discrete prolate sequences of an axis of n voxels of pitch d
+// for |q| <= qh, as many as hold cos(q r), sin(q r) on the voxel centres to EW_TOL of
+// their norm; half[h] is the value at voxel n - 1 - h (coordinate >= 0).  limit: give
+// up (false) if more than this many modes are needed.
+bool ew_basis(int n, double d, double qh, int limit, int* ke, int* ko, std::vector<double>* even,
+              std::vector<double>* odd);
+
+// One request of a launch: a plan's descriptor (device memory), its buffers, and the
+// pixels [p0, p1) to write.
+struct EwReq {
+    const EwDesc* d;
+    const float* delta;
+    const float* beta;
+    float* intensity;
+    float* amplitude;
+    double* ws;
+    int64_t p0, p1;
+};
+constexpr int EW_MAX_REQ = 24;
+struct EwBatch {
+    EwReq req[EW_MAX_REQ];
+    int32_t begin[EW_MAX_REQ + 1];   // first workgroup of each request
+    int32_t n;
+};
+
+// Adjoint of one request: h = g conj(A) per pixel in, gradients out.
+struct EwAdj {
+    const EwDesc* d;
+    const float* delta;
+    const float* beta;
+    const float* amplitude;
+    const float* grad_intensity;
+    float* grad_delta;
+    float* grad_beta;
+    double* ws;
+};
+
+// Launchers (ewald.hip, ewald_adj.hip); dims: the host copies of the requests' descriptors.
+// Device tables made on the device: cosN, sinN, cm, cz (the last two zeroed by the caller)
+// from the angles and half-axis modes; dev holds the device pointers of phie, phio.
+struct EwTables {
+    const double *ang_a, *ang_b, *phize, *phizo;
+    double *cosN, *sinN, *cm, *cz;
+};
+int launch_ew_tables(const EwHost& h, const EwDesc& dev, const EwTables& t, void* stream);
+int launch_ew_scan(EwBatch b, const EwDesc* const* dims, void* stream);
+int launch_ew_contract(EwBatch b, const EwDesc* const* dims, void* stream);
+int launch_ew_adjoint(const EwAdj& a, const EwDesc& dims, void* stream);
+
+}  // namespace msft

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "ewald.h"
 #include "msft.h"
 
 namespace msft {
@@ -376,6 +377,9 @@ struct msft_plan_s {
     uint8_t* tyT = nullptr;       // separable detector, adjoint: exp(-i q_y(j) y), rows y
     bool separable = false;
     msft::SepDims sep;
+    msft::EwHost ew;              // the spherical-coordinate form, where ew.use
+    msft::EwDesc* ew_dev = nullptr;
+    void* ew_tables = nullptr;    // the tables it points to
     size_t resident_bytes = 0;
     size_t workspace_bytes = 0;   // max of the two below
     size_t fwd_workspace = 0;     // msft_simulate: W tiles (+ H tiles, separable detector)

@@ -1,0 +1,83 @@
+"""The spherical-coordinate form of the forward model and its adjoint (the path of every
+flat-detector plan with work enough) at the sizes where its kernels change shape, against the
+FP64 oracle.
+
+Tolerance: the sums run in FP64 on bases truncated at 3e-11, so what is left is the FP32
+strength (exp, sincos and three products, at most 8 roundings of 2^-24 per voxel) and the
+FP32 result: 1e-6 of the amplitude's norm; twice that for the intensity, and for the
+gradients, which take T and the FP32 amplitudes.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2202_03411_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+MODES = {"msft": oracle.MSFT, "born": inputs.MODE_BORN, "density": inputs.MODE_DENSITY}
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2202_03411_amd import msft
+    return torch, msft
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(np.ravel(a) - np.ravel(b)) / np.linalg.norm(np.ravel(b)))
+
+
+CASES = [
+    # grid, detector side, pitch, theta, strength: what is at its edge
+    ((64, 64, 64), 71, (5.0, 5.0, 5.0), 60.0, "msft"),      # whole scan round, odd detector
+    ((63, 65, 65), 72, (5.0, 5.0, 5.0), 60.0, "msft"),      # odd axes, one slice past a round
+    ((40, 33, 130), 48, (9.0, 9.0, 9.0), 60.0, "born"),     # modes of z past three tiles
+    ((33, 40, 127), 50, (4.0, 4.0, 1.1), 60.0, "density"),  # unaligned columns, 16 or fewer z modes
+    ((200, 17, 20), 40, (9.0, 2.0, 3.0), 75.0, "msft"),     # many nodes, few modes
+    ((17, 200, 20), 40, (2.0, 9.0, 3.0), 75.0, "msft"),     # few nodes, many modes
+    ((2, 3, 300), 128, (9.0, 9.0, 9.0), 60.0, "msft"),      # short axes, a column of five rounds
+    ((150, 140, 100), 4, (6.0, 6.0, 6.0), 45.0, "msft"),    # fewer pixels than nodes
+    ((24, 22, 26), 300, (1.0, 1.0, 1.0), 5.0, "msft"),      # a narrow range: few modes and nodes
+    ((30, 30, 30), 128, (25.0, 25.0, 24.0), 30.0, "msft"),  # pitch near the sampling limit
+]
+
+
+@pytest.mark.parametrize("detector", ["flat"])
+@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c[0])) + f"_{c[1]}" for c in CASES])
+def test_forward_and_adjoint_match_oracle(env, case, detector):
+    torch, msft = env
+    grid, det, pitch, theta, strength = case
+    print(f"[gpu] {detector} grid={grid} det={det} {strength}", flush=True)
+    rng = np.random.default_rng(inputs.SEED_BASE + det)
+    d = rng.uniform(0.0, 0.05, grid).astype(np.float32)
+    b = rng.uniform(0.0, 0.05, grid).astype(np.float32)
+    g = rng.normal(size=det * det).astype(np.float32)
+    q = oracle.qmap(45.0, theta, det) if detector == "flat" else oracle.qmap_uniform(45.0, theta, det)
+    ok = np.flatnonzero(~np.isnan(q[:, 2]))
+    pix = ok[:: max(1, ok.size // 512)]
+    d64, b64 = d.astype(np.float64), b.astype(np.float64)
+    Ao = oracle.amplitude(q[pix], oracle.strength(MODES[strength], d64, b64, pitch, 45.0), pitch, 1)
+    with msft.Plan(45.0, theta, det, grid, pitch, "fp32", strength, detector=detector) as plan:
+        dt, bt = torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda()
+        I, A = plan.simulate(dt, bt, amplitude=True)
+        gd, gb = torch.full_like(dt, float("nan")), torch.full_like(bt, float("nan"))
+        msft.msft_backward(plan.handle, dt, bt, torch.view_as_real(A).contiguous(),
+                           torch.from_numpy(g).cuda(), gd, gb, plan.workspace())
+        torch.cuda.synchronize()
+        I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
+        gd, gb = (t.cpu().numpy().astype(np.float64).reshape(-1, grid[2]) for t in (gd, gb))
+    rim = np.isnan(q[:, 2])
+    assert np.all(A[rim] == 0.0) and np.all(I[rim] == 0.0)
+    errs = [_rel(A[pix], Ao), _rel(I[pix], np.abs(Ao) ** 2)]
+    cols = np.sort(rng.choice(grid[0] * grid[1], size=min(24, grid[0] * grid[1]), replace=False))
+    od, ob = oracle.backward(MODES[strength], q[ok], g[ok].astype(np.float64), A[ok], d64, b64, pitch,
+                             45.0, cols=cols)
+    errs += [_rel(gd[cols], od), _rel(gb[cols], ob)]
+    print(f"  amplitude {errs[0]:.2e} intensity {errs[1]:.2e} gradients {errs[2]:.2e} {errs[3]:.2e}")
+    assert np.isfinite(gd).all() and np.isfinite(gb).all()
+    assert errs[0] <= TOL and max(errs[1:]) <= 2 * TOL
