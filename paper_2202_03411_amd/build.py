@@ -20,6 +20,10 @@ HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-Wno-unused-parameter"]
 
+# The FP64 matrix kernels keep their accumulators in vector registers: the default form
+# copies them to and from the accumulation registers around every loop.
+HIP_EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("ewald.hip", "ewald_adj.hip")}
+
 SOURCES_HOST = ["geometry.cpp", "ewald.cpp", "abi.cpp"]
 SOURCES_HIP = ["kernels.hip", "gauss.hip", "backward.hip", "render.hip", "detector.hip",
                "noalloc.hip", "sepg.hip", "peaks.hip", "ewald.hip", "ewald_adj.hip"]
@@ -45,7 +49,7 @@ def build(verbose: bool = False) -> str:
         objs.append(obj)
     for src in SOURCES_HIP:
         obj = os.path.join(BUILD, src + ".o")
-        _run([HIPCC, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+        _run([HIPCC, *HIP_FLAGS, *HIP_EXTRA.get(src, []), *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)
     tmp = LIB + ".tmp%d" % os.getpid()
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs,

@@ -102,7 +102,7 @@ msft_status build_ew_tables(msft_plan_s* p)
     Part parts[] = {of(h.rot), of(h.phiz), of(h.phie), of(h.phio), of(h.dcte), of(h.dcto), of(h.tq),
                     zeros((size_t)d.nhNp * d.nap), zeros((size_t)d.nhNp * d.nap),
                     zeros((size_t)d.na * d.km * d.nbp), zeros((size_t)d.na * d.nbp * d.kzp),
-                    of(h.ang_a), of(h.ang_b), of(h.phize), of(h.phizo)};
+                    of(h.ang_a), of(h.ang_b), of(h.phize), of(h.phizo), of(h.wre), of(h.wro)};
     size_t bytes = 0, total = 0;
     for (Part& q : parts) {
         q.off = bytes;
@@ -125,11 +125,15 @@ msft_status build_ew_tables(msft_plan_s* p)
         d.dcte = at(4);
         d.dcto = at(5);
         d.tq = at(6);
+        d.phize = at(13);
+        d.phizo = at(14);
+        d.wre = at(15);
+        d.wro = at(16);
         d.cosN = at(7);
         d.sinN = at(8);
         d.cm = at(9);
         d.cz = at(10);
-        const EwTables t = {at(11), at(12), at(13), at(14), at(7), at(8), at(9), at(10)};
+        const EwTables t = {at(11), at(12), at(7), at(8), at(9), at(10)};
         e = hipMemcpyAsync(p->ew_dev, &d, sizeof d, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = (hipError_t)launch_ew_tables(h, d, t, s);
     }
@@ -142,8 +146,8 @@ msft_status build_ew_tables(msft_plan_s* p)
         free_device(p);
         return hip_fail(e, "plan tables");
     }
-    for (auto* v : {&h.rot, &h.phiz, &h.phie, &h.phio, &h.dcte, &h.dcto, &h.tq, &h.ang_a, &h.ang_b,
-                    &h.phize, &h.phizo})
+    for (auto* v : {&h.rot, &h.phiz, &h.phie, &h.phio, &h.dcte, &h.dcto, &h.wre, &h.wro, &h.tq,
+                    &h.ang_a, &h.ang_b, &h.phize, &h.phizo})
         std::vector<double>().swap(*v);
     p->resident_bytes = total;
     return MSFT_OK;

@@ -240,50 +240,79 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     d.uniform = uni;
     d.det_n = N;
     d.rows = half;
+    d.rowsp = pad(half, 16);
     H.k0 = k0;
-    // row and column angles of the pixels at non-negative coordinates (index N - 1 - h)
+    // the rows' angle, and per pixel the other one, at non-negative coordinates (index N - 1 - h)
     H.tq.assign((size_t)half * half, 0.0);
-    std::vector<double> pos(half);
-    double range;
-    int terms;
-    if (!uni) {
-        const double t = std::tan(theta);
-        for (int h = 0; h < half; ++h) pos[h] = ((double)(N - 1 - 2 * h) * t) / (double)N;
-        range = std::atan(pos[0]);
-        double r = 0.0;
-        for (int h = 0; h < half; ++h) {
-            const double b = std::atan(pos[h]);
-            r = std::max(r, hy * std::sin(b) + hz * std::cos(b));
-            H.ang_b.push_back(b);
+    std::vector<double> pos(half), row(half);
+    double range = 0.0;
+    for (int h = 0; h < half; ++h)
+        pos[h] = ((double)(N - 1 - 2 * h) * (uni ? k0 * std::sin(theta) : std::tan(theta))) / (double)N;
+    for (int j = 0; j < half; ++j) {
+        row[j] = uni ? std::asin(std::min(1.0, pos[j] / k0)) : std::atan(pos[j]);
+        const double cb = std::cos(row[j]), kk = k0 * k0;
+        for (int i = 0; i < half; ++i) {
+            const double s = pos[i] * pos[i] + pos[j] * pos[j];
+            double& t = H.tq[(size_t)j * half + i];
+            if (!uni) t = std::atan(pos[i] * cb);
+            else t = s < kk ? std::atan2(pos[i], std::sqrt(kk - s)) : std::nan("");
+            if (t > range) range = t;
         }
-        terms = range > 0.0 ? series_terms(k0 * hx, k0 * r, range, 2 * EW_MAX_NODES) : 1;
-    } else {
-        const double qm = k0 * std::sin(theta);
-        for (int h = 0; h < half; ++h) pos[h] = ((double)(N - 1 - 2 * h) * qm) / (double)N;
-        range = 0.0;
-        for (int j = 0; j < half; ++j) {
-            H.ang_a.push_back(std::asin(std::min(1.0, pos[j] / k0)));
-            for (int i = 0; i < half; ++i) {
-                const double s = pos[i] * pos[i] + pos[j] * pos[j], kk = k0 * k0;
-                double& t = H.tq[(size_t)j * half + i];
-                t = s < kk ? std::atan2(pos[i], std::sqrt(kk - s)) : std::nan("");
-                if (s < kk) range = std::max(range, t);
-            }
-        }
-        terms = range > 0.0 ? series_terms(k0 * hx, k0 * hz, range, 2 * EW_MAX_NODES) : 1;
     }
-    if (terms == 0 || (terms + 1) / 2 > EW_MAX_NODES) return;
-    const int n = (terms + 1) / 2;
-    const double scale = range > 0.0 ? 1.0 / range : 0.0;
+    const double scale = range > 0.0 ? 1.0 / range : 0.0, rrange = row[0];
+    for (double& t : H.tq) t *= scale;
+    // largest M sin b + z cos b of the box over |b| <= w: what exp(-i q r) holds beside N sin a
+    const double hN = uni ? hy : hx, hM = uni ? hx : hy, wb = uni ? range : rrange;
+    const double top = std::atan2(hM, hz), r = top <= wb ? std::hypot(hM, hz) : hM * std::sin(wb) + hz * std::cos(wb);
+    const int most = 2 * EW_MAX_NODES;
+    const double wa = uni ? rrange : range;
+    const int ta = wa > 0.0 ? series_terms(k0 * hN, k0 * r, wa, most) : 1;
+    const int tb = wb > 0.0 ? series_terms(k0 * hM, k0 * hz, wb, most) : 1;
+    const int n = ((uni ? tb : ta) + 1) / 2;
+    int nr = ((uni ? ta : tb) + 1) / 2;
+    if (ta == 0 || tb == 0 || n > EW_MAX_NODES) return;
+    const bool exact = nr >= half;   // no more rows than nodes: the rows themselves
+    if (exact) nr = half;
+    if (nr > EW_MAX_NODES) return;
     d.n = n;
-    std::vector<double>& node = uni ? H.ang_b : H.ang_a;
-    for (int k = 0; k < n; ++k) node.push_back(range * std::cos((k + 0.5) * kPi / (2.0 * n)));
-    if (!uni)
-        for (int j = 0; j < half; ++j)
-            for (int i = 0; i < half; ++i)
-                H.tq[(size_t)j * half + i] = std::atan(pos[i] * std::cos(H.ang_b[j])) * scale;
-    else
-        for (double& t : H.tq) t *= scale;
+    d.nr = nr;
+    d.nrp = pad(nr, 16);
+    std::vector<double> col(n);
+    std::vector<double> rn(row);
+    for (int k = 0; k < n; ++k) col[k] = range * std::cos((k + 0.5) * kPi / (2.0 * n));
+    if (!exact) {
+        rn.resize(nr);
+        for (int k = 0; k < nr; ++k) rn[k] = rrange * std::cos((k + 0.5) * kPi / (2.0 * nr));
+    }
+    H.ang_a = uni ? rn : col;
+    H.ang_b = uni ? col : rn;
+    // values at the rows from values at the row nodes: Lagrange's polynomials of the 2 nr
+    // Chebyshev points in barycentric form, those of +- a node folded for even and odd parts
+    H.wre.assign((size_t)d.nrp * d.rowsp, 0.0);
+    H.wro.assign((size_t)d.nrp * d.rowsp, 0.0);
+    for (int j = 0; j < half; ++j) {
+        if (exact) {
+            H.wre[(size_t)j * d.rowsp + j] = H.wro[(size_t)j * d.rowsp + j] = 1.0;
+            continue;
+        }
+        const double t = row[j] / rrange;
+        double sum = 0.0;
+        std::vector<double> lp(nr), lm(nr);
+        int hit = -1;
+        for (int k = 0; k < nr; ++k) {
+            const double w = (k + 0.5) * kPi / (2.0 * nr), x = std::cos(w);
+            const double s = (k & 1 ? -1.0 : 1.0) * std::sin(w);
+            if (t == x) hit = k;
+            lp[k] = s / (t - x);
+            lm[k] = -s / (t + x);   // point 2 nr - 1 - k, at -x: the other sign
+            sum += lp[k] + lm[k];
+        }
+        for (int k = 0; k < nr; ++k) {
+            const double p = hit >= 0 ? (double)(k == hit) : lp[k] / sum, m = hit >= 0 ? 0.0 : lm[k] / sum;
+            H.wre[(size_t)k * d.rowsp + j] = p + m;
+            H.wro[(size_t)k * d.rowsp + j] = p - m;
+        }
+    }
     d.na = (int)H.ang_a.size();
     d.nb = (int)H.ang_b.size();
     d.nap = pad(d.na, 16);
@@ -308,8 +337,6 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     d.strength = g.strength;
     d.k0dz64 = k0 * g.dz;
     d.dV64 = g.dx * g.dy * g.dz;
-    d.k0dz = (float)d.k0dz64;
-    d.dV = (float)d.dV64;
     d.nN = uni ? g.ny : g.nx;
     d.nM = uni ? g.nx : g.ny;
     d.zsN = uni ? 1 : g.ny;
@@ -338,40 +365,45 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     H.phiz.assign((size_t)nzp * d.kzt, 0.0);
     for (int z = 0; z < g.nz; ++z) {
         const double ph = H.qc * (((double)(2 * z + 1 - g.nz) * g.dz) / 2.0);
-        H.rot[2 * z] = std::cos(ph);
-        H.rot[2 * z + 1] = -std::sin(ph);
+        H.rot[2 * z] = d.dV64 * std::cos(ph);
+        H.rot[2 * z + 1] = -d.dV64 * std::sin(ph);
         const int h = std::min(z, g.nz - 1 - z);
         const double sign = 2 * z + 1 >= g.nz ? 1.0 : -1.0;
         for (int l = 0; l < kze; ++l) H.phiz[(size_t)z * d.kzt + l] = ze[(size_t)h * kze + l];
         for (int l = 0; l < kzo; ++l) H.phiz[(size_t)z * d.kzt + kze + l] = sign * zo[(size_t)h * kzo + l];
     }
-    const int nhzp = pad(nhz, 16);
-    H.phize = ze;
-    H.phize.resize((size_t)nhzp * kze, 0.0);
-    H.phizo = zo;
-    H.phizo.resize((size_t)nhzp * std::max(kzo, 1), 0.0);
+    d.kzet = pad(kze, 16);
+    d.kzot = pad(std::max(kzo, 1), 16);
+    H.phize.assign((size_t)pad(nhz, 16) * d.kzet, 0.0);
+    H.phizo.assign((size_t)pad(nhz, 16) * d.kzot, 0.0);
+    for (int h = 0; h < nhz; ++h) {
+        for (int l = 0; l < kze; ++l) H.phize[(size_t)h * d.kzet + l] = ze[(size_t)h * kze + l];
+        for (int l = 0; l < kzo; ++l) H.phizo[(size_t)h * d.kzot + l] = zo[(size_t)h * kzo + l];
+    }
     H.phie.assign((size_t)d.nhMp * d.ket, 0.0);
     H.phio.assign((size_t)d.nhMp * d.kot, 0.0);
     for (int h = 0; h < d.nhM; ++h) {
         for (int m = 0; m < ke; ++m) H.phie[(size_t)h * d.ket + m] = me[(size_t)h * ke + m];
         for (int m = 0; m < ko; ++m) H.phio[(size_t)h * d.kot + m] = mo[(size_t)h * ko + m];
     }
-    H.dcte.resize((size_t)n * n);
-    H.dcto.resize((size_t)n * n);
+    const int np = pad(n, 16);
+    H.dcte.assign((size_t)np * np, 0.0);
+    H.dcto.assign((size_t)np * np, 0.0);
     for (int a = 0; a < n; ++a)
         for (int k = 0; k < n; ++k) {
             const double w = (a + 0.5) * kPi / (2.0 * n);
-            H.dcte[(size_t)a * n + k] = (k ? 2.0 : 1.0) / n * std::cos(2.0 * k * w);
-            H.dcto[(size_t)a * n + k] = 2.0 / n * std::cos((2.0 * k + 1.0) * w);
+            H.dcte[(size_t)a * np + k] = (k ? 2.0 : 1.0) / n * std::cos(2.0 * k * w);
+            H.dcto[(size_t)a * np + k] = 2.0 / n * std::cos((2.0 * k + 1.0) * w);
         }
     // workspace: Z is kept for a second contraction, so nothing shares its place
     const int64_t z = (int64_t)g.nx * g.ny * d.ld, y = (int64_t)d.nN * d.km * d.ld;
-    const int64_t gg = (int64_t)d.na * 2 * d.km * d.ld, a = (int64_t)d.rows * n * 8;
+    const int64_t gg = (int64_t)d.na * 2 * d.km * d.ld;
     auto up = [](int64_t v) { return (v + 31) / 32 * 32; };
     d.offY = up(z);
     d.offG = d.offY + up(y);
-    d.offA = d.offG + up(gg);
-    H.workspace = (size_t)(d.offA + up(a)) * 8;
+    d.offS = d.offG + up(gg);
+    d.offC = d.offS + up((int64_t)d.nr * n * 8);
+    H.workspace = (size_t)(d.offC + up((int64_t)d.rows * n * 8)) * 8;
     H.use = true;
 }
 

@@ -5,16 +5,18 @@
 //   q + k0 zhat = k0 (sin a, cos a sin b, cos a cos b)   along (N, M, z),
 // so q_N depends on a alone.  The flat detector takes N = x, M = y: tan b = v, so a
 // pixel row j is one value of b, and tan a = u cos b.  The uniform-q detector takes
-// N = y, M = x: a pixel row j is one value of a (sin a = q_y / k0).  Either way a row
-// of pixels is a curve in one angle (a or b), and A along it is an entire function of
-// that angle whose Chebyshev series over the detector's range ends, to rounding, after
-// about k0 |r|_max range terms, however many pixels the row has.  So
+// N = y, M = x: a pixel row j is one value of a (sin a = q_y / k0).  Either way one
+// angle belongs to the row and the other to the pixel, and A is an entire function of
+// both: its Chebyshev series over the detector's range end, to rounding, after about
+// k0 |r|_max range terms, however many pixels there are.  So
 //   scan    Z_l(x, y)   = sum_z phi_l(z) exp(-i qc z) w            (modes l of q_z)
 //   modal   Y_ml(N)     = sum_M phi_m(M) Z_l                       (modes m of q_M)
-//   nodes   G_ml(a)     = sum_N {cos, sin}(q_N(a) N) Y_ml          (per value of a)
-//   yz      S(a, b)     = sum_m c_m(q_M) sum_l c_l(q_z) G_ml(a)    (per pair a, b)
-//   eval    A(pixel)    = sum_k T_k(t) [Chebyshev coefficients of S along the row]
-// in FP64 throughout (w itself is the FP32 scan's).  phi are the discrete prolate
+//   nodes   G_ml(a)     = sum_N {cos, sin}(q_N(a) N) Y_ml          (per node a)
+//   yz      S(a, b)     = sum_m c_m(q_M) sum_l c_l(q_z) G_ml(a)    (per pair of nodes)
+//   coef    C(row, k)   = S interpolated to the rows' angle, its Chebyshev
+//                         coefficients k in the other
+//   eval    A(pixel)    = sum_k T_k(t) C(row, k)
+// in FP64 throughout, w included.  phi are the discrete prolate
 // sequences of each axis's momentum range: the smallest basis that holds exp(-i q r)
 // of every q in the range on the axis's voxel centres.  They are even or odd, as are
 // cos and sin, so the sums run over half an axis of folded values, and the four
@@ -30,40 +32,52 @@ namespace msft {
 
 constexpr double EW_MIN_TERMS = 2e7;  // least pixels x voxels
 constexpr int EW_COLS = 16;       // columns (x, y) of one scan workgroup: the MFMA rows
-constexpr int EW_ZC = 64;         // slices of one scan round
+constexpr int EW_ZC = 64;         // slices of one scan round: a column's 16 lanes, four each
+// Columns of at most 256 slices are held whole, a workgroup's 256 threads in groups of
+// lanes to a column: 16 columns of 16 lanes up to 128 slices (4 or 8 a lane), 8 columns of
+// 32 lanes beyond (6 or 8 a lane), so that their strengths take at most 35 KB of LDS and
+// four workgroups share a CU.
+constexpr int EW_WHOLE_NZ = 256;
+inline int ew_rounds(int nz) { return nz > EW_WHOLE_NZ ? 0 : (nz + EW_ZC - 1) / EW_ZC; }
+inline int ew_columns(int nz) { return nz > 2 * EW_ZC && nz <= EW_WHOLE_NZ ? 8 : EW_COLS; }
 constexpr int EW_MAX_KZ = 256;    // most modes of z: a scan wave keeps them in registers
 constexpr int EW_MAX_KM = 1024;   // most modes of the M axis
-constexpr int EW_MAX_NODES = 512;  // most Chebyshev nodes: a row's values and coefficients fill 64 KB of LDS
+constexpr int EW_MAX_NODES = 400; // most Chebyshev nodes: 17 doubles each within 64 KB of LDS
 
 // One plan's sizes and resident tables, as the kernels see them (device memory).
 // Modes are ordered even, then odd; counts ending in p are padded (tables hold zeros there).
 struct EwDesc {
     int32_t nx, ny, nz, strength;
-    float k0dz, dV;
     double k0dz64, dV64;
     int32_t uniform;            // N = y and M = x (else N = x, M = y)
     int32_t nN, nM, nhN, nhM;   // voxels along N and M, and half of them rounded up
     int32_t zsN, zsM;           // column strides of N and M in Z (columns x * ny + y)
     int32_t kze, kz, kzp, kzt;  // even z modes, all, padded to 4, padded to 16
+    int32_t kzet, kzot;         // row lengths of phize, phizo (padded to 16)
     int32_t kep, kop, km;       // M modes: even and odd padded to 4, their sum
     int32_t ket, kot;           // row lengths of phi_e, phi_o (padded to 16)
     int32_t ld;                 // 2 kzp: doubles of one complex mode vector
-    int32_t na, nap, nb, nbp;   // values of a and b, padded to 16
+    int32_t na, nap, nb, nbp;   // nodes a and b, padded to 16
     int32_t nhNp, nhMp;         // half axes padded to 16
-    int32_t n, rows;            // Chebyshev nodes, pixel rows (half the detector, rounded up)
+    int32_t n, nr, nrp;         // nodes of the pixels' angle and of the rows' (padded to 16)
+    int32_t rows, rowsp;        // pixel rows: half the detector, rounded up; padded to 16
     int32_t det_n;
-    const double* rot;          // [nz padded to EW_ZC] (cos, -sin)(qc z)
+    const double* rot;          // [nz padded to EW_ZC] dV (cos, -sin)(qc z)
     const double* phiz;         // [nz padded to EW_ZC][kzt]
+    const double* phize;        // even and odd z modes on the half axis, [(nz + 1) / 2 padded to 16]
+    const double* phizo;        // x [kzet], [kzot]
     const double* phie;         // [nhMp][ket]
     const double* phio;         // [nhMp][kot]
     const double* cosN;         // [nhNp][nap]
     const double* sinN;
     const double* cm;           // [na][km][nbp]
     const double* cz;           // [na][nbp][kzp]
-    const double* dcte;         // [n node][n k]: coefficient k of the even series from node values
+    const double* dcte;         // [node][k], both padded to 16: coefficient k of the even series
     const double* dcto;
+    const double* wre;          // [row node][row], padded to nrp x rowsp: interpolation to the rows of
+    const double* wro;          // parts even and odd in the rows' angle
     const double* tq;           // [row][column] Chebyshev argument, NaN beyond the rim
-    int64_t offY, offG, offA;   // workspace offsets in doubles (Z at 0)
+    int64_t offY, offG, offS, offC;   // workspace offsets in doubles (Z at 0)
 };
 
 // Host side of a plan: the sizes, and what the device tables are made from.
@@ -73,10 +87,10 @@ struct EwHost {
     size_t workspace = 0;                       // bytes, forward and adjoint alike
     double qc = 0.0, k0 = 0.0;
     double pitchN = 0.0, pitchM = 0.0, pitchZ = 0.0;
-    std::vector<double> ang_a, ang_b;           // the values of a and b
+    std::vector<double> ang_a, ang_b;           // the nodes a and b
     std::vector<double> phiz, phie, phio;       // as in EwDesc
-    std::vector<double> phize, phizo;           // half-axis z modes [nhzp][kze], [nhzp][kz - kze]
-    std::vector<double> rot, dcte, dcto, tq;
+    std::vector<double> phize, phizo;           // half-axis z modes, as in EwDesc
+    std::vector<double> rot, dcte, dcto, wre, wro, tq;
 };
 
 // Fill h for the geometry (detector plans only); h->use says whether the form applies:
@@ -122,9 +136,9 @@ struct EwAdj {
 
 // Launchers (ewald.hip, ewald_adj.hip); dims: the host copies of the requests' descriptors.
 // Device tables made on the device: cosN, sinN, cm, cz (the last two zeroed by the caller)
-// from the angles and half-axis modes; dev holds the device pointers of phie, phio.
+// from the angles and the half-axis modes dev points to.
 struct EwTables {
-    const double *ang_a, *ang_b, *phize, *phizo;
+    const double *ang_a, *ang_b;
     double *cosN, *sinN, *cm, *cz;
 };
 int launch_ew_tables(const EwHost& h, const EwDesc& dev, const EwTables& t, void* stream);

@@ -9,6 +9,8 @@
 // launches are bound by their own latency and by reading delta and beta once.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ewald.h"
 #include "msft_internal.h"
 #include "wave_f64.h"
@@ -18,7 +20,7 @@ namespace msft {
 namespace {
 
 constexpr int EW_THREADS = 256;
-constexpr int EW_WAVES = EW_THREADS / 64;
+constexpr int EW_LD = EW_COLS + 1;   // doubles of a slice's columns in LDS
 
 // The request a workgroup belongs to and its index within it.
 __device__ __forceinline__ const EwReq& ew_request(const EwBatch& b, int& item)
@@ -30,363 +32,591 @@ __device__ __forceinline__ const EwReq& ew_request(const EwBatch& b, int& item)
 }
 
 // ---------------------------------------------------------------------------
-// Scan: w of 16 columns, EW_ZC slices a round, and Z_l = sum_z phi_l(z) exp(-i qc z) w.
+// Scan: w of 16 columns and Z_l = sum_z phi_l(z) exp(-i qc z) w.
 //
-// Thread (column tid / 16, slices 4 (tid % 16) ..) holds four slices: the 16 lanes of a
-// column read 256 contiguous bytes of delta and beta.  The exclusive prefix
+// The 16 lanes of a column hold K consecutive slices each.  The exclusive prefix
 // S = sum_{s'<s} (beta + i delta) is the carry of earlier rounds plus a DPP prefix over
-// the column's 16 lanes, in FP64; T = exp(-k0 dz S) in FP32 with the phase reduced in
-// FP64.  The rotated w goes to LDS (a row of 16 columns per slice, padded to 17 doubles)
-// and from there into the matrix instruction: rows are columns, K the slices, columns
-// the modes.  Wave w takes Re (w even) or Im of mode tiles w / 2, w / 2 + 2, ...  The
-// next round's voxels are loaded before this round's products.
+// the column's lanes; T = exp(-k0 dz S) is evaluated in full at a lane's first slice and
+// by the slices' own factors after it.  dV times the rotated w goes to LDS (a row of
+// columns per slice) and from there into the matrix instruction: rows are columns, K the
+// slices, columns the modes.  FP64 vector work and the FP64 matrix instruction add up
+// here (91 vector instructions a voxel took 16 us and the products 12 of 36 at 192^3), so
+// both are kept small: more slices a lane share a prefix and a full T, and where a
+// workgroup holds whole columns (R rounds of 64 slices) the products take the sums and
+// differences of mirror slices against the half-axis modes, half as many.
 // ---------------------------------------------------------------------------
-struct Voxels {
-    float d[4], b[4];
-};
 
-__device__ __forceinline__ Voxels ew_load(const float* dc, const float* bc, int z, int nz, bool in)
+// dV w exp(-i qc z) of a lane's K slices into LDS (a slice's row is EW_LD doubles), (Sb, Sd)
+// the sums before the first.
+template <int STRENGTH, int K>
+__device__ __forceinline__ void ew_strength(const float* d, const float* b, double Sb, double Sd, double k0dz,
+                                            gcdouble rot, double* re, double* im)
 {
-    Voxels v;
-    if (in && z + 3 < nz && (nz & 3) == 0) {
-        const float4 d = *(const float4*)(dc + z), b = *(const float4*)(bc + z);
-        v.d[0] = d.x; v.d[1] = d.y; v.d[2] = d.z; v.d[3] = d.w;
-        v.b[0] = b.x; v.b[1] = b.y; v.b[2] = b.z; v.b[3] = b.w;
-        return v;
-    }
+    Transmission T;
+    if (STRENGTH == MSFT_STRENGTH_MSFT) T.start<K>(Sb, Sd, b, d, k0dz);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const bool ok = in && z + k < nz;
-        v.d[k] = ok ? dc[z + k] : 0.0f;
-        v.b[k] = ok ? bc[z + k] : 0.0f;
+    for (int k = 0; k < K; ++k) {
+        const double dk = d[k], bk = b[k];
+        double wr = dk, wi = bk;
+        if (STRENGTH != MSFT_STRENGTH_DENSITY) {
+            const double chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * (1.0 - dk);
+            wr = STRENGTH == MSFT_STRENGTH_MSFT ? chr * T.tr - chi * T.ti : chr;
+            wi = STRENGTH == MSFT_STRENGTH_MSFT ? chr * T.ti + chi * T.tr : chi;
+        }
+        const double ex = rot[2 * k], ey = rot[2 * k + 1];
+        re[k * EW_LD] = wr * ex - wi * ey;
+        im[k * EW_LD] = wr * ey + wi * ex;
+        if (STRENGTH == MSFT_STRENGTH_MSFT && k + 1 < K) T.next(bk, dk);
     }
-    return v;
 }
 
-constexpr int EW_LD = EW_COLS + 1;
-
-template <int NT>
-__global__ __launch_bounds__(EW_THREADS) void ew_scan_kernel(EwBatch batch)
+// Whole columns: COLS of them, 256 / COLS lanes of K slices each.  The products' rows are
+// 16 columns, Re and Im apart (COLS = 16: a wave takes one of them and one parity of the
+// modes), or 8 columns' (Re, Im) (COLS = 8: a wave takes one parity and half of the slices).
+template <int STRENGTH, int COLS, int K>
+__device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* sm)
 {
-    __shared__ double sm[2][EW_ZC * EW_LD];
+    constexpr int L = EW_THREADS / COLS, NZ = L * K;
+    const EwDesc& D = *q.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
+    const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)item * COLS;
+    const bool in = c0 + cl < ncol;
+    const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
+    float d[K], b[K];
+    load_slices<K>(q.delta + off, q.beta + off, z0, nz, in, d, b);
+    double Sb = 0.0, Sd = 0.0;
+    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+        double sb = 0.0, sd = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            sb += (double)b[k];
+            sd += (double)d[k];
+        }
+        Sb = group_prefix_f64<L>(sb) - sb;
+        Sd = group_prefix_f64<L>(sd) - sd;
+    }
+    double* o = sm + z0 * EW_LD + (COLS == 16 ? cl : 2 * cl);
+    ew_strength<STRENGTH, K>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * z0, o, o + (COLS == 16 ? NZ * EW_LD : 1));
+    __syncthreads();
+    const int odd = wave & 1, sub = wave >> 1, kze = D.kze, kz = odd ? D.kz - kze : kze, kzt = odd ? D.kzot : D.kzet;
+    const int full = nz >> 3, nh = (nz + 1) >> 1;   // whole steps of four mirror pairs; half the column
+    // steps of this wave: all of them, or every other one
+    const int first = COLS == 16 ? 0 : sub, stride = COLS == 16 ? 1 : 2, steps = (full - first + stride - 1) / stride;
+    const bool tail = 4 * full < nh && (COLS == 16 || sub == (full & 1));
+    const gcdouble phi = as_global(odd ? D.phizo : D.phize);
+    const double* a = sm + (COLS == 16 ? sub * NZ * EW_LD : 0) + li;
+    const double mirror = odd ? -1.0 : 1.0;
+    const uint32_t po = 8 * (lk * kzt + li);
+    gdouble out = as_global(q.ws) + c0 * D.ld;
+    // up to three tiles of 16 modes share the operand; both parities make the same passes, one
+    // past its last tile repeats the first and stores nothing
+    for (int t0 = 0; t0 < max(kze, D.kz - kze); t0 += 48) {
+        const int at = t0 < kzt ? t0 : 0, n1 = t0 + 16 < kzt ? 16 : 0, n2 = t0 + 32 < kzt ? 32 : 0;
+        f64x4 t[3] = {F64X4_ZERO, F64X4_ZERO, F64X4_ZERO};
+        const gcdouble p = phi + at + 4 * first * kzt;
+        const int64_t inc = (int64_t)4 * stride * kzt;
+        auto operand = [&](int ks) {
+            const int h = 4 * (first + stride * ks) + lk;
+            return a[(nz - 1 - h) * EW_LD] + mirror * a[h * EW_LD];
+        };
+        if (n2) {
+            const Stream s[3] = {{p, inc, po}, {p + n1, inc, po}, {p + n2, inc, po}};
+            staged<4>(s, steps, [&](int ks, const double* x) {
+                const double v = operand(ks);
+                t[0] = mfma_f64(v, x[0], t[0]);
+                t[1] = mfma_f64(v, x[1], t[1]);
+                t[2] = mfma_f64(v, x[2], t[2]);
+            });
+        } else if (n1) {
+            const Stream s[2] = {{p, inc, po}, {p + n1, inc, po}};
+            staged<4>(s, steps, [&](int ks, const double* x) {
+                const double v = operand(ks);
+                t[0] = mfma_f64(v, x[0], t[0]);
+                t[1] = mfma_f64(v, x[1], t[1]);
+            });
+        } else {
+            const Stream s[1] = {{p, inc, po}};
+            staged<8>(s, steps, [&](int ks, const double* x) { t[0] = mfma_f64(operand(ks), x[0], t[0]); });
+        }
+        if (tail) {   // the last pairs and an odd column's middle; phi is zero past it
+            const int h = min(4 * full + lk, nh - 1), m = nz - 1 - h;
+            const double v = a[m * EW_LD] + (m == h ? 0.0 : mirror * a[h * EW_LD]);
+            const gcdouble pt = phi + 4 * full * kzt + at;
+            t[0] = mfma_f64(v, load_at(pt, po), t[0]);
+            if (n1) t[1] = mfma_f64(v, load_at(pt + n1, po), t[1]);
+            if (n2) t[2] = mfma_f64(v, load_at(pt + n2, po), t[2]);
+        }
+        if (COLS == 8) {   // the halves' sums, in the first half's wave
+            double* red = sm + NZ * EW_LD + odd * (3 * 4 * 64);
+            if (t0) __syncthreads();
+            if (sub)
+#pragma unroll
+                for (int k = 0; k < 12; ++k) red[k * 64 + lane] = t[k >> 2][k & 3];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 12; ++k) t[k >> 2][k & 3] += sub ? 0.0 : red[k * 64 + lane];
+        }
+        if (COLS == 8 && sub) continue;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int l = t0 + 16 * k + li;
+            if (l < kz)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 4 * r + lk, col = COLS == 16 ? row : row >> 1, ri = COLS == 16 ? sub : row & 1;
+                    // odd modes carry -i: (re, im) -> (im, -re)
+                    if (c0 + col < ncol)
+                        out[col * D.ld + 2 * (odd ? kze + l : l) + (odd ? 1 - ri : ri)] =
+                            odd && ri == 0 ? -t[k][r] : t[k][r];
+                }
+        }
+    }
+    // the padding of the mode vectors, zero
+    const int pad = 2 * (D.kzp - D.kz);
+    if (tid % L < pad && in) out[cl * D.ld + 2 * D.kz + tid % L] = 0.0;
+}
+
+template <int COLS, int K>
+__global__ __launch_bounds__(EW_THREADS, COLS == 8 && K == 8 ? 3 : 4) void ew_scan_kernel(EwBatch batch)
+{
+    // COLS = 16: Re and Im; 8: (Re, Im) rows, then the halves' sums of three tiles a parity
+    __shared__ double sm[COLS == 16 ? 2 * 16 * K * EW_LD : 32 * K * EW_LD + 2 * 3 * 4 * 64];
     int item;
     const EwReq& q = ew_request(batch, item);
+    const int strength = q.d->strength;
+    if (strength == MSFT_STRENGTH_MSFT) ew_scan_whole<MSFT_STRENGTH_MSFT, COLS, K>(q, item, sm);
+    else if (strength == MSFT_STRENGTH_BORN) ew_scan_whole<MSFT_STRENGTH_BORN, COLS, K>(q, item, sm);
+    else ew_scan_whole<MSFT_STRENGTH_DENSITY, COLS, K>(q, item, sm);
+}
+
+// Longer columns, in rounds of 64 slices against the full-axis modes.  Wave w takes Re (w
+// even) or Im of mode tiles w / 2, w / 2 + 2, ...
+template <int STRENGTH, int NT>
+__device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double* sm)
+{
     const EwDesc& D = *q.d;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, kzt = D.kzt;
     const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)item * EW_COLS;
     const bool in = c0 + cl < ncol;
-    const int64_t col = in ? c0 + cl : ncol - 1;
-    const float* dc = q.delta + col * nz;
-    const float* bc = q.beta + col * nz;
-    const int ri = wave & 1, t0 = wave >> 1, kzt = D.kzt, strength = D.strength;
+    const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
+    const int ri = wave & 1, t0 = wave >> 1;
+    const gcdouble phi = as_global(D.phiz) + t0 * 16;
+    const uint32_t po = 8 * (lk * kzt + li);
     f64x4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < NT; ++t) acc[t] = F64X4_ZERO;
     double carry_b = 0.0, carry_d = 0.0;
-    Voxels v = ew_load(dc, bc, zl, nz, in);
+    float d[4], b[4];
     for (int z0 = 0; z0 < nz; z0 += EW_ZC) {
+        load_slices<4>(q.delta + off, q.beta + off, z0 + zl, nz, in, d, b);
         double Sb = 0.0, Sd = 0.0;
-        if (strength == MSFT_STRENGTH_MSFT) {
-            const double sb = ((double)v.b[0] + v.b[1]) + ((double)v.b[2] + v.b[3]);
-            const double sd = ((double)v.d[0] + v.d[1]) + ((double)v.d[2] + v.d[3]);
+        if (STRENGTH == MSFT_STRENGTH_MSFT) {
+            const double sb = ((double)b[0] + b[1]) + ((double)b[2] + b[3]);
+            const double sd = ((double)d[0] + d[1]) + ((double)d[2] + d[3]);
             const double ib = row_prefix_f64(sb), id = row_prefix_f64(sd);
             Sb = carry_b + (ib - sb);
             Sd = carry_d + (id - sd);
             carry_b += row_last_f64(ib);
             carry_d += row_last_f64(id);
         }
-        const double2* rot = (const double2*)D.rot + z0 + zl;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float d = v.d[k], b = v.b[k];
-            float wr = d, wi = b;
-            if (strength != MSFT_STRENGTH_DENSITY) {
-                const float chr = d * (d - 2.0f) - b * b, chi = 2.0f * b * (1.0f - d);
-                wr = chr;
-                wi = chi;
-                if (strength == MSFT_STRENGTH_MSFT) {
-                    constexpr double kTwoPi = 6.283185307179586476925286766559;
-                    const double ph = -D.k0dz64 * Sd;
-                    const float mag = expf((float)(-D.k0dz64 * Sb));
-                    float sn, cs;
-                    sincosf((float)(ph - kTwoPi * rint(ph * (1.0 / kTwoPi))), &sn, &cs);
-                    const float tr = mag * cs, ti = mag * sn;
-                    wr = chr * tr - chi * ti;
-                    wi = chr * ti + chi * tr;
-                    Sb += (double)b;
-                    Sd += (double)d;
-                }
-            }
-            wr *= D.dV;
-            wi *= D.dV;
-            const double2 e = rot[k];
-            sm[0][(zl + k) * EW_LD + cl] = (double)wr * e.x - (double)wi * e.y;
-            sm[1][(zl + k) * EW_LD + cl] = (double)wr * e.y + (double)wi * e.x;
-        }
+        double* o = sm + zl * EW_LD + cl;
+        ew_strength<STRENGTH, 4>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * (z0 + zl), o, o + EW_ZC * EW_LD);
         __syncthreads();
-        if (z0 + EW_ZC < nz) v = ew_load(dc, bc, z0 + EW_ZC + zl, nz, in);
-        const double* a = sm[ri] + (lane >> 4) * EW_LD + (lane & 15);
-        const double* p = D.phiz + (size_t)(z0 + (lane >> 4)) * kzt + t0 * 16 + (lane & 15);
-#pragma unroll 4
-        for (int kk = 0; kk < EW_ZC / 4; ++kk) {
-            const double av = a[4 * kk * EW_LD];
+        const double* a = sm + ri * EW_ZC * EW_LD + lk * EW_LD + li;
+        for_steps<4>(EW_ZC / 4, [&](int ks) {
+            const double v = a[4 * ks * EW_LD];
+            const gcdouble p = phi + (int64_t)(z0 + 4 * ks) * kzt;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                if ((t0 + 2 * t) * 16 < kzt) acc[t] = mfma_f64(av, p[(size_t)4 * kk * kzt + 32 * t], acc[t]);
-        }
+            for (int t = 0; t < NT; ++t)   // a wave past the last tile repeats the first and stores nothing
+                acc[t] = mfma_f64(v, load_at(p + ((t0 + 2 * t) * 16 < kzt ? 32 * t : -16 * t0), po), acc[t]);
+        });
         __syncthreads();
     }
-    // odd modes carry -i: (re, im) -> (im, -re)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int l = (t0 + 2 * t) * 16 + (lane & 15);
+        const int l = (t0 + 2 * t) * 16 + li;
         if (l >= D.kzp) continue;
-        const bool odd = l >= D.kze;
+        const bool odd = l >= D.kze;   // -i: (re, im) -> (im, -re)
         const int comp = odd ? 1 - ri : ri;
         const double sign = odd && ri == 0 ? -1.0 : 1.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int64_t c = c0 + 4 * r + (lane >> 4);
-            if (c < ncol) q.ws[c * D.ld + 2 * l + comp] = sign * acc[t][r];
+            const int64_t col = c0 + 4 * r + lk;
+            if (col < ncol) q.ws[col * D.ld + 2 * l + comp] = sign * acc[t][r];
         }
+    }
+}
+
+__global__ __launch_bounds__(EW_THREADS) void ew_scan_rounds_kernel(EwBatch batch)
+{
+    constexpr int NT = EW_MAX_KZ / 32;
+    __shared__ double sm[2 * EW_ZC * EW_LD];
+    int item;
+    const EwReq& q = ew_request(batch, item);
+    const int strength = q.d->strength;
+    if (strength == MSFT_STRENGTH_MSFT) ew_scan_rounds<MSFT_STRENGTH_MSFT, NT>(q, item, sm);
+    else if (strength == MSFT_STRENGTH_BORN) ew_scan_rounds<MSFT_STRENGTH_BORN, NT>(q, item, sm);
+    else ew_scan_rounds<MSFT_STRENGTH_DENSITY, NT>(q, item, sm);
+}
+
+// ---------------------------------------------------------------------------
+// Sums over half an axis: t[0], t[1] += te (v[hi] + v[lo]), t[2], t[3] += to (v[hi] - v[lo])
+// for voxels hi = n - 1 - h, lo = h, rows of `stride` doubles at v, the lane's column at
+// byte 8 cc; te, to tables of `ldE`, `ldO` doubles a row, two tiles each.  The waves of
+// the workgroup take every fourth step of four pairs; the last step (its pairs, an odd
+// axis's middle voxel; the tables are zero past it) is one wave's.  The addresses of
+// whole steps are scalar.
+// ---------------------------------------------------------------------------
+struct HalfAxis {
+    gcdouble v, e0, e1, o0, o1;
+    int64_t stride;
+    int n, ldE, ldO, cc;
+};
+
+__device__ __forceinline__ void half_axis_sums(const HalfAxis& x, int wave, int li, int lk, f64x4* t)
+{
+    const int full = x.n >> 3, nh = (x.n + 1) >> 1, h0 = 4 * wave;
+    const uint32_t pe = 8 * (lk * x.ldE + li), po = 8 * (lk * x.ldO + li);
+    const int64_t v16 = 16 * x.stride, e16 = 16 * x.ldE, o16 = 16 * x.ldO;
+    const Stream s[6] = {{x.v + (x.n - 4 - h0) * x.stride, -v16, 8 * (uint32_t)((3 - lk) * x.stride + x.cc)},
+                         {x.v + h0 * x.stride, v16, 8 * (uint32_t)(lk * x.stride + x.cc)},
+                         {x.e0 + h0 * x.ldE, e16, pe},
+                         {x.e1 + h0 * x.ldE, e16, pe},
+                         {x.o0 + h0 * x.ldO, o16, po},
+                         {x.o1 + h0 * x.ldO, o16, po}};
+    staged<4>(s, (full - wave + 3) >> 2, [&](int, const double* y) {
+        const double sum = y[0] + y[1], diff = y[0] - y[1];
+        t[0] = mfma_f64(y[2], sum, t[0]);
+        t[1] = mfma_f64(y[3], sum, t[1]);
+        t[2] = mfma_f64(y[4], diff, t[2]);
+        t[3] = mfma_f64(y[5], diff, t[3]);
+    });
+    if (4 * full < nh && wave == (full & 3)) {
+        const int h = min(4 * full + lk, nh - 1), hi = x.n - 1 - h;
+        const double vh = x.v[hi * x.stride + x.cc], vl = hi == h ? 0.0 : x.v[h * x.stride + x.cc];
+        t[0] = mfma_f64(load_at(x.e0 + 4 * full * x.ldE, pe), vh + vl, t[0]);
+        t[1] = mfma_f64(load_at(x.e1 + 4 * full * x.ldE, pe), vh + vl, t[1]);
+        t[2] = mfma_f64(load_at(x.o0 + 4 * full * x.ldO, po), vh - vl, t[2]);
+        t[3] = mfma_f64(load_at(x.o1 + 4 * full * x.ldO, po), vh - vl, t[3]);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Modal: Y[N][m][c] = sum_h phi_m(h) (Z[hi] +- Z[lo])[c], c the 2 kzp doubles of a mode
-// vector.  A wave takes one N, 16 values of c and two tiles of 16 modes of one parity.
+// vector.  A workgroup takes one N, 16 values of c and two tiles of 16 modes of each
+// parity: a pair of loads feeds four products.  The groups of modes of one (N, c) follow
+// each other on one XCD (workgroups go to the eight XCDs in turn), so that its L2 holds
+// their Z after the first.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(EW_THREADS) void ew_modal_kernel(EwBatch batch)
 {
+    __shared__ double red[SUM_WAVES_LDS];
     int item;
     const EwReq& q = ew_request(batch, item);
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int ld = D.ld, ct = (ld + 15) >> 4, ge = (D.ket + 31) >> 5, go = D.kop ? (D.kot + 31) >> 5 : 0;
-    int64_t u = (int64_t)item * EW_WAVES + (threadIdx.x >> 6);
-    const int g = (int)(u % (ge + go));
-    u /= ge + go;
-    const int c = (int)(u % ct) * 16 + li;
-    const int N = (int)(u / ct);
-    if (N >= D.nN) return;
-    const bool odd = g >= ge;
-    const int t = (odd ? g - ge : g) * 32, ldt = odd ? D.kot : D.ket;
-    const bool two = t + 16 < ldt;
-    const double* phi = (odd ? D.phio : D.phie) + t + li;
-    const double* z = q.ws + (int64_t)N * D.zsN * ld + min(c, ld - 1);
-    const int64_t zs = (int64_t)D.zsM * ld;
-    f64x4 a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
-    const int last = D.nhM - 1, steps = D.nhMp >> 2;
-    for_steps<4>(steps, [&](int ks) {
-        const int h = 4 * ks + lk, hc = min(h, last), hi = D.nM - 1 - hc;
-        const double vh = z[hi * zs], vl = hi == hc ? 0.0 : z[hc * zs];
-        const double b = odd ? vh - vl : vh + vl;
-        a0 = mfma_f64(phi[(size_t)h * ldt], b, a0);
-        if (two) a1 = mfma_f64(phi[(size_t)h * ldt + 16], b, a1);
-    });
-    if (c >= ld) return;
-    const int kp = odd ? D.kop : D.kep;
-    double* y = q.ws + D.offY + ((int64_t)N * D.km + (odd ? D.kep : 0)) * ld + c;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int ld = D.ld, ct = (ld + 15) >> 4, groups = (max(D.ket, D.kop ? D.kot : 0) + 31) >> 5;
+    const int g = (item >> 3) % groups, u = (item >> 3) / groups * 8 + (item & 7);
+    const int N = u / ct, c = u % ct * 16 + li;
+    if (N >= D.nN) return;   // workgroup-uniform
+    const int ket = D.ket, kot = D.kot;
+    // tiles past a parity's last repeat its first; their rows are not stored
+    HalfAxis x;
+    x.v = as_global(q.ws) + (int64_t)N * D.zsN * ld;
+    x.stride = (int64_t)D.zsM * ld;
+    x.n = D.nM;
+    x.cc = min(c, ld - 1);
+    x.ldE = ket;
+    x.ldO = kot;
+    x.e0 = as_global(D.phie) + (g * 32 < ket ? g * 32 : 0);
+    x.e1 = as_global(D.phie) + (g * 32 + 16 < ket ? g * 32 + 16 : 0);
+    x.o0 = as_global(D.phio) + (g * 32 < kot ? g * 32 : 0);
+    x.o1 = as_global(D.phio) + (g * 32 + 16 < kot ? g * 32 + 16 : 0);
+    f64x4 t[4] = {F64X4_ZERO, F64X4_ZERO, F64X4_ZERO, F64X4_ZERO};
+    half_axis_sums(x, wave, li, lk, t);
+    const f64x4 s = sum_waves(red, t, wave, lane);
+    const bool odd = wave >= 2;
+    const int m0 = g * 32 + 16 * (wave & 1), kp = odd ? D.kop : D.kep;
+    gdouble y = as_global(q.ws) + D.offY + ((int64_t)N * D.km + (odd ? D.kep : 0) + m0) * ld;
+    if (c < ld)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = t + 4 * r + lk;
-        if (m < kp) y[(int64_t)m * ld] = a0[r];
-        if (two && m + 16 < kp) y[(int64_t)(m + 16) * ld] = a1[r];
-    }
+        for (int r = 0; r < 4; ++r)
+            if (m0 + 4 * r + lk < kp) y[(4 * r + lk) * ld + c] = s[r];
 }
 
 // ---------------------------------------------------------------------------
 // Nodes: G[a][cos|sin][m][c] = sum_h {cos, sin}(q_N(a) N_h) (Y[hi] +- Y[lo])[m][c].  A
-// wave takes 16 of the km * 2 kzp columns and up to two tiles of 16 values of a, both
-// parities, so a pair of loads feeds four products.
+// workgroup takes 16 of the km * 2 kzp columns and two tiles of 16 values of a, both
+// parities; the groups of a of one column tile on one XCD.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(EwBatch batch)
 {
+    __shared__ double red[SUM_WAVES_LDS];
     int item;
     const EwReq& q = ew_request(batch, item);
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int ncols = D.km * D.ld, ct = (ncols + 15) >> 4, nap = D.nap, ga = (nap + 31) >> 5;
-    const int64_t u = (int64_t)item * EW_WAVES + (threadIdx.x >> 6);
-    const int c = (int)(u % ct) * 16 + li, g = (int)(u / ct);
-    if (g >= ga) return;
-    const bool two = g * 32 + 16 < nap;
-    const double* tc = D.cosN + g * 32 + li;
-    const double* ts = D.sinN + g * 32 + li;
-    const double* y = q.ws + D.offY + min(c, ncols - 1);
-    f64x4 e0 = {0.0, 0.0, 0.0, 0.0}, e1 = e0, o0 = e0, o1 = e0;
-    const int last = D.nhN - 1, steps = D.nhNp >> 2;
-    for_steps<4>(steps, [&](int ks) {
-        const int h = 4 * ks + lk, hc = min(h, last), hi = D.nN - 1 - hc;
-        const double vh = y[(int64_t)hi * ncols], vl = hi == hc ? 0.0 : y[(int64_t)hc * ncols];
-        const double s = vh + vl, d = vh - vl;
-        const size_t at = (size_t)h * nap;
-        e0 = mfma_f64(tc[at], s, e0);
-        o0 = mfma_f64(ts[at], d, o0);
-        if (two) {
-            e1 = mfma_f64(tc[at + 16], s, e1);
-            o1 = mfma_f64(ts[at + 16], d, o1);
-        }
-    });
-    if (c >= ncols) return;
-    double* out = q.ws + D.offG + c;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int ncols = D.km * D.ld, nap = D.nap, ga = (nap + 31) >> 5;
+    const int g = (item >> 3) % ga, cb = ((item >> 3) / ga * 8 + (item & 7)) * 16;
+    if (cb >= ncols) return;   // workgroup-uniform
+    const int a0 = g * 32, a1 = a0 + 16 < nap ? a0 + 16 : a0, c = cb + li;
+    HalfAxis x;
+    x.v = as_global(q.ws) + D.offY;
+    x.stride = ncols;
+    x.n = D.nN;
+    x.cc = min(c, ncols - 1);
+    x.ldE = x.ldO = nap;
+    x.e0 = as_global(D.cosN) + a0;
+    x.e1 = as_global(D.cosN) + a1;
+    x.o0 = as_global(D.sinN) + a0;
+    x.o1 = as_global(D.sinN) + a1;
+    f64x4 t[4] = {F64X4_ZERO, F64X4_ZERO, F64X4_ZERO, F64X4_ZERO};
+    half_axis_sums(x, wave, li, lk, t);
+    const f64x4 s = sum_waves(red, t, wave, lane);
+    const int first = a0 + 16 * (wave & 1);
+    gdouble out = as_global(q.ws) + D.offG + (2 * first + (wave >> 1)) * (int64_t)ncols;
+    if (c < ncols && first < nap)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int a = g * 32 + 4 * r + lk;
-        if (a < D.na) {
-            out[(int64_t)(2 * a) * ncols] = e0[r];
-            out[(int64_t)(2 * a + 1) * ncols] = o0[r];
-        }
-        if (two && a + 16 < D.na) {
-            out[(int64_t)(2 * a + 32) * ncols] = e1[r];
-            out[(int64_t)(2 * a + 33) * ncols] = o1[r];
-        }
-    }
+        for (int r = 0; r < 4; ++r)
+            if (first + 4 * r + lk < D.na) out[(int64_t)(2 * (4 * r + lk)) * ncols + c] = s[r];
 }
 
 // ---------------------------------------------------------------------------
-// yz: S[pN][pM](a, b) = sum_l c_l(a, b) sum_{m in pM} c_m(a, b) G[a][pN][m][l].  A wave
-// takes one a and 16 values of b (the rows); K runs over the modes m of a parity and
-// columns over (l, re | im), both pN sharing the c_m operand; c_l multiplies each
-// product tile, the lanes' columns are summed at the end.  The result goes to
-// [pixel row][node][4 px + 2 py + (re | im)], px and py the parities along x and y.
+// yz: S[pN][pM](a, b) = sum_l c_l(a, b) sum_{m in pM} c_m(a, b) G[a][pN][m][l].  A
+// workgroup takes one a and BT tiles of 16 b (the rows); a wave one pM and every other
+// tile of 16 columns (l, re | im), K running over the modes m, both pN sharing the c_m
+// operand and the BT tiles the G operand.  c_l multiplies each product tile, and the
+// columns are summed at the end over lanes and waves.  The result goes to
+// [4 px + 2 py + (re | im)][row node][node], px and py the parities along x and y.  The
+// groups of b of one a follow each other on one XCD.
 // ---------------------------------------------------------------------------
+template <int BT>
 __global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(EwBatch batch)
 {
+    __shared__ double red[2][2][2][BT * 16][2];   // [column half][pM][pN][b][ri]
     int item;
     const EwReq& q = ew_request(batch, item);
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int bt = D.nbp >> 4, ld = D.ld, nbp = D.nbp, kzp = D.kzp;
-    const int64_t u = (int64_t)item * EW_WAVES + (threadIdx.x >> 6);
-    const int a = (int)(u / bt), b0 = (int)(u % bt) * 16;
-    if (a >= D.na) return;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int ld = D.ld, nbp = D.nbp, kzp = D.kzp, bg = (nbp + 16 * BT - 1) / (16 * BT);
+    const int a = (item >> 3) / bg * 8 + (item & 7), b0 = (item >> 3) % bg * (16 * BT);
+    if (a >= D.na) return;   // workgroup-uniform
+    const int pm = wave & 1, half = wave >> 1;
+    const int m0 = pm ? D.kep : 0, steps = (pm ? D.kop : D.kep) >> 2;
     const int64_t gs = (int64_t)D.km * ld;
-    const double* ga = q.ws + D.offG + 2 * a * gs;
-    const double* cz = D.cz + ((size_t)a * nbp + b0 + lk) * kzp;
-    double s[2][2][4];   // [pN][pM][row]
+    const gcdouble gm = as_global(q.ws) + D.offG + 2 * a * gs + (int64_t)m0 * ld;
+    const gcdouble cm = as_global(D.cm) + ((int64_t)a * D.km + m0) * nbp;
+    const gcdouble cz = as_global(D.cz) + (int64_t)a * nbp * kzp;
+    const uint32_t om = 8 * (lk * nbp + li);
+    int bt[BT];   // a tile past the last repeats it
 #pragma unroll
-    for (int k = 0; k < 16; ++k) s[k >> 3][(k >> 2) & 1][k & 3] = 0.0;
+    for (int k = 0; k < BT; ++k) bt[k] = min(b0 + 16 * k, nbp - 16);
+    double s[2][BT][4];
 #pragma unroll
-    for (int pm = 0; pm < 2; ++pm) {
-        const int m0 = pm ? D.kep : 0, steps = (pm ? D.kop : D.kep) >> 2;
-        const double* cm = D.cm + ((size_t)a * D.km + m0 + lk) * nbp + b0 + li;
-        const double* gm = ga + (int64_t)(m0 + lk) * ld;
-        for (int c0 = 0; c0 < ld; c0 += 32) {
-            const int ca = c0 + li, cb = c0 + 16 + li;
-            const int xa = min(ca, ld - 1), xb = min(cb, ld - 1);
-            f64x4 ea = {0.0, 0.0, 0.0, 0.0}, eb = ea, oa = ea, ob = ea;
-            for_steps<3>(steps, [&](int ks) {
-                const double av = cm[(size_t)4 * ks * nbp];
-                const double* g = gm + (int64_t)4 * ks * ld;
-                ea = mfma_f64(av, g[xa], ea);
-                oa = mfma_f64(av, g[gs + xa], oa);
-                eb = mfma_f64(av, g[xb], eb);
-                ob = mfma_f64(av, g[gs + xb], ob);
-            });
+    for (int k = 0; k < BT; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[0][k][r] = s[1][k][r] = 0.0;
+    for (int c0 = 16 * half; c0 < ld; c0 += 32) {
+        const int c = c0 + li, x = min(c, ld - 1);
+        const uint32_t og = 8 * (lk * ld + x), oz = 8 * (lk * kzp + (x >> 1));
+        double z[BT][4];
+#pragma unroll
+        for (int k = 0; k < BT; ++k)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const double za = ca < ld ? cz[(size_t)4 * r * kzp + (xa >> 1)] : 0.0;
-                const double zb = cb < ld ? cz[(size_t)4 * r * kzp + (xb >> 1)] : 0.0;
-                s[0][pm][r] += ea[r] * za + eb[r] * zb;
-                s[1][pm][r] += oa[r] * za + ob[r] * zb;
+                z[k][r] = load_at(cz + (bt[k] + 4 * r) * kzp, oz);
+                if (c >= ld) z[k][r] = 0.0;
             }
-        }
+        f64x4 e[BT], o[BT];
+#pragma unroll
+        for (int k = 0; k < BT; ++k) e[k] = o[k] = F64X4_ZERO;
+        Stream g[2 + BT];
+        g[0] = {gm, 4 * ld, og};
+        g[1] = {gm + gs, 4 * ld, og};
+#pragma unroll
+        for (int k = 0; k < BT; ++k) g[2 + k] = {cm + bt[k], 4 * nbp, om};
+        staged<6>(g, steps, [&](int, const double* y) {
+#pragma unroll
+            for (int k = 0; k < BT; ++k) {
+                e[k] = mfma_f64(y[2 + k], y[0], e[k]);
+                o[k] = mfma_f64(y[2 + k], y[1], o[k]);
+            }
+        });
+#pragma unroll
+        for (int k = 0; k < BT; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[0][k][r] += e[k][r] * z[k][r];
+                s[1][k][r] += o[k][r] * z[k][r];
+            }
     }
     // sum the lanes of one row with the same re | im (lane bits 1 - 3)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        double& v = s[k >> 3][(k >> 2) & 1][k & 3];
-        v += __shfl_xor(v, 2, 64);
-        v += __shfl_xor(v, 4, 64);
-        v += __shfl_xor(v, 8, 64);
-    }
-    if (li >= 2) return;
+    for (int k = 0; k < BT; ++k)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int b = b0 + 4 * r + lk;
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                double v = s[p][k][r];
+                v += dpp_f64<0x4E, 0xF>(v);    // quad_perm 2,3,0,1
+                v += dpp_f64<0x124, 0xF>(v);   // row_ror 4
+                v += dpp_f64<0x128, 0xF>(v);   // row_ror 8
+                if (li < 2) red[half][pm][p][16 * k + 4 * r + lk][li] = v;
+            }
+    __syncthreads();
+    const int uni = D.uniform;
+    for (int t = threadIdx.x; t < BT * 16 * 8; t += EW_THREADS) {
+        const int comp = t / (BT * 16), bl = t % (BT * 16), b = b0 + bl;
         if (b >= D.nb) continue;
-        const int row = D.uniform ? a : b, node = D.uniform ? b : a;
-        double* out = q.ws + D.offA + ((int64_t)row * D.n + node) * 8 + li;
-#pragma unroll
-        for (int pn = 0; pn < 2; ++pn)
-#pragma unroll
-            for (int pm = 0; pm < 2; ++pm) out[D.uniform ? 4 * pm + 2 * pn : 4 * pn + 2 * pm] = s[pn][pm][r];
+        const int px = comp >> 2, py = (comp >> 1) & 1, pn = uni ? py : px, p = uni ? px : py;
+        const double v = red[0][p][pn][bl][comp & 1] + red[1][p][pn][bl][comp & 1];
+        const int row = uni ? a : b, node = uni ? b : a;
+        q.ws[D.offS + ((int64_t)comp * D.nr + row) * D.n + node] = v;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Eval: one workgroup per pixel row.  Node values -> Chebyshev coefficients (even
-// series for px = 0, odd for px = 1) in LDS, then each thread runs the recurrence of
-// T_2k and T_2k+1 in x = 2 t^2 - 1 for its column and sums the eight parts:
+// Coef: C[row][k][comp] = sum_a D[a][k] sum_r W[row][r] S[comp][r][a] for 16 pixel rows and
+// one of the eight parts: two products on the matrix instruction, the first one's result
+// through LDS (a row of 16 per node, padded to 17), a wave to a tile of 16 nodes and then
+// of 16 coefficients.  W by the part's parity in the rows' angle (along y), D by its
+// parity in the pixels' (along x).  The eight parts of a row follow each other on one
+// XCD, whose L2 merges their pieces of C.
+// ---------------------------------------------------------------------------
+constexpr int CF_THREADS = 1024;   // at most: a wave to every 16 nodes
+
+__global__ __launch_bounds__(CF_THREADS) void ew_coef_kernel(EwBatch batch)
+{
+    extern __shared__ double lds[];   // [n][17]
+    int item;
+    const EwReq& q = ew_request(batch, item);
+    const EwDesc& D = *q.d;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int n = D.n, nr = D.nr, rowsp = D.rowsp, np = (n + 15) & ~15, waves = blockDim.x >> 6;
+    const int comp = (item >> 3) & 7, j0 = ((item >> 6) * 8 + (item & 7)) * 16;
+    if (j0 >= D.rows) return;
+    const int px = comp >> 2, py = (comp >> 1) & 1;
+    {
+        const gcdouble w = as_global(py ? D.wro : D.wre) + j0, s = as_global(q.ws) + D.offS + (int64_t)comp * nr * n;
+        const uint32_t ow = 8 * (lk * rowsp + li);
+        for (int a0 = 16 * wave; a0 < n; a0 += 16 * waves) {
+            const int a = min(a0 + li, n - 1);
+            const uint32_t os = 8 * (lk * n + a);
+            f64x4 t = F64X4_ZERO;
+            const Stream x[2] = {{w, 4 * rowsp, ow}, {s, 4 * n, os}};
+            staged<8>(x, nr >> 2, [&](int, const double* y) { t = mfma_f64(y[0], y[1], t); });
+            if (nr & 3) {   // W is zero past nr
+                const int r = nr & ~3;
+                t = mfma_f64(load_at(w + r * rowsp, ow), s[min(r + lk, nr - 1) * n + a], t);
+            }
+            if (a0 + li < n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lds[(a0 + li) * 17 + 4 * r + lk] = t[r];
+        }
+    }
+    __syncthreads();
+    const gcdouble m = as_global(px ? D.dcto : D.dcte);
+    const uint32_t om = 8 * (lk * np + li);
+    gdouble out = as_global(q.ws) + D.offC + comp;
+    for (int k0 = 16 * wave; k0 < n; k0 += 16 * waves) {
+        f64x4 t = F64X4_ZERO;
+        const Stream x[1] = {{m + k0, 4 * np, om}};
+        staged<8>(x, n >> 2, [&](int ks, const double* y) { t = mfma_f64(lds[(4 * ks + lk) * 17 + li], y[0], t); });
+        if (n & 3) {   // D is zero past n
+            const int a = n & ~3;
+            t = mfma_f64(lds[min(a + lk, n - 1) * 17 + li], load_at(m + a * np + k0, om), t);
+        }
+        const int k = k0 + li;
+        if (k < n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = j0 + 4 * r + lk;
+                if (j < D.rows) out[((int64_t)j * n + k) * 8] = t[r];
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Eval: a workgroup takes 256 columns of one pixel row, the row's coefficients in LDS;
+// each thread runs the recurrence of T_2k and T_2k+1 in x = 2 t^2 - 1 for two columns, so
+// that a coefficient read serves both, and sums the eight parts:
 //   A(sx, sy) = (ee - sx sy oo) - i (sx oe + sy eo)          (px, py)
 // for the four mirror pixels.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(EW_THREADS) void ew_eval_kernel(EwBatch batch)
+__device__ __forceinline__ void ew_store(const EwReq& q, int N, int i, int j, bool rim, const double* s)
 {
-    extern __shared__ double lds[];   // [2][n][8]: node values, coefficients
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const bool px = !(m & 1), py = !(m & 2);   // the pixel at +u, +v
+        const int ii = px ? N - 1 - i : i, jj = py ? N - 1 - j : j;
+        if ((!px && ii == N - 1 - i) || (!py && jj == N - 1 - j)) continue;   // the middle, done at +
+        const double sx = px ? 1.0 : -1.0, sy = py ? 1.0 : -1.0;
+        // s: ee re, ee im, eo re, eo im, oe re, oe im, oo re, oo im
+        double re = s[0] - sx * sy * s[6] + (sx * s[5] + sy * s[3]);
+        double im = s[1] - sx * sy * s[7] - (sx * s[4] + sy * s[2]);
+        if (rim) re = im = 0.0;
+        const int64_t p = (int64_t)jj * N + ii;
+        if (p < q.p0 || p >= q.p1) continue;
+        q.intensity[p] = (float)(re * re + im * im);
+        if (q.amplitude) ((float2*)q.amplitude)[p] = make_float2((float)re, (float)im);
+    }
+}
+
+constexpr int EV_THREADS = 128;
+
+__global__ __launch_bounds__(EV_THREADS) void ew_eval_kernel(EwBatch batch)
+{
+    extern __shared__ double C[];   // [n][8]
     int item;
     const EwReq& q = ew_request(batch, item);
     const EwDesc& D = *q.d;
     const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x;
-    const int j = item;
-    // rows of this request's pixel range only
-    const int jh = N - 1 - j;
-    const int64_t lo = (int64_t)j * N, hi = (int64_t)jh * N;
+    const int chunks = (half + 2 * EV_THREADS - 1) / (2 * EV_THREADS), j = item / chunks;
+    // nothing to do where the row and its mirror lie outside [p0, p1)
+    const int64_t lo = (int64_t)j * N, hi = (int64_t)(N - 1 - j) * N;
     if ((lo + N <= q.p0 || lo >= q.p1) && (hi + N <= q.p0 || hi >= q.p1)) return;
-    double* val = lds;
-    double* coef = lds + (size_t)n * 8;
-    const double* src = q.ws + D.offA + (int64_t)j * n * 8;
-    for (int k = tid; k < n * 8; k += EW_THREADS) val[k] = src[k];
+    const gcdouble tq = as_global(D.tq) + (int64_t)j * half;
+    const int i = item % chunks * (2 * EV_THREADS) + tid, i2 = i + EV_THREADS;
+    const double t0 = tq[min(i, half - 1)], t1 = tq[min(i2, half - 1)];
+    const double2* src = (const double2*)(q.ws + D.offC + (int64_t)j * n * 8);
+    for (int k = tid; k < n * 4; k += EV_THREADS) ((double2*)C)[k] = src[k];
     __syncthreads();
-    for (int o = tid; o < n * 8; o += EW_THREADS) {
-        const int comp = o & 7, k = o >> 3;
-        const double* m = (comp & 4 ? D.dcto : D.dcte) + k;
-        double s = 0.0;
+    if (i < half) {
+        double e0[2], e1[2], o0[2], o1[2], x2[2], s[2][8];
+        bool rim[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const double t = p ? t1 : t0;
+            rim[p] = !(t == t);
+            const double tt = rim[p] ? 0.0 : t;
+            x2[p] = 2.0 * (2.0 * tt * tt - 1.0);
+            e0[p] = 1.0;                      // T_0, T_2
+            e1[p] = 0.5 * x2[p];
+            o0[p] = tt;                       // T_1, T_3 = (2 x - 1) t
+            o1[p] = (x2[p] - 1.0) * tt;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s[p][c] = 0.0;
+        }
 #pragma unroll 4
-        for (int a = 0; a < n; ++a) s += m[(size_t)a * n] * val[a * 8 + comp];
-        coef[o] = s;
-    }
-    __syncthreads();
-    for (int i = tid; i < half; i += EW_THREADS) {
-        const double t = D.tq[(int64_t)j * half + i];
-        const bool rim = !(t == t);
-        const double tt = rim ? 0.0 : t, x2 = 2.0 * (2.0 * tt * tt - 1.0);
-        double e0 = 1.0, e1 = 0.5 * x2;           // T_0, T_2
-        double o0 = tt, o1 = (x2 - 1.0) * tt;     // T_1, T_3 = (2 x - 1) t
-        double s[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s[c] = 0.0;
-#pragma unroll 2
         for (int k = 0; k < n; ++k) {
-            const double* C = coef + k * 8;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                s[c] += e0 * C[c];
-                s[4 + c] += o0 * C[4 + c];
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    s[p][c] += e0[p] * C[k * 8 + c];
+                    s[p][4 + c] += o0[p] * C[k * 8 + 4 + c];
+                }
+                const double e2 = x2[p] * e1[p] - e0[p], o2 = x2[p] * o1[p] - o0[p];
+                e0[p] = e1[p];
+                e1[p] = e2;
+                o0[p] = o1[p];
+                o1[p] = o2;
             }
-            const double e2 = x2 * e1 - e0, o2 = x2 * o1 - o0;
-            e0 = e1;
-            e1 = e2;
-            o0 = o1;
-            o1 = o2;
         }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const bool px = !(m & 1), py = !(m & 2);   // the pixel at +u, +v
-            const int ii = px ? N - 1 - i : i, jj = py ? jh : j;
-            if ((!px && ii == N - 1 - i) || (!py && jj == jh)) continue;   // the middle, done at +
-            const double sx = px ? 1.0 : -1.0, sy = py ? 1.0 : -1.0;
-            // s: ee re, ee im, eo re, eo im, oe re, oe im, oo re, oo im
-            double re = s[0] - sx * sy * s[6] + (sx * s[5] + sy * s[3]);
-            double im = s[1] - sx * sy * s[7] - (sx * s[4] + sy * s[2]);
-            if (rim) re = im = 0.0;
-            const int64_t p = (int64_t)jj * N + ii;
-            if (p < q.p0 || p >= q.p1) continue;
-            q.intensity[p] = (float)(re * re + im * im);
-            if (q.amplitude) ((float2*)q.amplitude)[p] = make_float2((float)re, (float)im);
-        }
+        ew_store(q, N, i, j, rim[0], s[0]);
+        if (i2 < half) ew_store(q, N, i2, j, rim[1], s[1]);
     }
 }
 
@@ -418,7 +648,7 @@ struct CoefArgs {
 // Coefficients of exp(-i q r) on an axis's modes: 2 sum_h phi_m(h) cos(q r_h) (even m),
 // sin (odd m), the middle voxel of an odd axis once; q = q_M(a, b), or q_z(a, b) - qc.
 // Workgroup (16 values of b, one a); the trigonometric values of 64 h at a time in LDS.
-__global__ __launch_bounds__(256) void ew_coef_kernel(CoefArgs c)
+__global__ __launch_bounds__(256) void ew_mode_kernel(CoefArgs c)
 {
     __shared__ double cs[64][16], sn[64][16];
     const int tid = threadIdx.x, bl = tid & 15, mg = tid >> 4;
@@ -454,16 +684,10 @@ __global__ __launch_bounds__(256) void ew_coef_kernel(CoefArgs c)
     }
 }
 
-int ew_lds(const EwBatch& b, const EwDesc* const* dims)
-{
-    int n = 0;
-    for (int r = 0; r < b.n; ++r) n = dims[r]->n > n ? dims[r]->n : n;
-    return n * 16 * (int)sizeof(double);
-}
-
 // Workgroups per request by `f`, then one launch over all of them.
 template <typename K, typename F>
-void ew_launch(K kernel, EwBatch& b, const EwDesc* const* dims, int lds, hipStream_t s, F f)
+void ew_launch(K kernel, EwBatch& b, const EwDesc* const* dims, int lds, hipStream_t s, F f,
+               int threads = EW_THREADS)
 {
     int64_t total = 0;
     for (int r = 0; r < b.n; ++r) {
@@ -471,7 +695,18 @@ void ew_launch(K kernel, EwBatch& b, const EwDesc* const* dims, int lds, hipStre
         total += f(*dims[r]);
     }
     b.begin[b.n] = (int32_t)total;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(EW_THREADS), lds, s, b);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(threads), lds, s, b);
+}
+
+// Workgroups of a kernel whose `inner` workgroups of each of `outer` units follow each
+// other on one XCD.
+int64_t ew_on_xcd(int64_t outer, int64_t inner) { return ceil_div(outer, 8) * 8 * inner; }
+
+template <int BT>
+void ew_launch_yz(EwBatch& b, const EwDesc* const* dims, hipStream_t s)
+{
+    ew_launch(ew_yz_kernel<BT>, b, dims, 0, s,
+              [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 16 * BT)); });
 }
 
 }  // namespace
@@ -479,30 +714,49 @@ void ew_launch(K kernel, EwBatch& b, const EwDesc* const* dims, int lds, hipStre
 int launch_ew_scan(EwBatch b, const EwDesc* const* dims, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    int kzt = 0;
-    for (int r = 0; r < b.n; ++r) kzt = dims[r]->kzt > kzt ? dims[r]->kzt : kzt;
-    auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, EW_COLS); };
-    const int nt = (kzt / 16 + 1) / 2;   // mode tiles per wave
-    if (nt <= 1) ew_launch(ew_scan_kernel<1>, b, dims, 0, s, items);
-    else if (nt <= 2) ew_launch(ew_scan_kernel<2>, b, dims, 0, s, items);
-    else if (nt <= 4) ew_launch(ew_scan_kernel<4>, b, dims, 0, s, items);
-    else ew_launch(ew_scan_kernel<EW_MAX_KZ / 32>, b, dims, 0, s, items);
+    // a request's kernel, and so its rounding, goes by its own columns in any batch
+    for (int rounds = 0; rounds <= EW_WHOLE_NZ / EW_ZC; ++rounds) {
+        EwBatch part;
+        const EwDesc* d[EW_MAX_REQ];
+        part.n = 0;
+        for (int r = 0; r < b.n; ++r)
+            if (ew_rounds(dims[r]->nz) == rounds) {
+                d[part.n] = dims[r];
+                part.req[part.n++] = b.req[r];
+            }
+        if (part.n == 0) continue;
+        auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, ew_columns(d.nz)); };
+        if (rounds == 0) ew_launch(ew_scan_rounds_kernel, part, d, 0, s, items);
+        else if (rounds == 1) ew_launch(ew_scan_kernel<16, 4>, part, d, 0, s, items);
+        else if (rounds == 2) ew_launch(ew_scan_kernel<16, 8>, part, d, 0, s, items);
+        else if (rounds == 3) ew_launch(ew_scan_kernel<8, 6>, part, d, 0, s, items);
+        else ew_launch(ew_scan_kernel<8, 8>, part, d, 0, s, items);
+    }
     return (int)hipGetLastError();
 }
 
 int launch_ew_contract(EwBatch b, const EwDesc* const* dims, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
+    int64_t bt = 0;
+    int n = 0;
+    for (int r = 0; r < b.n; ++r) {
+        bt += (int64_t)dims[r]->na * (dims[r]->nbp / 16);
+        n = std::max(n, dims[r]->n);
+    }
     ew_launch(ew_modal_kernel, b, dims, 0, s, [](const EwDesc& d) {
-        const int64_t g = ceil_div(d.ket, 32) + (d.kop ? ceil_div(d.kot, 32) : 0);
-        return ceil_div(g * ceil_div(d.ld, 16) * d.nN, EW_WAVES);
+        return ew_on_xcd(d.nN * ceil_div(d.ld, 16), ceil_div(std::max(d.ket, d.kop ? d.kot : 0), 32));
     });
     ew_launch(ew_nodes_kernel, b, dims, 0, s, [](const EwDesc& d) {
-        return ceil_div(ceil_div((int64_t)d.km * d.ld, 16) * ceil_div(d.nap, 32), EW_WAVES);
+        return ew_on_xcd(ceil_div((int64_t)d.km * d.ld, 16), ceil_div(d.nap, 32));
     });
-    ew_launch(ew_yz_kernel, b, dims, 0, s,
-              [](const EwDesc& d) { return ceil_div((int64_t)d.na * (d.nbp / 16), EW_WAVES); });
-    ew_launch(ew_eval_kernel, b, dims, ew_lds(b, dims), s, [](const EwDesc& d) { return (int64_t)d.rows; });
+    if (bt >= 8 * CHIP_CUS) ew_launch_yz<2>(b, dims, s);
+    else ew_launch_yz<1>(b, dims, s);
+    ew_launch(ew_coef_kernel, b, dims, n * 17 * (int)sizeof(double), s,
+              [](const EwDesc& d) { return ew_on_xcd(d.rowsp / 16, 8); },
+              std::min(CF_THREADS, std::max(4, (n + 15) / 16) * 64));
+    ew_launch(ew_eval_kernel, b, dims, n * 8 * (int)sizeof(double), s,
+              [](const EwDesc& d) { return d.rows * ceil_div(d.rows, 2 * EV_THREADS); }, EV_THREADS);
     return (int)hipGetLastError();
 }
 
@@ -535,11 +789,11 @@ int launch_ew_tables(const EwHost& h, const EwDesc& D, const EwTables& t, void* 
     c.sa = (int64_t)D.km * D.nbp;
     c.sb = 1;
     c.sm = D.nbp;
-    hipLaunchKernelGGL(ew_coef_kernel, grid, dim3(256), 0, s, c);
-    c.even = t.phize;
-    c.odd = t.phizo;
-    c.ldE = D.kze;
-    c.ldO = D.kz - D.kze;
+    hipLaunchKernelGGL(ew_mode_kernel, grid, dim3(256), 0, s, c);
+    c.even = D.phize;
+    c.odd = D.phizo;
+    c.ldE = D.kzet;
+    c.ldO = D.kzot;
     c.out = t.cz;
     c.pitch = h.pitchZ;
     c.n = D.nz;
@@ -551,7 +805,7 @@ int launch_ew_tables(const EwHost& h, const EwDesc& D, const EwTables& t, void* 
     c.sa = (int64_t)D.nbp * D.kzp;
     c.sb = D.kzp;
     c.sm = 1;
-    hipLaunchKernelGGL(ew_coef_kernel, grid, dim3(256), 0, s, c);
+    hipLaunchKernelGGL(ew_mode_kernel, grid, dim3(256), 0, s, c);
     return (int)hipGetLastError();
 }
 

@@ -1,13 +1,16 @@
-// Adjoint of the spherical-coordinate forward model (see ewald.h): the five stages of
-// the forward transposed, in FP64, and the column walk of the chain rule.
+// Adjoint of the spherical-coordinate forward model (see ewald.h): the stages of the
+// forward transposed, in FP64, and the column walk of the chain rule.
 //
-//   rows   H(row, k)  = sum over the row's pixels of T_k(t) h     (h = g conj(A), folded
-//          over the four mirror pixels), then node values' gradients
-//   yz     Gh[a]      = sum_b c_m(a, b) c_l(a, b) H(a, b)
-//   nodes  Yh[N]      = sum_a {cos, sin}(q_N(a) N) Gh[a]
-//   modal  Zh[N][M]   = sum_m phi_m(M) Yh[N]
-//   walk   R(z)       = exp(-i qc z) sum_l phi_l(z) Zh, then along each column
+//   rows   C(row, k)  = sum over the row's pixels of T_k(t) h
+//          (h = g conj(A), folded over the four mirror pixels)
+//   coef   S(r, a)    = sum_k D[a][k] sum over the rows of W[row][r] C
+//   yz     G_ml(a)    = sum_b c_m(a, b) c_l(a, b) S(a, b)
+//   nodes  Y_ml(N)    = sum_a {cos, sin}(q_N(a) N) G_ml(a)
+//   modal  Z_l(N, M)  = sum_m phi_m(M) Y_ml(N)
+//   walk   R(z)       = exp(-i qc z) sum_l phi_l(z) Z_l, then along each column
 //          dL/d delta, dL/d beta from R (Eqs. (7)-(9))
+//
+// Every array takes the place of the forward's of the same letter.
 #include <hip/hip_runtime.h>
 
 #include "ewald.h"
@@ -18,344 +21,499 @@ namespace msft {
 
 namespace {
 
-constexpr int EA_THREADS = 256;   // of a workgroup, but for the rows of more than 256 nodes: 128
+constexpr int EA_THREADS = 256;
 constexpr int EA_WAVES = EA_THREADS / 64;
-
-// Sums of eight values over a wave: two exchange steps leave a lane two of the eight
-// (indices 4 bit0(lane) + 2 bit1(lane) + {0, 1}), which are then summed over the lanes
-// of the same two bits.
-__device__ __forceinline__ void wave_sum8(const double* v, int lane, double* out)
-{
-    const bool b0 = lane & 1, b1 = lane & 2;
-    double w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double keep = b0 ? v[4 + k] : v[k], send = b0 ? v[k] : v[4 + k];
-        w[k] = keep + dpp_f64<0xB1, 0xF>(send);   // quad_perm 1,0,3,2
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double keep = b1 ? w[2 + k] : w[k], send = b1 ? w[k] : w[2 + k];
-        double s = keep + dpp_f64<0x4E, 0xF>(send);   // quad_perm 2,3,0,1
-        s += dpp_f64<0x124, 0xF>(s);                  // row_ror 4
-        s += dpp_f64<0x128, 0xF>(s);                  // row_ror 8
-        s += __shfl_xor(s, 16, 64);
-        s += __shfl_xor(s, 32, 64);
-        out[k] = s;
-    }
-}
+constexpr int EA_LD = EW_COLS + 1;
 
 // ---------------------------------------------------------------------------
-// Rows: one workgroup per pixel row.  A thread folds h of its columns' mirror pixels
-// into the eight parts, runs the Chebyshev recurrences and, for every k, the workgroup
-// sums T_k times the parts over the row; the sums go through LDS to the transposed
-// node transform.
+// Rows: one workgroup per pixel row, 256 columns at a time, 64 to a wave.  A lane folds h
+// of its column's mirror pixels into the eight parts and runs the recurrences of T_2k and
+// T_2k+1, eight orders at a time into the wave's own LDS (a row of pixels per order: the
+// writes are contiguous, the reads of 16 orders by 4 pixels meet distinct banks).  The
+// sums over pixels are products on the four-block matrix instruction, blocks 0 and 1 the
+// even orders, 2 and 3 the odd ones with their four parts: no lane is idle, where on the
+// 16 x 16 one three quarters of the columns would be.  The waves' sums of 32 orders meet
+// in LDS.
 // ---------------------------------------------------------------------------
+constexpr int RW_ORDERS = 32;
+
 __global__ __launch_bounds__(EA_THREADS) void ew_rows_kernel(EwAdj q)
 {
-    extern __shared__ double lds[];   // [waves][n][8]
+    __shared__ double T[EA_WAVES][16][65], Hs[EA_WAVES][8][65], sums[EA_WAVES][RW_ORDERS * 8];
     const EwDesc& D = *q.d;
-    const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = blockIdx.x, jh = N - 1 - j, threads = blockDim.x;
-    double* part = lds + (size_t)wave * n * 8;
-    for (int k = lane; k < n * 8; k += 64) part[k] = 0.0;
-    __syncthreads();
-    const float2* A = (const float2*)q.amplitude;
-    for (int i0 = 0; i0 < half; i0 += threads) {
+    const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+    const int j = blockIdx.x, jh = N - 1 - j, li = lane & 15, lk = lane >> 4, par = li >> 3, lc = lane & 3;
+    const gcdouble tq = as_global(D.tq) + (int64_t)j * half;
+    const float __attribute__((address_space(1)))* g = as_global(q.grad_intensity);
+    const float __attribute__((address_space(1)))* A = as_global(q.amplitude);
+    gdouble C = as_global(q.ws) + D.offC + (int64_t)j * n * 8;
+    for (int i0 = 0; i0 < half; i0 += EA_THREADS) {
         const int i = i0 + tid;
+        const double t = tq[min(i, half - 1)];
+        const bool rim = !(t == t) || i >= half;
         double H[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) H[c] = 0.0;
-        double t = 0.0;
-        if (i < half) {
-            t = D.tq[(int64_t)j * half + i];
-            const bool rim = !(t == t);
-            if (rim) t = 0.0;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const bool px = !(m & 1), py = !(m & 2);
-                const int ii = px ? N - 1 - i : i, jj = py ? jh : j;
-                if (rim || (!px && ii == N - 1 - i) || (!py && jj == jh)) continue;
-                const double sx = px ? 1.0 : -1.0, sy = py ? 1.0 : -1.0;
-                const int64_t p = (int64_t)jj * N + ii;
-                const double g = (double)q.grad_intensity[p];
-                const float2 a = A[p];
-                const double hr = g * (double)a.x, hi = -g * (double)a.y;
-                // transposes of ee - sx sy oo - i (sx oe + sy eo)
-                H[0] += hr;
-                H[1] += hi;
-                H[2] += sy * hi;
-                H[3] -= sy * hr;
-                H[4] += sx * hi;
-                H[5] -= sx * hr;
-                H[6] -= sx * sy * hr;
-                H[7] -= sx * sy * hi;
-            }
+        for (int m = 0; m < 4; ++m) {
+            const bool px = !(m & 1), py = !(m & 2);   // the pixel at +u, +v
+            const int ii = px ? N - 1 - i : i;
+            if (rim || (!px && ii == N - 1 - i) || (!py && j == jh)) continue;
+            const double sx = px ? 1.0 : -1.0, sy = py ? 1.0 : -1.0;
+            const int64_t p = (int64_t)(py ? jh : j) * N + ii;
+            const double gv = g[p], hr = gv * (double)A[2 * p], hi = -gv * (double)A[2 * p + 1];
+            // transposes of ee - sx sy oo - i (sx oe + sy eo)
+            H[0] += hr;
+            H[1] += hi;
+            H[2] += sy * hi;
+            H[3] -= sy * hr;
+            H[4] += sx * hi;
+            H[5] -= sx * hr;
+            H[6] -= sx * sy * hr;
+            H[7] -= sx * sy * hi;
         }
-        const double x2 = 2.0 * (2.0 * t * t - 1.0);
-        double e0 = 1.0, e1 = 0.5 * x2, o0 = t, o1 = (x2 - 1.0) * t;
-        for (int k = 0; k < n; ++k) {
-            double v[8], s[2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                v[c] = e0 * H[c];
-                v[4 + c] = o0 * H[4 + c];
+        for (int c = 0; c < 8; ++c) Hs[wave][c][lane] = H[c];
+        const double tt = rim ? 0.0 : t, x2 = 2.0 * (2.0 * tt * tt - 1.0);
+        double e0 = 1.0, e1 = 0.5 * x2, o0 = tt, o1 = (x2 - 1.0) * tt;
+        for (int k0 = 0; k0 < n; k0 += RW_ORDERS) {
+#pragma unroll 1
+            for (int kb = 0; kb < RW_ORDERS; kb += 8) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    T[wave][k][lane] = e0;
+                    T[wave][8 + k][lane] = o0;
+                    const double e2 = x2 * e1 - e0, o2 = x2 * o1 - o0;
+                    e0 = e1;
+                    e1 = e2;
+                    o0 = o1;
+                    o1 = o2;
+                }
+                __builtin_amdgcn_wave_barrier();   // the wave's own LDS, in order
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 16; ++s)
+                    acc[s & 3] = mfma_f64_4b(T[wave][li][4 * s + lk], Hs[wave][4 * par + lc][4 * s + lk], acc[s & 3]);
+                __builtin_amdgcn_wave_barrier();
+                sums[wave][(kb + (li & 4) + lk) * 8 + 4 * par + lc] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
-            wave_sum8(v, lane, s);
-            if (lane < 4) {
-                double* out = part + k * 8 + 4 * (lane & 1) + (lane & 2);
-                out[0] += s[0];
-                out[1] += s[1];
-            }
-            const double e2 = x2 * e1 - e0, o2 = x2 * o1 - o0;
-            e0 = e1;
-            e1 = e2;
-            o0 = o1;
-            o1 = o2;
+            __syncthreads();
+            const double s = (sums[0][tid] + sums[1][tid]) + (sums[2][tid] + sums[3][tid]);
+            if (k0 + (tid >> 3) < n) C[k0 * 8 + tid] = i0 ? C[k0 * 8 + tid] + s : s;
+            __syncthreads();
         }
-    }
-    __syncthreads();
-    for (int k = tid; k < n * 8; k += threads) {
-        double s = lds[k];
-        for (int w = 1; w < threads >> 6; ++w) s += lds[(size_t)w * n * 8 + k];
-        lds[k] = s;
-    }
-    __syncthreads();
-    double* out = q.ws + D.offA + (int64_t)j * n * 8;
-    for (int o = tid; o < n * 8; o += threads) {
-        const int comp = o & 7, a = o >> 3;
-        const double* m = (comp & 4 ? D.dcto : D.dcte) + (size_t)a * n;
-        double s = 0.0;
-#pragma unroll 4
-        for (int k = 0; k < n; ++k) s += m[k] * lds[k * 8 + comp];
-        out[o] = s;
     }
 }
 
 // ---------------------------------------------------------------------------
-// yz transposed: Gh[a][pN][m][(l, ri)] = sum_b c_m(a, b) c_l(a, b) H(a, b)[pN][pM(m)][ri].
-// A wave takes one a, one pN, 16 modes m of a parity (the rows) and up to four tiles of
-// 16 columns (l, ri); K runs over b, the second operand formed from c_l and H.
+// Coef transposed: S[comp][r][a] = sum_k D[a][k] sum over rows of W[row][r] C[row][k][comp]
+// for 16 row nodes and one part: 16 waves, four to the rows and four to the tiles of 16
+// orders k, their sums through LDS (a row of 16 row nodes per order, padded to 17), then a
+// wave to each tile of 16 nodes a.
+// ---------------------------------------------------------------------------
+constexpr int CA_THREADS = 1024;
+
+__global__ __launch_bounds__(CA_THREADS) void ew_coef_adj_kernel(EwAdj q)
+{
+    extern __shared__ double lds[];              // [n][17]
+    __shared__ double red[3][4][4 * 64];         // rows' part, tile
+    const EwDesc& D = *q.d;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int n = D.n, nr = D.nr, rowsp = D.rowsp, np = (n + 15) & ~15;
+    const int comp = blockIdx.x & 7, r0 = (blockIdx.x >> 3) * 16, part = wave >> 2;
+    const int px = comp >> 2, py = (comp >> 1) & 1, last = D.rows - 1;
+    const gcdouble w = as_global(py ? D.wro : D.wre) + (int64_t)r0 * rowsp;
+    const gcdouble C = as_global(q.ws) + D.offC + comp;
+    const uint32_t ow = 8 * (li * rowsp + lk);
+    const int steps = rowsp >> 4;   // of four rows, per part
+    for (int t0 = 0; t0 < np; t0 += 64) {
+        const int k = min(t0 + 16 * (wave & 3) + li, n - 1);
+        f64x4 t = F64X4_ZERO;
+        for_steps<8>(steps, [&](int ks) {
+            const int j = 4 * (part * steps + ks);   // W is zero for rows past the last
+            t = mfma_f64(load_at(w + j, ow), C[((int64_t)min(j + lk, last) * n + k) * 8], t);
+        });
+        if (part)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[part - 1][wave & 3][r * 64 + lane] = t[r];
+        __syncthreads();
+        if (!part && t0 + 16 * wave + li < n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                lds[(t0 + 16 * wave + li) * 17 + 4 * r + lk] =
+                    ((t[r] + red[0][wave][r * 64 + lane]) + red[1][wave][r * 64 + lane]) + red[2][wave][r * 64 + lane];
+        __syncthreads();
+    }
+    const gcdouble m = as_global(px ? D.dcto : D.dcte);
+    gdouble out = as_global(q.ws) + D.offS + (int64_t)comp * nr * n;
+    for (int a0 = 16 * wave; a0 < n; a0 += 16 * (CA_THREADS / 64)) {
+        f64x4 t = F64X4_ZERO;
+        for_steps<8>((n + 3) >> 2, [&](int ks) {   // D is zero for k >= n
+            const int k = 4 * ks;
+            t = mfma_f64(lds[min(k + lk, n - 1) * 17 + li], load_at(m + (int64_t)a0 * np + k, 8 * (li * np + lk)), t);
+        });
+        if (a0 + li < n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (r0 + 4 * r + lk < nr) out[(int64_t)(r0 + 4 * r + lk) * n + a0 + li] = t[r];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// yz transposed: G[a][pN][m][(l, ri)] = sum_b c_m(a, b) c_l(a, b) S(a, b)[pN][pM(m)][ri].
+// A workgroup takes one a, one pN and two tiles of 16 columns (l, ri); a wave one parity
+// of m and one tile of 16 of its modes; K runs over b, the second operand formed from
+// c_l and S.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(EA_THREADS) void ew_yz_adj_kernel(EwAdj q)
 {
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int te = (D.kep + 15) >> 4, to = (D.kop + 15) >> 4, cg = (D.ld + 63) >> 6;
-    int64_t u = (int64_t)blockIdx.x * EA_WAVES + (threadIdx.x >> 6);
-    const int g = (int)(u % cg);
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int ld = D.ld, cg = (ld + 31) >> 5, mg = (max(D.kep, D.kop) + 31) >> 5;
+    // the workgroups of one a follow each other on one XCD
+    int u = blockIdx.x >> 3;
+    const int g = u % cg;
     u /= cg;
-    const int mt = (int)(u % (te + to));
-    u /= te + to;
-    const int pn = (int)(u & 1), a = (int)(u >> 1);
-    if (a >= D.na) return;
-    const int pm = mt >= te, m0 = (pm ? mt - te : mt) * 16, kp = pm ? D.kop : D.kep;
-    const int nbp = D.nbp, kzp = D.kzp, nb = D.nb, ld = D.ld;
-    // rows beyond the parity's modes read its last row and are not stored
-    const double* cm = D.cm + ((size_t)a * D.km + (pm ? D.kep : 0) + min(m0 + li, kp - 1)) * nbp + lk;
-    const int px = D.uniform ? pm : pn, py = D.uniform ? pn : pm;
-    const double* H = q.ws + D.offA + 4 * px + 2 * py + (li & 1);
-    const int64_t hs = D.uniform ? 8 : (int64_t)D.n * 8, ha = D.uniform ? (int64_t)D.n * 8 : 8;
-    H += a * ha;
-    f64x4 acc[4];
-    int lz[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-        lz[t] = min(g * 64 + t * 16 + li, ld - 1) >> 1;
-    }
-    const int nt = min(4, (ld - g * 64 + 15) >> 4);
-    for_steps<2>(nbp / 4, [&](int ks) {
-        const int b = 4 * ks + lk, bc = min(b, nb - 1);
-        const double av = cm[4 * ks], h = H[bc * hs];   // cm is zero for b >= nb
-        const double* cz = D.cz + ((size_t)a * nbp + bc) * kzp;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (t < nt) acc[t] = mfma_f64(av, cz[lz[t]] * h, acc[t]);
+    const int pm = wave & 1, m0 = u % mg * 32 + 16 * (wave >> 1), kp = pm ? D.kop : D.kep;
+    u /= mg;
+    const int pn = u & 1, a = (u >> 1) * 8 + (blockIdx.x & 7);
+    if (a >= D.na || m0 >= kp) return;   // nothing waits for a wave that is done
+    const int nbp = D.nbp, kzp = D.kzp, nb = D.nb, uni = D.uniform;
+    // rows past the parity's modes read its last and are not stored
+    const gcdouble cm = as_global(D.cm) + ((int64_t)a * D.km + (pm ? D.kep : 0) + m0) * nbp;
+    const uint32_t om = 8 * (min(li, kp - 1 - m0) * nbp + lk);
+    const int px = uni ? pm : pn, py = uni ? pn : pm, ss = uni ? 1 : D.n;
+    const gcdouble S = as_global(q.ws) + D.offS + (int64_t)(4 * px + 2 * py) * D.nr * D.n + (uni ? (int64_t)a * D.n : a);
+    const gcdouble cz = as_global(D.cz) + (int64_t)a * nbp * kzp;
+    const int ca = g * 32 + li, cb = ca + 16, la = min(ca, ld - 1) >> 1, lb = min(cb, ld - 1) >> 1;
+    const uint32_t os = 8 * ((li & 1) * D.nr * D.n + lk * ss), oa = 8 * (lk * kzp + la), ob = 8 * (lk * kzp + lb);
+    f64x4 t0 = F64X4_ZERO, t1 = F64X4_ZERO;
+    const Stream x[4] = {{cm, 4, om}, {S, 4 * ss, os}, {cz, 4 * kzp, oa}, {cz, 4 * kzp, ob}};
+    staged<4>(x, nb >> 2, [&](int, const double* y) {
+        t0 = mfma_f64(y[0], y[2] * y[1], t0);
+        t1 = mfma_f64(y[0], y[3] * y[1], t1);
     });
-    double* out = q.ws + D.offG + ((int64_t)(2 * a + pn) * D.km + (pm ? D.kep : 0)) * ld;
+    if (nb & 3) {   // c_m is zero past nb
+        const int b0 = nb & ~3, b = min(b0 + lk, nb - 1);
+        const double av = load_at(cm + b0, om), h = S[(li & 1) * D.nr * D.n + b * ss];
+        t0 = mfma_f64(av, cz[b * kzp + la] * h, t0);
+        t1 = mfma_f64(av, cz[b * kzp + lb] * h, t1);
+    }
+    gdouble out = as_global(q.ws) + D.offG + ((int64_t)(2 * a + pn) * D.km + (pm ? D.kep : 0) + m0) * ld;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int c = g * 64 + t * 16 + li;
-        if (t >= nt || c >= ld) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = m0 + 4 * r + lk;
-            if (m < kp) out[(int64_t)m * ld + c] = acc[t][r];
-        }
+    for (int r = 0; r < 4; ++r) {
+        const int m = 4 * r + lk;
+        if (m0 + m >= kp) continue;
+        if (ca < ld) out[m * ld + ca] = t0[r];
+        if (cb < ld) out[m * ld + cb] = t1[r];
     }
 }
 
 // ---------------------------------------------------------------------------
-// Nodes transposed: E = sum_a cos Gh[a][0], O = sum_a sin Gh[a][1] at 16 half-axis
-// positions (the rows) and 16 columns (m, c); Yh[hi] = E + O, Yh[lo] = E - O.
+// Nodes transposed: E = sum_a cos G[a][0], O = sum_a sin G[a][1] at half-axis positions
+// (the rows) and 16 columns (m, c); Y[hi] = E + O, Y[lo] = E - O.  A workgroup takes two
+// tiles of 16 positions; a wave one of them and half of the nodes.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(EA_THREADS) void ew_nodes_adj_kernel(EwAdj q)
 {
+    __shared__ double red[2][2][4][64];
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int ncols = D.km * D.ld, ct = (ncols + 15) >> 4, nap = D.nap, gh = (D.nhNp + 31) >> 5;
-    const int64_t u = (int64_t)blockIdx.x * EA_WAVES + (threadIdx.x >> 6);
-    const int c = (int)(u % ct) * 16 + li, g = (int)(u / ct);
-    if (g >= gh) return;
-    const bool two = g * 32 + 16 < D.nhNp;
-    const size_t at = (size_t)(g * 32 + li) * nap + lk;
-    const double* tc = D.cosN + at;
-    const double* ts = D.sinN + at;
-    const int64_t step16 = two ? (int64_t)16 * nap : 0;
-    const double* G = q.ws + D.offG + min(c, ncols - 1);
-    f64x4 e0 = {0.0, 0.0, 0.0, 0.0}, e1 = e0, o0 = e0, o1 = e0;
-    for_steps<4>(nap / 4, [&](int ks) {
-        const int a = min(4 * ks + lk, D.na - 1);   // the tables are zero beyond na
-        const double ge = G[(int64_t)(2 * a) * ncols], go = G[(int64_t)(2 * a + 1) * ncols];
-        e0 = mfma_f64(tc[4 * ks], ge, e0);
-        o0 = mfma_f64(ts[4 * ks], go, o0);
-        if (two) {
-            e1 = mfma_f64(tc[step16 + 4 * ks], ge, e1);
-            o1 = mfma_f64(ts[step16 + 4 * ks], go, o1);
-        }
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int ncols = D.km * D.ld, nap = D.nap, na = D.na, gh = (D.nhNp + 31) >> 5;
+    // the groups of positions of one column tile on one XCD, as in the forward
+    const int item = blockIdx.x, g = (item >> 3) % gh, cb = ((item >> 3) / gh * 8 + (item & 7)) * 16;
+    if (cb >= ncols) return;   // workgroup-uniform
+    const int ht = wave & 1, kh = wave >> 1, h0 = min(g * 32 + 16 * ht, D.nhNp - 16), c = cb + li;
+    const gcdouble tc = as_global(D.cosN) + (int64_t)h0 * nap, ts = as_global(D.sinN) + (int64_t)h0 * nap;
+    const gcdouble G = as_global(q.ws) + D.offG;
+    const int full = na >> 2, cc = min(c, ncols - 1);
+    const uint32_t ot = 8 * (li * nap + lk), og = 8 * (uint32_t)(2 * lk * ncols + cc);
+    f64x4 e = F64X4_ZERO, o = F64X4_ZERO;
+    const gcdouble G0 = G + 8 * kh * (int64_t)ncols;   // every other step of four nodes
+    const Stream x[4] = {{tc + 4 * kh, 8, ot}, {ts + 4 * kh, 8, ot}, {G0, 16 * (int64_t)ncols, og},
+                         {G0 + ncols, 16 * (int64_t)ncols, og}};
+    staged<4>(x, (full - kh + 1) >> 1, [&](int, const double* y) {
+        e = mfma_f64(y[0], y[2], e);
+        o = mfma_f64(y[1], y[3], o);
     });
-    if (c >= ncols) return;
-    double* out = q.ws + D.offY + c;
+    if ((na & 3) && kh == (full & 1)) {   // the tables are zero past na
+        const int a0 = 4 * full;
+        const int64_t a = min(a0 + lk, na - 1);
+        e = mfma_f64(load_at(tc + a0, ot), G[2 * a * ncols + cc], e);
+        o = mfma_f64(load_at(ts + a0, ot), G[(2 * a + 1) * ncols + cc], o);
+    }
+    if (kh)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            red[ht][0][r][lane] = e[r];
+            red[ht][1][r][lane] = o[r];
+        }
+    __syncthreads();
+    if (kh || c >= ncols || g * 32 + 16 * ht >= D.nhNp) return;
+    gdouble out = as_global(q.ws) + D.offY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int h = g * 32 + 4 * r + lk;
-        if (h < D.nhN) {
-            out[(int64_t)(D.nN - 1 - h) * ncols] = e0[r] + o0[r];
-            if (D.nN - 1 - h != h) out[(int64_t)h * ncols] = e0[r] - o0[r];
-        }
-        if (two && h + 16 < D.nhN) {
-            const int k = h + 16;
-            out[(int64_t)(D.nN - 1 - k) * ncols] = e1[r] + o1[r];
-            if (D.nN - 1 - k != k) out[(int64_t)k * ncols] = e1[r] - o1[r];
-        }
+        const int h = h0 + 4 * r + lk, hi = D.nN - 1 - h;
+        if (h >= D.nhN) continue;
+        const double ev = e[r] + red[ht][0][r][lane], ov = o[r] + red[ht][1][r][lane];
+        out[(int64_t)hi * ncols + c] = ev + ov;
+        if (hi != h) out[(int64_t)h * ncols + c] = ev - ov;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Modal transposed: E = sum_{m even} phi_m(h) Yh[m], O = the odd modes, at 16 half-axis
-// positions and 16 columns of one N; Zh[hi] = E + O, Zh[lo] = E - O.
+// Modal transposed: E = sum_{m even} phi_m(h) Y[m], O = the odd modes, at half-axis
+// positions (the rows) and 16 columns of one N; Z[hi] = E + O, Z[lo] = E - O.  A
+// workgroup takes two tiles of 16 positions; a wave one of them and one parity.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(EA_THREADS) void ew_modal_adj_kernel(EwAdj q)
 {
+    __shared__ double red[2][4][64];
     const EwDesc& D = *q.d;
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, ct = (ld + 15) >> 4, gh = (D.nhMp + 31) >> 5;
-    int64_t u = (int64_t)blockIdx.x * EA_WAVES + (threadIdx.x >> 6);
-    const int g = (int)(u % gh);
-    u /= gh;
-    const int c = (int)(u % ct) * 16 + li, N = (int)(u / ct);
-    if (N >= D.nN) return;
-    const bool two = g * 32 + 16 < D.nhMp;
-    const double* y = q.ws + D.offY + ((int64_t)N * D.km + lk) * ld + min(c, ld - 1);
-    const double* pe = D.phie + (size_t)(g * 32 + li) * D.ket + lk;
-    const double* po = D.phio + (size_t)(g * 32 + li) * D.kot + lk;
-    const int64_t se = two ? (int64_t)16 * D.ket : 0, so = two ? (int64_t)16 * D.kot : 0;
-    f64x4 e0 = {0.0, 0.0, 0.0, 0.0}, e1 = e0, o0 = e0, o1 = e0;
-    for_steps<3>(D.kep / 4, [&](int ks) {
-        const double v = y[(int64_t)4 * ks * ld];
-        e0 = mfma_f64(pe[4 * ks], v, e0);
-        if (two) e1 = mfma_f64(pe[se + 4 * ks], v, e1);
-    });
-    y += (int64_t)D.kep * ld;
-    for_steps<3>(D.kop / 4, [&](int ks) {
-        const double v = y[(int64_t)4 * ks * ld];
-        o0 = mfma_f64(po[4 * ks], v, o0);
-        if (two) o1 = mfma_f64(po[so + 4 * ks], v, o1);
-    });
-    if (c >= ld) return;
+    const int item = blockIdx.x, g = (item >> 3) % gh, u = (item >> 3) / gh * 8 + (item & 7);
+    const int c = u % ct * 16 + li, N = u / ct;
+    if (N >= D.nN) return;   // workgroup-uniform
+    const int ht = wave & 1, odd = wave >> 1, h0 = min(g * 32 + 16 * ht, D.nhMp - 16), kt = odd ? D.kot : D.ket;
+    const gcdouble y = as_global(q.ws) + D.offY + ((int64_t)N * D.km + (odd ? D.kep : 0)) * ld;
+    const gcdouble p = as_global(odd ? D.phio : D.phie) + (int64_t)h0 * kt;
+    const uint32_t op = 8 * (li * kt + lk), oy = 8 * (lk * ld + min(c, ld - 1));
+    f64x4 t = F64X4_ZERO;
+    const Stream x[2] = {{p, 4, op}, {y, 4 * ld, oy}};
+    staged<6>(x, (odd ? D.kop : D.kep) >> 2, [&](int, const double* v) { t = mfma_f64(v[0], v[1], t); });
+    if (odd)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[ht][r][lane] = t[r];
+    __syncthreads();
+    if (odd || c >= ld || g * 32 + 16 * ht >= D.nhMp) return;
     const int64_t zs = (int64_t)D.zsM * ld;
-    double* out = q.ws + (int64_t)N * D.zsN * ld + c;
+    gdouble out = as_global(q.ws) + (int64_t)N * D.zsN * ld + c;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int h = g * 32 + 4 * r + lk;
-        if (h < D.nhM) {
-            out[(D.nM - 1 - h) * zs] = e0[r] + o0[r];
-            if (D.nM - 1 - h != h) out[h * zs] = e0[r] - o0[r];
-        }
-        if (two && h + 16 < D.nhM) {
-            const int k = h + 16;
-            out[(D.nM - 1 - k) * zs] = e1[r] + o1[r];
-            if (D.nM - 1 - k != k) out[k * zs] = e1[r] - o1[r];
-        }
+        const int h = h0 + 4 * r + lk, hi = D.nM - 1 - h;
+        if (h >= D.nhM) continue;
+        const double o = red[ht][r][lane];
+        out[hi * zs] = t[r] + o;
+        if (hi != h) out[h * zs] = t[r] - o;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Walk: 16 columns, rounds of EW_ZC slices from the exit face back.  A first pass sums
-// beta + i delta of each round (the exclusive prefix S of a round's first slice); then,
-// round by round, R = exp(-i qc z) sum_l phi_l(z) Zh comes from the matrix instruction
-// (rows columns, K the modes, columns the slices) through LDS to the thread that holds
-// the slice, and sum_{s'>s} R w accumulates on the way.  FP64, T in FP32 as the scan
-// forms it.
+// Walk: R = dV exp(-i qc z) sum_l phi_l(z) Z of 16 columns from the matrix instruction
+// (rows columns, K the modes, columns the slices) through LDS to the lane that holds the
+// slice, then the chain rule along the column.  With P = R T and n = 1 - delta + i beta
+// the slice's own terms are -4 P n (real part for delta, imaginary for beta),
+// R w = P (n^2 - 1), and sum_{s'>s} R w is the later lanes' plus the lane's own.  Lanes,
+// slices and T as in the scan.
 // ---------------------------------------------------------------------------
-constexpr int EA_LD = EW_COLS + 1;
+
+// The chain rule of a lane's K slices, L lanes to a column; (ur, ui): LDS of
+// sum_l phi_l Z at its first slice.  In: carry = sum of R w past the round; out: that of
+// the round added.
+template <int STRENGTH, int K, int L>
+__device__ __forceinline__ void ew_chain(const float* d, const float* b, double Sb, double Sd, double k0dz,
+                                         gcdouble rot, const double* ur, const double* ui, double* carry,
+                                         float* gd, float* gb)
+{
+    Transmission T;
+    if (STRENGTH == MSFT_STRENGTH_MSFT) T.start<K>(Sb, Sd, b, d, k0dz);
+    const double scale = 2.0 * k0dz;
+    double vd[K], vb[K], wr = 0.0, wi = 0.0;   // the slices' own terms; sum of R w so far
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double xr = ur[k * EA_LD], xi = ui[k * EA_LD], ex = rot[2 * k], ey = rot[2 * k + 1];
+        double pr = xr * ex - xi * ey, pi = xr * ey + xi * ex;
+        if (STRENGTH == MSFT_STRENGTH_DENSITY) {
+            vd[k] = 2.0 * pr;
+            vb[k] = -2.0 * pi;
+            continue;
+        }
+        const double dk = d[k], bk = b[k], nr = 1.0 - dk;
+        if (STRENGTH == MSFT_STRENGTH_MSFT) {
+            const double t = pr, chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * nr;
+            pr = t * T.tr - pi * T.ti;
+            pi = t * T.ti + pi * T.tr;
+            wr += pr * chr - pi * chi;
+            wi += pr * chi + pi * chr;
+        }
+        vd[k] = -4.0 * (pr * nr - pi * bk);
+        vb[k] = -4.0 * (pr * bk + pi * nr);
+        if (STRENGTH == MSFT_STRENGTH_MSFT) {
+            // what follows the slice is the sum past the lane's last, less what the lane had here
+            vd[k] -= scale * wi;
+            vb[k] += scale * wr;
+            if (k + 1 < K) T.next(bk, dk);
+        }
+    }
+    double er = 0.0, ei = 0.0;
+    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+        const double qr = group_prefix_f64<L>(wr), qi = group_prefix_f64<L>(wi);
+        const double sr = group_last_f64<L>(qr), si = group_last_f64<L>(qi);
+        er = scale * ((carry[0] + (sr - qr)) + wr);
+        ei = scale * ((carry[1] + (si - qi)) + wi);
+        carry[0] += sr;
+        carry[1] += si;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        gd[k] = (float)(vd[k] + ei);
+        gb[k] = (float)(vb[k] - er);
+    }
+}
+
+template <int K>
+__device__ __forceinline__ void store_slices(float* od, float* ob, int z, int nz, const float* gd, const float* gb)
+{
+    if (K % 4 == 0 && (nz & 3) == 0) {
+#pragma unroll
+        for (int k = 0; k + 3 < K; k += 4)
+            if (z + k < nz) {
+                *(float4*)(od + z + k) = make_float4(gd[k], gd[k + 1], gd[k + 2], gd[k + 3]);
+                *(float4*)(ob + z + k) = make_float4(gb[k], gb[k + 1], gb[k + 2], gb[k + 3]);
+            }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (z + k < nz) {
+            od[z + k] = gd[k];
+            ob[z + k] = gb[k];
+        }
+}
+
+// Whole columns, as in the scan (rows of the products: 16 columns, Re and Im apart, or 8
+// columns' (Re, Im)): even and odd modes on the half axis, E + O and E - O the mirror
+// slices.  A wave takes every fourth (Re or Im and every other) tile of 16 half-axis slices.
+template <int STRENGTH, int COLS, int K>
+__device__ __forceinline__ void ew_walk_whole(const EwAdj& q, double* sm)
+{
+    constexpr int L = EA_THREADS / COLS, NZ = L * K;
+    const EwDesc& D = *q.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
+    const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)blockIdx.x * COLS;
+    const bool in = c0 + cl < ncol;
+    const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
+    float d[K], b[K];
+    load_slices<K>(q.delta + off, q.beta + off, z0, nz, in, d, b);
+    // slices past the column's end
+    for (int k = nz * EA_LD + tid; k < NZ * EA_LD; k += EA_THREADS) {
+        sm[k] = 0.0;
+        if (COLS == 16) sm[NZ * EA_LD + k] = 0.0;
+    }
+    {
+        const int set = COLS == 16 ? wave & 1 : 0, nh = (nz + 1) >> 1, kze = D.kze, kzo = D.kz - kze, last = D.kzp - 1;
+        const int col = COLS == 16 ? li : li >> 1, ri = COLS == 16 ? set : li & 1;
+        const uint32_t oz = 8 * (uint32_t)((min(c0 + col, ncol - 1) - c0) * D.ld + 2 * lk);
+        const uint32_t ze = oz + 8 * ri, zo = oz + 8 * (1 - ri);   // -i of the odd modes: (im, -re)
+        const double sign = ri ? -1.0 : 1.0;
+        const gcdouble z = as_global(q.ws) + c0 * D.ld;
+        const int step = COLS == 16 ? 32 : 64;
+        for (int h0 = COLS == 16 ? 16 * (wave >> 1) : 16 * wave; h0 < nh; h0 += step) {
+            f64x4 e = F64X4_ZERO, o = F64X4_ZERO;
+            const Stream se[2] = {{z, 8, ze}, {as_global(D.phize) + (int64_t)h0 * D.kzet, 4, (uint32_t)(8 * (li * D.kzet + lk))}};
+            const Stream so[2] = {{z + 2 * kze, 8, zo},
+                                  {as_global(D.phizo) + (int64_t)h0 * D.kzot, 4, (uint32_t)(8 * (li * D.kzot + lk))}};
+            staged<4>(se, kze >> 2, [&](int, const double* x) { e = mfma_f64(x[0], x[1], e); });
+            staged<4>(so, kzo >> 2, [&](int, const double* x) { o = mfma_f64(x[0] * sign, x[1], o); });
+            // the last modes; the half-axis modes are zero past them, what they meet is finite
+            if (kze & 3) {
+                const int l = kze & ~3;
+                e = mfma_f64(load_at(z, ze + 16 * (min(l + lk, last) - lk)), load_at(se[1].p + l, se[1].off), e);
+            }
+            if (kzo & 3) {
+                const int l = kzo & ~3;
+                o = mfma_f64(sign * load_at(z, zo + 16 * (min(kze + l + lk, last) - lk)), load_at(so[1].p + l, so[1].off), o);
+            }
+            const int h = h0 + li;
+            if (h < nh) {
+                double* hi = sm + (set * NZ + nz - 1 - h) * EA_LD + lk;
+                double* lo = sm + (set * NZ + h) * EA_LD + lk;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    lo[4 * r] = e[r] - o[r];
+                    hi[4 * r] = e[r] + o[r];   // an odd column's middle: o is zero
+                }
+            }
+        }
+    }
+    __syncthreads();
+    double Sb = 0.0, Sd = 0.0;
+    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+        double sb = 0.0, sd = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            sb += (double)b[k];
+            sd += (double)d[k];
+        }
+        Sb = group_prefix_f64<L>(sb) - sb;
+        Sd = group_prefix_f64<L>(sd) - sd;
+    }
+    double carry[2] = {0.0, 0.0};
+    float gd[K], gb[K];
+    const double* u = sm + z0 * EA_LD + (COLS == 16 ? cl : 2 * cl);
+    ew_chain<STRENGTH, K, L>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * z0, u, u + (COLS == 16 ? NZ * EA_LD : 1),
+                             carry, gd, gb);
+    if (in) store_slices<K>(q.grad_delta + off, q.grad_beta + off, z0, nz, gd, gb);
+}
+
+template <int COLS, int K>
+__global__ __launch_bounds__(EA_THREADS, K == 8 ? 3 : 4) void ew_walk_kernel(EwAdj q)
+{
+    __shared__ double sm[32 * K * EA_LD];   // Re and Im of 16 lanes' slices, or 32 lanes'
+    const int strength = q.d->strength;
+    if (strength == MSFT_STRENGTH_MSFT) ew_walk_whole<MSFT_STRENGTH_MSFT, COLS, K>(q, sm);
+    else if (strength == MSFT_STRENGTH_BORN) ew_walk_whole<MSFT_STRENGTH_BORN, COLS, K>(q, sm);
+    else ew_walk_whole<MSFT_STRENGTH_DENSITY, COLS, K>(q, sm);
+}
+
+// Longer columns, in rounds of 64 slices from the exit face back, after a pass that sums
+// beta + i delta of each round.
 constexpr int EA_ROUNDS = 4096 / EW_ZC;
 
-__global__ __launch_bounds__(EA_THREADS) void ew_walk_kernel(EwAdj q)
+template <int STRENGTH>
+__device__ __forceinline__ void ew_walk_rounds(const EwAdj& q, double* sm, double* pre)
 {
-    __shared__ double sm[2][EW_ZC * EA_LD];
-    __shared__ double pre[2][EA_ROUNDS][EW_COLS];   // beta, delta before each round
     const EwDesc& D = *q.d;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, strength = D.strength;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
+    const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, kzt = D.kzt, kze = D.kze;
     const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)blockIdx.x * EW_COLS;
     const bool in = c0 + cl < ncol;
-    const int64_t col = in ? c0 + cl : ncol - 1;
-    const float* dc = q.delta + col * nz;
-    const float* bc = q.beta + col * nz;
-    const bool vec = (nz & 3) == 0;
+    const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
     const int rounds = (nz + EW_ZC - 1) / EW_ZC;
     float d[4], b[4];
-    auto load = [&](int z) {
-        if (in && vec && z < nz) {
-            const float4 dv = *(const float4*)(dc + z), bv = *(const float4*)(bc + z);
-            d[0] = dv.x; d[1] = dv.y; d[2] = dv.z; d[3] = dv.w;
-            b[0] = bv.x; b[1] = bv.y; b[2] = bv.z; b[3] = bv.w;
-            return;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool ok = in && z + k < nz;
-            d[k] = ok ? dc[z + k] : 0.0f;
-            b[k] = ok ? bc[z + k] : 0.0f;
-        }
-    };
-    if (strength == MSFT_STRENGTH_MSFT) {
+    if (STRENGTH == MSFT_STRENGTH_MSFT) {
         double tb = 0.0, td = 0.0;
-        for (int r = 0; r + 1 < rounds; ++r) {
-            load(r * EW_ZC + zl);
+        for (int r = 0; r < rounds; ++r) {
             if ((tid & 15) == 0) {
-                pre[0][r][cl] = tb;
-                pre[1][r][cl] = td;
+                pre[(2 * r) * EW_COLS + cl] = tb;
+                pre[(2 * r + 1) * EW_COLS + cl] = td;
             }
+            if (r + 1 == rounds) break;
+            load_slices<4>(q.delta + off, q.beta + off, r * EW_ZC + zl, nz, in, d, b);
             tb += row_last_f64(row_prefix_f64(((double)b[0] + b[1]) + ((double)b[2] + b[3])));
             td += row_last_f64(row_prefix_f64(((double)d[0] + d[1]) + ((double)d[2] + d[3])));
         }
-        if ((tid & 15) == 0) {
-            pre[0][rounds - 1][cl] = tb;
-            pre[1][rounds - 1][cl] = td;
-        }
     }
-    const double dV = D.dV64, k0dz = D.k0dz64;
     const int ri = wave & 1, zt = (wave >> 1) * 32;
-    const double* zh = q.ws + min(c0 + (lane & 15), ncol - 1) * D.ld;
-    double carry_r = 0.0, carry_i = 0.0;
+    const double* zh = q.ws + min(c0 + li, ncol - 1) * D.ld;
+    double carry[2] = {0.0, 0.0};
     for (int rd = rounds - 1; rd >= 0; --rd) {
         const int z0 = rd * EW_ZC;
-        load(z0 + zl);
+        load_slices<4>(q.delta + off, q.beta + off, z0 + zl, nz, in, d, b);
         {
-            f64x4 r0 = {0.0, 0.0, 0.0, 0.0}, r1 = r0;
-            const double* p = D.phiz + (size_t)(z0 + zt + (lane & 15)) * D.kzt;
-            for_steps<2>(D.kzp / 4, [&](int ks) {
-                const int l = 4 * ks + (lane >> 4);
-                const bool odd = l >= D.kze;   // -i of the odd modes: (im, -re)
+            f64x4 r0 = F64X4_ZERO, r1 = F64X4_ZERO;
+            gcdouble p = as_global(D.phiz) + (int64_t)(z0 + zt + li) * kzt;
+            for_steps<4>(D.kzp / 4, [&](int ks) {
+                const int l = 4 * ks + lk;
+                const bool odd = l >= kze;   // -i of the odd modes: (im, -re)
                 double v = zh[2 * l + (odd ? 1 - ri : ri)];
                 if (odd && ri) v = -v;
                 r0 = mfma_f64(v, p[l], r0);
-                r1 = mfma_f64(v, p[(size_t)16 * D.kzt + l], r1);
+                r1 = mfma_f64(v, p[16 * kzt + l], r1);
             });
-            double* o = sm[ri] + (zt + (lane & 15)) * EA_LD + (lane >> 4);
+            double* o = sm + (ri * EW_ZC + zt + li) * EA_LD + lk;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 o[4 * r] = r0[r];
@@ -363,81 +521,30 @@ __global__ __launch_bounds__(EA_THREADS) void ew_walk_kernel(EwAdj q)
             }
         }
         __syncthreads();
-        double gd[4], gb[4], rwr[4], rwi[4];
         double Sb = 0.0, Sd = 0.0;
-        if (strength == MSFT_STRENGTH_MSFT) {
+        if (STRENGTH == MSFT_STRENGTH_MSFT) {
             const double sb = ((double)b[0] + b[1]) + ((double)b[2] + b[3]);
             const double sd = ((double)d[0] + d[1]) + ((double)d[2] + d[3]);
-            Sb = pre[0][rd][cl] + (row_prefix_f64(sb) - sb);
-            Sd = pre[1][rd][cl] + (row_prefix_f64(sd) - sd);
+            Sb = pre[2 * rd * EW_COLS + cl] + (row_prefix_f64(sb) - sb);
+            Sd = pre[(2 * rd + 1) * EW_COLS + cl] + (row_prefix_f64(sd) - sd);
         }
-        const double2* rot = (const double2*)D.rot + z0 + zl;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double ur = sm[0][(zl + k) * EA_LD + cl], ui = sm[1][(zl + k) * EA_LD + cl];
-            const double2 e = rot[k];
-            const double rr = ur * e.x - ui * e.y, rim = ur * e.y + ui * e.x;
-            rwr[k] = rwi[k] = 0.0;
-            if (strength == MSFT_STRENGTH_DENSITY) {
-                gd[k] = 2.0 * dV * rr;
-                gb[k] = -2.0 * dV * rim;
-                continue;
-            }
-            const double dd = d[k], bb = b[k];
-            double tr = 1.0, ti = 0.0;
-            if (strength == MSFT_STRENGTH_MSFT) {
-                constexpr double kTwoPi = 6.283185307179586476925286766559;
-                const double ph = -k0dz * Sd;
-                const float mag = expf((float)(-k0dz * Sb));
-                float sn, cs;
-                sincosf((float)(ph - kTwoPi * rint(ph * (1.0 / kTwoPi))), &sn, &cs);
-                tr = (double)mag * (double)cs;
-                ti = (double)mag * (double)sn;
-            }
-            // dw/d delta = dV T (-2 n), dw/d beta = dV T (2 i n), n = 1 - delta + i beta
-            const double nr = 1.0 - dd;
-            const double xr = 2.0 * dV * (tr * nr - ti * bb), xi = 2.0 * dV * (tr * bb + ti * nr);
-            gd[k] = -2.0 * (rr * xr - rim * xi);
-            gb[k] = -2.0 * (rr * xi + rim * xr);
-            if (strength == MSFT_STRENGTH_MSFT) {
-                const double chr = dd * (dd - 2.0) - bb * bb, chi = 2.0 * bb * (1.0 - dd);
-                const double wr = dV * (chr * tr - chi * ti), wi = dV * (chr * ti + chi * tr);
-                rwr[k] = rr * wr - rim * wi;
-                rwi[k] = rr * wi + rim * wr;
-                Sb += bb;
-                Sd += dd;
-            }
-        }
-        if (strength == MSFT_STRENGTH_MSFT) {
-            const double lr = (rwr[0] + rwr[1]) + (rwr[2] + rwr[3]), im = (rwi[0] + rwi[1]) + (rwi[2] + rwi[3]);
-            const double pr = row_prefix_f64(lr), pi = row_prefix_f64(im);
-            const double tr = row_last_f64(pr), ti = row_last_f64(pi);
-            double er = carry_r + (tr - pr), ei = carry_i + (ti - pi);   // later lanes and rounds
-#pragma unroll
-            for (int k = 3; k >= 0; --k) {
-                gd[k] += 2.0 * k0dz * ei;
-                gb[k] -= 2.0 * k0dz * er;
-                er += rwr[k];
-                ei += rwi[k];
-            }
-            carry_r += tr;
-            carry_i += ti;
-        }
-        float* od = q.grad_delta + col * nz + z0 + zl;
-        float* ob = q.grad_beta + col * nz + z0 + zl;
-        if (in && vec && z0 + zl < nz) {
-            *(float4*)od = make_float4((float)gd[0], (float)gd[1], (float)gd[2], (float)gd[3]);
-            *(float4*)ob = make_float4((float)gb[0], (float)gb[1], (float)gb[2], (float)gb[3]);
-        } else if (in) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (z0 + zl + k < nz) {
-                    od[k] = (float)gd[k];
-                    ob[k] = (float)gb[k];
-                }
-        }
+        float gd[4], gb[4];
+        const double* u = sm + zl * EA_LD + cl;
+        ew_chain<STRENGTH, 4, 16>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * (z0 + zl), u, u + EW_ZC * EA_LD, carry,
+                              gd, gb);
+        if (in) store_slices<4>(q.grad_delta + off, q.grad_beta + off, z0 + zl, nz, gd, gb);
         __syncthreads();   // the next round rewrites sm
     }
+}
+
+__global__ __launch_bounds__(EA_THREADS) void ew_walk_rounds_kernel(EwAdj q)
+{
+    __shared__ double sm[2 * EW_ZC * EA_LD];
+    __shared__ double pre[2 * EA_ROUNDS * EW_COLS];   // beta, delta before each round
+    const int strength = q.d->strength;
+    if (strength == MSFT_STRENGTH_MSFT) ew_walk_rounds<MSFT_STRENGTH_MSFT>(q, sm, pre);
+    else if (strength == MSFT_STRENGTH_BORN) ew_walk_rounds<MSFT_STRENGTH_BORN>(q, sm, pre);
+    else ew_walk_rounds<MSFT_STRENGTH_DENSITY>(q, sm, pre);
 }
 
 }  // namespace
@@ -445,17 +552,25 @@ __global__ __launch_bounds__(EA_THREADS) void ew_walk_kernel(EwAdj q)
 int launch_ew_adjoint(const EwAdj& a, const EwDesc& d, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    auto blocks = [](int64_t waves) { return dim3((unsigned)ceil_div(waves, EA_WAVES)); };
-    const dim3 th(EA_THREADS);
-    // a wave's sums are 64 n bytes of LDS: four waves up to 256 nodes, two up to the limit of 512
-    const int rw = d.n <= 256 ? EA_WAVES : 2;
-    hipLaunchKernelGGL(ew_rows_kernel, dim3(d.rows), dim3(64 * rw), d.n * 8 * rw * sizeof(double), s, a);
-    const int64_t mt = ceil_div(d.kep, 16) + ceil_div(d.kop, 16);
-    hipLaunchKernelGGL(ew_yz_adj_kernel, blocks(2 * d.na * mt * ceil_div(d.ld, 64)), th, 0, s, a);
-    hipLaunchKernelGGL(ew_nodes_adj_kernel,
-                       blocks(ceil_div((int64_t)d.km * d.ld, 16) * ceil_div(d.nhNp, 32)), th, 0, s, a);
-    hipLaunchKernelGGL(ew_modal_adj_kernel, blocks(ceil_div(d.ld, 16) * ceil_div(d.nhMp, 32) * d.nN), th, 0, s, a);
-    hipLaunchKernelGGL(ew_walk_kernel, dim3((unsigned)ceil_div((int64_t)d.nx * d.ny, EW_COLS)), th, 0, s, a);
+    auto launch = [&](auto kernel, int64_t blocks, int threads, size_t lds) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), lds, s, a);
+    };
+    // `inner` workgroups of each of `outer` units on one XCD
+    auto on_xcd = [](int64_t outer, int64_t inner) { return ceil_div(outer, 8) * 8 * inner; };
+    launch(ew_rows_kernel, d.rows, EA_THREADS, 0);
+    launch(ew_coef_adj_kernel, d.nrp / 16 * 8, CA_THREADS, d.n * 17 * sizeof(double));
+    launch(ew_yz_adj_kernel, on_xcd(d.na, 2 * ceil_div(d.kep > d.kop ? d.kep : d.kop, 32) * ceil_div(d.ld, 32)),
+           EA_THREADS, 0);
+    launch(ew_nodes_adj_kernel, on_xcd(ceil_div((int64_t)d.km * d.ld, 16), ceil_div(d.nhNp, 32)), EA_THREADS, 0);
+    launch(ew_modal_adj_kernel, on_xcd(ceil_div(d.ld, 16) * d.nN, ceil_div(d.nhMp, 32)), EA_THREADS, 0);
+    const int64_t cols = ceil_div((int64_t)d.nx * d.ny, ew_columns(d.nz));
+    switch (ew_rounds(d.nz)) {
+    case 1: launch(ew_walk_kernel<16, 4>, cols, EA_THREADS, 0); break;
+    case 2: launch(ew_walk_kernel<16, 8>, cols, EA_THREADS, 0); break;
+    case 3: launch(ew_walk_kernel<8, 6>, cols, EA_THREADS, 0); break;
+    case 4: launch(ew_walk_kernel<8, 8>, cols, EA_THREADS, 0); break;
+    default: launch(ew_walk_rounds_kernel, cols, EA_THREADS, 0);
+    }
     return (int)hipGetLastError();
 }
 

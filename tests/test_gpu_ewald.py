@@ -1,5 +1,5 @@
 """The spherical-coordinate form of the forward model and its adjoint (the path of every
-flat-detector plan with work enough) at the sizes where its kernels change shape, against the
+detector plan with work enough) at the sizes where its kernels change shape, against the
 FP64 oracle.
 
 Tolerance: the sums run in FP64 on bases truncated at 3e-11, so what is left is the FP32
@@ -44,6 +44,9 @@ CASES = [
     ((150, 140, 100), 4, (6.0, 6.0, 6.0), 45.0, "msft"),    # fewer pixels than nodes
     ((24, 22, 26), 300, (1.0, 1.0, 1.0), 5.0, "msft"),      # a narrow range: few modes and nodes
     ((30, 30, 30), 128, (25.0, 25.0, 24.0), 30.0, "msft"),  # pitch near the sampling limit
+    ((40, 41, 200), 40, (6.0, 6.0, 3.0), 60.0, "msft"),     # columns of four rounds, one not whole
+    ((41, 40, 150), 41, (6.0, 6.0, 3.0), 60.0, "born"),     # three rounds, unaligned rows
+    ((190, 190, 4), 20, (22.0, 22.0, 5.0), 80.0, "msft"),   # over 300 nodes
 ]
 
 
