@@ -507,14 +507,6 @@ EwReq ew_request(const msft_plan_s* p, const float* delta, const float* beta, fl
     return EwReq{p->ew_dev, delta, beta, intensity, amplitude, (double*)workspace, p0, p1};
 }
 
-EwBatch ew_single(const EwReq& r)
-{
-    EwBatch b;
-    b.req[0] = r;
-    b.n = 1;
-    return b;
-}
-
 // The contraction of a plan after the scan: one launch for the flat detector,
 // the two stages for the separable one.
 int launch_contraction(const msft_plan_s* p, const void* workspace, float* intensity,
@@ -522,8 +514,10 @@ int launch_contraction(const msft_plan_s* p, const void* workspace, float* inten
 {
     if (p->ew.use) {
         const EwDesc* dims = &p->ew.d;
-        return launch_ew_contract(ew_single(ew_request(p, nullptr, nullptr, intensity, amplitude, workspace,
-                                                       0, p->dims.npix)), &dims, stream);
+        EwBatch b;
+        b.n = 1;
+        b.req[0] = ew_request(p, nullptr, nullptr, intensity, amplitude, workspace, 0, p->dims.npix);
+        return launch_ew_contract(b, &dims, stream);
     }
     const int prec = p->geo.g.precision;
     if (p->separable && p->sep.gauss) return launch_sepg(sepg_args(p, workspace, intensity, amplitude), stream);
@@ -565,7 +559,10 @@ int launch_target_scan(const msft_plan_s* p, const float* delta, const float* be
 {
     if (!p->ew.use) return launch_scan(p->geo.g.precision, scan_args(p, delta, beta, workspace), stream);
     const EwDesc* dims = &p->ew.d;
-    return launch_ew_scan(ew_single(ew_request(p, delta, beta, nullptr, nullptr, workspace, 0, 0)), &dims, stream);
+    EwBatch b;
+    b.n = 1;
+    b.req[0] = ew_request(p, delta, beta, nullptr, nullptr, workspace, 0, 0);
+    return launch_ew_scan(b, &dims, stream);
 }
 
 msft_status check_runnable(const msft_plan_s* p)

@@ -337,6 +337,8 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     d.strength = g.strength;
     d.k0dz64 = k0 * g.dz;
     d.dV64 = g.dx * g.dy * g.dz;
+    d.step_r = std::cos(H.qc * g.dz);
+    d.step_i = -std::sin(H.qc * g.dz);
     d.nN = uni ? g.ny : g.nx;
     d.nM = uni ? g.nx : g.ny;
     d.zsN = uni ? 1 : g.ny;

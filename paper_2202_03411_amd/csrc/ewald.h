@@ -62,7 +62,8 @@ struct EwDesc {
     int32_t n, nr, nrp;         // nodes of the pixels' angle and of the rows' (padded to 16)
     int32_t rows, rowsp;        // pixel rows: half the detector, rounded up; padded to 16
     int32_t det_n;
-    const double* rot;          // [nz padded to EW_ZC] dV (cos, -sin)(qc z)
+    double step_r, step_i;      // exp(-i qc dz)
+    const double* rot;          // [nz padded to EW_ZC] dV exp(-i qc z)
     const double* phiz;         // [nz padded to EW_ZC][kzt]
     const double* phize;        // even and odd z modes on the half axis, [(nz + 1) / 2 padded to 16]
     const double* phizo;        // x [kzet], [kzot]
@@ -142,8 +143,8 @@ struct EwTables {
     double *cosN, *sinN, *cm, *cz;
 };
 int launch_ew_tables(const EwHost& h, const EwDesc& dev, const EwTables& t, void* stream);
-int launch_ew_scan(EwBatch b, const EwDesc* const* dims, void* stream);
-int launch_ew_contract(EwBatch b, const EwDesc* const* dims, void* stream);
+int launch_ew_scan(const EwBatch& b, const EwDesc* const* dims, void* stream);
+int launch_ew_contract(EwBatch& b, const EwDesc* const* dims, void* stream);
 int launch_ew_adjoint(const EwAdj& a, const EwDesc& dims, void* stream);
 
 }  // namespace msft

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ewald.h"
 #include "msft_internal.h"
@@ -20,15 +21,20 @@ namespace msft {
 namespace {
 
 constexpr int EW_THREADS = 256;
-constexpr int EW_LD = EW_COLS + 1;   // doubles of a slice's columns in LDS
 
-// The request a workgroup belongs to and its index within it.
+// The request a workgroup belongs to and its index within it.  The kernels take one request
+// (72 bytes of arguments: 2.7 us a launch on the host) or a batch (1.5 KB: 4.0 us).
 __device__ __forceinline__ const EwReq& ew_request(const EwBatch& b, int& item)
 {
     int r = 0;
     while (r + 1 < b.n && (int)blockIdx.x >= b.begin[r + 1]) ++r;
     item = (int)blockIdx.x - b.begin[r];
     return b.req[r];
+}
+__device__ __forceinline__ const EwReq& ew_request(const EwReq& r, int& item)
+{
+    item = (int)blockIdx.x;
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -46,37 +52,43 @@ __device__ __forceinline__ const EwReq& ew_request(const EwBatch& b, int& item)
 // differences of mirror slices against the half-axis modes, half as many.
 // ---------------------------------------------------------------------------
 
-// dV w exp(-i qc z) of a lane's K slices into LDS (a slice's row is EW_LD doubles), (Sb, Sd)
-// the sums before the first.
-template <int STRENGTH, int K>
-__device__ __forceinline__ void ew_strength(const float* d, const float* b, double Sb, double Sd, double k0dz,
-                                            gcdouble rot, double* re, double* im)
+// dV w exp(-i qc z) of a lane's K slices from z on into LDS, (Sb, Sd) the sums before the
+// first, (r0, r1) the rotation there.
+template <bool MSFT, int K>
+__device__ __forceinline__ void ew_strength(const EwDesc& D, const float* d, const float* b, double Sb, double Sd,
+                                            double r0, double r1, int z, double* re, double* im)
 {
-    Transmission T;
-    if (STRENGTH == MSFT_STRENGTH_MSFT) T.start<K>(Sb, Sd, b, d, k0dz);
+    Propagator<MSFT> P;
+    P.template start<K>(Sb, Sd, b, d, D.k0dz64, r0, r1, D.step_r, D.step_i);
+    const bool density = !MSFT && D.strength == MSFT_STRENGTH_DENSITY;
+    auto slices = [&](auto small) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double dk = d[k], bk = b[k];
-        double wr = dk, wi = bk;
-        if (STRENGTH != MSFT_STRENGTH_DENSITY) {
-            const double chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * (1.0 - dk);
-            wr = STRENGTH == MSFT_STRENGTH_MSFT ? chr * T.tr - chi * T.ti : chr;
-            wi = STRENGTH == MSFT_STRENGTH_MSFT ? chr * T.ti + chi * T.tr : chi;
+        for (int k = 0; k < K; ++k) {
+            const double dk = d[k], bk = b[k];
+            double chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * (1.0 - dk);
+            if (density) {
+                chr = dk;
+                chi = bk;
+            }
+            re[slice_row(z + k)] = chr * P.tr - chi * P.ti;
+            im[slice_row(z + k)] = chr * P.ti + chi * P.tr;
+            if (k + 1 < K) P.template next<decltype(small)::value>(bk, dk);
         }
-        const double ex = rot[2 * k], ey = rot[2 * k + 1];
-        re[k * EW_LD] = wr * ex - wi * ey;
-        im[k * EW_LD] = wr * ey + wi * ex;
-        if (STRENGTH == MSFT_STRENGTH_MSFT && k + 1 < K) T.next(bk, dk);
-    }
+    };
+    if (!MSFT || P.small) slices(std::true_type{});
+    else slices(std::false_type{});
 }
 
 // Whole columns: COLS of them, 256 / COLS lanes of K slices each.  The products' rows are
 // 16 columns, Re and Im apart (COLS = 16: a wave takes one of them and one parity of the
-// modes), or 8 columns' (Re, Im) (COLS = 8: a wave takes one parity and half of the slices).
-template <int STRENGTH, int COLS, int K>
+// modes), or 8 columns' (Re, Im) (COLS = 8: a wave takes one parity and every other step).
+// NT tiles of 16 modes share an operand.  Nothing the first products need but the strength
+// itself is waited for after it: their mode operands are loaded with the voxels, later ones
+// a block of steps ahead.
+template <bool MSFT, int COLS, int K, int NT>
 __device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* sm)
 {
-    constexpr int L = EW_THREADS / COLS, NZ = L * K;
+    constexpr int L = EW_THREADS / COLS, NZ = L * K, U = NT == 1 ? 8 : NT == 2 ? 6 : 4;
     const EwDesc& D = *q.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
@@ -85,8 +97,30 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* 
     const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
     float d[K], b[K];
     load_slices<K>(q.delta + off, q.beta + off, z0, nz, in, d, b);
+    const gcdouble rot = as_global(D.rot) + 2 * min(z0, (nz + EW_ZC - 1) / EW_ZC * EW_ZC - 1);
+    const double r0 = rot[0], r1 = rot[1];
+    const int odd = wave & 1, sub = wave >> 1, kze = D.kze, kz = odd ? D.kz - kze : kze, kzt = odd ? D.kzot : D.kzet;
+    const int full = nz >> 3, nh = (nz + 1) >> 1;   // whole steps of four mirror pairs; half the column
+    // this wave's steps: all of them, or every other one; the last may be the rest (its pairs,
+    // an odd column's middle)
+    constexpr int stride = COLS == 16 ? 1 : 2;
+    const int first = COLS == 16 ? 0 : sub;
+    const int steps = ((4 * full < nh ? full + 1 : full) - first + stride - 1) / stride;
+    const gcdouble phi = as_global(odd ? D.phizo : D.phize);
+    const uint32_t po = 8 * (lk * kzt + li);
+    auto load = [&](int k, int at, double (*x)[NT]) {   // steps k ... k + U - 1, past the end the last
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const gcdouble p = phi + 4 * (first + stride * max(min(k + u, steps - 1), 0)) * kzt;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) x[u][t] = load_at(p + (at + 16 * t < kzt ? at + 16 * t : 0), po);
+        }
+    };
+    double x[U][NT];
+    load(0, 0, x);
+    __builtin_amdgcn_sched_barrier(0);
     double Sb = 0.0, Sd = 0.0;
-    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+    if (MSFT) {
         double sb = 0.0, sd = 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -96,77 +130,78 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* 
         Sb = group_prefix_f64<L>(sb) - sb;
         Sd = group_prefix_f64<L>(sd) - sd;
     }
-    double* o = sm + z0 * EW_LD + (COLS == 16 ? cl : 2 * cl);
-    ew_strength<STRENGTH, K>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * z0, o, o + (COLS == 16 ? NZ * EW_LD : 1));
+    double* o = sm + (COLS == 16 ? cl : 2 * cl);
+    ew_strength<MSFT, K>(D, d, b, Sb, Sd, r0, r1, z0, o, o + (COLS == 16 ? slice_row(NZ) : 1));
     __syncthreads();
-    const int odd = wave & 1, sub = wave >> 1, kze = D.kze, kz = odd ? D.kz - kze : kze, kzt = odd ? D.kzot : D.kzet;
-    const int full = nz >> 3, nh = (nz + 1) >> 1;   // whole steps of four mirror pairs; half the column
-    // steps of this wave: all of them, or every other one
-    const int first = COLS == 16 ? 0 : sub, stride = COLS == 16 ? 1 : 2, steps = (full - first + stride - 1) / stride;
-    const bool tail = 4 * full < nh && (COLS == 16 || sub == (full & 1));
-    const gcdouble phi = as_global(odd ? D.phizo : D.phize);
-    const double* a = sm + (COLS == 16 ? sub * NZ * EW_LD : 0) + li;
+    const double* a = sm + (COLS == 16 ? sub * slice_row(NZ) : 0) + li;
     const double mirror = odd ? -1.0 : 1.0;
-    const uint32_t po = 8 * (lk * kzt + li);
-    gdouble out = as_global(q.ws) + c0 * D.ld;
-    // up to three tiles of 16 modes share the operand; both parities make the same passes, one
-    // past its last tile repeats the first and stores nothing
-    for (int t0 = 0; t0 < max(kze, D.kz - kze); t0 += 48) {
-        const int at = t0 < kzt ? t0 : 0, n1 = t0 + 16 < kzt ? 16 : 0, n2 = t0 + 32 < kzt ? 32 : 0;
-        f64x4 t[3] = {F64X4_ZERO, F64X4_ZERO, F64X4_ZERO};
-        const gcdouble p = phi + at + 4 * first * kzt;
-        const int64_t inc = (int64_t)4 * stride * kzt;
-        auto operand = [&](int ks) {
-            const int h = 4 * (first + stride * ks) + lk;
-            return a[(nz - 1 - h) * EW_LD] + mirror * a[h * EW_LD];
-        };
-        if (n2) {
-            const Stream s[3] = {{p, inc, po}, {p + n1, inc, po}, {p + n2, inc, po}};
-            staged<4>(s, steps, [&](int ks, const double* x) {
-                const double v = operand(ks);
-                t[0] = mfma_f64(v, x[0], t[0]);
-                t[1] = mfma_f64(v, x[1], t[1]);
-                t[2] = mfma_f64(v, x[2], t[2]);
-            });
-        } else if (n1) {
-            const Stream s[2] = {{p, inc, po}, {p + n1, inc, po}};
-            staged<4>(s, steps, [&](int ks, const double* x) {
-                const double v = operand(ks);
-                t[0] = mfma_f64(v, x[0], t[0]);
-                t[1] = mfma_f64(v, x[1], t[1]);
-            });
-        } else {
-            const Stream s[1] = {{p, inc, po}};
-            staged<8>(s, steps, [&](int ks, const double* x) { t[0] = mfma_f64(operand(ks), x[0], t[0]); });
+    auto operand = [&](int k) {
+        const int s = first + stride * k;
+        if (s < full) {
+            const int h = 4 * s + lk;
+            return a[slice_row(nz - 1 - h)] + mirror * a[slice_row(h)];
         }
-        if (tail) {   // the last pairs and an odd column's middle; phi is zero past it
-            const int h = min(4 * full + lk, nh - 1), m = nz - 1 - h;
-            const double v = a[m * EW_LD] + (m == h ? 0.0 : mirror * a[h * EW_LD]);
-            const gcdouble pt = phi + 4 * full * kzt + at;
-            t[0] = mfma_f64(v, load_at(pt, po), t[0]);
-            if (n1) t[1] = mfma_f64(v, load_at(pt + n1, po), t[1]);
-            if (n2) t[2] = mfma_f64(v, load_at(pt + n2, po), t[2]);
+        const int h = min(4 * full + lk, nh - 1), m = nz - 1 - h;   // phi is zero past the middle
+        return a[slice_row(m)] + (m == h ? 0.0 : mirror * a[slice_row(h)]);
+    };
+    gdouble out = as_global(q.ws) + c0 * D.ld;
+    const bool whole = c0 + COLS <= ncol;
+    // both parities make the same passes; one past its last tile repeats the first and stores nothing
+    for (int t0 = 0; t0 < max(kze, D.kz - kze); t0 += 16 * NT) {
+        f64x4 t[NT];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) t[k] = F64X4_ZERO;
+        if (t0) load(0, t0, x);
+        for (int k = 0; k < steps; k += U) {
+            double y[U][NT];
+            if (k + U < steps) load(k + U, t0, y);
+            __builtin_amdgcn_sched_barrier(0);
+            if (first + stride * (k + U - 1) < full) {
+                double v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int h = 4 * (first + stride * (k + u)) + lk;
+                    v[u] = a[slice_row(nz - 1 - h)] + mirror * a[slice_row(h)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) t[i] = mfma_f64(v[u], x[u][i], t[i]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (k + u < steps) {
+                        const double v = operand(k + u);
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) t[i] = mfma_f64(v, x[u][i], t[i]);
+                    }
+            }
+            if (k + U < steps)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) x[u][i] = y[u][i];
         }
         if (COLS == 8) {   // the halves' sums, in the first half's wave
-            double* red = sm + NZ * EW_LD + odd * (3 * 4 * 64);
+            double* red = sm + slice_row(NZ) + odd * (NT * 4 * 64);
             if (t0) __syncthreads();
             if (sub)
 #pragma unroll
-                for (int k = 0; k < 12; ++k) red[k * 64 + lane] = t[k >> 2][k & 3];
+                for (int k = 0; k < 4 * NT; ++k) red[k * 64 + lane] = t[k >> 2][k & 3];
             __syncthreads();
+            if (sub) continue;
 #pragma unroll
-            for (int k = 0; k < 12; ++k) t[k >> 2][k & 3] += sub ? 0.0 : red[k * 64 + lane];
+            for (int k = 0; k < 4 * NT; ++k) t[k >> 2][k & 3] += red[k * 64 + lane];
         }
-        if (COLS == 8 && sub) continue;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < NT; ++k) {
             const int l = t0 + 16 * k + li;
             if (l < kz)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = 4 * r + lk, col = COLS == 16 ? row : row >> 1, ri = COLS == 16 ? sub : row & 1;
                     // odd modes carry -i: (re, im) -> (im, -re)
-                    if (c0 + col < ncol)
+                    if (whole || c0 + col < ncol)
                         out[col * D.ld + 2 * (odd ? kze + l : l) + (odd ? 1 - ri : ri)] =
                             odd && ri == 0 ? -t[k][r] : t[k][r];
                 }
@@ -177,24 +212,25 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* 
     if (tid % L < pad && in) out[cl * D.ld + 2 * D.kz + tid % L] = 0.0;
 }
 
-template <int COLS, int K>
-__global__ __launch_bounds__(EW_THREADS, COLS == 8 && K == 8 ? 3 : 4) void ew_scan_kernel(EwBatch batch)
+template <typename A, bool MSFT, int COLS, int K, int NT>
+__global__ __launch_bounds__(EW_THREADS, NT > 1 || (COLS == 8 && K == 8) ? 3 : 4) void ew_scan_kernel(A args)
 {
-    // COLS = 16: Re and Im; 8: (Re, Im) rows, then the halves' sums of three tiles a parity
-    __shared__ double sm[COLS == 16 ? 2 * 16 * K * EW_LD : 32 * K * EW_LD + 2 * 3 * 4 * 64];
+    // COLS = 16: Re and Im; 8: (Re, Im) rows, then the halves' sums of a parity's tiles
+    __shared__ double sm[COLS == 16 ? 2 * slice_row(16 * K) : slice_row(32 * K) + 2 * NT * 4 * 64];
     int item;
-    const EwReq& q = ew_request(batch, item);
-    const int strength = q.d->strength;
-    if (strength == MSFT_STRENGTH_MSFT) ew_scan_whole<MSFT_STRENGTH_MSFT, COLS, K>(q, item, sm);
-    else if (strength == MSFT_STRENGTH_BORN) ew_scan_whole<MSFT_STRENGTH_BORN, COLS, K>(q, item, sm);
-    else ew_scan_whole<MSFT_STRENGTH_DENSITY, COLS, K>(q, item, sm);
+    const EwReq& q = ew_request(args, item);
+    ew_scan_whole<MSFT, COLS, K, NT>(q, item, sm);
 }
 
 // Longer columns, in rounds of 64 slices against the full-axis modes.  Wave w takes Re (w
 // even) or Im of mode tiles w / 2, w / 2 + 2, ...
-template <int STRENGTH, int NT>
-__device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double* sm)
+template <typename A, bool MSFT>
+__global__ __launch_bounds__(EW_THREADS) void ew_scan_rounds_kernel(A args)
 {
+    constexpr int NT = EW_MAX_KZ / 32;
+    __shared__ double sm[2 * slice_row(EW_ZC)];
+    int item;
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, kzt = D.kzt;
@@ -202,7 +238,7 @@ __device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double*
     const bool in = c0 + cl < ncol;
     const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
     const int ri = wave & 1, t0 = wave >> 1;
-    const gcdouble phi = as_global(D.phiz) + t0 * 16;
+    const gcdouble phi = as_global(D.phiz) + t0 * 16, rot = as_global(D.rot) + 2 * zl;
     const uint32_t po = 8 * (lk * kzt + li);
     f64x4 acc[NT];
 #pragma unroll
@@ -212,7 +248,7 @@ __device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double*
     for (int z0 = 0; z0 < nz; z0 += EW_ZC) {
         load_slices<4>(q.delta + off, q.beta + off, z0 + zl, nz, in, d, b);
         double Sb = 0.0, Sd = 0.0;
-        if (STRENGTH == MSFT_STRENGTH_MSFT) {
+        if (MSFT) {
             const double sb = ((double)b[0] + b[1]) + ((double)b[2] + b[3]);
             const double sd = ((double)d[0] + d[1]) + ((double)d[2] + d[3]);
             const double ib = row_prefix_f64(sb), id = row_prefix_f64(sd);
@@ -221,12 +257,11 @@ __device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double*
             carry_b += row_last_f64(ib);
             carry_d += row_last_f64(id);
         }
-        double* o = sm + zl * EW_LD + cl;
-        ew_strength<STRENGTH, 4>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * (z0 + zl), o, o + EW_ZC * EW_LD);
+        ew_strength<MSFT, 4>(D, d, b, Sb, Sd, rot[2 * z0], rot[2 * z0 + 1], zl, sm + cl, sm + slice_row(EW_ZC) + cl);
         __syncthreads();
-        const double* a = sm + ri * EW_ZC * EW_LD + lk * EW_LD + li;
+        const double* a = sm + ri * slice_row(EW_ZC) + li;
         for_steps<4>(EW_ZC / 4, [&](int ks) {
-            const double v = a[4 * ks * EW_LD];
+            const double v = a[slice_row(4 * ks + lk)];
             const gcdouble p = phi + (int64_t)(z0 + 4 * ks) * kzt;
 #pragma unroll
             for (int t = 0; t < NT; ++t)   // a wave past the last tile repeats the first and stores nothing
@@ -247,18 +282,6 @@ __device__ __forceinline__ void ew_scan_rounds(const EwReq& q, int item, double*
             if (col < ncol) q.ws[col * D.ld + 2 * l + comp] = sign * acc[t][r];
         }
     }
-}
-
-__global__ __launch_bounds__(EW_THREADS) void ew_scan_rounds_kernel(EwBatch batch)
-{
-    constexpr int NT = EW_MAX_KZ / 32;
-    __shared__ double sm[2 * EW_ZC * EW_LD];
-    int item;
-    const EwReq& q = ew_request(batch, item);
-    const int strength = q.d->strength;
-    if (strength == MSFT_STRENGTH_MSFT) ew_scan_rounds<MSFT_STRENGTH_MSFT, NT>(q, item, sm);
-    else if (strength == MSFT_STRENGTH_BORN) ew_scan_rounds<MSFT_STRENGTH_BORN, NT>(q, item, sm);
-    else ew_scan_rounds<MSFT_STRENGTH_DENSITY, NT>(q, item, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -310,11 +333,12 @@ __device__ __forceinline__ void half_axis_sums(const HalfAxis& x, int wave, int 
 // each other on one XCD (workgroups go to the eight XCDs in turn), so that its L2 holds
 // their Z after the first.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(EW_THREADS) void ew_modal_kernel(EwBatch batch)
+template <typename A>
+__global__ __launch_bounds__(EW_THREADS) void ew_modal_kernel(A args)
 {
     __shared__ double red[SUM_WAVES_LDS];
     int item;
-    const EwReq& q = ew_request(batch, item);
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, ct = (ld + 15) >> 4, groups = (max(D.ket, D.kop ? D.kot : 0) + 31) >> 5;
@@ -351,11 +375,12 @@ __global__ __launch_bounds__(EW_THREADS) void ew_modal_kernel(EwBatch batch)
 // workgroup takes 16 of the km * 2 kzp columns and two tiles of 16 values of a, both
 // parities; the groups of a of one column tile on one XCD.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(EwBatch batch)
+template <typename A>
+__global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(A args)
 {
     __shared__ double red[SUM_WAVES_LDS];
     int item;
-    const EwReq& q = ew_request(batch, item);
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ncols = D.km * D.ld, nap = D.nap, ga = (nap + 31) >> 5;
@@ -392,12 +417,12 @@ __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(EwBatch batch)
 // [4 px + 2 py + (re | im)][row node][node], px and py the parities along x and y.  The
 // groups of b of one a follow each other on one XCD.
 // ---------------------------------------------------------------------------
-template <int BT>
-__global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(EwBatch batch)
+template <typename A, int BT>
+__global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(A args)
 {
     __shared__ double red[2][2][2][BT * 16][2];   // [column half][pM][pN][b][ri]
     int item;
-    const EwReq& q = ew_request(batch, item);
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, nbp = D.nbp, kzp = D.kzp, bg = (nbp + 16 * BT - 1) / (16 * BT);
@@ -487,11 +512,12 @@ __global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(EwBatch batch)
 // ---------------------------------------------------------------------------
 constexpr int CF_THREADS = 1024;   // at most: a wave to every 16 nodes
 
-__global__ __launch_bounds__(CF_THREADS) void ew_coef_kernel(EwBatch batch)
+template <typename A>
+__global__ __launch_bounds__(CF_THREADS) void ew_coef_kernel(A args)
 {
     extern __shared__ double lds[];   // [n][17]
     int item;
-    const EwReq& q = ew_request(batch, item);
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int n = D.n, nr = D.nr, rowsp = D.rowsp, np = (n + 15) & ~15, waves = blockDim.x >> 6;
@@ -566,11 +592,12 @@ __device__ __forceinline__ void ew_store(const EwReq& q, int N, int i, int j, bo
 
 constexpr int EV_THREADS = 128;
 
-__global__ __launch_bounds__(EV_THREADS) void ew_eval_kernel(EwBatch batch)
+template <typename A>
+__global__ __launch_bounds__(EV_THREADS) void ew_eval_kernel(A args)
 {
     extern __shared__ double C[];   // [n][8]
     int item;
-    const EwReq& q = ew_request(batch, item);
+    const EwReq& q = ew_request(args, item);
     const EwDesc& D = *q.d;
     const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x;
     const int chunks = (half + 2 * EV_THREADS - 1) / (2 * EV_THREADS), j = item / chunks;
@@ -684,58 +711,88 @@ __global__ __launch_bounds__(256) void ew_mode_kernel(CoefArgs c)
     }
 }
 
-// Workgroups per request by `f`, then one launch over all of them.
-template <typename K, typename F>
-void ew_launch(K kernel, EwBatch& b, const EwDesc* const* dims, int lds, hipStream_t s, F f,
-               int threads = EW_THREADS)
+// One launch over all requests, f(plan) workgroups to each.
+template <typename F>
+void ew_launch(void (*one)(EwReq), void (*many)(EwBatch), EwBatch& b, const EwDesc* const* dims, int lds,
+               hipStream_t s, F f, int threads = EW_THREADS)
 {
+    if (b.n == 1) {
+        hipLaunchKernelGGL(one, dim3((unsigned)f(*dims[0])), dim3(threads), lds, s, b.req[0]);
+        return;
+    }
     int64_t total = 0;
     for (int r = 0; r < b.n; ++r) {
         b.begin[r] = (int32_t)total;
         total += f(*dims[r]);
     }
     b.begin[b.n] = (int32_t)total;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(threads), lds, s, b);
+    hipLaunchKernelGGL(many, dim3((unsigned)total), dim3(threads), lds, s, b);
 }
 
 // Workgroups of a kernel whose `inner` workgroups of each of `outer` units follow each
 // other on one XCD.
 int64_t ew_on_xcd(int64_t outer, int64_t inner) { return ceil_div(outer, 8) * 8 * inner; }
 
-template <int BT>
-void ew_launch_yz(EwBatch& b, const EwDesc* const* dims, hipStream_t s)
+// The scan's form for a plan: its rounding goes by its own columns in any batch.
+struct ScanForm {
+    int rounds, tiles;
+    bool msft;
+    explicit ScanForm(const EwDesc& d)
+        : rounds(ew_rounds(d.nz)), tiles(rounds ? std::min(3, std::max(d.kzet, d.kzot) / 16) : 0),
+          msft(d.strength == MSFT_STRENGTH_MSFT)
+    {
+    }
+    bool operator==(const ScanForm& o) const { return rounds == o.rounds && tiles == o.tiles && msft == o.msft; }
+};
+
+template <bool MSFT, int COLS, int K>
+void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, int tiles, hipStream_t s)
 {
-    ew_launch(ew_yz_kernel<BT>, b, dims, 0, s,
-              [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 16 * BT)); });
+    auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, COLS); };
+    if (tiles == 1) ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 1>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 1>, b, dims, 0, s, items);
+    else if (tiles == 2) ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 2>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 2>, b, dims, 0, s, items);
+    else ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 3>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 3>, b, dims, 0, s, items);
+}
+
+template <bool MSFT>
+void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, const ScanForm& f, hipStream_t s)
+{
+    switch (f.rounds) {
+    case 1: ew_launch_scan<MSFT, 16, 4>(b, dims, f.tiles, s); break;
+    case 2: ew_launch_scan<MSFT, 16, 8>(b, dims, f.tiles, s); break;
+    case 3: ew_launch_scan<MSFT, 8, 6>(b, dims, f.tiles, s); break;
+    case 4: ew_launch_scan<MSFT, 8, 8>(b, dims, f.tiles, s); break;
+    default:
+        ew_launch(ew_scan_rounds_kernel<EwReq, MSFT>, ew_scan_rounds_kernel<EwBatch, MSFT>, b, dims, 0, s,
+                  [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, EW_COLS); });
+    }
 }
 
 }  // namespace
 
-int launch_ew_scan(EwBatch b, const EwDesc* const* dims, void* stream)
+int launch_ew_scan(const EwBatch& b, const EwDesc* const* dims, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    // a request's kernel, and so its rounding, goes by its own columns in any batch
-    for (int rounds = 0; rounds <= EW_WHOLE_NZ / EW_ZC; ++rounds) {
+    bool done[EW_MAX_REQ] = {};
+    for (int first = 0; first < b.n; ++first) {   // the requests of one form together
+        if (done[first]) continue;
+        const ScanForm form(*dims[first]);
         EwBatch part;
         const EwDesc* d[EW_MAX_REQ];
         part.n = 0;
-        for (int r = 0; r < b.n; ++r)
-            if (ew_rounds(dims[r]->nz) == rounds) {
+        for (int r = first; r < b.n; ++r)
+            if (!done[r] && ScanForm(*dims[r]) == form) {
+                done[r] = true;
                 d[part.n] = dims[r];
                 part.req[part.n++] = b.req[r];
             }
-        if (part.n == 0) continue;
-        auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, ew_columns(d.nz)); };
-        if (rounds == 0) ew_launch(ew_scan_rounds_kernel, part, d, 0, s, items);
-        else if (rounds == 1) ew_launch(ew_scan_kernel<16, 4>, part, d, 0, s, items);
-        else if (rounds == 2) ew_launch(ew_scan_kernel<16, 8>, part, d, 0, s, items);
-        else if (rounds == 3) ew_launch(ew_scan_kernel<8, 6>, part, d, 0, s, items);
-        else ew_launch(ew_scan_kernel<8, 8>, part, d, 0, s, items);
+        if (form.msft) ew_launch_scan<true>(part, d, form, s);
+        else ew_launch_scan<false>(part, d, form, s);
     }
     return (int)hipGetLastError();
 }
 
-int launch_ew_contract(EwBatch b, const EwDesc* const* dims, void* stream)
+int launch_ew_contract(EwBatch& b, const EwDesc* const* dims, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
     int64_t bt = 0;
@@ -744,18 +801,22 @@ int launch_ew_contract(EwBatch b, const EwDesc* const* dims, void* stream)
         bt += (int64_t)dims[r]->na * (dims[r]->nbp / 16);
         n = std::max(n, dims[r]->n);
     }
-    ew_launch(ew_modal_kernel, b, dims, 0, s, [](const EwDesc& d) {
+    ew_launch(ew_modal_kernel<EwReq>, ew_modal_kernel<EwBatch>, b, dims, 0, s, [](const EwDesc& d) {
         return ew_on_xcd(d.nN * ceil_div(d.ld, 16), ceil_div(std::max(d.ket, d.kop ? d.kot : 0), 32));
     });
-    ew_launch(ew_nodes_kernel, b, dims, 0, s, [](const EwDesc& d) {
+    ew_launch(ew_nodes_kernel<EwReq>, ew_nodes_kernel<EwBatch>, b, dims, 0, s, [](const EwDesc& d) {
         return ew_on_xcd(ceil_div((int64_t)d.km * d.ld, 16), ceil_div(d.nap, 32));
     });
-    if (bt >= 8 * CHIP_CUS) ew_launch_yz<2>(b, dims, s);
-    else ew_launch_yz<1>(b, dims, s);
-    ew_launch(ew_coef_kernel, b, dims, n * 17 * (int)sizeof(double), s,
+    if (bt >= 8 * CHIP_CUS)
+        ew_launch(ew_yz_kernel<EwReq, 2>, ew_yz_kernel<EwBatch, 2>, b, dims, 0, s,
+                  [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 32)); });
+    else
+        ew_launch(ew_yz_kernel<EwReq, 1>, ew_yz_kernel<EwBatch, 1>, b, dims, 0, s,
+                  [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 16)); });
+    ew_launch(ew_coef_kernel<EwReq>, ew_coef_kernel<EwBatch>, b, dims, n * 17 * (int)sizeof(double), s,
               [](const EwDesc& d) { return ew_on_xcd(d.rowsp / 16, 8); },
               std::min(CF_THREADS, std::max(4, (n + 15) / 16) * 64));
-    ew_launch(ew_eval_kernel, b, dims, n * 8 * (int)sizeof(double), s,
+    ew_launch(ew_eval_kernel<EwReq>, ew_eval_kernel<EwBatch>, b, dims, n * 8 * (int)sizeof(double), s,
               [](const EwDesc& d) { return d.rows * ceil_div(d.rows, 2 * EV_THREADS); }, EV_THREADS);
     return (int)hipGetLastError();
 }

@@ -10,8 +10,10 @@
 //   walk   R(z)       = exp(-i qc z) sum_l phi_l(z) Z_l, then along each column
 //          dL/d delta, dL/d beta from R (Eqs. (7)-(9))
 //
-// Every array takes the place of the forward's of the same letter.
+// Every array takes the place of the forward's of the same letter (C its parts in planes).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "ewald.h"
 #include "msft_internal.h"
@@ -23,7 +25,6 @@ namespace {
 
 constexpr int EA_THREADS = 256;
 constexpr int EA_WAVES = EA_THREADS / 64;
-constexpr int EA_LD = EW_COLS + 1;
 
 // ---------------------------------------------------------------------------
 // Rows: one workgroup per pixel row, 256 columns at a time, 64 to a wave.  A lane folds h
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(EA_THREADS) void ew_rows_kernel(EwAdj q)
     const gcdouble tq = as_global(D.tq) + (int64_t)j * half;
     const float __attribute__((address_space(1)))* g = as_global(q.grad_intensity);
     const float __attribute__((address_space(1)))* A = as_global(q.amplitude);
-    gdouble C = as_global(q.ws) + D.offC + (int64_t)j * n * 8;
+    gdouble C = as_global(q.ws) + D.offC + ((int64_t)(tid & 7) * half + j) * n + (tid >> 3);   // [part][row][order]
     for (int i0 = 0; i0 < half; i0 += EA_THREADS) {
         const int i = i0 + tid;
         const double t = tq[min(i, half - 1)];
@@ -99,14 +100,14 @@ __global__ __launch_bounds__(EA_THREADS) void ew_rows_kernel(EwAdj q)
             }
             __syncthreads();
             const double s = (sums[0][tid] + sums[1][tid]) + (sums[2][tid] + sums[3][tid]);
-            if (k0 + (tid >> 3) < n) C[k0 * 8 + tid] = i0 ? C[k0 * 8 + tid] + s : s;
+            if (k0 + (tid >> 3) < n) C[k0] = i0 ? C[k0] + s : s;
             __syncthreads();
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// Coef transposed: S[comp][r][a] = sum_k D[a][k] sum over rows of W[row][r] C[row][k][comp]
+// Coef transposed: S[comp][r][a] = sum_k D[a][k] sum over rows of W[row][r] C[comp][row][k]
 // for 16 row nodes and one part: 16 waves, four to the rows and four to the tiles of 16
 // orders k, their sums through LDS (a row of 16 row nodes per order, padded to 17), then a
 // wave to each tile of 16 nodes a.
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(CA_THREADS) void ew_coef_adj_kernel(EwAdj q)
     const int comp = blockIdx.x & 7, r0 = (blockIdx.x >> 3) * 16, part = wave >> 2;
     const int px = comp >> 2, py = (comp >> 1) & 1, last = D.rows - 1;
     const gcdouble w = as_global(py ? D.wro : D.wre) + (int64_t)r0 * rowsp;
-    const gcdouble C = as_global(q.ws) + D.offC + comp;
+    const gcdouble C = as_global(q.ws) + D.offC + (int64_t)comp * D.rows * n;
     const uint32_t ow = 8 * (li * rowsp + lk);
     const int steps = rowsp >> 4;   // of four rows, per part
     for (int t0 = 0; t0 < np; t0 += 64) {
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(CA_THREADS) void ew_coef_adj_kernel(EwAdj q)
         f64x4 t = F64X4_ZERO;
         for_steps<8>(steps, [&](int ks) {
             const int j = 4 * (part * steps + ks);   // W is zero for rows past the last
-            t = mfma_f64(load_at(w + j, ow), C[((int64_t)min(j + lk, last) * n + k) * 8], t);
+            t = mfma_f64(load_at(w + j, ow), C[min(j + lk, last) * n + k], t);
         });
         if (part)
 #pragma unroll
@@ -308,46 +309,45 @@ __global__ __launch_bounds__(EA_THREADS) void ew_modal_adj_kernel(EwAdj q)
 // slices and T as in the scan.
 // ---------------------------------------------------------------------------
 
-// The chain rule of a lane's K slices, L lanes to a column; (ur, ui): LDS of
-// sum_l phi_l Z at its first slice.  In: carry = sum of R w past the round; out: that of
-// the round added.
-template <int STRENGTH, int K, int L>
-__device__ __forceinline__ void ew_chain(const float* d, const float* b, double Sb, double Sd, double k0dz,
-                                         gcdouble rot, const double* ur, const double* ui, double* carry,
+// The chain rule of a lane's K slices from z on, L lanes to a column; (ur, ui): LDS of
+// sum_l phi_l Z, (r0, r1) the rotation at its first slice.  In: carry = sum of R w
+// past the round; out: that of the round added.
+template <bool MSFT, int K, int L>
+__device__ __forceinline__ void ew_chain(const EwDesc& D, const float* d, const float* b, double Sb, double Sd,
+                                         double r0, double r1, int z, const double* ur, const double* ui, double* carry,
                                          float* gd, float* gb)
 {
-    Transmission T;
-    if (STRENGTH == MSFT_STRENGTH_MSFT) T.start<K>(Sb, Sd, b, d, k0dz);
-    const double scale = 2.0 * k0dz;
+    Propagator<MSFT> P;
+    P.template start<K>(Sb, Sd, b, d, D.k0dz64, r0, r1, D.step_r, D.step_i);
+    const bool density = !MSFT && D.strength == MSFT_STRENGTH_DENSITY;
+    const double scale = 2.0 * D.k0dz64;
     double vd[K], vb[K], wr = 0.0, wi = 0.0;   // the slices' own terms; sum of R w so far
+    auto slices = [&](auto small) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double xr = ur[k * EA_LD], xi = ui[k * EA_LD], ex = rot[2 * k], ey = rot[2 * k + 1];
-        double pr = xr * ex - xi * ey, pi = xr * ey + xi * ex;
-        if (STRENGTH == MSFT_STRENGTH_DENSITY) {
-            vd[k] = 2.0 * pr;
-            vb[k] = -2.0 * pi;
-            continue;
+        for (int k = 0; k < K; ++k) {
+            const double xr = ur[slice_row(z + k)], xi = ui[slice_row(z + k)], dk = d[k], bk = b[k], nr = 1.0 - dk;
+            const double pr = xr * P.tr - xi * P.ti, pi = xr * P.ti + xi * P.tr;
+            vd[k] = -4.0 * (pr * nr - pi * bk);
+            vb[k] = -4.0 * (pr * bk + pi * nr);
+            if (density) {
+                vd[k] = 2.0 * pr;
+                vb[k] = -2.0 * pi;
+            }
+            if (MSFT) {
+                const double chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * nr;
+                wr += pr * chr - pi * chi;
+                wi += pr * chi + pi * chr;
+                // what follows the slice is the sum past the lane's last, less what the lane had here
+                vd[k] -= scale * wi;
+                vb[k] += scale * wr;
+            }
+            if (k + 1 < K) P.template next<decltype(small)::value>(bk, dk);
         }
-        const double dk = d[k], bk = b[k], nr = 1.0 - dk;
-        if (STRENGTH == MSFT_STRENGTH_MSFT) {
-            const double t = pr, chr = dk * (dk - 2.0) - bk * bk, chi = 2.0 * bk * nr;
-            pr = t * T.tr - pi * T.ti;
-            pi = t * T.ti + pi * T.tr;
-            wr += pr * chr - pi * chi;
-            wi += pr * chi + pi * chr;
-        }
-        vd[k] = -4.0 * (pr * nr - pi * bk);
-        vb[k] = -4.0 * (pr * bk + pi * nr);
-        if (STRENGTH == MSFT_STRENGTH_MSFT) {
-            // what follows the slice is the sum past the lane's last, less what the lane had here
-            vd[k] -= scale * wi;
-            vb[k] += scale * wr;
-            if (k + 1 < K) T.next(bk, dk);
-        }
-    }
+    };
+    if (!MSFT || P.small) slices(std::true_type{});
+    else slices(std::false_type{});
     double er = 0.0, ei = 0.0;
-    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+    if (MSFT) {
         const double qr = group_prefix_f64<L>(wr), qi = group_prefix_f64<L>(wi);
         const double sr = group_last_f64<L>(qr), si = group_last_f64<L>(qi);
         er = scale * ((carry[0] + (sr - qr)) + wr);
@@ -384,11 +384,14 @@ __device__ __forceinline__ void store_slices(float* od, float* ob, int z, int nz
 
 // Whole columns, as in the scan (rows of the products: 16 columns, Re and Im apart, or 8
 // columns' (Re, Im)): even and odd modes on the half axis, E + O and E - O the mirror
-// slices.  A wave takes every fourth (Re or Im and every other) tile of 16 half-axis slices.
-template <int STRENGTH, int COLS, int K>
-__device__ __forceinline__ void ew_walk_whole(const EwAdj& q, double* sm)
+// slices.  A wave takes every fourth (Re or Im and every other) tile of 16 half-axis
+// slices, at most two, both against one operand; 16 modes of each parity at a time, all
+// their loads ahead of the products.
+template <bool MSFT, int COLS, int K>
+__global__ __launch_bounds__(EA_THREADS, K == 8 ? 3 : 4) void ew_walk_kernel(EwAdj q)
 {
     constexpr int L = EA_THREADS / COLS, NZ = L * K;
+    __shared__ double sm[COLS == 16 ? 2 * slice_row(16 * K) : slice_row(32 * K)];   // Re and Im of 16 lanes' slices, or 32 lanes'
     const EwDesc& D = *q.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
@@ -397,50 +400,68 @@ __device__ __forceinline__ void ew_walk_whole(const EwAdj& q, double* sm)
     const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
     float d[K], b[K];
     load_slices<K>(q.delta + off, q.beta + off, z0, nz, in, d, b);
+    const gcdouble rot = as_global(D.rot) + 2 * min(z0, (nz + EW_ZC - 1) / EW_ZC * EW_ZC - 1);
+    const double r0 = rot[0], r1 = rot[1];
     // slices past the column's end
-    for (int k = nz * EA_LD + tid; k < NZ * EA_LD; k += EA_THREADS) {
+    for (int k = slice_row(nz) + tid; k < slice_row(NZ); k += EA_THREADS) {
         sm[k] = 0.0;
-        if (COLS == 16) sm[NZ * EA_LD + k] = 0.0;
+        if (COLS == 16) sm[slice_row(NZ) + k] = 0.0;
     }
     {
         const int set = COLS == 16 ? wave & 1 : 0, nh = (nz + 1) >> 1, kze = D.kze, kzo = D.kz - kze, last = D.kzp - 1;
         const int col = COLS == 16 ? li : li >> 1, ri = COLS == 16 ? set : li & 1;
-        const uint32_t oz = 8 * (uint32_t)((min(c0 + col, ncol - 1) - c0) * D.ld + 2 * lk);
-        const uint32_t ze = oz + 8 * ri, zo = oz + 8 * (1 - ri);   // -i of the odd modes: (im, -re)
-        const double sign = ri ? -1.0 : 1.0;
+        const int h0 = COLS == 16 ? 16 * (wave >> 1) : 16 * wave, h1 = h0 + (COLS == 16 ? 32 : 64);
+        const uint32_t oz = 8 * (uint32_t)((min(c0 + col, ncol - 1) - c0) * D.ld);
+        const double sign = ri ? -1.0 : 1.0;   // -i of the odd modes: (im, -re)
         const gcdouble z = as_global(q.ws) + c0 * D.ld;
-        const int step = COLS == 16 ? 32 : 64;
-        for (int h0 = COLS == 16 ? 16 * (wave >> 1) : 16 * wave; h0 < nh; h0 += step) {
-            f64x4 e = F64X4_ZERO, o = F64X4_ZERO;
-            const Stream se[2] = {{z, 8, ze}, {as_global(D.phize) + (int64_t)h0 * D.kzet, 4, (uint32_t)(8 * (li * D.kzet + lk))}};
-            const Stream so[2] = {{z + 2 * kze, 8, zo},
-                                  {as_global(D.phizo) + (int64_t)h0 * D.kzot, 4, (uint32_t)(8 * (li * D.kzot + lk))}};
-            staged<4>(se, kze >> 2, [&](int, const double* x) { e = mfma_f64(x[0], x[1], e); });
-            staged<4>(so, kzo >> 2, [&](int, const double* x) { o = mfma_f64(x[0] * sign, x[1], o); });
-            // the last modes; the half-axis modes are zero past them, what they meet is finite
-            if (kze & 3) {
-                const int l = kze & ~3;
-                e = mfma_f64(load_at(z, ze + 16 * (min(l + lk, last) - lk)), load_at(se[1].p + l, se[1].off), e);
+        const int a0 = h0 < nh ? h0 : 0, a1 = h1 < nh ? h1 : a0;   // a tile past the middle is not stored
+        const gcdouble e0 = as_global(D.phize) + (int64_t)a0 * D.kzet, e1 = as_global(D.phize) + (int64_t)a1 * D.kzet;
+        const gcdouble o0 = as_global(D.phizo) + (int64_t)a0 * D.kzot, o1 = as_global(D.phizo) + (int64_t)a1 * D.kzot;
+        const uint32_t oe = 8 * (li * D.kzet + lk), oo = 8 * (li * D.kzot + lk);
+        f64x4 te[2] = {F64X4_ZERO, F64X4_ZERO}, to[2] = {F64X4_ZERO, F64X4_ZERO};
+        for (int l0 = 0; l0 < max(kze, kzo); l0 += 16) {
+            // the half-axis modes are zero past their last; what they meet there is finite
+            double x[4][6];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int le = l0 < D.kzet ? l0 + 4 * u : 0, lo = l0 < D.kzot ? l0 + 4 * u : 0;
+                x[u][0] = load_at(z, oz + 8 * (2 * min(le + lk, last) + ri));
+                x[u][1] = load_at(z, oz + 8 * (2 * min(kze + lo + lk, last) + 1 - ri));
+                x[u][2] = load_at(e0 + le, oe);
+                x[u][3] = load_at(e1 + le, oe);
+                x[u][4] = load_at(o0 + lo, oo);
+                x[u][5] = load_at(o1 + lo, oo);
             }
-            if (kzo & 3) {
-                const int l = kzo & ~3;
-                o = mfma_f64(sign * load_at(z, zo + 16 * (min(kze + l + lk, last) - lk)), load_at(so[1].p + l, so[1].off), o);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (l0 + 4 * u < kze) {
+                    te[0] = mfma_f64(x[u][0], x[u][2], te[0]);
+                    te[1] = mfma_f64(x[u][0], x[u][3], te[1]);
+                }
+                if (l0 + 4 * u < kzo) {
+                    const double v = sign * x[u][1];
+                    to[0] = mfma_f64(v, x[u][4], to[0]);
+                    to[1] = mfma_f64(v, x[u][5], to[1]);
+                }
             }
-            const int h = h0 + li;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int h = (k ? h1 : h0) + li;
             if (h < nh) {
-                double* hi = sm + (set * NZ + nz - 1 - h) * EA_LD + lk;
-                double* lo = sm + (set * NZ + h) * EA_LD + lk;
+                double* hi = sm + set * slice_row(NZ) + slice_row(nz - 1 - h) + lk;
+                double* lo = sm + set * slice_row(NZ) + slice_row(h) + lk;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    lo[4 * r] = e[r] - o[r];
-                    hi[4 * r] = e[r] + o[r];   // an odd column's middle: o is zero
+                    lo[4 * r] = te[k][r] - to[k][r];
+                    hi[4 * r] = te[k][r] + to[k][r];   // an odd column's middle: the odd part is zero
                 }
             }
         }
     }
-    __syncthreads();
     double Sb = 0.0, Sd = 0.0;
-    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+    if (MSFT) {
         double sb = 0.0, sd = 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -450,31 +471,23 @@ __device__ __forceinline__ void ew_walk_whole(const EwAdj& q, double* sm)
         Sb = group_prefix_f64<L>(sb) - sb;
         Sd = group_prefix_f64<L>(sd) - sd;
     }
+    __syncthreads();
     double carry[2] = {0.0, 0.0};
     float gd[K], gb[K];
-    const double* u = sm + z0 * EA_LD + (COLS == 16 ? cl : 2 * cl);
-    ew_chain<STRENGTH, K, L>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * z0, u, u + (COLS == 16 ? NZ * EA_LD : 1),
-                             carry, gd, gb);
+    const double* u = sm + (COLS == 16 ? cl : 2 * cl);
+    ew_chain<MSFT, K, L>(D, d, b, Sb, Sd, r0, r1, z0, u, u + (COLS == 16 ? slice_row(NZ) : 1), carry, gd, gb);
     if (in) store_slices<K>(q.grad_delta + off, q.grad_beta + off, z0, nz, gd, gb);
-}
-
-template <int COLS, int K>
-__global__ __launch_bounds__(EA_THREADS, K == 8 ? 3 : 4) void ew_walk_kernel(EwAdj q)
-{
-    __shared__ double sm[32 * K * EA_LD];   // Re and Im of 16 lanes' slices, or 32 lanes'
-    const int strength = q.d->strength;
-    if (strength == MSFT_STRENGTH_MSFT) ew_walk_whole<MSFT_STRENGTH_MSFT, COLS, K>(q, sm);
-    else if (strength == MSFT_STRENGTH_BORN) ew_walk_whole<MSFT_STRENGTH_BORN, COLS, K>(q, sm);
-    else ew_walk_whole<MSFT_STRENGTH_DENSITY, COLS, K>(q, sm);
 }
 
 // Longer columns, in rounds of 64 slices from the exit face back, after a pass that sums
 // beta + i delta of each round.
 constexpr int EA_ROUNDS = 4096 / EW_ZC;
 
-template <int STRENGTH>
-__device__ __forceinline__ void ew_walk_rounds(const EwAdj& q, double* sm, double* pre)
+template <bool MSFT>
+__global__ __launch_bounds__(EA_THREADS) void ew_walk_rounds_kernel(EwAdj q)
 {
+    __shared__ double sm[2 * slice_row(EW_ZC)];
+    __shared__ double pre[2 * EA_ROUNDS * EW_COLS];   // beta, delta before each round
     const EwDesc& D = *q.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, kzt = D.kzt, kze = D.kze;
@@ -483,7 +496,7 @@ __device__ __forceinline__ void ew_walk_rounds(const EwAdj& q, double* sm, doubl
     const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
     const int rounds = (nz + EW_ZC - 1) / EW_ZC;
     float d[4], b[4];
-    if (STRENGTH == MSFT_STRENGTH_MSFT) {
+    if (MSFT) {
         double tb = 0.0, td = 0.0;
         for (int r = 0; r < rounds; ++r) {
             if ((tid & 15) == 0) {
@@ -498,53 +511,56 @@ __device__ __forceinline__ void ew_walk_rounds(const EwAdj& q, double* sm, doubl
     }
     const int ri = wave & 1, zt = (wave >> 1) * 32;
     const double* zh = q.ws + min(c0 + li, ncol - 1) * D.ld;
+    const gcdouble rot = as_global(D.rot) + 2 * zl;
     double carry[2] = {0.0, 0.0};
     for (int rd = rounds - 1; rd >= 0; --rd) {
         const int z0 = rd * EW_ZC;
         load_slices<4>(q.delta + off, q.beta + off, z0 + zl, nz, in, d, b);
         {
-            f64x4 r0 = F64X4_ZERO, r1 = F64X4_ZERO;
-            gcdouble p = as_global(D.phiz) + (int64_t)(z0 + zt + li) * kzt;
+            f64x4 t0 = F64X4_ZERO, t1 = F64X4_ZERO;
+            const gcdouble p = as_global(D.phiz) + (int64_t)(z0 + zt + li) * kzt;
             for_steps<4>(D.kzp / 4, [&](int ks) {
                 const int l = 4 * ks + lk;
                 const bool odd = l >= kze;   // -i of the odd modes: (im, -re)
                 double v = zh[2 * l + (odd ? 1 - ri : ri)];
                 if (odd && ri) v = -v;
-                r0 = mfma_f64(v, p[l], r0);
-                r1 = mfma_f64(v, p[16 * kzt + l], r1);
+                t0 = mfma_f64(v, p[l], t0);
+                t1 = mfma_f64(v, p[16 * kzt + l], t1);
             });
-            double* o = sm + (ri * EW_ZC + zt + li) * EA_LD + lk;
+            double* o = sm + ri * slice_row(EW_ZC) + slice_row(zt + li) + lk;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                o[4 * r] = r0[r];
-                o[16 * EA_LD + 4 * r] = r1[r];
+                o[4 * r] = t0[r];
+                o[slice_row(16) + 4 * r] = t1[r];
             }
         }
         __syncthreads();
         double Sb = 0.0, Sd = 0.0;
-        if (STRENGTH == MSFT_STRENGTH_MSFT) {
+        if (MSFT) {
             const double sb = ((double)b[0] + b[1]) + ((double)b[2] + b[3]);
             const double sd = ((double)d[0] + d[1]) + ((double)d[2] + d[3]);
             Sb = pre[2 * rd * EW_COLS + cl] + (row_prefix_f64(sb) - sb);
             Sd = pre[(2 * rd + 1) * EW_COLS + cl] + (row_prefix_f64(sd) - sd);
         }
         float gd[4], gb[4];
-        const double* u = sm + zl * EA_LD + cl;
-        ew_chain<STRENGTH, 4, 16>(d, b, Sb, Sd, D.k0dz64, as_global(D.rot) + 2 * (z0 + zl), u, u + EW_ZC * EA_LD, carry,
-                              gd, gb);
+        ew_chain<MSFT, 4, 16>(D, d, b, Sb, Sd, rot[2 * z0], rot[2 * z0 + 1], zl, sm + cl, sm + slice_row(EW_ZC) + cl,
+                              carry, gd, gb);
         if (in) store_slices<4>(q.grad_delta + off, q.grad_beta + off, z0 + zl, nz, gd, gb);
         __syncthreads();   // the next round rewrites sm
     }
 }
 
-__global__ __launch_bounds__(EA_THREADS) void ew_walk_rounds_kernel(EwAdj q)
+template <bool MSFT>
+void launch_walk(const EwAdj& a, const EwDesc& d, hipStream_t s)
 {
-    __shared__ double sm[2 * EW_ZC * EA_LD];
-    __shared__ double pre[2 * EA_ROUNDS * EW_COLS];   // beta, delta before each round
-    const int strength = q.d->strength;
-    if (strength == MSFT_STRENGTH_MSFT) ew_walk_rounds<MSFT_STRENGTH_MSFT>(q, sm, pre);
-    else if (strength == MSFT_STRENGTH_BORN) ew_walk_rounds<MSFT_STRENGTH_BORN>(q, sm, pre);
-    else ew_walk_rounds<MSFT_STRENGTH_DENSITY>(q, sm, pre);
+    const dim3 grid((unsigned)ceil_div((int64_t)d.nx * d.ny, ew_columns(d.nz))), th(EA_THREADS);
+    switch (ew_rounds(d.nz)) {
+    case 1: hipLaunchKernelGGL((ew_walk_kernel<MSFT, 16, 4>), grid, th, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((ew_walk_kernel<MSFT, 16, 8>), grid, th, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((ew_walk_kernel<MSFT, 8, 6>), grid, th, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((ew_walk_kernel<MSFT, 8, 8>), grid, th, 0, s, a); break;
+    default: hipLaunchKernelGGL(ew_walk_rounds_kernel<MSFT>, grid, th, 0, s, a);
+    }
 }
 
 }  // namespace
@@ -563,14 +579,8 @@ int launch_ew_adjoint(const EwAdj& a, const EwDesc& d, void* stream)
            EA_THREADS, 0);
     launch(ew_nodes_adj_kernel, on_xcd(ceil_div((int64_t)d.km * d.ld, 16), ceil_div(d.nhNp, 32)), EA_THREADS, 0);
     launch(ew_modal_adj_kernel, on_xcd(ceil_div(d.ld, 16) * d.nN, ceil_div(d.nhMp, 32)), EA_THREADS, 0);
-    const int64_t cols = ceil_div((int64_t)d.nx * d.ny, ew_columns(d.nz));
-    switch (ew_rounds(d.nz)) {
-    case 1: launch(ew_walk_kernel<16, 4>, cols, EA_THREADS, 0); break;
-    case 2: launch(ew_walk_kernel<16, 8>, cols, EA_THREADS, 0); break;
-    case 3: launch(ew_walk_kernel<8, 6>, cols, EA_THREADS, 0); break;
-    case 4: launch(ew_walk_kernel<8, 8>, cols, EA_THREADS, 0); break;
-    default: launch(ew_walk_rounds_kernel, cols, EA_THREADS, 0);
-    }
+    if (d.strength == MSFT_STRENGTH_MSFT) launch_walk<true>(a, d, s);
+    else launch_walk<false>(a, d, s);
     return (int)hipGetLastError();
 }
 

@@ -220,23 +220,35 @@ __device__ __forceinline__ void sincos_reduced(double x, double* sn, double* cs)
     *cs = (k + 1) & 2 ? -b : b;
 }
 
-// T = exp(-k0 dz S) along a lane's slices: in full at the first, (Sb, Sd) the sums of beta
-// and delta before it, then multiplied by each slice's own factor.  A wave that holds a
-// factor's exponent of 1/8 or more evaluates every slice in full.
-struct Transmission {
-    double Sb, Sd, k0dz, tr, ti;
+// dV exp(-i qc z) T along a lane's slices, T = exp(-k0 dz S) (1 without MSFT).  In full at
+// the first slice, (Sb, Sd) the sums of beta and delta before it and (rr, ri) the table's
+// dV exp(-i qc z) there, then multiplied by each slice's own factor and the rotation's step
+// exp(-i qc dz).  A wave that holds a factor's exponent of 1/8 or more evaluates T in full
+// at every slice.
+template <bool MSFT>
+struct Propagator {
+    double Sb, Sd, k0dz, rr, ri, cr, ci, tr, ti;
     bool small;
 
     __device__ __forceinline__ void full()
     {
+        double sn, cs;
         const double m = exp_reduced(-k0dz * Sb);
-        sincos_reduced(-k0dz * Sd, &ti, &tr);
-        tr *= m;
-        ti *= m;
+        sincos_reduced(-k0dz * Sd, &sn, &cs);
+        sn *= m;
+        cs *= m;
+        tr = cs * rr - sn * ri;
+        ti = cs * ri + sn * rr;
     }
     template <int K>
-    __device__ __forceinline__ void start(double sb, double sd, const float* b, const float* d, double k)
+    __device__ __forceinline__ void start(double sb, double sd, const float* b, const float* d, double k, double r0,
+                                          double r1, double step_r, double step_i)
     {
+        rr = tr = r0;
+        ri = ti = r1;
+        cr = step_r;
+        ci = step_i;
+        if (!MSFT) return;
         float big = 0.0f;
 #pragma unroll
         for (int e = 0; e + 1 < K; ++e) big = fmaxf(big, fmaxf(fabsf(b[e]), fabsf(d[e])));
@@ -246,18 +258,29 @@ struct Transmission {
         small = __all(k * (double)big < 0.125);
         full();
     }
+    // To the slice after one of (b, d); SMALL is `small`, taken out of the callers' loops.
+    template <bool SMALL>
     __device__ __forceinline__ void next(double b, double d)
     {
-        if (small) {
+        if (MSFT && SMALL) {
             double er, ei;
             slice_factor(-k0dz * b, -k0dz * d, &er, &ei);
-            const double t = tr;
-            tr = t * er - ti * ei;
-            ti = t * ei + ti * er;
-        } else {
+            const double fr = er * cr - ei * ci, fi = er * ci + ei * cr, t = tr;
+            tr = t * fr - ti * fi;
+            ti = t * fi + ti * fr;
+            return;
+        }
+        const double t = rr;
+        rr = t * cr - ri * ci;
+        ri = t * ci + ri * cr;
+        if (MSFT) {
             Sb += b;
             Sd += d;
             full();
+            __builtin_amdgcn_sched_barrier(0);   // one slice at a time: the registers are the common case's
+        } else {
+            tr = rr;
+            ti = ri;
         }
     }
 };
@@ -316,5 +339,10 @@ __device__ __forceinline__ void load_slices(const float* dc, const float* bc, in
         b[k] = ok ? b[k] : 0.0f;
     }
 }
+
+// LDS row of slice z in an array of slices by 16 (columns, parts): 17 doubles each and one
+// more every eight slices, so that the lanes of a column, four to eight slices apart, meet
+// different banks.
+constexpr int slice_row(int z) { return z * 17 + (z >> 3); }
 
 }  // namespace msft
