@@ -279,15 +279,15 @@ size_t sep_adj_layout(const msft_plan_s* p, size_t* k_off, size_t* r_off)
     return hb + kb + rb;
 }
 
-// Whether a plan is one for the spherical-coordinate form: the flat detector (its rows are
-// curves in one angle), in a precision whose outputs it does not change beyond their
-// rounding (plain BF16's are defined by it), and work enough that five launches beat the
-// direct form's two (32^3 voxels, 64^2 pixels, 1.3e8 terms: 28 us against 68).
+// Whether a plan is one for the spherical-coordinate form: a detector whose rows or columns
+// are curves in one angle (not a list of momenta), in a precision whose outputs it does not
+// change beyond their rounding (plain BF16's are defined by it), and work enough.
 bool ew_applies(const msft_plan_s* p)
 {
     const msft_geometry& g = p->geo.g;
     const double terms = (double)p->geo.npix * g.nx * g.ny * g.nz;
-    return !p->qlist && !p->separable && g.precision != MSFT_BF16 && terms >= EW_MIN_TERMS;
+    return !p->qlist && g.precision != MSFT_BF16 &&
+           terms >= (p->separable ? EW_MIN_TERMS_UNIFORM : EW_MIN_TERMS);
 }
 
 msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix, int device,

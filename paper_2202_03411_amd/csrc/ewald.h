@@ -30,7 +30,13 @@
 
 namespace msft {
 
-constexpr double EW_MIN_TERMS = 2e7;  // least pixels x voxels
+// Least pixels x voxels.  The form's six launches take 19 us of the host each way, the direct
+// form's two or three 6 to 9.  Flat, a pattern and a gradient: 16^3 voxels on 64^2 pixels
+// (1.7e7) 23 and 162 us against 33 and 145, 32^3 on 64^2 (1.3e8) 24 and 163 against 70 and
+// 171.  Uniform: 32^3 on 128^2 (5.4e8) 26 and 161 against 23 and 150, 64^3 on 64^2 (1.1e9) 30
+// and 163 against 35 and 177, on 256^2 32 and 161 against 47 and 177.
+constexpr double EW_MIN_TERMS = 2e7;
+constexpr double EW_MIN_TERMS_UNIFORM = 8e8;
 constexpr int EW_COLS = 16;       // columns (x, y) of one scan workgroup: the MFMA rows
 constexpr int EW_ZC = 64;         // slices of one scan round: a column's 16 lanes, four each
 // Columns of at most 256 slices are held whole, a workgroup's 256 threads in groups of

@@ -152,8 +152,8 @@ def _check(status: int, where: str):
 
 # Addresses cross as plain integers: every function above declares its argument types, and
 # c_void_p objects and the Stream object cost a forward 3.7 us of its 30 (26.5 now, 18.7 of
-# them launches). A gradient at
-# 128^3/512^2, whose backward runs on autograd's own thread, went from 166 to 131 us.
+# them launches); a gradient at 128^3/512^2, whose backward runs on autograd's own thread,
+# went from 166 to 131 us.
 
 def _ptr(t):
     if t is None:
