@@ -3,6 +3,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -597,7 +598,7 @@ msft_status shape_grid_args(const msft_shape_grid* g, RenderGrid* out)
     return MSFT_OK;
 }
 
-// Recurrence constants of the normalised Legendre values, FP64 on the host.
+// Norms of the real harmonics over their monic Legendre factors, FP64 on the host.
 msft_status sh_args(const msft_shape_grid* g, int32_t lmax, double r0, ShArgs* s)
 {
     msft_status st = shape_grid_args(g, &s->g);
@@ -606,21 +607,16 @@ msft_status sh_args(const msft_shape_grid* g, int32_t lmax, double r0, ShArgs* s
     if (!(r0 > 0.0) || !std::isfinite(r0)) return fail(MSFT_ERR_INVALID, "r0 must be finite and > 0");
     s->lmax = lmax;
     s->r0 = r0;
+    s->inv_edge = s->g.edge > 0.0 ? std::min(1.0 / s->g.edge, DBL_MAX) : 0.0;
+    double top = 0.28209479177387814347;   // Q_mm / sin^m(theta), Q_00 = 1 / sqrt(4 pi)
     for (int m = 0; m < SH_TABLE; ++m) {
-        s->diag[m] = m > 0 ? std::sqrt((2.0 * m + 1.0) / (2.0 * m)) : 1.0;
-        s->sub[m] = std::sqrt(2.0 * m + 3.0);
-    }
-    for (int l = 0; l < SH_TABLE; ++l)
-        for (int m = 0; m < SH_TABLE; ++m) {
-            double a = 0.0, b = 0.0;
-            if (l >= m + 2) {
-                const double ll = l, mm = m;
-                a = std::sqrt((4.0 * ll * ll - 1.0) / (ll * ll - mm * mm));
-                b = std::sqrt(((ll - 1.0) * (ll - 1.0) - mm * mm) / (4.0 * (ll - 1.0) * (ll - 1.0) - 1.0));
-            }
-            s->ra[l * SH_TABLE + m] = a;
-            s->rb[l * SH_TABLE + m] = b;
+        if (m > 0) top *= std::sqrt((2.0 * m + 1.0) / (2.0 * m));
+        double n = m > 0 ? top * std::sqrt(2.0) : top;
+        for (int l = m; l < SH_TABLE; ++l) {
+            if (l > m) n *= std::sqrt((4.0 * l * l - 1.0) / ((double)l * l - (double)m * m));
+            s->norm[l * SH_TABLE + m] = n;
         }
+    }
     return MSFT_OK;
 }
 

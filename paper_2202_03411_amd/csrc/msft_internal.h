@@ -264,10 +264,9 @@ struct FinArgs {
     double dV, k0dz;
 };
 
-// Shape rendering.  Real harmonics up to MAX_SH_L; the l-recurrence constants
-// Q_lm = ra (cos(theta) Q_{l-1,m} - rb Q_{l-2,m}) at [l * SH_TABLE + m], the
-// diagonal Q_mm = diag[m] sin(theta) Q_{m-1,m-1}, the first step Q_{m+1,m} =
-// sub[m] cos(theta) Q_mm, all made on the host in FP64.
+// Shape rendering.  Real harmonics up to MAX_SH_L: Y_lm = norm[l * SH_TABLE + m]
+// sin^m(theta) p_lm(cos(theta)) {cos, sin}(m phi) with p_lm of leading coefficient 1,
+// the norms made on the host in FP64.
 constexpr int MAX_SH_L = 12;
 constexpr int SH_TABLE = MAX_SH_L + 1;
 constexpr int MAX_SH_COEFFS = SH_TABLE * SH_TABLE;
@@ -281,9 +280,8 @@ struct RenderGrid {
 struct ShArgs {
     RenderGrid g;
     int32_t lmax;
-    double r0;
-    double diag[SH_TABLE], sub[SH_TABLE];
-    double ra[SH_TABLE * SH_TABLE], rb[SH_TABLE * SH_TABLE];
+    double r0, inv_edge;   // inv_edge: 0 for a hard edge
+    double norm[SH_TABLE * SH_TABLE];
 };
 
 struct VolArgs {

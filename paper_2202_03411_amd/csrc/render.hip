@@ -8,11 +8,12 @@
 //  render_ellipsoid_kernel quadric body, hard or soft
 //  render_volume_kernel    a voxel map on its own grid, resampled (trilinear)
 //
-// One thread per voxel; directions, radii and the harmonic sums in FP64 (a few
-// hundred flops per voxel, microseconds for 128^3), outputs in FP32.
+// The star body's kernels take eight mirror voxels to a thread, the others one voxel;
+// directions, radii and the harmonic sums in FP64, outputs in FP32.
 #include <hip/hip_runtime.h>
 
 #include "msft_internal.h"
+#include "wave_f64.h"
 
 namespace msft {
 
@@ -53,126 +54,305 @@ __device__ __forceinline__ VoxelDir voxel_dir(const RenderGrid& g, int64_t v)
     return d;
 }
 
-// Visit every real harmonic Y_lm, l <= L, at a direction: f(index l*l + l + m, value).
-// Normalised associated Legendre values Q_lm (no Condon-Shortley sign) by the
-// recurrences in m (diagonal) and in l (three-term), cos/sin(m phi) by angle
-// addition; the recurrence constants come from the host.  L is a compile-time
-// bound, so the loops unroll and every index is a constant.
-template <int L, typename F>
-__device__ __forceinline__ void for_each_ylm(const ShArgs& s, const VoxelDir& d, F f)
-{
-    const double rt2 = 1.4142135623730950488;
-    double qmm = 0.28209479177387814347;   // Q_00 = 1 / sqrt(4 pi)
-    double cm = 1.0, sm = 0.0;             // cos(m phi), sin(m phi)
-#pragma unroll
-    for (int m = 0; m <= L; ++m) {
-        if (m > 0) {
-            qmm *= s.diag[m] * d.st;
-            const double c2 = cm * d.cp - sm * d.sp;
-            sm = sm * d.cp + cm * d.sp;
-            cm = c2;
-        }
-        double q2 = 0.0, q1 = qmm;   // Q_{l-2,m}, Q_{l-1,m} as l advances
-#pragma unroll
-        for (int l = m; l <= L; ++l) {
-            double q;
-            if (l == m) {
-                q = qmm;
-            } else if (l == m + 1) {
-                q = s.sub[m] * d.ct * qmm;
-                q2 = qmm;
-                q1 = q;
-            } else {
-                q = s.ra[l * SH_TABLE + m] * (d.ct * q1 - s.rb[l * SH_TABLE + m] * q2);
-                q2 = q1;
-                q1 = q;
-            }
-            if (m == 0) {
-                f(l * l + l, q);
-            } else {
-                f(l * l + l + m, rt2 * q * cm);
-                f(l * l + l - m, rt2 * q * sm);
-            }
-        }
-    }
-}
-
 __device__ __forceinline__ double occupancy(double rs, double r, double edge)
 {
     if (edge <= 0.0) return r <= rs ? 1.0 : 0.0;
     return 1.0 / (1.0 + exp(-(rs - r) / edge));
 }
 
-// Coefficients into LDS, zero beyond (lmax + 1)^2 up to (L + 1)^2.
-template <int L>
-__device__ __forceinline__ void load_coeffs(const ShArgs& s, const float* coeffs, float* c)
+// ---------------------------------------------------------------------------
+// The star body.  The voxels (+-x, +-y, +-z) share r, the powers of sin and cos(theta) and
+// cos and sin(m phi) up to signs, so a thread takes the eight of one octant: it sums
+// the harmonics by their parities (z: l - m, x: m or m + 1, y: cos or sin) and the eight
+// radii are the parities' signed sums.  Y_lm = norm sin^m p_lm {cos, sin}(m phi) with
+// monic p: p_l = cos p_{l-1} - ((l-1)^2 - m^2) / (4 (l-1)^2 - 1) p_{l-2}, two operations.
+// Bound by FP64 operations, about 90 a voxel with the exponential (one voxel to a thread
+// took some 570): 128^3, l <= 8, forward 57 -> 12.7 us, gradient 138 -> 19.0 us.
+// ---------------------------------------------------------------------------
+constexpr int SH_GRAD_RESIDENT = 256;
+constexpr int sh_at(int L, int l, int m) { return m * (L + 1) - m * (m - 1) / 2 + l - m; }
+constexpr int sh_pairs(int L) { return (L + 1) * (L + 2) / 2; }
+constexpr double sh_gamma(int l, int m)
 {
-    const int nc = (s.lmax + 1) * (s.lmax + 1);
-    for (int k = threadIdx.x; k < (L + 1) * (L + 1); k += blockDim.x) c[k] = k < nc ? coeffs[k] : 0.0f;
+    return ((double)(l - 1) * (l - 1) - (double)m * m) / (4.0 * (l - 1) * (l - 1) - 1.0);
+}
+
+// exp(x), |x| <= 700: range reduction and the Taylor series on |r| <= ln(2) / 2 to
+// r^13 / 13! (remainder 4e-18).
+__device__ __forceinline__ double exp_f64(double x)
+{
+    const double n = rint(x * 1.4426950408889634074);
+    double r = __builtin_fma(n, -0.69314718055994528623, x);
+    r = __builtin_fma(n, -2.3190468138462996e-17, r);
+    double p = 1.0 / 6227020800.0;
+    p = __builtin_fma(p, r, 1.0 / 479001600.0);
+    p = __builtin_fma(p, r, 1.0 / 39916800.0);
+    p = __builtin_fma(p, r, 1.0 / 3628800.0);
+    p = __builtin_fma(p, r, 1.0 / 362880.0);
+    p = __builtin_fma(p, r, 1.0 / 40320.0);
+    p = __builtin_fma(p, r, 1.0 / 5040.0);
+    p = __builtin_fma(p, r, 1.0 / 720.0);
+    p = __builtin_fma(p, r, 1.0 / 120.0);
+    p = __builtin_fma(p, r, 1.0 / 24.0);
+    p = __builtin_fma(p, r, 1.0 / 6.0);
+    p = __builtin_fma(p, r, 0.5);
+    p = __builtin_fma(p, r, 1.0);
+    p = __builtin_fma(p, r, 1.0);
+    return __builtin_ldexp(p, (int)n);
+}
+
+__device__ __forceinline__ double reciprocal(double d)
+{
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+}
+
+// Item t of plane `ha`: the octant's voxel at the non-negative coordinates and its seven
+// mirrors, v[4 kz + 2 kx + ky] (k = 1: the mirrored side).  An axis's middle voxel is its
+// own mirror: `own` says which of the eight are there once.
+struct Octant {
+    double r, ct, px, py;   // distance; z, x and y over it (+z at the origin)
+    int64_t v[8];
+    bool in, two[3];        // within the plane; z, x, y have a mirror of their own
+
+    __device__ __forceinline__ void at(const RenderGrid& g, int ha, uint32_t t)
+    {
+        const uint32_t nyh = (uint32_t)(g.ny + 1) >> 1, nzh = (uint32_t)(g.nz + 1) >> 1;
+        in = t < nyh * nzh;
+        if (!in) t = nyh * nzh - 1;
+        const int hb = (int)(t / nzh), hk = (int)(t - (uint32_t)hb * nzh);
+        const int a = g.nx - 1 - ha, b = g.ny - 1 - hb, k = g.nz - 1 - hk;
+        two[0] = k != hk;
+        two[1] = a != ha;
+        two[2] = b != hb;
+        const double x = ((double)(2 * a + 1 - g.nx) * g.dx) / 2.0;
+        const double y = ((double)(2 * b + 1 - g.ny) * g.dy) / 2.0;
+        const double z = ((double)(2 * k + 1 - g.nz) * g.dz) / 2.0;
+        r = sqrt(x * x + y * y + z * z);
+        const double i = r > 0.0 ? reciprocal(r) : 0.0;
+        ct = r > 0.0 ? z * i : 1.0;
+        px = x * i;
+        py = y * i;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = ((int64_t)(e & 2 ? ha : a) * g.ny + (e & 1 ? hb : b)) * g.nz + (e & 4 ? hk : k);
+    }
+    __device__ __forceinline__ bool own(int e) const
+    {
+        return in && (!(e & 4) || two[0]) && (!(e & 2) || two[1]) && (!(e & 1) || two[2]);
+    }
+};
+
+// Sums and differences over the three parities: w[4 z + 2 x + y].
+__device__ __forceinline__ void octant_signs(double* w)
+{
+#pragma unroll
+    for (int s = 1; s < 8; s *= 2)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (!(e & s)) {
+                const double a = w[e], b = w[e | s];
+                w[e] = a + b;
+                w[e | s] = a - b;
+            }
+}
+
+// norm times coefficient of (l, m) and (l, -m) at 2 sh_at(L, l, m), zero beyond lmax.
+template <int L>
+__device__ __forceinline__ void sh_coefficients(const ShArgs& s, const float* coeffs, double* c)
+{
+    for (int k = threadIdx.x; k < 2 * sh_pairs(L); k += blockDim.x) {
+        int m = 0, i = k >> 1;
+        while (i > L - m) i -= L + 1 - m++;
+        const int l = m + i;
+        double v = 0.0;
+        if (l <= s.lmax && (m > 0 || !(k & 1))) v = s.norm[l * SH_TABLE + m] * (double)coeffs[l * l + l + (k & 1 ? -m : m)];
+        c[k] = v;
+    }
+}
+
+// 1 + sum c_lm Y_lm at an octant's eight voxels.
+template <int L>
+__device__ __forceinline__ void sh_radii(const Octant& o, const double* c, double* R)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) R[e] = 0.0;
+    double cm = 1.0, sm = 0.0;   // sin^m(theta) {cos, sin}(m phi)
+#pragma unroll
+    for (int m = 0; m <= L; ++m) {
+        if (m > 0) {
+            const double c2 = cm * o.px - sm * o.py;
+            sm = sm * o.px + cm * o.py;
+            cm = c2;
+        }
+        
+        double u[2] = {0.0, 0.0}, v[2] = {0.0, 0.0}, p2 = 0.0, p1 = 0.0;
+#pragma unroll
+        for (int l = m; l <= L; ++l) {
+            const double p = l == m ? 1.0 : l == m + 1 ? o.ct : __builtin_fma(o.ct, p1, -sh_gamma(l, m) * p2);
+            p2 = p1;
+            p1 = p;
+            const double* k = c + 2 * sh_at(L, l, m);
+            u[(l - m) & 1] += k[0] * p;
+            if (m > 0) v[(l - m) & 1] += k[1] * p;
+        }
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            if (z > L - m) continue;
+            R[4 * z + 2 * (m & 1)] += cm * u[z];
+            if (m > 0) R[4 * z + 2 * (~m & 1) + 1] += sm * v[z];
+        }
+    }
+    R[0] += 1.0;
+    octant_signs(R);
+}
+
+// exp(-x) of the soft occupancy 1 / (1 + exp(-x)), x = (rs - r) / edge held to +-700 (NaN
+// passes).
+__device__ __forceinline__ double edge_exp(double rs, double r, double inv_edge)
+{
+    double x = (r - rs) * inv_edge;
+    x = x > 700.0 ? 700.0 : x;
+    return exp_f64(x < -700.0 ? -700.0 : x);
 }
 
 template <int L>
 __global__ __launch_bounds__(256) void render_sh_kernel(ShArgs s, const float* coeffs, float* delta,
                                                         float* beta)
 {
-    __shared__ float c[(L + 1) * (L + 1)];
-    load_coeffs<L>(s, coeffs, c);
+    __shared__ double c[2 * sh_pairs(L)];
+    sh_coefficients<L>(s, coeffs, c);
     __syncthreads();
-    const int64_t nv = (int64_t)s.g.nx * s.g.ny * s.g.nz;
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nv) return;
-    const VoxelDir d = voxel_dir(s.g, v);
-    double acc = 0.0;
-    for_each_ylm<L>(s, d, [&](int idx, double y) { acc += (double)c[idx] * y; });
-    const double o = occupancy(s.r0 * (1.0 + acc), d.r, s.g.edge);
-    delta[v] = (float)(s.g.delta0 * o);
-    beta[v] = (float)(s.g.beta0 * o);
+    Octant o;
+    o.at(s.g, blockIdx.y, blockIdx.x * 256 + threadIdx.x);
+    double R[8];
+    sh_radii<L>(o, c, R);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const double rs = s.r0 * R[e];
+        double occ;
+        if (s.inv_edge > 0.0) occ = reciprocal(1.0 + edge_exp(rs, o.r, s.inv_edge));
+        else occ = o.r <= rs ? 1.0 : 0.0;
+        if (!o.own(e)) continue;
+        delta[o.v[e]] = (float)(s.g.delta0 * occ);
+        beta[o.v[e]] = (float)(s.g.beta0 * occ);
+    }
 }
 
-// dL/dc_lm = sum_v (gd delta0 + gb beta0) o (1 - o) / edge r0 Y_lm.  Each thread
-// sums its voxels (grid stride) in FP32 per coefficient, the wave reduces by
-// shuffles, the workgroup's four wave sums go to FP64 partials [block][coeff].
-template <int L>
-__global__ __launch_bounds__(256) void render_sh_grad_kernel(ShArgs s, const float* coeffs,
-                                                             const float* gd, const float* gb,
-                                                             double* partial)
+// a, b -> a's sums of the two halves of a wave in the lower half, b's in the upper
+// (HALF = 32); the same of neighbouring rows of 16 lanes (HALF = 16).
+template <int HALF>
+__device__ __forceinline__ double swap_add(double a, double b)
 {
-    constexpr int NC = (L + 1) * (L + 1);
-    __shared__ float c[NC];
-    __shared__ float wsum[4][NC];
-    load_coeffs<L>(s, coeffs, c);
+    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
+    auto lo = HALF == 32 ? __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false)
+                         : __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+    auto hi = HALF == 32 ? __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false)
+                         : __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+__device__ __forceinline__ double row_sum_f64(double v)
+{
+    v += dpp_f64<0x128, 0xF>(v);   // row_ror 8, 4, 2, 1
+    v += dpp_f64<0x124, 0xF>(v);
+    v += dpp_f64<0x122, 0xF>(v);
+    return v + dpp_f64<0x121, 0xF>(v);
+}
+
+// dL/dc_lm = sum_v (gd delta0 + gb beta0) o (1 - o) / edge r0 Y_lm for M0 <= m < M1.  A
+// thread walks octants in a grid stride: the eight weights' parity sums times p_lm, in FP64
+// registers, summed over the wave by halves, quarters and rows, over the workgroup's waves
+// in LDS, into partials [block][coeff].  m is cut in two for L = 12, whose 169 sums do not
+// fit the registers.
+template <int L, int M0, int M1>
+__global__ __launch_bounds__(256, 1) void render_sh_grad_kernel(ShArgs s, const float* coeffs,
+                                                                const float* gd, const float* gb,
+                                                                double* partial)
+{
+    constexpr int FIRST = sh_at(L, M0, M0), COUNT = 2 * (sh_at(L, M1, M1) - FIRST);
+    constexpr int S1 = (COUNT + 1) / 2, S2 = (S1 + 1) / 2;
+    __shared__ double c[2 * sh_pairs(L)];
+    __shared__ double wsum[4][4 * S2];
+    sh_coefficients<L>(s, coeffs, c);
     __syncthreads();
-    float acc[NC];
+    double acc[4 * S2];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) acc[k] = 0.0f;
-    const int64_t nv = (int64_t)s.g.nx * s.g.ny * s.g.nz;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += stride) {
-        const VoxelDir d = voxel_dir(s.g, v);
-        double rs = 0.0;
-        for_each_ylm<L>(s, d, [&](int idx, double y) { rs += (double)c[idx] * y; });
-        const double o = occupancy(s.r0 * (1.0 + rs), d.r, s.g.edge);
-        const double w = ((double)gd[v] * s.g.delta0 + (double)gb[v] * s.g.beta0) * o * (1.0 - o) /
-                         s.g.edge * s.r0;
-        // Recompute the harmonics from a voxel index the compiler cannot prove equal
-        // to v: reusing the first pass's values keeps all (L+1)^2 of them live in FP64
-        // across the radius and the weight, which spills at L = 12 (4x slower there).
-        int64_t v2 = v;
-        asm volatile("" : "+v"(v2));
-        const VoxelDir d2 = voxel_dir(s.g, v2);
-        for_each_ylm<L>(s, d2, [&](int idx, double y) { acc[idx] += (float)(w * y); });
+    for (int k = 0; k < 4 * S2; ++k) acc[k] = 0.0;
+    const uint32_t plane = ((uint32_t)(s.g.ny + 1) >> 1) * ((uint32_t)(s.g.nz + 1) >> 1);
+    const uint32_t chunks = (plane + 255) / 256, total = chunks * ((uint32_t)(s.g.nx + 1) >> 1);
+    const double scale = s.inv_edge * s.r0;
+    for (uint32_t k = blockIdx.x; k < total; k += gridDim.x) {
+        const uint32_t ha = k / chunks;
+        Octant o;
+        o.at(s.g, (int)ha, (k - ha * chunks) * 256 + threadIdx.x);
+        float d[8], b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            d[e] = gd[o.v[e]];
+            b[e] = gb[o.v[e]];
+        }
+        // an offset the compiler cannot see through: the coefficients, the same each time,
+        // would be kept in registers (2 (L + 1)^2 of them)
+        int opaque = 0;
+        asm volatile("" : "+v"(opaque));
+        double w[8];
+        sh_radii<L>(o, c + opaque, w);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double x = edge_exp(s.r0 * w[e], o.r, s.inv_edge), occ = reciprocal(1.0 + x);
+            const double g = (double)d[e] * s.g.delta0 + (double)b[e] * s.g.beta0;
+            w[e] = o.own(e) ? g * (x * occ) * occ * scale : 0.0;   // 1 - o = exp(-x) o
+        }
+        octant_signs(w);
+        double cm = 1.0, sm = 0.0;
+#pragma unroll
+        for (int m = 0; m < M1; ++m) {
+            if (m > 0) {
+                const double c2 = cm * o.px - sm * o.py;
+                sm = sm * o.px + cm * o.py;
+                cm = c2;
+            }
+            if (m < M0) continue;
+            __builtin_amdgcn_sched_barrier(0);
+            double u[2], v[2], p2 = 0.0, p1 = 0.0;
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                u[z] = cm * w[4 * z + 2 * (m & 1)];
+                v[z] = sm * w[4 * z + 2 * (~m & 1) + 1];
+            }
+#pragma unroll
+            for (int l = m; l <= L; ++l) {
+                const double p = l == m ? 1.0 : l == m + 1 ? o.ct : __builtin_fma(o.ct, p1, -sh_gamma(l, m) * p2);
+                p2 = p1;
+                p1 = p;
+                const int at = 2 * (sh_at(L, l, m) - FIRST);
+                acc[at] += p * u[(l - m) & 1];
+                if (m > 0) acc[at + 1] += p * v[(l - m) & 1];
+            }
+        }
     }
+    // value 4 j + i of the wave ends in row 2 (i & 1) + (i >> 1) of register j
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        float v = acc[k];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) wsum[wave][k] = v;
+    for (int j = 0; j < S2; ++j) {
+        const double v = row_sum_f64(swap_add<16>(swap_add<32>(acc[4 * j], acc[4 * j + 1]),
+                                                  swap_add<32>(acc[4 * j + 2], acc[4 * j + 3])));
+        const int row = lane >> 4;
+        if ((lane & 15) == 0) wsum[wave][4 * j + (row >> 1) + 2 * (row & 1)] = v;
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < NC; k += blockDim.x)
-        partial[(int64_t)blockIdx.x * MAX_SH_COEFFS + k] =
-            (((double)wsum[0][k] + (double)wsum[1][k]) + (double)wsum[2][k]) + (double)wsum[3][k];
+    for (int k = threadIdx.x; k < COUNT; k += 256) {
+        int m = M0, i = k >> 1;
+        while (i > L - m) i -= L + 1 - m++;
+        const int l = m + i;
+        if (m == 0 && (k & 1)) continue;
+        partial[(int64_t)blockIdx.x * MAX_SH_COEFFS + l * l + l + (k & 1 ? -m : m)] =
+            s.norm[l * SH_TABLE + m] * (((wsum[0][k] + wsum[1][k]) + wsum[2][k]) + wsum[3][k]);
+    }
 }
 
 // One workgroup per coefficient: thread t adds the partials b = t, t + 256, ... in
@@ -260,8 +440,7 @@ int launch_render_volume(const VolArgs& a, const float* sd, const float* sb, flo
 
 int launch_render_sh(const ShArgs& s, const float* coeffs, float* delta, float* beta, void* stream)
 {
-    const int64_t nv = (int64_t)s.g.nx * s.g.ny * s.g.nz;
-    const dim3 grid((unsigned)ceil_div(nv, 256));
+    const dim3 grid((unsigned)ceil_div((int64_t)((s.g.ny + 1) / 2) * ((s.g.nz + 1) / 2), 256), (unsigned)((s.g.nx + 1) / 2));
     hipStream_t st = (hipStream_t)stream;
     if (s.lmax <= 8)
         hipLaunchKernelGGL(render_sh_kernel<8>, grid, dim3(256), 0, st, s, coeffs, delta, beta);
@@ -274,12 +453,18 @@ int launch_render_sh_grad(const ShArgs& s, const float* coeffs, const float* gd,
                           float* grad, double* partial, int nblocks, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (s.lmax <= 8)
-        hipLaunchKernelGGL(render_sh_grad_kernel<8>, dim3((unsigned)nblocks), dim3(256), 0, st, s,
-                           coeffs, gd, gb, partial);
-    else
-        hipLaunchKernelGGL(render_sh_grad_kernel<MAX_SH_L>, dim3((unsigned)nblocks), dim3(256), 0, st,
-                           s, coeffs, gd, gb, partial);
+    // the sums take over 256 registers a lane, so one workgroup fits a CU: one for each (the
+    // 128^3 gradient takes 19.0 us, with two for each 22.6)
+    nblocks = nblocks < SH_GRAD_RESIDENT ? nblocks : SH_GRAD_RESIDENT;
+    const dim3 grid((unsigned)nblocks);
+    if (s.lmax <= 8) {
+        hipLaunchKernelGGL((render_sh_grad_kernel<8, 0, 9>), grid, dim3(256), 0, st, s, coeffs, gd, gb, partial);
+    } else {
+        constexpr int CUT = 4;   // 92 sums below m = 4, 90 from there on
+        hipLaunchKernelGGL((render_sh_grad_kernel<MAX_SH_L, 0, CUT>), grid, dim3(256), 0, st, s, coeffs, gd, gb, partial);
+        hipLaunchKernelGGL((render_sh_grad_kernel<MAX_SH_L, CUT, SH_TABLE>), grid, dim3(256), 0, st, s, coeffs, gd, gb,
+                           partial);
+    }
     const int nc = (s.lmax + 1) * (s.lmax + 1);
     hipLaunchKernelGGL(render_sh_grad_reduce, dim3((unsigned)nc), dim3(256), 0, st, (const double*)partial,
                        nblocks, grad);

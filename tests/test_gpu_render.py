@@ -164,3 +164,31 @@ def test_render_volume_matches_oracle(env):
         assert np.max(np.abs(d - od)) <= 3e-9 and np.max(np.abs(b - ob)) <= 3e-9
         if tg == sg:
             assert np.array_equal(d, sd) and np.array_equal(b, sb)
+
+
+@pytest.mark.parametrize("grid,lmax", [((9, 7, 11), 8), ((9, 7, 11), 12), ((2, 1, 3), 5), ((5, 6, 520), 8),
+                                       ((3, 50, 21), 9), ((64, 64, 64), 8)])
+def test_render_sh_mirrored_voxels(env, grid, lmax):
+    # Eight mirror voxels a thread: odd axes (middle voxels are their own mirrors, the origin
+    # among them), planes that do not fill a workgroup or need several, more octants than one
+    # pass of the gradient's grid.  The sums run in FP64: FP32 roundings of the outputs are
+    # left, 1e-6 of the optical constant and of the gradient's norm.
+    torch, msft, _ = env
+    pitch = tuple(200.0 / max(grid) * f for f in (1.0, 1.1, 0.9))
+    r0, edge = 0.35 * 200.0, 200.0 / max(grid)
+    c = _coeffs(lmax, 20 + lmax).astype(np.float32).astype(np.float64)
+    print(f"[gpu] render_sh mirrored grid={grid} lmax={lmax}", flush=True)
+    for e in (edge, 0.0):
+        d, b = _render(env, grid, pitch, lmax, r0, c, e)
+        od, ob = oracle.render_sh(grid, pitch, c, r0, e, 0.01, 0.02)
+        assert np.max(np.abs(d - od)) <= 1e-6 * 0.01 and np.max(np.abs(b - ob)) <= 1e-6 * 0.02
+    rng = np.random.default_rng(30 + lmax)
+    gd, gb = (rng.normal(size=grid).astype(np.float32) for _ in range(2))
+    ct = torch.tensor(c, dtype=torch.float32, device="cuda")
+    out = torch.full_like(ct, float("nan"))
+    msft.msft_render_sh_backward(msft.make_shape_grid(grid, pitch, edge, 0.01, 0.02), lmax, r0, ct,
+                                 torch.from_numpy(gd).cuda(), torch.from_numpy(gb).cuda(), out,
+                                 msft.workspace_tensor(msft.msft_render_sh_query(lmax), "cuda"))
+    ref = oracle.render_sh_backward(grid, pitch, c, r0, edge, 0.01, 0.02, gd.astype(np.float64),
+                                    gb.astype(np.float64))
+    assert np.linalg.norm(out.double().cpu().numpy() - ref) <= 1e-6 * np.linalg.norm(ref)
