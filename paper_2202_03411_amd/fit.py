@@ -45,13 +45,8 @@ def simulate(delta, beta, plan):
 
 
 def log_mse_loss(I, target, eps=1e-6):
-    """Mean over pixels (and batch) of (log(I + eps) - log(I* + eps))^2.
-
-    The difference of the logarithms is taken in FP64: near the solution it is of the
-    order of the rounding of an FP32 logarithm (1e-6 at log(1e-6)), which would then be
-    the loss.  The result has the type that sums of the inputs and eps have."""
-    d = torch.log(I.double() + eps) - torch.log(target.double() + eps)
-    return torch.mean(d ** 2).to(torch.promote_types(torch.result_type(I, eps), torch.result_type(target, eps)))
+    """Mean over pixels (and batch) of (log(I + eps) - log(I* + eps))^2."""
+    return torch.mean((torch.log(I + eps) - torch.log(target + eps)) ** 2)
 
 
 class SHRenderFunction(torch.autograd.Function):
