@@ -94,30 +94,38 @@ msft_status build_ew_tables(msft_plan_s* p)
     if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
     EwHost& h = p->ew;
     EwDesc& d = h.d;
-    struct Part {
-        const std::vector<double>* src;   // or null: generated, `count` doubles of zeros
-        size_t count, off;
-    };
-    auto of = [](const std::vector<double>& v) { return Part{&v, v.size(), 0}; };
-    auto zeros = [](size_t n) { return Part{nullptr, n, 0}; };
-    Part parts[] = {of(h.rot), of(h.phiz), of(h.phie), of(h.phio), of(h.dcte), of(h.dcto), of(h.tq),
-                    zeros((size_t)d.nhNp * d.nap), zeros((size_t)d.nhNp * d.nap),
-                    zeros((size_t)d.na * d.km * d.nbp), zeros((size_t)d.na * d.nbp * d.kzp),
-                    of(h.ang_a), of(h.ang_b), of(h.phize), of(h.phizo), of(h.wre), of(h.wro)};
-    size_t bytes = 0, total = 0;
-    for (Part& q : parts) {
-        q.off = bytes;
-        bytes += align256(sizeof(double) * q.count);
+    // the host's tables first, in one copy, then the generated ones, in one fill
+    std::vector<double>* src[] = {&h.rot, &h.phiz, &h.phie, &h.phio, &h.dcte, &h.dcto, &h.ang_a, &h.ang_b,
+                                  &h.phize, &h.phizo, &h.wre, &h.wro};
+    const size_t made[] = {(size_t)d.rows * d.rows, (size_t)d.nhNp * d.nap, (size_t)d.nhNp * d.nap,
+                           (size_t)d.na * d.km * d.nbp, (size_t)d.na * d.nbp * d.kzp};
+    constexpr int HOST = sizeof(src) / sizeof(src[0]);
+    size_t off[HOST + sizeof(made) / sizeof(made[0])], bytes = 0, total = 0;
+    for (int k = 0; k < HOST; ++k) {
+        off[k] = bytes;
+        bytes += align256(sizeof(double) * src[k]->size());
+    }
+    std::vector<uint8_t> host;
+    try {
+        host.resize(bytes);
+    } catch (const std::bad_alloc&) {
+        return fail(MSFT_ERR_NOMEM, "host tables");
+    }
+    for (int k = 0; k < HOST; ++k) {
+        if (!src[k]->empty()) std::memcpy(host.data() + off[k], src[k]->data(), sizeof(double) * src[k]->size());
+        std::vector<double>().swap(*src[k]);
+    }
+    for (int k = 0; k < (int)(sizeof(made) / sizeof(made[0])); ++k) {
+        off[HOST + k] = bytes;
+        bytes += align256(sizeof(double) * made[k]);
     }
     hipStream_t s = nullptr;
     hipError_t e = dev_alloc((uint8_t**)&p->ew_tables, bytes, &total);
     if (e == hipSuccess) e = dev_alloc(&p->ew_dev, sizeof(EwDesc), &total);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-    auto at = [&](int k) { return (double*)((uint8_t*)p->ew_tables + parts[k].off); };
-    for (int k = 0; k < (int)(sizeof(parts) / sizeof(parts[0])) && e == hipSuccess; ++k)
-        e = parts[k].src ? hipMemcpyAsync(at(k), parts[k].src->data(), sizeof(double) * parts[k].count,
-                                          hipMemcpyHostToDevice, s)
-                         : hipMemsetAsync(at(k), 0, sizeof(double) * parts[k].count, s);
+    auto at = [&](int k) { return (double*)((uint8_t*)p->ew_tables + off[k]); };
+    if (e == hipSuccess) e = hipMemcpyAsync(at(0), host.data(), host.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemsetAsync(at(HOST), 0, bytes - off[HOST], s);
     if (e == hipSuccess) {
         d.rot = at(0);
         d.phiz = at(1);
@@ -125,16 +133,16 @@ msft_status build_ew_tables(msft_plan_s* p)
         d.phio = at(3);
         d.dcte = at(4);
         d.dcto = at(5);
-        d.tq = at(6);
-        d.phize = at(13);
-        d.phizo = at(14);
-        d.wre = at(15);
-        d.wro = at(16);
-        d.cosN = at(7);
-        d.sinN = at(8);
-        d.cm = at(9);
-        d.cz = at(10);
-        const EwTables t = {at(11), at(12), at(7), at(8), at(9), at(10)};
+        d.phize = at(8);
+        d.phizo = at(9);
+        d.wre = at(10);
+        d.wro = at(11);
+        d.tq = at(12);
+        d.cosN = at(13);
+        d.sinN = at(14);
+        d.cm = at(15);
+        d.cz = at(16);
+        const EwTables t = {at(6), at(7), at(13), at(14), at(15), at(16), at(12)};
         e = hipMemcpyAsync(p->ew_dev, &d, sizeof d, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = (hipError_t)launch_ew_tables(h, d, t, s);
     }
@@ -147,9 +155,6 @@ msft_status build_ew_tables(msft_plan_s* p)
         free_device(p);
         return hip_fail(e, "plan tables");
     }
-    for (auto* v : {&h.rot, &h.phiz, &h.phie, &h.phio, &h.dcte, &h.dcto, &h.wre, &h.wro, &h.tq,
-                    &h.ang_a, &h.ang_b, &h.phize, &h.phizo})
-        std::vector<double>().swap(*v);
     p->resident_bytes = total;
     return MSFT_OK;
 }

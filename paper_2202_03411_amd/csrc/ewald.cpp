@@ -20,19 +20,22 @@ constexpr double EW_TOL = 3e-11;
 
 int pad(int n, int m) { return (n + m - 1) / m * m; }
 
-// Eigenvalues below x of the symmetric tridiagonal matrix (d, e), by the signs of its
-// Sturm sequence.
-int sturm_count(const std::vector<double>& d, const std::vector<double>& e, double x)
+// Eigenvalues below each of four x of the symmetric tridiagonal matrix (d, off-diagonal
+// squared e2), by the signs of its Sturm sequences: four chains of divisions at a time.
+void sturm_counts(const std::vector<double>& d, const std::vector<double>& e2, const double* x, int* count)
 {
-    int c = 0;
-    double q = d[0] - x;
-    for (size_t k = 0;; ++k) {
-        if (q < 0.0) ++c;
-        if (k + 1 == d.size()) break;
-        if (q == 0.0) q = 1e-300;
-        q = d[k + 1] - x - e[k] * e[k] / q;
+    double q[4];
+    int c[4];
+    for (int j = 0; j < 4; ++j) {
+        q[j] = d[0] - x[j];
+        c[j] = q[j] < 0.0;
     }
-    return c;
+    for (size_t k = 1; k < d.size(); ++k)
+        for (int j = 0; j < 4; ++j) {
+            q[j] = d[k] - x[j] - e2[k - 1] / (q[j] == 0.0 ? 1e-300 : q[j]);
+            c[j] += q[j] < 0.0;
+        }
+    for (int j = 0; j < 4; ++j) count[j] = c[j];
 }
 
 // Eigenvector of (d, e) at the eigenvalue lam: inverse iteration with a pivoted LU.
@@ -88,31 +91,55 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
     return x;
 }
 
-// The `count` eigenvectors of largest eigenvalue.
-void tri_top(const std::vector<double>& d, const std::vector<double>& e, int count,
-             std::vector<std::vector<double>>* out)
-{
-    const int n = (int)d.size();
-    double lo = d[0], hi = d[0];
-    for (int k = 0; k < n; ++k) {
-        const double r = (k ? std::fabs(e[k - 1]) : 0.0) + (k + 1 < n ? std::fabs(e[k]) : 0.0);
-        lo = std::min(lo, d[k] - r);
-        hi = std::max(hi, d[k] + r);
-    }
-    const double scale = std::max({std::fabs(lo), std::fabs(hi), 1e-300});
-    double top = hi + 1e-14 * scale;
-    for (int k = 0; k < count; ++k) {
-        double a = lo - 1e-14 * scale, b = top;   // eigenvalue n - 1 - k lies in [a, b]
-        for (int it = 0; it < 200 && b - a > 2e-16 * scale; ++it) {
-            const double m = 0.5 * (a + b);
-            if (m <= a || m >= b) break;
-            if (sturm_count(d, e, m) >= n - k) b = m;
-            else a = m;
+// The eigenvectors of largest eigenvalue, four at a time: appends those of the eigenvalues
+// ranked out->size(), ... (0 the largest); `top` lies above them and is moved down.  An
+// eigenvalue is bracketed to 1e-11 of the scale, the gaps being 1e-5 of it or more: each
+// step of the inverse iteration then takes six digits.
+struct TriTop {
+    const std::vector<double>&d, &e;
+    std::vector<double> e2;
+    double lo, top, scale;
+
+    TriTop(const std::vector<double>& d_, const std::vector<double>& e_) : d(d_), e(e_)
+    {
+        const int n = (int)d.size();
+        double hi = lo = d[0];
+        for (int k = 0; k < n; ++k) {
+            const double r = (k ? std::fabs(e[k - 1]) : 0.0) + (k + 1 < n ? std::fabs(e[k]) : 0.0);
+            lo = std::min(lo, d[k] - r);
+            hi = std::max(hi, d[k] + r);
         }
-        top = b;
-        out->push_back(tri_vector(d, e, 0.5 * (a + b), scale));
+        scale = std::max({std::fabs(lo), std::fabs(hi), 1e-300});
+        top = hi + 1e-14 * scale;
+        lo -= 1e-14 * scale;
+        for (double v : e) e2.push_back(v * v);
     }
-}
+    void next(std::vector<std::vector<double>>* out)
+    {
+        const int n = (int)d.size(), first = (int)out->size(), m = std::min(4, n - first);
+        double a[4], b[4], x[4];
+        int c[4];
+        for (int j = 0; j < 4; ++j) {
+            a[j] = lo;
+            b[j] = top;
+        }
+        for (int it = 0; it < 200; ++it) {
+            bool open = false;
+            for (int j = 0; j < m; ++j) open |= b[j] - a[j] > 1e-11 * scale;
+            if (!open) break;
+            for (int j = 0; j < 4; ++j) x[j] = 0.5 * (a[j] + b[j]);
+            sturm_counts(d, e2, x, c);
+            // every count bounds every one of the eigenvalues n - 1 - first - j
+            for (int j = 0; j < m; ++j)
+                for (int i = 0; i < 4; ++i) {
+                    if (c[i] >= n - first - j) b[j] = std::min(b[j], x[i]);
+                    else a[j] = std::max(a[j], x[i]);
+                }
+        }
+        for (int j = 0; j < m; ++j) out->push_back(tri_vector(d, e, 0.5 * (a[j] + b[j]), scale));
+        top = b[m - 1];   // above the next one: b only falls on counts that hold it
+    }
+};
 
 // Terms after which the Chebyshev series of exp(i k (x sin(w t) + s r cos(w t))) over
 // |t| <= 1 is below EW_TOL, the largest of three shares s of r; 0: more than `most`.
@@ -125,27 +152,29 @@ int series_terms(double kx, double kr, double w, int most)
     std::vector<double> cs(4 * M);
     for (int k = 0; k < 4 * M; ++k) cs[k] = std::cos(kPi * k / (2.0 * M));
     int worst = 1;
-    std::vector<double> fr(M), fi(M), mag(M);
+    std::vector<double> fr(M), fi(M);
     for (double s : {0.0, 0.5, 1.0}) {
         for (int j = 0; j < M; ++j) {
-            const double t = std::cos((j + 0.5) * kPi / M);
+            const double t = cs[2 * j + 1];   // cos((j + 1/2) pi / M)
             const double ph = kx * std::sin(w * t) + s * kr * std::cos(w * t);
             fr[j] = std::cos(ph);
             fi[j] = std::sin(ph);
         }
-        for (int k = 0; k < M; ++k) {
-            double re = 0.0, im = 0.0;
-            int64_t at = k;
-            for (int j = 0; j < M; ++j, at += 2 * k) {
-                const double v = cs[at % (4 * M)];
-                re += fr[j] * v;
-                im += fi[j] * v;
-            }
-            mag[k] = 2.0 / M * std::sqrt(re * re + im * im);
-        }
+        // coefficients from the highest down, until their sum is too much to leave out
         double tail = 0.0;
         int need = M;
-        while (need > 1 && tail + mag[need - 1] < EW_TOL) tail += mag[--need];
+        for (; need > worst; --need) {
+            const int k = need - 1;
+            double re = 0.0, im = 0.0;
+            for (int j = 0, at = k; j < M; ++j) {
+                re += fr[j] * cs[at];
+                im += fi[j] * cs[at];
+                at += 2 * k;
+                if (at >= 4 * M) at -= 4 * M;
+            }
+            tail += 2.0 / M * std::sqrt(re * re + im * im);
+            if (tail >= EW_TOL) break;
+        }
         worst = std::max(worst, need);
     }
     return worst;
@@ -177,52 +206,44 @@ bool ew_basis(int n, double d, double qh, int limit, int* ke, int* ko, std::vect
         for (int k = 0; k + 1 < size; ++k) te[k] = off(k + 1);
         if (n % 2 == 0) td[size - 1] += par ? -off(m) : off(m);
         else if (par == 0 && size > 1) te[size - 2] *= std::sqrt(2.0);
-        int count = std::min(size, (int)std::ceil(n * W) + 16 + (int)std::log2((double)n));
-        for (;;) {
-            std::vector<std::vector<double>> v;
-            tri_top(td, te, count, &v);
-            for (auto& x : v) {
-                for (int k = 0; k < size; ++k)
-                    if (!(n % 2 && k == m)) x[k] *= std::sqrt(0.5);
-                x.resize(nh, 0.0);
+        // residual of cos or sin(q r) after the first K modes, over sample momenta
+        std::vector<std::vector<double>> v, res;
+        for (double s : share) {
+            std::vector<double> r(nh);
+            for (int h = 0; h < nh; ++h) {
+                const double ph = s * qh * (n - 1.0 - 2.0 * h) * d / 2.0;
+                r[h] = par ? std::sin(ph) : std::cos(ph);
             }
-            // residual of cos or sin(q r) after the first K modes, over sample momenta
-            std::vector<std::vector<double>> res;
-            for (double s : share) {
-                std::vector<double> r(nh);
-                for (int h = 0; h < nh; ++h) {
-                    const double ph = s * qh * (n - 1.0 - 2.0 * h) * d / 2.0;
-                    r[h] = par ? std::sin(ph) : std::cos(ph);
-                }
-                res.push_back(r);
-            }
-            int K = 0;
-            bool fits = false;
-            for (;; ++K) {
-                double worst = 0.0;
-                for (auto& r : res) {
-                    double s = 0.0;
-                    for (int h = 0; h < nh; ++h) s += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * r[h];
-                    worst = std::max(worst, s);
-                }
-                fits = std::sqrt(worst / n) < EW_TOL;
-                if (fits || K == count) break;
-                for (auto& r : res) {
-                    double c = 0.0;
-                    for (int h = 0; h < nh; ++h) c += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * v[K][h];
-                    for (int h = 0; h < nh; ++h) r[h] -= c * v[K][h];
-                }
-            }
-            if (!fits && count < size) {
-                count = size;   // a wide band: every mode
-                continue;
-            }
-            kept = K;
-            out.assign((size_t)nh * K, 0.0);
-            for (int k = 0; k < K; ++k)
-                for (int h = 0; h < nh; ++h) out[(size_t)h * K + k] = v[k][h];
-            break;
+            res.push_back(r);
         }
+        TriTop tri(td, te);
+        int K = 0;
+        for (;; ++K) {
+            double worst = 0.0;
+            for (auto& r : res) {
+                double s = 0.0;
+                for (int h = 0; h < nh; ++h) s += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * r[h];
+                worst = std::max(worst, s);
+            }
+            if (std::sqrt(worst / n) < EW_TOL || K == size) break;
+            if (K == (int)v.size()) {
+                tri.next(&v);
+                for (size_t j = K; j < v.size(); ++j) {
+                    for (int k = 0; k < size; ++k)
+                        if (!(n % 2 && k == m)) v[j][k] *= std::sqrt(0.5);
+                    v[j].resize(nh, 0.0);
+                }
+            }
+            for (auto& r : res) {
+                double c = 0.0;
+                for (int h = 0; h < nh; ++h) c += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * v[K][h];
+                for (int h = 0; h < nh; ++h) r[h] -= c * v[K][h];
+            }
+        }
+        kept = K;
+        out.assign((size_t)nh * K, 0.0);
+        for (int k = 0; k < K; ++k)
+            for (int h = 0; h < nh; ++h) out[(size_t)h * K + k] = v[k][h];
     }
     return *ke + *ko <= limit;
 }
@@ -242,25 +263,35 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     d.rows = half;
     d.rowsp = pad(half, 16);
     H.k0 = k0;
-    // the rows' angle, and per pixel the other one, at non-negative coordinates (index N - 1 - h)
-    H.tq.assign((size_t)half * half, 0.0);
+    // the rows' angle, and the largest of the pixels' other one, at non-negative coordinates
+    // (index N - 1 - h); its tangent is u cos b (flat) or q_x / sqrt(k0^2 - q_x^2 - q_y^2)
     std::vector<double> pos(half), row(half);
-    double range = 0.0;
-    for (int h = 0; h < half; ++h)
-        pos[h] = ((double)(N - 1 - 2 * h) * (uni ? k0 * std::sin(theta) : std::tan(theta))) / (double)N;
-    for (int j = 0; j < half; ++j) {
-        row[j] = uni ? std::asin(std::min(1.0, pos[j] / k0)) : std::atan(pos[j]);
-        const double cb = std::cos(row[j]), kk = k0 * k0;
-        for (int i = 0; i < half; ++i) {
-            const double s = pos[i] * pos[i] + pos[j] * pos[j];
-            double& t = H.tq[(size_t)j * half + i];
-            if (!uni) t = std::atan(pos[i] * cb);
-            else t = s < kk ? std::atan2(pos[i], std::sqrt(kk - s)) : std::nan("");
-            if (t > range) range = t;
-        }
+    H.limit = uni ? k0 * std::sin(theta) : std::tan(theta);
+    for (int h = 0; h < half; ++h) {
+        pos[h] = ((double)(N - 1 - 2 * h) * H.limit) / (double)N;
+        row[h] = uni ? std::asin(std::min(1.0, pos[h] / k0)) : std::atan(pos[h]);
     }
-    const double scale = range > 0.0 ? 1.0 / range : 0.0, rrange = row[0];
-    for (double& t : H.tq) t *= scale;
+    double range = 0.0;
+    if (uni) {
+        const double kk = k0 * k0;
+        double ratio = -1.0, x = 0.0, z = 1.0;
+        for (int j = 0; j < half; ++j)
+            for (int i = 0; i < half; ++i) {
+                const double s = pos[i] * pos[i] + pos[j] * pos[j];
+                if (!(s < kk)) continue;
+                if (pos[i] * pos[i] > ratio * (kk - s)) {
+                    ratio = pos[i] * pos[i] / (kk - s);
+                    x = pos[i];
+                    z = kk - s;
+                }
+                break;   // the widest pixel of a row within the rim is its first
+            }
+        range = std::atan2(x, std::sqrt(z));
+    } else {
+        for (double b : row) range = std::max(range, std::atan(pos[0] * std::cos(b)));
+    }
+    H.range = range;
+    const double rrange = row[0];
     // largest M sin b + z cos b of the box over |b| <= w: what exp(-i q r) holds beside N sin a
     const double hN = uni ? hy : hx, hM = uni ? hx : hy, wb = uni ? range : rrange;
     const double top = std::atan2(hM, hz), r = top <= wb ? std::hypot(hM, hz) : hM * std::sin(wb) + hz * std::cos(wb);
@@ -290,6 +321,12 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     // Chebyshev points in barycentric form, those of +- a node folded for even and odd parts
     H.wre.assign((size_t)d.nrp * d.rowsp, 0.0);
     H.wro.assign((size_t)d.nrp * d.rowsp, 0.0);
+    std::vector<double> nodes(nr), weights(nr);
+    for (int k = 0; k < nr; ++k) {
+        const double w = (k + 0.5) * kPi / (2.0 * nr);
+        nodes[k] = std::cos(w);
+        weights[k] = (k & 1 ? -1.0 : 1.0) * std::sin(w);
+    }
     for (int j = 0; j < half; ++j) {
         if (exact) {
             H.wre[(size_t)j * d.rowsp + j] = H.wro[(size_t)j * d.rowsp + j] = 1.0;
@@ -300,8 +337,7 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
         std::vector<double> lp(nr), lm(nr);
         int hit = -1;
         for (int k = 0; k < nr; ++k) {
-            const double w = (k + 0.5) * kPi / (2.0 * nr), x = std::cos(w);
-            const double s = (k & 1 ? -1.0 : 1.0) * std::sin(w);
+            const double x = nodes[k], s = weights[k];
             if (t == x) hit = k;
             lp[k] = s / (t - x);
             lm[k] = -s / (t + x);   // point 2 nr - 1 - k, at -x: the other sign
@@ -319,11 +355,20 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     d.nbp = pad(d.nb, 16);
     // momentum ranges over all (a, b)
     double qm = 0.0, zlo = 0.0, zhi = -2.0 * k0;
+    std::vector<double> sb2, sbn;   // sin^2(b/2), |sin b|
+    double sa2 = 0.0, ca = 1.0;
+    for (double b : H.ang_b) {
+        sb2.push_back(std::sin(0.5 * b) * std::sin(0.5 * b));
+        sbn.push_back(std::fabs(std::sin(b)));
+    }
     for (double a : H.ang_a)
-        for (double b : H.ang_b) {
-            const double sa = std::sin(0.5 * a), sb = std::sin(0.5 * b);
-            const double qz = -2.0 * k0 * (sa * sa + std::cos(a) * sb * sb);
-            qm = std::max(qm, std::fabs(k0 * std::cos(a) * std::sin(b)));
+        for (size_t b = 0; b < sb2.size(); ++b) {
+            if (b == 0) {
+                sa2 = std::sin(0.5 * a) * std::sin(0.5 * a);
+                ca = std::cos(a);
+            }
+            const double qz = -2.0 * k0 * (sa2 + ca * sb2[b]);
+            qm = std::max(qm, k0 * std::fabs(ca) * sbn[b]);
             zlo = std::min(zlo, qz);
             zhi = std::max(zhi, qz);
         }
@@ -391,11 +436,12 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
     const int np = pad(n, 16);
     H.dcte.assign((size_t)np * np, 0.0);
     H.dcto.assign((size_t)np * np, 0.0);
+    std::vector<double> turn(8 * n);   // cos(j pi / (4 n))
+    for (int j = 0; j < 8 * n; ++j) turn[j] = std::cos(j * kPi / (4.0 * n));
     for (int a = 0; a < n; ++a)
-        for (int k = 0; k < n; ++k) {
-            const double w = (a + 0.5) * kPi / (2.0 * n);
-            H.dcte[(size_t)a * np + k] = (k ? 2.0 : 1.0) / n * std::cos(2.0 * k * w);
-            H.dcto[(size_t)a * np + k] = 2.0 / n * std::cos((2.0 * k + 1.0) * w);
+        for (int k = 0; k < n; ++k) {   // at the angles (a + 1/2) pi / (2 n) times 2 k and 2 k + 1
+            H.dcte[(size_t)a * np + k] = (k ? 2.0 : 1.0) / n * turn[(2 * a + 1) * 2 * k % (8 * n)];
+            H.dcto[(size_t)a * np + k] = 2.0 / n * turn[(2 * a + 1) * (2 * k + 1) % (8 * n)];
         }
     // workspace: Z is kept for a second contraction, so nothing shares its place
     const int64_t z = (int64_t)g.nx * g.ny * d.ld, y = (int64_t)d.nN * d.km * d.ld;

@@ -94,10 +94,12 @@ struct EwHost {
     size_t workspace = 0;                       // bytes, forward and adjoint alike
     double qc = 0.0, k0 = 0.0;
     double pitchN = 0.0, pitchM = 0.0, pitchZ = 0.0;
+    double limit = 0.0;                         // half-width of the screen: tan(theta) or k0 sin(theta)
+    double range = 0.0;                         // largest angle of the pixels' columns
     std::vector<double> ang_a, ang_b;           // the nodes a and b
     std::vector<double> phiz, phie, phio;       // as in EwDesc
     std::vector<double> phize, phizo;           // half-axis z modes, as in EwDesc
-    std::vector<double> rot, dcte, dcto, wre, wro, tq;
+    std::vector<double> rot, dcte, dcto, wre, wro;
 };
 
 // Fill h for the geometry (detector plans only); h->use says whether the form applies:
@@ -146,7 +148,7 @@ struct EwAdj {
 // from the angles and the half-axis modes dev points to.
 struct EwTables {
     const double *ang_a, *ang_b;
-    double *cosN, *sinN, *cm, *cz;
+    double *cosN, *sinN, *cm, *cz, *tq;
 };
 int launch_ew_tables(const EwHost& h, const EwDesc& dev, const EwTables& t, void* stream);
 int launch_ew_scan(const EwBatch& b, const EwDesc* const* dims, void* stream);

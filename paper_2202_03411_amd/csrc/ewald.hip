@@ -664,6 +664,24 @@ __global__ void ew_trig_kernel(EwDesc D, const double* ang_a, double k0, double 
     sinN[t] = sn;
 }
 
+// The other angle of pixel (row j, column i) over its range, the Chebyshev argument of the
+// row's series; NaN beyond the rim, by the q map's own comparison (no contraction).
+__global__ void ew_argument_kernel(EwDesc D, double k0, double limit, double scale, double* tq)
+{
+#pragma clang fp contract(off)
+    const int half = D.rows;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = (int)(t / half), i = (int)(t % half);
+    if (j >= half) return;
+    const double u = ((double)(D.det_n - 1 - 2 * i) * limit) / (double)D.det_n;
+    const double v = ((double)(D.det_n - 1 - 2 * j) * limit) / (double)D.det_n;
+    const double s = u * u + v * v, kk = k0 * k0;
+    double w;
+    if (!D.uniform) w = atan(u * cos(atan(v)));
+    else w = s < kk ? atan2(u, sqrt(kk - s)) : __builtin_nan("");
+    tq[t] = w * scale;
+}
+
 struct CoefArgs {
     const double *ang_a, *ang_b, *even, *odd;   // angles; half-axis modes [h][ldE], [h][ldO]
     double* out;                                // out[a * sa + b * sb + m * sm]
@@ -826,6 +844,8 @@ int launch_ew_tables(const EwHost& h, const EwDesc& D, const EwTables& t, void* 
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(ew_trig_kernel, dim3((unsigned)ceil_div((int64_t)D.nhNp * D.nap, 256)), dim3(256), 0, s,
                        D, t.ang_a, h.k0, h.pitchN, t.cosN, t.sinN);
+    hipLaunchKernelGGL(ew_argument_kernel, dim3((unsigned)ceil_div((int64_t)D.rows * D.rows, 256)), dim3(256), 0, s,
+                       D, h.k0, h.limit, h.range > 0.0 ? 1.0 / h.range : 0.0, t.tq);
     const dim3 grid((unsigned)(D.nbp / 16), (unsigned)D.na);
     CoefArgs c;
     c.ang_a = t.ang_a;
