@@ -124,6 +124,10 @@ struct EwReq {
     double* ws;
     int64_t p0, p1;
 };
+struct EwOne {
+    EwReq req;
+    EwDesc d;   // *req.d
+};
 constexpr int EW_MAX_REQ = 24;
 struct EwBatch {
     EwReq req[EW_MAX_REQ];

@@ -23,7 +23,9 @@ namespace {
 constexpr int EW_THREADS = 256;
 
 // The request a workgroup belongs to and its index within it.  The kernels take one request
-// (72 bytes of arguments: 2.7 us a launch on the host) or a batch (1.5 KB: 4.0 us).
+// (72 bytes of arguments: 2.7 us a launch on the host) or a batch (1.5 KB: 4.0 us); the scan,
+// whose many workgroups would each wait for the sizes and table pointers first, has them
+// among the arguments (192^3: 39.3 -> 36.7 us; the other kernels gain nothing by it).
 __device__ __forceinline__ const EwReq& ew_request(const EwBatch& b, int& item)
 {
     int r = 0;
@@ -36,6 +38,14 @@ __device__ __forceinline__ const EwReq& ew_request(const EwReq& r, int& item)
     item = (int)blockIdx.x;
     return r;
 }
+__device__ __forceinline__ const EwReq& ew_request(const EwOne& r, int& item)
+{
+    item = (int)blockIdx.x;
+    return r.req;
+}
+template <typename A>
+__device__ __forceinline__ const EwDesc& ew_desc(const A&, const EwReq& q) { return *q.d; }
+__device__ __forceinline__ const EwDesc& ew_desc(const EwOne& r, const EwReq&) { return r.d; }
 
 // ---------------------------------------------------------------------------
 // Scan: w of 16 columns and Z_l = sum_z phi_l(z) exp(-i qc z) w.
@@ -86,10 +96,9 @@ __device__ __forceinline__ void ew_strength(const EwDesc& D, const float* d, con
 // itself is waited for after it: their mode operands are loaded with the voxels, later ones
 // a block of steps ahead.
 template <bool MSFT, int COLS, int K, int NT>
-__device__ __forceinline__ void ew_scan_whole(const EwReq& q, int item, double* sm)
+__device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, int item, double* sm)
 {
     constexpr int L = EW_THREADS / COLS, NZ = L * K, U = NT == 1 ? 8 : NT == 2 ? 6 : 4;
-    const EwDesc& D = *q.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
     const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)item * COLS;
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(EW_THREADS, NT > 1 || (COLS == 8 && K == 8) ? 3 : 4
     __shared__ double sm[COLS == 16 ? 2 * slice_row(16 * K) : slice_row(32 * K) + 2 * NT * 4 * 64];
     int item;
     const EwReq& q = ew_request(args, item);
-    ew_scan_whole<MSFT, COLS, K, NT>(q, item, sm);
+    ew_scan_whole<MSFT, COLS, K, NT>(q, ew_desc(args, q), item, sm);
 }
 
 // Longer columns, in rounds of 64 slices against the full-axis modes.  Wave w takes Re (w
@@ -231,7 +240,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_scan_rounds_kernel(A args)
     __shared__ double sm[2 * slice_row(EW_ZC)];
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int cl = tid >> 4, zl = (tid & 15) * 4, nz = D.nz, kzt = D.kzt;
     const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)item * EW_COLS;
@@ -339,7 +348,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_modal_kernel(A args)
     __shared__ double red[SUM_WAVES_LDS];
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, ct = (ld + 15) >> 4, groups = (max(D.ket, D.kop ? D.kot : 0) + 31) >> 5;
     const int g = (item >> 3) % groups, u = (item >> 3) / groups * 8 + (item & 7);
@@ -381,7 +390,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(A args)
     __shared__ double red[SUM_WAVES_LDS];
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ncols = D.km * D.ld, nap = D.nap, ga = (nap + 31) >> 5;
     const int g = (item >> 3) % ga, cb = ((item >> 3) / ga * 8 + (item & 7)) * 16;
@@ -423,7 +432,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(A args)
     __shared__ double red[2][2][2][BT * 16][2];   // [column half][pM][pN][b][ri]
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, nbp = D.nbp, kzp = D.kzp, bg = (nbp + 16 * BT - 1) / (16 * BT);
     const int a = (item >> 3) / bg * 8 + (item & 7), b0 = (item >> 3) % bg * (16 * BT);
@@ -518,7 +527,7 @@ __global__ __launch_bounds__(CF_THREADS) void ew_coef_kernel(A args)
     extern __shared__ double lds[];   // [n][17]
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int n = D.n, nr = D.nr, rowsp = D.rowsp, np = (n + 15) & ~15, waves = blockDim.x >> 6;
     const int comp = (item >> 3) & 7, j0 = ((item >> 6) * 8 + (item & 7)) * 16;
@@ -598,7 +607,7 @@ __global__ __launch_bounds__(EV_THREADS) void ew_eval_kernel(A args)
     extern __shared__ double C[];   // [n][8]
     int item;
     const EwReq& q = ew_request(args, item);
-    const EwDesc& D = *q.d;
+    const EwDesc& D = ew_desc(args, q);
     const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x;
     const int chunks = (half + 2 * EV_THREADS - 1) / (2 * EV_THREADS), j = item / chunks;
     // nothing to do where the row and its mirror lie outside [p0, p1)
@@ -729,13 +738,16 @@ __global__ __launch_bounds__(256) void ew_mode_kernel(CoefArgs c)
     }
 }
 
+EwReq ew_one(const EwReq& r, const EwDesc&, EwReq*) { return r; }
+EwOne ew_one(const EwReq& r, const EwDesc& d, EwOne*) { return {r, d}; }
+
 // One launch over all requests, f(plan) workgroups to each.
-template <typename F>
-void ew_launch(void (*one)(EwReq), void (*many)(EwBatch), EwBatch& b, const EwDesc* const* dims, int lds,
+template <typename A, typename F>
+void ew_launch(void (*one)(A), void (*many)(EwBatch), EwBatch& b, const EwDesc* const* dims, int lds,
                hipStream_t s, F f, int threads = EW_THREADS)
 {
     if (b.n == 1) {
-        hipLaunchKernelGGL(one, dim3((unsigned)f(*dims[0])), dim3(threads), lds, s, b.req[0]);
+        hipLaunchKernelGGL(one, dim3((unsigned)f(*dims[0])), dim3(threads), lds, s, ew_one(b.req[0], *dims[0], (A*)nullptr));
         return;
     }
     int64_t total = 0;
@@ -767,9 +779,9 @@ template <bool MSFT, int COLS, int K>
 void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, int tiles, hipStream_t s)
 {
     auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, COLS); };
-    if (tiles == 1) ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 1>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 1>, b, dims, 0, s, items);
-    else if (tiles == 2) ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 2>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 2>, b, dims, 0, s, items);
-    else ew_launch(ew_scan_kernel<EwReq, MSFT, COLS, K, 3>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 3>, b, dims, 0, s, items);
+    if (tiles == 1) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 1>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 1>, b, dims, 0, s, items);
+    else if (tiles == 2) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 2>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 2>, b, dims, 0, s, items);
+    else ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 3>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 3>, b, dims, 0, s, items);
 }
 
 template <bool MSFT>
@@ -781,7 +793,7 @@ void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, const ScanForm& f, hi
     case 3: ew_launch_scan<MSFT, 8, 6>(b, dims, f.tiles, s); break;
     case 4: ew_launch_scan<MSFT, 8, 8>(b, dims, f.tiles, s); break;
     default:
-        ew_launch(ew_scan_rounds_kernel<EwReq, MSFT>, ew_scan_rounds_kernel<EwBatch, MSFT>, b, dims, 0, s,
+        ew_launch(ew_scan_rounds_kernel<EwOne, MSFT>, ew_scan_rounds_kernel<EwBatch, MSFT>, b, dims, 0, s,
                   [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, EW_COLS); });
     }
 }
