@@ -574,11 +574,15 @@ __global__ __launch_bounds__(CF_THREADS) void ew_coef_kernel(A args)
 }
 
 // ---------------------------------------------------------------------------
-// Eval: a workgroup takes 256 columns of one pixel row, the row's coefficients in LDS;
-// each thread runs the recurrence of T_2k and T_2k+1 in x = 2 t^2 - 1 for two columns, so
-// that a coefficient read serves both, and sums the eight parts:
+// Eval: a workgroup takes up to 128 CPL columns of one pixel row, the row's coefficients in
+// LDS.  Of each pair of waves one runs the recurrence of T_2k in x = 2 t^2 - 1 with the four
+// parts even along the row, the other that of T_2k+1 with the odd ones, for CPL columns a
+// lane.  It is bound by the vector unit and by LDS, whose broadcast of a coefficient takes
+// as long as four products: at CPL = 4 as at 2 a lane's columns share it, at 4 enough that
+// the vector unit is the longer of the two.  The parts' sums meet in the even wave,
 //   A(sx, sy) = (ee - sx sy oo) - i (sx oe + sy eo)          (px, py)
-// for the four mirror pixels.
+// for the four mirror pixels.  One wave for both series, two columns a lane, took 8.0 us at
+// 128^3/512^2 and 43.7 at 256^3/1024^2, against 5.4 and 32.8.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void ew_store(const EwReq& q, int N, int i, int j, bool rim, const double* s)
 {
@@ -599,60 +603,65 @@ __device__ __forceinline__ void ew_store(const EwReq& q, int N, int i, int j, bo
     }
 }
 
-constexpr int EV_THREADS = 128;
+constexpr int EV_THREADS = 256;   // at most: two pairs of waves
 
-template <typename A>
+template <typename A, int CPL>
 __global__ __launch_bounds__(EV_THREADS) void ew_eval_kernel(A args)
 {
-    extern __shared__ double C[];   // [n][8]
+    extern __shared__ double C[];   // [n][8], then the odd sums [pair][column][4][64]
     int item;
     const EwReq& q = ew_request(args, item);
     const EwDesc& D = ew_desc(args, q);
-    const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x;
-    const int chunks = (half + 2 * EV_THREADS - 1) / (2 * EV_THREADS), j = item / chunks;
+    const int n = D.n, N = D.det_n, half = D.rows, tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+    const int cols = blockDim.x / 2 * CPL, chunks = (half + cols - 1) / cols, j = item / chunks;
     // nothing to do where the row and its mirror lie outside [p0, p1)
     const int64_t lo = (int64_t)j * N, hi = (int64_t)(N - 1 - j) * N;
     if ((lo + N <= q.p0 || lo >= q.p1) && (hi + N <= q.p0 || hi >= q.p1)) return;
     const gcdouble tq = as_global(D.tq) + (int64_t)j * half;
-    const int i = item % chunks * (2 * EV_THREADS) + tid, i2 = i + EV_THREADS;
-    const double t0 = tq[min(i, half - 1)], t1 = tq[min(i2, half - 1)];
+    const int odd = wave & 1, pair = wave >> 1, i = item % chunks * cols + pair * (64 * CPL) + lane;
+    double f0[CPL], f1[CPL], x2[CPL], s[CPL][8];
+#pragma unroll
+    for (int p = 0; p < CPL; ++p) f0[p] = tq[min(i + 64 * p, half - 1)];
     const double2* src = (const double2*)(q.ws + D.offC + (int64_t)j * n * 8);
-    for (int k = tid; k < n * 4; k += EV_THREADS) ((double2*)C)[k] = src[k];
+    for (int k = tid; k < n * 4; k += blockDim.x) ((double2*)C)[k] = src[k];
+    uint32_t rim = 0;
+#pragma unroll
+    for (int p = 0; p < CPL; ++p) {
+        if (!(f0[p] == f0[p])) {
+            rim |= 1u << p;
+            f0[p] = 0.0;
+        }
+        const double t = f0[p];
+        x2[p] = 2.0 * (2.0 * t * t - 1.0);
+        f0[p] = odd ? t : 1.0;                              // T_1 or T_0
+        f1[p] = odd ? (x2[p] - 1.0) * t : 0.5 * x2[p];      // T_3 or T_2
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[p][c] = 0.0;
+    }
     __syncthreads();
-    if (i < half) {
-        double e0[2], e1[2], o0[2], o1[2], x2[2], s[2][8];
-        bool rim[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const double t = p ? t1 : t0;
-            rim[p] = !(t == t);
-            const double tt = rim[p] ? 0.0 : t;
-            x2[p] = 2.0 * (2.0 * tt * tt - 1.0);
-            e0[p] = 1.0;                      // T_0, T_2
-            e1[p] = 0.5 * x2[p];
-            o0[p] = tt;                       // T_1, T_3 = (2 x - 1) t
-            o1[p] = (x2[p] - 1.0) * tt;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) s[p][c] = 0.0;
-        }
+    const double* c4 = C + 4 * odd;
 #pragma unroll 4
-        for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < n; ++k)
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
+        for (int p = 0; p < CPL; ++p) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    s[p][c] += e0[p] * C[k * 8 + c];
-                    s[p][4 + c] += o0[p] * C[k * 8 + 4 + c];
-                }
-                const double e2 = x2[p] * e1[p] - e0[p], o2 = x2[p] * o1[p] - o0[p];
-                e0[p] = e1[p];
-                e1[p] = e2;
-                o0[p] = o1[p];
-                o1[p] = o2;
-            }
+            for (int c = 0; c < 4; ++c) s[p][c] += f0[p] * c4[k * 8 + c];
+            const double f2 = x2[p] * f1[p] - f0[p];
+            f0[p] = f1[p];
+            f1[p] = f2;
         }
-        ew_store(q, N, i, j, rim[0], s[0]);
-        if (i2 < half) ew_store(q, N, i2, j, rim[1], s[1]);
+    double* sums = C + n * 8 + pair * (CPL * 4 * 64) + lane;
+    if (odd)
+#pragma unroll
+        for (int k = 0; k < CPL * 4; ++k) sums[k * 64] = s[k >> 2][k & 3];
+    __syncthreads();
+    if (odd) return;
+#pragma unroll
+    for (int p = 0; p < CPL; ++p) {
+        if (i + 64 * p >= half) break;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[p][4 + c] = sums[(p * 4 + c) * 64];
+        ew_store(q, N, i + 64 * p, j, rim >> p & 1, s[p]);
     }
 }
 
@@ -846,8 +855,20 @@ int launch_ew_contract(EwBatch& b, const EwDesc* const* dims, void* stream)
     ew_launch(ew_coef_kernel<EwReq>, ew_coef_kernel<EwBatch>, b, dims, n * 17 * (int)sizeof(double), s,
               [](const EwDesc& d) { return ew_on_xcd(d.rowsp / 16, 8); },
               std::min(CF_THREADS, std::max(4, (n + 15) / 16) * 64));
-    ew_launch(ew_eval_kernel<EwReq>, ew_eval_kernel<EwBatch>, b, dims, n * 8 * (int)sizeof(double), s,
-              [](const EwDesc& d) { return d.rows * ceil_div(d.rows, 2 * EV_THREADS); }, EV_THREADS);
+    // four columns a lane where that leaves two waves to a SIMD and the series are long
+    // (512^2 quarter pixels, 235 coefficients: 33 us against 39; 57: 12.7 against 13.2, eight
+    // mixed requests of 57: 18.6 against 18.1), else two; a pair of waves only for what a row has
+    int64_t waves = 0;
+    int rows = 0;
+    for (int r = 0; r < b.n; ++r) {
+        waves += 2 * dims[r]->rows * ceil_div(dims[r]->rows, 256);
+        rows = std::max(rows, dims[r]->rows);
+    }
+    const int cpl = waves >= 8 * CHIP_CUS && n >= 128 ? 4 : 2, pairs = rows > 64 * cpl ? 2 : 1;
+    const int lds = (n * 8 + pairs * cpl * 4 * 64) * (int)sizeof(double);
+    auto items = [&](const EwDesc& d) { return d.rows * ceil_div(d.rows, pairs * 64 * cpl); };
+    if (cpl == 4) ew_launch(ew_eval_kernel<EwReq, 4>, ew_eval_kernel<EwBatch, 4>, b, dims, lds, s, items, pairs * 128);
+    else ew_launch(ew_eval_kernel<EwReq, 2>, ew_eval_kernel<EwBatch, 2>, b, dims, lds, s, items, pairs * 128);
     return (int)hipGetLastError();
 }
 

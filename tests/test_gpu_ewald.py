@@ -86,3 +86,20 @@ def test_forward_and_adjoint_match_oracle(env, case, detector):
     print(f"  amplitude {errs[0]:.2e} intensity {errs[1]:.2e} gradients {errs[2]:.2e} {errs[3]:.2e}")
     assert np.isfinite(gd).all() and np.isfinite(gb).all()
     assert errs[0] <= TOL and max(errs[1:]) <= 2 * TOL
+
+
+def test_long_series_on_a_large_detector(env):
+    # over 128 nodes and 512 pixel columns to a quarter row: four columns to a lane
+    torch, msft = env
+    grid, det, pitch = (200, 17, 20), 1031, (11.0, 2.0, 3.0)
+    print(f"[gpu] long series grid={grid} det={det}", flush=True)
+    rng = np.random.default_rng(inputs.SEED_BASE + det)
+    d, b = (rng.uniform(0.0, 0.05, grid).astype(np.float32) for _ in range(2))
+    q = oracle.qmap(45.0, 75.0, det)
+    pix = np.sort(rng.choice(det * det, size=512, replace=False))
+    Ao = oracle.amplitude(q[pix], oracle.strength(oracle.MSFT, d.astype(np.float64), b.astype(np.float64), pitch, 45.0),
+                          pitch, 1)
+    with msft.Plan(45.0, 75.0, det, grid, pitch) as plan:
+        I, A = plan.simulate(torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda(), amplitude=True)
+        I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
+    assert _rel(A[pix], Ao) <= TOL and _rel(I[pix], np.abs(Ao) ** 2) <= 2 * TOL
