@@ -39,10 +39,11 @@ constexpr double EW_MIN_TERMS = 2e7;
 constexpr double EW_MIN_TERMS_UNIFORM = 8e8;
 constexpr int EW_COLS = 16;       // columns (x, y) of one scan workgroup: the MFMA rows
 constexpr int EW_ZC = 64;         // slices of one scan round: a column's 16 lanes, four each
-// Columns of at most 256 slices are held whole, a workgroup's 256 threads in groups of
-// lanes to a column: 16 columns of 16 lanes up to 128 slices (4 or 8 a lane), 8 columns of
-// 32 lanes beyond (6 or 8 a lane), so that their strengths take at most 35 KB of LDS and
-// four workgroups share a CU.
+// Columns of at most 256 slices are held whole: 16 columns of 16 lanes up to 128 slices (4 or
+// 8 a lane), beyond that 8 columns, in the scan 16 lanes of 12 or 16 slices each (32 lanes of
+// 6, whose prefixes and addresses weigh twice as much, took 36.7 us at 192^3 against 30.8),
+// in the adjoint's walk, which holds more registers a slice, 32 lanes of 6 or 8.  The
+// strengths take at most 35 KB of LDS.
 constexpr int EW_WHOLE_NZ = 256;
 inline int ew_rounds(int nz) { return nz > EW_WHOLE_NZ ? 0 : (nz + EW_ZC - 1) / EW_ZC; }
 inline int ew_columns(int nz) { return nz > 2 * EW_ZC && nz <= EW_WHOLE_NZ ? 8 : EW_COLS; }

@@ -56,10 +56,10 @@ __device__ __forceinline__ const EwDesc& ew_desc(const EwOne& r, const EwReq&) {
 // by the slices' own factors after it.  dV times the rotated w goes to LDS (a row of
 // columns per slice) and from there into the matrix instruction: rows are columns, K the
 // slices, columns the modes.  FP64 vector work and the FP64 matrix instruction add up
-// here (91 vector instructions a voxel took 16 us and the products 12 of 36 at 192^3), so
-// both are kept small: more slices a lane share a prefix and a full T, and where a
-// workgroup holds whole columns (R rounds of 64 slices) the products take the sums and
-// differences of mirror slices against the half-axis modes, half as many.
+// here (at 192^3 some 65 vector instructions a voxel take 12 us and the products 6 of 31), so
+// both are kept small: more slices a lane share a prefix, a full T and the addresses, and
+// where a workgroup holds whole columns the products take the sums and differences of
+// mirror slices against the half-axis modes, half as many.
 // ---------------------------------------------------------------------------
 
 // dV w exp(-i qc z) of a lane's K slices from z on into LDS, (Sb, Sd) the sums before the
@@ -89,18 +89,18 @@ __device__ __forceinline__ void ew_strength(const EwDesc& D, const float* d, con
     else slices(std::false_type{});
 }
 
-// Whole columns: COLS of them, 256 / COLS lanes of K slices each.  The products' rows are
-// 16 columns, Re and Im apart (COLS = 16: a wave takes one of them and one parity of the
-// modes), or 8 columns' (Re, Im) (COLS = 8: a wave takes one parity and every other step).
-// NT tiles of 16 modes share an operand.  Nothing the first products need but the strength
-// itself is waited for after it: their mode operands are loaded with the voxels, later ones
-// a block of steps ahead.
+// Whole columns: COLS of them, 16 lanes of K slices each.  The products' rows are 16
+// columns, Re and Im apart (COLS = 16: four waves, each one of them and one parity of the
+// modes), or 8 columns' (Re, Im) (COLS = 8: two waves, a parity each).  NT tiles of 16 modes
+// share an operand.  Nothing the first products need but the strength itself is waited for
+// after it: their mode operands are loaded with the voxels, later ones a block of steps
+// ahead.
 template <bool MSFT, int COLS, int K, int NT>
 __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, int item, double* sm)
 {
-    constexpr int L = EW_THREADS / COLS, NZ = L * K, U = NT == 1 ? 8 : NT == 2 ? 6 : 4;
+    constexpr int NZ = 16 * K, U = NT == 1 ? 8 : NT == 2 ? 6 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
-    const int cl = tid / L, z0 = tid % L * K, nz = D.nz;
+    const int cl = tid >> 4, z0 = (tid & 15) * K, nz = D.nz;
     const int64_t ncol = (int64_t)D.nx * D.ny, c0 = (int64_t)item * COLS;
     const bool in = c0 + cl < ncol;
     const int64_t off = (in ? c0 + cl : ncol - 1) * nz;
@@ -109,18 +109,14 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
     const gcdouble rot = as_global(D.rot) + 2 * min(z0, (nz + EW_ZC - 1) / EW_ZC * EW_ZC - 1);
     const double r0 = rot[0], r1 = rot[1];
     const int odd = wave & 1, sub = wave >> 1, kze = D.kze, kz = odd ? D.kz - kze : kze, kzt = odd ? D.kzot : D.kzet;
-    const int full = nz >> 3, nh = (nz + 1) >> 1;   // whole steps of four mirror pairs; half the column
-    // this wave's steps: all of them, or every other one; the last may be the rest (its pairs,
-    // an odd column's middle)
-    constexpr int stride = COLS == 16 ? 1 : 2;
-    const int first = COLS == 16 ? 0 : sub;
-    const int steps = ((4 * full < nh ? full + 1 : full) - first + stride - 1) / stride;
+    // whole steps of four mirror pairs; the last may be the rest (its pairs, an odd column's middle)
+    const int full = nz >> 3, nh = (nz + 1) >> 1, steps = 4 * full < nh ? full + 1 : full;
     const gcdouble phi = as_global(odd ? D.phizo : D.phize);
     const uint32_t po = 8 * (lk * kzt + li);
     auto load = [&](int k, int at, double (*x)[NT]) {   // steps k ... k + U - 1, past the end the last
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const gcdouble p = phi + 4 * (first + stride * max(min(k + u, steps - 1), 0)) * kzt;
+            const gcdouble p = phi + 4 * min(k + u, steps - 1) * kzt;
 #pragma unroll
             for (int t = 0; t < NT; ++t) x[u][t] = load_at(p + (at + 16 * t < kzt ? at + 16 * t : 0), po);
         }
@@ -136,23 +132,17 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
             sb += (double)b[k];
             sd += (double)d[k];
         }
-        Sb = group_prefix_f64<L>(sb) - sb;
-        Sd = group_prefix_f64<L>(sd) - sd;
+        Sb = row_prefix_f64(sb) - sb;
+        Sd = row_prefix_f64(sd) - sd;
     }
     double* o = sm + (COLS == 16 ? cl : 2 * cl);
     ew_strength<MSFT, K>(D, d, b, Sb, Sd, r0, r1, z0, o, o + (COLS == 16 ? slice_row(NZ) : 1));
     __syncthreads();
     const double* a = sm + (COLS == 16 ? sub * slice_row(NZ) : 0) + li;
     const double mirror = odd ? -1.0 : 1.0;
-    auto operand = [&](int k) {
-        const int s = first + stride * k;
-        if (s < full) {
-            const int h = 4 * s + lk;
-            return a[slice_row(nz - 1 - h)] + mirror * a[slice_row(h)];
-        }
-        const int h = min(4 * full + lk, nh - 1), m = nz - 1 - h;   // phi is zero past the middle
-        return a[slice_row(m)] + (m == h ? 0.0 : mirror * a[slice_row(h)]);
-    };
+    // slices 4 s + lk and their mirrors: eight slices on, a row offset of slice_row(8)
+    const double *lo0 = a + slice_row(lk), *lo1 = a + slice_row(lk + 4);
+    const double *hi0 = a + slice_row(nz - 1 - lk), *hi1 = a + slice_row(nz - 5 - lk);
     gdouble out = as_global(q.ws) + c0 * D.ld;
     const bool whole = c0 + COLS <= ncol;
     // both parities make the same passes; one past its last tile repeats the first and stores nothing
@@ -165,12 +155,13 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
             double y[U][NT];
             if (k + U < steps) load(k + U, t0, y);
             __builtin_amdgcn_sched_barrier(0);
-            if (first + stride * (k + U - 1) < full) {
+            const int at = (k >> 1) * slice_row(8);
+            if (k + U <= full) {
                 double v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int h = 4 * (first + stride * (k + u)) + lk;
-                    v[u] = a[slice_row(nz - 1 - h)] + mirror * a[slice_row(h)];
+                    const int w = at + (u >> 1) * slice_row(8);
+                    v[u] = (u & 1 ? hi1 : hi0)[-w] + mirror * (u & 1 ? lo1 : lo0)[w];
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
@@ -180,7 +171,8 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (k + u < steps) {
-                        const double v = operand(k + u);
+                        const int h = min(4 * (k + u) + lk, nh - 1), m = nz - 1 - h;   // phi is zero past the middle
+                        const double v = a[slice_row(m)] + (m == h ? 0.0 : mirror * a[slice_row(h)]);
 #pragma unroll
                         for (int i = 0; i < NT; ++i) t[i] = mfma_f64(v, x[u][i], t[i]);
                     }
@@ -190,17 +182,6 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int i = 0; i < NT; ++i) x[u][i] = y[u][i];
-        }
-        if (COLS == 8) {   // the halves' sums, in the first half's wave
-            double* red = sm + slice_row(NZ) + odd * (NT * 4 * 64);
-            if (t0) __syncthreads();
-            if (sub)
-#pragma unroll
-                for (int k = 0; k < 4 * NT; ++k) red[k * 64 + lane] = t[k >> 2][k & 3];
-            __syncthreads();
-            if (sub) continue;
-#pragma unroll
-            for (int k = 0; k < 4 * NT; ++k) t[k >> 2][k & 3] += red[k * 64 + lane];
         }
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
@@ -218,14 +199,13 @@ __device__ __forceinline__ void ew_scan_whole(const EwReq& q, const EwDesc& D, i
     }
     // the padding of the mode vectors, zero
     const int pad = 2 * (D.kzp - D.kz);
-    if (tid % L < pad && in) out[cl * D.ld + 2 * D.kz + tid % L] = 0.0;
+    if ((tid & 15) < pad && in) out[cl * D.ld + 2 * D.kz + (tid & 15)] = 0.0;
 }
 
 template <typename A, bool MSFT, int COLS, int K, int NT>
-__global__ __launch_bounds__(EW_THREADS, NT > 1 || (COLS == 8 && K == 8) ? 3 : 4) void ew_scan_kernel(A args)
+__global__ __launch_bounds__(16 * COLS, K == 16 ? 2 : NT > 1 || COLS == 8 ? 3 : 4) void ew_scan_kernel(A args)
 {
-    // COLS = 16: Re and Im; 8: (Re, Im) rows, then the halves' sums of a parity's tiles
-    __shared__ double sm[COLS == 16 ? 2 * slice_row(16 * K) : slice_row(32 * K) + 2 * NT * 4 * 64];
+    __shared__ double sm[(COLS == 16 ? 2 : 1) * slice_row(16 * K)];   // Re and Im; or (Re, Im) rows
     int item;
     const EwReq& q = ew_request(args, item);
     ew_scan_whole<MSFT, COLS, K, NT>(q, ew_desc(args, q), item, sm);
@@ -788,9 +768,9 @@ template <bool MSFT, int COLS, int K>
 void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, int tiles, hipStream_t s)
 {
     auto items = [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, COLS); };
-    if (tiles == 1) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 1>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 1>, b, dims, 0, s, items);
-    else if (tiles == 2) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 2>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 2>, b, dims, 0, s, items);
-    else ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 3>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 3>, b, dims, 0, s, items);
+    if (tiles == 1) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 1>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 1>, b, dims, 0, s, items, 16 * COLS);
+    else if (tiles == 2) ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 2>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 2>, b, dims, 0, s, items, 16 * COLS);
+    else ew_launch(ew_scan_kernel<EwOne, MSFT, COLS, K, 3>, ew_scan_kernel<EwBatch, MSFT, COLS, K, 3>, b, dims, 0, s, items, 16 * COLS);
 }
 
 template <bool MSFT>
@@ -799,8 +779,8 @@ void ew_launch_scan(EwBatch& b, const EwDesc* const* dims, const ScanForm& f, hi
     switch (f.rounds) {
     case 1: ew_launch_scan<MSFT, 16, 4>(b, dims, f.tiles, s); break;
     case 2: ew_launch_scan<MSFT, 16, 8>(b, dims, f.tiles, s); break;
-    case 3: ew_launch_scan<MSFT, 8, 6>(b, dims, f.tiles, s); break;
-    case 4: ew_launch_scan<MSFT, 8, 8>(b, dims, f.tiles, s); break;
+    case 3: ew_launch_scan<MSFT, 8, 12>(b, dims, f.tiles, s); break;
+    case 4: ew_launch_scan<MSFT, 8, 16>(b, dims, f.tiles, s); break;
     default:
         ew_launch(ew_scan_rounds_kernel<EwOne, MSFT>, ew_scan_rounds_kernel<EwBatch, MSFT>, b, dims, 0, s,
                   [](const EwDesc& d) { return ceil_div((int64_t)d.nx * d.ny, EW_COLS); });

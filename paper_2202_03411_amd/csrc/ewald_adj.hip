@@ -305,8 +305,8 @@ __global__ __launch_bounds__(EA_THREADS) void ew_modal_adj_kernel(EwAdj q)
 // (rows columns, K the modes, columns the slices) through LDS to the lane that holds the
 // slice, then the chain rule along the column.  With P = R T and n = 1 - delta + i beta
 // the slice's own terms are -4 P n (real part for delta, imaginary for beta),
-// R w = P (n^2 - 1), and sum_{s'>s} R w is the later lanes' plus the lane's own.  Lanes,
-// slices and T as in the scan.
+// R w = P (n^2 - 1), and sum_{s'>s} R w is the later lanes' plus the lane's own.  T as in
+// the scan.
 // ---------------------------------------------------------------------------
 
 // The chain rule of a lane's K slices from z on, L lanes to a column; (ur, ui): LDS of
@@ -382,8 +382,7 @@ __device__ __forceinline__ void store_slices(float* od, float* ob, int z, int nz
         }
 }
 
-// Whole columns, as in the scan (rows of the products: 16 columns, Re and Im apart, or 8
-// columns' (Re, Im)): even and odd modes on the half axis, E + O and E - O the mirror
+// Whole columns (rows of the products: 16 columns, Re and Im apart, or 8 columns' (Re, Im)): even and odd modes on the half axis, E + O and E - O the mirror
 // slices.  A wave takes every fourth (Re or Im and every other) tile of 16 half-axis
 // slices, at most two, both against one operand; 16 modes of each parity at a time, all
 // their loads ahead of the products.
