@@ -372,17 +372,17 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
     }
     if (ew_applies(p)) {
         try {
-            ew_plan(*g, &p->ew);
+            // what the fixed scratch of msft_simulate_noalloc holds in the direct form stays within it
+            ew_plan(*g, fwd_ws <= MSFT_NOALLOC_MAX_BYTES ? (size_t)MSFT_NOALLOC_MAX_BYTES : SIZE_MAX, &p->ew);
         } catch (const std::bad_alloc&) {
             delete p;
             return fail(MSFT_ERR_NOMEM, "host tables");
         }
-        // what the fixed scratch of msft_simulate_noalloc holds in the direct form stays within it
         if (p->ew.use && fwd_ws <= MSFT_NOALLOC_MAX_BYTES && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES)
             p->ew.use = false;
         if (p->ew.use) {
             fwd_ws = std::max(fwd_ws, align256(p->ew.workspace));
-            adj_ws = align256(p->ew.workspace);
+            adj_ws = align256(p->ew.adj_workspace);
         }
     }
     p->fwd_workspace = fwd_ws;
@@ -510,7 +510,7 @@ Stage1Args sep_stage1_args(const msft_plan_s* p, const void* workspace)
 EwReq ew_request(const msft_plan_s* p, const float* delta, const float* beta, float* intensity,
                  float* amplitude, const void* workspace, int64_t p0, int64_t p1)
 {
-    return EwReq{p->ew_dev, delta, beta, intensity, amplitude, (double*)workspace, p0, p1};
+    return EwReq{p->ew_dev, delta, beta, intensity, amplitude, (double*)workspace, p0, p1, 0};
 }
 
 // The contraction of a plan after the scan: one launch for the flat detector,

@@ -248,7 +248,7 @@ bool ew_basis(int n, double d, double qh, int limit, int* ke, int* ko, std::vect
     return *ke + *ko <= limit;
 }
 
-void ew_plan(const msft_geometry& g, EwHost* hp)
+void ew_plan(const msft_geometry& g, size_t most_bytes, EwHost* hp)
 {
     EwHost& H = *hp;
     EwDesc& d = H.d;
@@ -445,13 +445,20 @@ void ew_plan(const msft_geometry& g, EwHost* hp)
         }
     // workspace: Z is kept for a second contraction, so nothing shares its place
     const int64_t z = (int64_t)g.nx * g.ny * d.ld, y = (int64_t)d.nN * d.km * d.ld;
-    const int64_t gg = (int64_t)d.na * 2 * d.km * d.ld;
+    const int64_t node = 2 * (int64_t)d.km * d.ld;   // G of one node
     auto up = [](int64_t v) { return (v + 31) / 32 * 32; };
     d.offY = up(z);
-    d.offG = d.offY + up(y);
-    d.offS = d.offG + up(gg);
+    d.offS = d.offY + up(y);
     d.offC = d.offS + up((int64_t)d.nr * n * 8);
-    H.workspace = (size_t)(d.offC + up((int64_t)d.rows * n * 8)) * 8;
+    d.offG = d.offC + up((int64_t)d.rows * n * 8);
+    d.chunk = d.na;
+    H.adj_workspace = H.workspace = (size_t)(d.offG + up(node * d.na)) * 8;
+    const int64_t left = ((int64_t)(most_bytes / 8) - d.offG) / node / 32 * 32;
+    if (H.workspace > most_bytes && left > 0) {
+        const int parts = (int)((d.na + left - 1) / left);
+        d.chunk = pad((d.na + parts - 1) / parts, 32);
+        H.workspace = (size_t)(d.offG + up(node * d.chunk)) * 8;
+    }
     H.use = true;
 }
 

@@ -85,14 +85,15 @@ struct EwDesc {
     const double* wre;          // [row node][row], padded to nrp x rowsp: interpolation to the rows of
     const double* wro;          // parts even and odd in the rows' angle
     const double* tq;           // [row][column] Chebyshev argument, NaN beyond the rim
-    int64_t offY, offG, offS, offC;   // workspace offsets in doubles (Z at 0)
+    int32_t chunk;              // nodes a whose G the forward holds at a time: na, or fewer, a multiple of 32
+    int64_t offY, offS, offC, offG;   // workspace offsets in doubles (Z at 0)
 };
 
 // Host side of a plan: the sizes, and what the device tables are made from.
 struct EwHost {
     bool use = false;
     EwDesc d;                                   // pointers unset
-    size_t workspace = 0;                       // bytes, forward and adjoint alike
+    size_t workspace = 0, adj_workspace = 0;    // bytes
     double qc = 0.0, k0 = 0.0;
     double pitchN = 0.0, pitchM = 0.0, pitchZ = 0.0;
     double limit = 0.0;                         // half-width of the screen: tan(theta) or k0 sin(theta)
@@ -104,8 +105,9 @@ struct EwHost {
 };
 
 // Fill h for the geometry (detector plans only); h->use says whether the form applies:
-// its sizes lie within the limits above.
-void ew_plan(const msft_geometry& g, EwHost* h);
+// its sizes lie within the limits above.  Where the forward's workspace would exceed `most`
+// bytes and holding G for fewer nodes at a time keeps it below, it does.
+void ew_plan(const msft_geometry& g, size_t most, EwHost* h);
 
 // Even and odd orthonormal discrete prolate sequences of an axis of n voxels of pitch d
 // for |q| <= qh, as many as hold cos(q r), sin(q r) on the voxel centres to EW_TOL of
@@ -124,6 +126,7 @@ struct EwReq {
     float* amplitude;
     double* ws;
     int64_t p0, p1;
+    int32_t a0;   // first node of G's part
 };
 struct EwOne {
     EwReq req;

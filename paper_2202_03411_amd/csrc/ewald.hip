@@ -372,10 +372,10 @@ __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(A args)
     const EwReq& q = ew_request(args, item);
     const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
-    const int ncols = D.km * D.ld, nap = D.nap, ga = (nap + 31) >> 5;
+    const int ncols = D.km * D.ld, nap = D.nap, ga = (min(nap - q.a0, D.chunk) + 31) >> 5;
     const int g = (item >> 3) % ga, cb = ((item >> 3) / ga * 8 + (item & 7)) * 16;
     if (cb >= ncols) return;   // workgroup-uniform
-    const int a0 = g * 32, a1 = a0 + 16 < nap ? a0 + 16 : a0, c = cb + li;
+    const int a0 = q.a0 + g * 32, a1 = a0 + 16 < nap ? a0 + 16 : a0, c = cb + li;
     HalfAxis x;
     x.v = as_global(q.ws) + D.offY;
     x.stride = ncols;
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(A args)
     half_axis_sums(x, wave, li, lk, t);
     const f64x4 s = sum_waves(red, t, wave, lane);
     const int first = a0 + 16 * (wave & 1);
-    gdouble out = as_global(q.ws) + D.offG + (2 * first + (wave >> 1)) * (int64_t)ncols;
+    gdouble out = as_global(q.ws) + D.offG + (2 * (first - q.a0) + (wave >> 1)) * (int64_t)ncols;
     if (c < ncols && first < nap)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -415,12 +415,12 @@ __global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(A args)
     const EwDesc& D = ew_desc(args, q);
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int ld = D.ld, nbp = D.nbp, kzp = D.kzp, bg = (nbp + 16 * BT - 1) / (16 * BT);
-    const int a = (item >> 3) / bg * 8 + (item & 7), b0 = (item >> 3) % bg * (16 * BT);
-    if (a >= D.na) return;   // workgroup-uniform
+    const int al = (item >> 3) / bg * 8 + (item & 7), a = q.a0 + al, b0 = (item >> 3) % bg * (16 * BT);
+    if (al >= D.chunk || a >= D.na) return;   // workgroup-uniform
     const int pm = wave & 1, half = wave >> 1;
     const int m0 = pm ? D.kep : 0, steps = (pm ? D.kop : D.kep) >> 2;
     const int64_t gs = (int64_t)D.km * ld;
-    const gcdouble gm = as_global(q.ws) + D.offG + 2 * a * gs + (int64_t)m0 * ld;
+    const gcdouble gm = as_global(q.ws) + D.offG + 2 * al * gs + (int64_t)m0 * ld;
     const gcdouble cm = as_global(D.cm) + ((int64_t)a * D.km + m0) * nbp;
     const gcdouble cz = as_global(D.cz) + (int64_t)a * nbp * kzp;
     const uint32_t om = 8 * (lk * nbp + li);
@@ -814,24 +814,37 @@ int launch_ew_scan(const EwBatch& b, const EwDesc* const* dims, void* stream)
 int launch_ew_contract(EwBatch& b, const EwDesc* const* dims, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    int64_t bt = 0;
     int n = 0;
-    for (int r = 0; r < b.n; ++r) {
-        bt += (int64_t)dims[r]->na * (dims[r]->nbp / 16);
-        n = std::max(n, dims[r]->n);
-    }
+    for (int r = 0; r < b.n; ++r) n = std::max(n, dims[r]->n);
     ew_launch(ew_modal_kernel<EwReq>, ew_modal_kernel<EwBatch>, b, dims, 0, s, [](const EwDesc& d) {
         return ew_on_xcd(d.nN * ceil_div(d.ld, 16), ceil_div(std::max(d.ket, d.kop ? d.kot : 0), 32));
     });
-    ew_launch(ew_nodes_kernel<EwReq>, ew_nodes_kernel<EwBatch>, b, dims, 0, s, [](const EwDesc& d) {
-        return ew_on_xcd(ceil_div((int64_t)d.km * d.ld, 16), ceil_div(d.nap, 32));
-    });
-    if (bt >= 8 * CHIP_CUS)
-        ew_launch(ew_yz_kernel<EwReq, 2>, ew_yz_kernel<EwBatch, 2>, b, dims, 0, s,
-                  [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 32)); });
-    else
-        ew_launch(ew_yz_kernel<EwReq, 1>, ew_yz_kernel<EwBatch, 1>, b, dims, 0, s,
-                  [](const EwDesc& d) { return ew_on_xcd(d.na, ceil_div(d.nbp, 16)); });
+    // G in parts where a request's workspace holds fewer nodes than all: part k of each request
+    for (int k = 0;; ++k) {
+        EwBatch part;
+        const EwDesc* d[EW_MAX_REQ];
+        int64_t bt = 0;
+        part.n = 0;
+        for (int r = 0; r < b.n; ++r) {
+            const int a0 = k * dims[r]->chunk;
+            if (a0 >= dims[r]->na) continue;
+            bt += (int64_t)std::min(dims[r]->chunk, dims[r]->na - a0) * (dims[r]->nbp / 16);
+            d[part.n] = dims[r];
+            part.req[part.n] = b.req[r];
+            part.req[part.n++].a0 = a0;
+        }
+        if (part.n == 0) break;
+        ew_launch(ew_nodes_kernel<EwReq>, ew_nodes_kernel<EwBatch>, part, d, 0, s, [&](const EwDesc& e) {
+            return ew_on_xcd(ceil_div((int64_t)e.km * e.ld, 16), ceil_div(std::min(e.nap - k * e.chunk, e.chunk), 32));
+        });
+        auto tiles = [&](const EwDesc& e, int b16) {
+            return ew_on_xcd(std::min(e.na - k * e.chunk, e.chunk), ceil_div(e.nbp, 16 * b16));
+        };
+        if (bt >= 8 * CHIP_CUS)
+            ew_launch(ew_yz_kernel<EwReq, 2>, ew_yz_kernel<EwBatch, 2>, part, d, 0, s, [&](const EwDesc& e) { return tiles(e, 2); });
+        else
+            ew_launch(ew_yz_kernel<EwReq, 1>, ew_yz_kernel<EwBatch, 1>, part, d, 0, s, [&](const EwDesc& e) { return tiles(e, 1); });
+    }
     ew_launch(ew_coef_kernel<EwReq>, ew_coef_kernel<EwBatch>, b, dims, n * 17 * (int)sizeof(double), s,
               [](const EwDesc& d) { return ew_on_xcd(d.rowsp / 16, 8); },
               std::min(CF_THREADS, std::max(4, (n + 15) / 16) * 64));

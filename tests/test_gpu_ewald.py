@@ -103,3 +103,27 @@ def test_long_series_on_a_large_detector(env):
         I, A = plan.simulate(torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda(), amplitude=True)
         I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
     assert _rel(A[pix], Ao) <= TOL and _rel(I[pix], np.abs(Ao) ** 2) <= 2 * TOL
+
+
+@pytest.mark.parametrize("detector", ["flat", "uniform_q"])
+def test_nodes_in_parts_within_the_fixed_scratch(env, detector):
+    # a plan whose nodes' sums are made in parts so that its scratch stays within what
+    # msft_simulate_noalloc has (as the direct form's does); the last part is a short one
+    torch, msft = env
+    grid, det, pitch, lam = (116, 115, 114), 90, (5.4, 5.4, 5.4), 13.5
+    print(f"[gpu] nodes in parts {detector} grid={grid} det={det}", flush=True)
+    rng = np.random.default_rng(inputs.SEED_BASE + det)
+    d, b = (rng.uniform(0.0, 0.05, grid).astype(np.float32) for _ in range(2))
+    q = oracle.qmap(lam, 80.0, det) if detector == "flat" else oracle.qmap_uniform(lam, 80.0, det)
+    ok = np.flatnonzero(~np.isnan(q[:, 2]))
+    pix = np.sort(rng.choice(ok, size=256, replace=False))
+    Ao = oracle.amplitude(q[pix], oracle.strength(oracle.MSFT, d.astype(np.float64), b.astype(np.float64), pitch, lam),
+                          pitch, 1)
+    with msft.Plan(lam, 80.0, det, grid, pitch, detector=detector) as plan:
+        dt, bt = torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda()
+        I, A = plan.simulate(dt, bt, amplitude=True)
+        In, An = torch.full_like(I, float("nan")), torch.full((plan.npix, 2), float("nan"), device="cuda")
+        msft.msft_simulate_noalloc(plan.handle, dt, bt, In, An)
+        assert torch.equal(I, In) and torch.equal(torch.view_as_real(A), An)
+        I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
+    assert _rel(A[pix], Ao) <= TOL and _rel(I[pix], np.abs(Ao) ** 2) <= 2 * TOL
