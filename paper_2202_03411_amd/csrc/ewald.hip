@@ -279,7 +279,9 @@ __global__ __launch_bounds__(EW_THREADS) void ew_scan_rounds_kernel(A args)
 // byte 8 cc; te, to tables of `ldE`, `ldO` doubles a row, two tiles each.  The waves of
 // the workgroup take every fourth step of four pairs; the last step (its pairs, an odd
 // axis's middle voxel; the tables are zero past it) is one wave's.  The addresses of
-// whole steps are scalar.
+// whole steps are scalar.  Two steps' loads are issued ahead: four take 144 registers
+// instead of 73, and the waves lost cost more (256^3/1024^2: modal 77 us instead of 64,
+// nodes 103 instead of 88; eight mixed requests 23.4 and 20.1 instead of 18.5 and 16.2).
 // ---------------------------------------------------------------------------
 struct HalfAxis {
     gcdouble v, e0, e1, o0, o1;
@@ -298,7 +300,7 @@ __device__ __forceinline__ void half_axis_sums(const HalfAxis& x, int wave, int 
                          {x.e1 + h0 * x.ldE, e16, pe},
                          {x.o0 + h0 * x.ldO, o16, po},
                          {x.o1 + h0 * x.ldO, o16, po}};
-    staged<4>(s, (full - wave + 3) >> 2, [&](int, const double* y) {
+    staged<2>(s, (full - wave + 3) >> 2, [&](int, const double* y) {
         const double sum = y[0] + y[1], diff = y[0] - y[1];
         t[0] = mfma_f64(y[2], sum, t[0]);
         t[1] = mfma_f64(y[3], sum, t[1]);
@@ -402,7 +404,9 @@ __global__ __launch_bounds__(EW_THREADS) void ew_nodes_kernel(A args)
 // workgroup takes one a and BT tiles of 16 b (the rows); a wave one pM and every other
 // tile of 16 columns (l, re | im), K running over the modes m, both pN sharing the c_m
 // operand and the BT tiles the G operand.  c_l multiplies each product tile, and the
-// columns are summed at the end over lanes and waves.  The result goes to
+// columns are summed at the end over lanes and waves.  With one tile three steps' loads are
+// issued ahead (more waves: 26.5 us against 31 with six at 132^3, 13.5 nm), with two, which
+// read G half as often, six (256^3/1024^2: 142 us, three 151; one tile 166).  The result goes to
 // [4 px + 2 py + (re | im)][row node][node], px and py the parities along x and y.  The
 // groups of b of one a follow each other on one XCD.
 // ---------------------------------------------------------------------------
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(EW_THREADS) void ew_yz_kernel(A args)
         g[1] = {gm + gs, 4 * ld, og};
 #pragma unroll
         for (int k = 0; k < BT; ++k) g[2 + k] = {cm + bt[k], 4 * nbp, om};
-        staged<6>(g, steps, [&](int, const double* y) {
+        staged<BT == 2 ? 6 : 3>(g, steps, [&](int, const double* y) {
 #pragma unroll
             for (int k = 0; k < BT; ++k) {
                 e[k] = mfma_f64(y[2 + k], y[0], e[k]);

@@ -138,20 +138,32 @@ __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstl
 
 constexpr f64x4 F64X4_ZERO = {0.0, 0.0, 0.0, 0.0};
 
-// Four waves' partial sums of four product tiles: wave w gets tile w's total.
-constexpr int SUM_WAVES_LDS = 4 * 4 * 4 * 64;
+// Four waves' partial sums of four product tiles: wave w gets tile w's total, the others'
+// parts of it through LDS.
+constexpr int SUM_WAVES_LDS = 4 * 3 * 4 * 64;
 __device__ __forceinline__ f64x4 sum_waves(double* red, const f64x4* t, int wave, int lane)
 {
+    f64x4 own = F64X4_ZERO;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < 4; ++k) {
+        if (k == wave) {
+            own = t[k];
+            continue;
+        }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[((wave * 4 + k) * 4 + r) * 64 + lane] = t[k][r];
+        for (int r = 0; r < 4; ++r) red[((k * 3 + (wave < k ? wave : wave - 1)) * 4 + r) * 64 + lane] = t[k][r];
+    }
     __syncthreads();
     f64x4 s = F64X4_ZERO;
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
+    for (int w = 0; w < 4; ++w) {
+        if (w == wave) {
+            s += own;
+            continue;
+        }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[r] += red[((w * 4 + wave) * 4 + r) * 64 + lane];
+        for (int r = 0; r < 4; ++r) s[r] += red[((wave * 3 + (w < wave ? w : w - 1)) * 4 + r) * 64 + lane];
+    }
     return s;
 }
 
