@@ -4,17 +4,16 @@
 Workload: a star-shaped harmonic body (l <= 6, R0 = 200 nm, delta = 0.01,
 beta = 0.02) on a 128^3 voxel grid, lambda = 45 nm, flat 512 x 512 detector to
 60 deg.  One step = one pattern through the whole forward path: column scan,
-MFMA contraction with the fused y/z reduction, |A|^2.  Inputs are resident in
-HBM before timing starts.  Prints ONE JSON line.
+contraction, |A|^2.  Inputs are resident in HBM before timing starts.  Prints ONE
+JSON line.
 
 Reported beside the headline (FP32, one pattern per launch; 100 timed patterns
 after 10 warm-ups by default):
-  - the BF16 hi+lo split contraction and plain BF16,
+  - the split precision and plain BF16 (the direct sum),
   - a batch of patterns in one batched launch against the same patterns
     launched one by one, and the FP32 adjoint,
-  - the dominant kernel against the FP32 matrix-core roofline (HIP events on
-    the stream the kernel runs on), with its HBM traffic from the committed
-    counter summary,
+  - the pattern against the HBM roofline on the bytes it cannot do without (plain
+    BF16: its contraction against the matrix-core peak),
   - the served stream (batched against plain), the uniform-q detector, the shape
     renderers and the Ideal detector,
   - the FP64 CPU oracle timed on a bounded pixel sample (cpu_baseline).
@@ -32,30 +31,27 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "MSFT patterns/s at 128³ grid, 512² detector (FP32 vs BF16-split vs plain); p99 ms"
-PEAK_TFLOPS = {"fp32": 157.3, "bf16x3": 2500.0, "bf16": 2500.0}   # MI355X dense matrix peaks
-# real flops the contraction executes on the matrix cores per voxel-pixel term
-EXEC_PER_TERM = {"fp32": 6, "bf16x3": 24, "bf16": 8}
+PEAK_TFLOPS = {"bf16": 2500.0}   # MI355X dense matrix peak
+# real flops the direct contraction executes on the matrix cores per voxel-pixel term; the
+# other precisions run the spherical-coordinate form, whose work is not per term
+EXEC_PER_TERM = {"bf16": 8}
 HBM_PEAK_GBS = 8000.0
 
 
-def profiled_traffic(prec):
-    """HBM bytes per launch of the contraction kernel from the committed counter
-    summary, or None when the kernel source has changed since it was counted."""
-    import hashlib
-    import re
-    kernel = "fwd_g3_kernel_fp32" if prec == "fp32" else f"fwd_pair_kernel_{prec}"
-    path = os.path.join(ROOT, "profiles", f"{kernel}_star128_det512_traffic.md")
-    if not os.path.exists(path):
-        return None
-    text = open(path).read()
-    m = re.search(r"^fwd[^\n]*traffic per launch[^:]*:\s*([0-9.eE+]+) bytes", text, re.M)
-    h = re.search(r"sha256 when counted:\s*([0-9a-f]{64})", text)
-    # the FP32 contraction is the three-product kernel of gauss.hip
-    src = os.path.join(ROOT, "paper_2202_03411_amd", "csrc",
-                       "gauss.hip" if prec == "fp32" else "kernels.hip")
-    if not m or not h or hashlib.sha256(open(src, "rb").read()).hexdigest() != h.group(1):
-        return None
-    return float(m.group(1))
+def roofline(prec, res, P, V):
+    """A pattern's roofline: for the direct sum the matrix cores' peak on the flops its
+    contraction executes, else HBM on delta and beta in and the intensity out."""
+    if prec in EXEC_PER_TERM:
+        executed = float(EXEC_PER_TERM[prec]) * P * V
+        tf = executed / (res["contract_ms"] * 1e-3) / 1e12
+        return {"bound": "mfma", "achieved": tf, "peak": PEAK_TFLOPS[prec], "unit": "TFLOP/s",
+                "frac": tf / PEAK_TFLOPS[prec], "kernel": f"fwd_pair_kernel<{prec}>",
+                "per_launch": f"{executed:.4e} executed flops"}
+    nbytes = 8.0 * V + 4.0 * P
+    gbs = nbytes / (res["ms_per_step"] * 1e-3) / 1e9
+    return {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
+            "kernel": "the pattern's six: ew_scan, ew_modal, ew_nodes, ew_yz, ew_coef, ew_eval",
+            "per_launch": f"{nbytes:.4e} bytes a pattern cannot do without"}
 
 
 def _pct(xs, p):
@@ -193,7 +189,7 @@ def time_fit(torch, batch, steps, warmup, log, detector="flat"):
 
 def time_uniform(msft, torch, wl, d, b, prec, steps, warmup):
     """The same body on the uniform transverse-q detector of the slice-transform
-    algorithm (separable two-stage contraction), checked on seeded pixels."""
+    algorithm, checked on seeded pixels."""
     import numpy as np
 
     import oracle
@@ -435,7 +431,7 @@ def main():
         with msft.Plan.for_workload(wl, "fp32") as plan:
             ms = time_backward(msft, torch, plan, d, b, args.steps, args.warmup)
         print(f"[bench] fp32 backward: {ms:.3f} ms/pattern, {flops / (ms * 1e-3) / 1e12:.1f} TFLOP/s "
-              "algorithmic", file=sys.stderr, flush=True)
+              "of the direct sum", file=sys.stderr, flush=True)
         print(json.dumps({"metric": "MSFT adjoint patterns/s, 128³ grid, 512² detector",
                           "value": 1000.0 / ms, "unit": "patterns/s", "n_gpus": 1, "steps": args.steps,
                           "warmup": args.warmup, "dtype": "f32", "higher_is_better": True,
@@ -459,16 +455,13 @@ def main():
                    "error_vs_fp64_oracle": oracle_error(wl, r["intensity"]),
                    "intensity": r["intensity"]}
             print(f"[bench] {prec}: {ms:.3f} ms/pattern (contract {cms:.3f} ms, scan {sms:.4f} ms), "
-                  f"{res['contract_tflops']:.1f} TFLOP/s algorithmic", file=sys.stderr, flush=True)
+                  f"{res['contract_tflops']:.1f} TFLOP/s of the direct sum", file=sys.stderr, flush=True)
             if prec == "fp32" and not args.only:
                 bms_adj = time_backward(msft, torch, plan, d, b, max(3, args.steps // 4), 1)
                 res["backward"] = {"ms_per_pattern": bms_adj,
-                                   "tflops_algorithmic": flops / (bms_adj * 1e-3) / 1e12,
-                                   "tflops_executed": 0.75 * flops / (bms_adj * 1e-3) / 1e12,
-                                   "frac_fp32_mfma_peak": 0.75 * flops / (bms_adj * 1e-3) / 1e12 /
-                                   PEAK_TFLOPS["fp32"]}
+                                   "tflops_direct_equivalent": flops / (bms_adj * 1e-3) / 1e12}
                 print(f"[bench] fp32 backward: {bms_adj:.3f} ms/pattern, "
-                      f"{res['backward']['tflops_algorithmic']:.1f} TFLOP/s algorithmic",
+                      f"{res['backward']['tflops_direct_equivalent']:.1f} TFLOP/s of the direct sum",
                       file=sys.stderr, flush=True)
             if args.batch > 1 and not args.only:
                 ds = [torch.roll(d, shifts=k, dims=0) for k in range(args.batch)]
@@ -485,9 +478,7 @@ def main():
 
     head = results.get("fp32") or results[precisions[0]]
     head_prec = "fp32" if "fp32" in results else precisions[0]
-    # scan: delta and beta in (8 B per voxel), w out in the tile layout (8 B per voxel:
-    # FP32 re/im, or BF16 hi/lo re/im)
-    scan_bytes = 16.0 * V
+    scan_bytes = 8.0 * V   # delta and beta in
     line = {
         "metric": METRIC,
         "value": head["patterns_per_s"],
@@ -507,20 +498,7 @@ def main():
         "p50_ms": head["p50_ms"],
         "p99_ms": head["p99_ms"],
         "terms_per_s": head["terms_per_s"],
-        # The contraction's roofline is the matrix cores' peak for its dtype against the
-        # flops the kernel executes on them: 6 real flops per voxel-pixel term for the
-        # FP32 three-product form, 24 for the BF16 hi+lo split (three 8-flop products).
-        # The 8-flop count of one complex multiply-add is reported beside it.
-        "roofline": {"bound": "mfma", "achieved": head["contract_tflops"] * EXEC_PER_TERM[head_prec] / 8.0,
-                     "peak": PEAK_TFLOPS[head_prec], "unit": "TFLOP/s",
-                     "frac": head["contract_tflops"] * EXEC_PER_TERM[head_prec] / 8.0
-                     / PEAK_TFLOPS[head_prec],
-                     "traffic": profiled_traffic(head_prec),
-                     "kernel": "fwd_g3_kernel" if head_prec == "fp32" else f"fwd_pair_kernel<{head_prec}>",
-                     "per_launch": f"{flops * EXEC_PER_TERM[head_prec] / 8.0:.4e} executed flops "
-                                   f"({EXEC_PER_TERM[head_prec]} per voxel-pixel term, {P * V:.4e} terms)",
-                     "achieved_algorithmic": head["contract_tflops"],
-                     "algorithmic_flops_per_term": 8},
+        "roofline": roofline(head_prec, head, P, V),
         "scan": {"ms": head["scan_ms"], "gbs": scan_bytes / (head["scan_ms"] * 1e-3) / 1e9,
                  "frac_hbm": scan_bytes / (head["scan_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS},
         "variants": results,
@@ -532,9 +510,7 @@ def main():
     for v in line["variants"].values():
         v.pop("intensity", None)
     for prec, r in results.items():
-        r["roofline_frac_executed"] = (r["contract_tflops"] * EXEC_PER_TERM[prec] / 8.0
-                                       / PEAK_TFLOPS[prec])
-        r["executed_flops_per_term"] = EXEC_PER_TERM[prec]
+        r["roofline"] = roofline(prec, r, P, V)
     if args.large and not args.only:
         lw = inputs.large_workload()
         lP, lV = lw.det_n ** 2, int(np.prod(lw.grid))
@@ -548,8 +524,8 @@ def main():
             cms = sum(r["contract_ms"]) / len(r["contract_ms"])
             line["large"][prec] = {"ms_per_pattern": ms, "patterns_per_s": 1000.0 / ms,
                                    "contract_tflops": 8.0 * lP * lV / (cms * 1e-3) / 1e12}
-            print(f"[bench] large {prec}: {ms:.1f} ms/pattern, "
-                  f"{line['large'][prec]['contract_tflops']:.1f} TFLOP/s algorithmic",
+            print(f"[bench] large {prec}: {ms:.3f} ms/pattern, "
+                  f"{line['large'][prec]['contract_tflops']:.1f} TFLOP/s of the direct sum",
                   file=sys.stderr, flush=True)
         del ld, lb
     if args.serving > 0 and not args.only:
@@ -565,7 +541,7 @@ def main():
             u = time_uniform(msft, torch, wl, d, b, prec, args.steps, args.warmup)
             line["uniform_q"][prec] = u
             print(f"[bench] uniform-q {prec}: {u['ms_per_step']:.3f} ms/pattern, "
-                  f"{u['contract_tflops']:.1f} TFLOP/s (two stages), error "
+                  f"{u['contract_tflops']:.1f} TFLOP/s of the separable sum, error "
                   f"{u['error_vs_fp64_oracle']['rel_l2_intensity']:.2e}", file=sys.stderr, flush=True)
     if not args.only:
         line["render"] = time_render(msft, torch, args.steps)
@@ -573,12 +549,10 @@ def main():
               f"gradient {line['render']['gradient_ms'] * 1e3:.1f} us", file=sys.stderr, flush=True)
     if not args.only:
         pk = time_peaks(msft, torch)
-        # the headline kernels against what the device sustains (roofline.peak stays the
-        # published figure)
-        pk["fwd_g3_frac_of_sustained"] = line["roofline"]["achieved"] / pk["fp32_mfma_tflops"]
-        v3 = line["variants"].get("bf16x3")
-        if v3:
-            pk["fwd_pair_bf16x3_frac_of_sustained"] = 3.0 * v3["contract_tflops"] / pk["bf16_mfma_tflops"]
+        # plain BF16 against what the device sustains (roofline.peak stays the published figure)
+        if "bf16" in line["variants"]:
+            pk["fwd_pair_bf16_frac_of_sustained"] = (line["variants"]["bf16"]["roofline"]["achieved"]
+                                                     / pk["bf16_mfma_tflops"])
         line["peaks"] = pk
         print(f"[bench] sustained: FP32 MFMA {pk['fp32_mfma_tflops']:.1f} TF/s, BF16 MFMA "
               f"{pk['bf16_mfma_tflops']:.1f} TF/s, HBM copy {pk['hbm_copy_gbs']:.0f} GB/s",
