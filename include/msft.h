@@ -57,7 +57,9 @@ typedef enum {
     MSFT_ERR_UNSUPPORTED = 6    /* the plan cannot run this call (host-only plan, ...) */
 } msft_status;
 
-/* Arithmetic of the x-sum contraction (the dominant step). */
+/* Arithmetic of the sums over the voxels.  In MSFT_FP32 and MSFT_BF16X3 a detector's pattern
+ * is summed in FP64 in spherical coordinates where its plan has work enough; what follows
+ * then holds for q lists and small plans only. */
 typedef enum {
     MSFT_FP32 = 0,   /* FP32 MFMA, FP32 accumulation; the complex x-sum as three real
                         products (Gauss), P1 = Tr Wr, P2 = Ti Wi, P3 = (Tr+Ti)(Wr+Wi) */
@@ -145,10 +147,10 @@ msft_status msft_plan_destroy(msft_plan_t plan);
  * Sizes of a plan (the HBM footprint a scheduler admits requests by):
  *   npix              P, the number of pixels (or q values);
  *   workspace_bytes   device scratch that one msft_simulate or msft_backward call
- *                     of this plan needs (the larger of the two: the effective
- *                     strength w in the contraction's tile layout, plus the
- *                     backward's partial sums);
- *   resident_bytes    device memory the plan itself holds (q map, twiddles);
+ *                     of this plan needs (the larger of the two: the sums
+ *                     between the stages, or the effective strength w in the
+ *                     contraction's tile layout and the backward's partial sums);
+ *   resident_bytes    device memory the plan itself holds (its tables);
  *   per_request_bytes device memory one request of this plan holds while it is
  *                     in flight: its delta and beta (8 bytes per voxel), its
  *                     intensity and amplitude (12 bytes per pixel) and its share
@@ -167,8 +169,8 @@ msft_status msft_plan_grid(msft_plan_t plan, double* x, double* y, double* z);
 
 /*
  * Forward model for one target (Eq. (9), Sec. 3 Blocks 5-11): column scan of
- * the incident field and strength, the x-sum as a contraction on the matrix
- * cores, the y/z phase-weighted reduction and |A|^2.
+ * the incident field and strength, the sums over the voxels on the matrix
+ * cores and |A|^2.
  *   delta, beta : device float32 [nx][ny][nz]
  *   intensity   : device float32 [P] (written)
  *   amplitude   : device complex64 [P] or NULL (written if given)
@@ -185,8 +187,8 @@ msft_status msft_simulate(msft_plan_t plan, const float* delta, const float* bet
 /*
  * The two stages of msft_simulate, for callers that time or reuse them:
  * msft_simulate_scan runs the column scan (Eq. (8)) and writes the effective
- * strength w into the workspace in the contraction's tile layout;
- * msft_simulate_contract then sums it against the plan's twiddles (Eq. (9)) and writes
+ * strength w (or its sums over z against the plan's modes) into the workspace;
+ * msft_simulate_contract then sums it against the plan's tables (Eq. (9)) and writes
  * intensity (and amplitude if non-NULL).  msft_simulate_scan followed by
  * msft_simulate_contract on one stream and one workspace equals msft_simulate bit for bit.
  */
@@ -214,9 +216,9 @@ msft_status msft_batch_query(const msft_request* reqs, int32_t n, size_t* worksp
 
 /*
  * Forward model for n requests of possibly different plans (same precision)
- * in one launch per 24 requests: every request's pixel blocks become
- * workgroups, numbered most expensive first so that the device dispatches them
- * in that order.  Each pixel written is bit-identical to what msft_simulate
+ * with each stage in one launch per 24 requests (in the direct sum every
+ * request's pixel blocks become workgroups, numbered most expensive first so that the
+ * device dispatches them in that order).  Each pixel written is bit-identical to what msft_simulate
  * writes for that request alone.
  * Returns MSFT_ERR_BUSY if ws_bytes is smaller than msft_batch_query reports,
  * and MSFT_ERR_UNSUPPORTED for a plan of the uniform-q detector.
@@ -249,8 +251,7 @@ msft_status msft_simulate_noalloc(msft_plan_t plan, const float* delta, const fl
  * chain rule through Eqs. (7)-(9) gives, along each column,
  *   dL/d delta_s = 2 Re(R_s dw_s/d delta_s) + 2 k0 dz Im(sum_{s'>s} R_s' w_s')
  *   dL/d beta_s  = 2 Re(R_s dw_s/d beta_s)  - 2 k0 dz Re(sum_{s'>s} R_s' w_s')
- * (second terms only for MSFT_STRENGTH_MSFT).  The twiddles are recomputed
- * on the fly, not read from the plan.  workspace: as for msft_simulate
+ * (second terms only for MSFT_STRENGTH_MSFT).  workspace: as for msft_simulate
  * (ws_bytes at least msft_plan_query's workspace_bytes).
  */
 msft_status msft_backward(msft_plan_t plan, const float* delta, const float* beta,

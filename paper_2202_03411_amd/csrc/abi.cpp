@@ -513,8 +513,8 @@ EwReq ew_request(const msft_plan_s* p, const float* delta, const float* beta, fl
     return EwReq{p->ew_dev, delta, beta, intensity, amplitude, (double*)workspace, p0, p1, 0};
 }
 
-// The contraction of a plan after the scan: one launch for the flat detector,
-// the two stages for the separable one.
+// The contraction of a plan after the scan: the stages of the spherical-coordinate form; in
+// the direct form one launch for the flat detector, the two stages for the separable one.
 int launch_contraction(const msft_plan_s* p, const void* workspace, float* intensity,
                        float* amplitude, void* stream)
 {

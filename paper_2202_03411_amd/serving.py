@@ -383,8 +383,8 @@ class GpuExecutor:
         n = nstreams if batched else 1
         self.streams = [torch.cuda.Stream() for _ in range(n)]
         self.free = list(range(n))
-        # pixel blocks resident at once: compute units x workgroups per CU of the
-        # contraction (two of the FP32 three-product kernel, one of the BF16 kernel)
+        # pixel blocks resident at once in the direct form: compute units x workgroups per
+        # CU of the contraction (two of the FP32 three-product kernel, one of the BF16 kernel)
         cus = torch.cuda.get_device_properties(plans.device).multi_processor_count
         self.wave_blocks = cus * (2 if plans.precision == "fp32" else 1)
 
