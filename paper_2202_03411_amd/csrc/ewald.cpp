@@ -67,8 +67,10 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
         }
     }
     a[n - 1] = std::fabs(p) > 1e-16 * scale ? p : 1e-16 * scale;
-    for (int k = 0; k < n; ++k) x[k] = 1.0 + 0.37 * std::sin(1.7 * k + 0.3);
-    for (int it = 0; it < 4; ++it) {
+    for (double& v : a) v = 1.0 / v;
+    uint32_t seed = 1;   // any start that is not orthogonal to the vector
+    for (double& v : x) v = 1.0 + 1e-10 * (double)(seed = seed * 1664525u + 1013904223u);
+    for (int it = 0; it < 3; ++it) {
         for (int k = 0; k + 1 < n; ++k) {
             if (swapped[k]) std::swap(x[k], x[k + 1]);
             x[k + 1] -= l[k] * x[k];
@@ -77,12 +79,13 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
             double v = x[k];
             if (k + 1 < n) v -= b[k] * x[k + 1];
             if (k + 2 < n) v -= c[k] * x[k + 2];
-            x[k] = v / a[k];
+            x[k] = v * a[k];
         }
         double big = 0.0, s = 0.0;
         for (double v : x) big = std::max(big, std::fabs(v));
+        big = 1.0 / big;
         for (double& v : x) {
-            v /= big;
+            v *= big;
             s += v * v;
         }
         s = 1.0 / std::sqrt(s);
@@ -93,8 +96,8 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
 
 // The eigenvectors of largest eigenvalue, four at a time: appends those of the eigenvalues
 // ranked out->size(), ... (0 the largest); `top` lies above them and is moved down.  An
-// eigenvalue is bracketed to 1e-11 of the scale, the gaps being 1e-5 of it or more: each
-// step of the inverse iteration then takes six digits.
+// eigenvalue is bracketed to 1e-11 of the scale, the gaps being 1e-5 of it or more: each of
+// the three steps of the inverse iteration then takes six digits.
 struct TriTop {
     const std::vector<double>&d, &e;
     std::vector<double> e2;
