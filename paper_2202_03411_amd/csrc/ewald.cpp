@@ -43,6 +43,7 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
                                double scale)
 {
     const int n = (int)d.size();
+    if (n == 1) return {1.0};   // an axis of one or two voxels; the matrix may be zero
     std::vector<double> a(n), b(n, 0.0), c(n, 0.0), l(n, 0.0), x(n);
     std::vector<char> swapped(n, 0);
     // rows hold (diagonal, first, second superdiagonal) after elimination

@@ -127,3 +127,11 @@ def test_nodes_in_parts_within_the_fixed_scratch(env, detector):
         assert torch.equal(I, In) and torch.equal(torch.view_as_real(A), An)
         I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
     assert _rel(A[pix], Ao) <= TOL and _rel(I[pix], np.abs(Ao) ** 2) <= 2 * TOL
+
+
+@pytest.mark.parametrize("grid,det,detector", [((1, 1, 128), 500, "flat"), ((200, 1, 1), 400, "flat"),
+                                               ((60, 60, 1), 120, "flat"), ((2, 70, 2), 300, "flat"),
+                                               ((1, 120, 64), 330, "uniform_q"), ((120, 1, 64), 330, "uniform_q")])
+def test_axes_of_one_voxel(env, grid, det, detector):
+    # the band's matrix of an axis of one voxel is the number zero
+    test_forward_and_adjoint_match_oracle(env, (grid, det, (5.0, 5.0, 5.0), 60.0, "msft"), detector)
