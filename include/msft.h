@@ -161,6 +161,22 @@ msft_status msft_plan_destroy(msft_plan_t plan);
 msft_status msft_plan_query(msft_plan_t plan, int64_t* npix, size_t* workspace_bytes,
                             size_t* resident_bytes, size_t* per_request_bytes);
 
+/* How a plan sums over the voxels. */
+typedef enum {
+    MSFT_FORM_DIRECT = 0,    /* every pixel's sum in the plan's precision */
+    MSFT_FORM_SPHERICAL = 1  /* FP64 separable sums in spherical coordinates about a detector axis */
+} msft_form;
+
+/*
+ * The form that msft_simulate (also its stages, its noalloc variant and batches) and
+ * msft_backward run for this plan.  Fixed when the plan is made: MSFT_FORM_SPHERICAL for
+ * detector plans in MSFT_FP32 or MSFT_BF16X3 with work enough, at most 400 angles and at
+ * most 256 and 1024 modes of its axes, unless the scratch of its forward would pass
+ * MSFT_NOALLOC_MAX_BYTES where the direct form's does not (msft_simulate_noalloc runs what
+ * msft_simulate runs).  Any output pointer may be NULL.
+ */
+msft_status msft_plan_forms(msft_plan_t plan, int32_t* forward, int32_t* adjoint);
+
 /* Copy the plan's FP64 transfer momenta, q_host[P][3] as (qx, qy, qz). */
 msft_status msft_plan_qmap(msft_plan_t plan, double* q_host);
 

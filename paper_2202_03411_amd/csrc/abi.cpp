@@ -797,6 +797,15 @@ msft_status msft_plan_query(msft_plan_t plan, int64_t* npix, size_t* workspace_b
     return ok();
 }
 
+msft_status msft_plan_forms(msft_plan_t plan, int32_t* forward, int32_t* adjoint)
+{
+    if (!plan) return fail(MSFT_ERR_INVALID, "plan is NULL");
+    const int32_t form = plan->ew.use ? MSFT_FORM_SPHERICAL : MSFT_FORM_DIRECT;
+    if (forward) *forward = form;
+    if (adjoint) *adjoint = form;
+    return ok();
+}
+
 msft_status msft_plan_qmap(msft_plan_t plan, double* q_host)
 {
     if (!plan || !q_host) return fail(MSFT_ERR_INVALID, "NULL argument");

@@ -26,6 +26,7 @@ MSFT_NOALLOC_MAX_BYTES = 64 << 20
 DETECTORS = {"flat": 0, "uniform_q": MSFT_DETECTOR_UNIFORM_Q}
 
 PRECISIONS = {"fp32": MSFT_FP32, "bf16x3": MSFT_BF16X3, "bf16": MSFT_BF16}
+FORMS = ("direct", "spherical")
 STRENGTHS = {"msft": MSFT_STRENGTH_MSFT, "born": MSFT_STRENGTH_BORN, "density": MSFT_STRENGTH_DENSITY}
 
 
@@ -90,6 +91,7 @@ def _load():
     lib.msft_plan_qlist.argtypes = [P(msft_geometry), VP, I64, ctypes.c_int, P(VP)]
     lib.msft_plan_destroy.argtypes = [VP]
     lib.msft_plan_query.argtypes = [VP, P(I64), P(S), P(S), P(S)]
+    lib.msft_plan_forms.argtypes = [VP, P(I32), P(I32)]
     lib.msft_plan_qmap.argtypes = [VP, VP]
     lib.msft_plan_grid.argtypes = [VP, VP, VP, VP]
     lib.msft_simulate.argtypes = [VP, VP, VP, VP, VP, VP, S, VP]
@@ -114,7 +116,7 @@ def _load():
     lib.msft_last_error.argtypes = []
     lib.msft_last_error.restype = ctypes.c_char_p
     for name in ("msft_plan", "msft_plan_qlist", "msft_plan_destroy", "msft_plan_query",
-                 "msft_plan_qmap", "msft_plan_grid", "msft_simulate", "msft_simulate_scan",
+                 "msft_plan_forms", "msft_plan_qmap", "msft_plan_grid", "msft_simulate", "msft_simulate_scan",
                  "msft_simulate_contract", "msft_simulate_noalloc", "msft_pixel_block", "msft_batch_query", "msft_simulate_batch",
                  "msft_backward", "msft_render_sh", "msft_render_sh_query", "msft_render_sh_backward",
                  "msft_render_ellipsoid", "msft_render_volume", "msft_detect_ideal", "msft_peak_mfma",
@@ -127,8 +129,8 @@ _lib = _load()
 LIBRARY_PATH = _build.LIB
 
 # every symbol the C header declares
-EXPORTS = ("msft_plan", "msft_plan_qlist", "msft_plan_destroy", "msft_plan_query", "msft_plan_qmap",
-           "msft_plan_grid", "msft_simulate", "msft_simulate_scan", "msft_simulate_contract",
+EXPORTS = ("msft_plan", "msft_plan_qlist", "msft_plan_destroy", "msft_plan_query", "msft_plan_forms",
+           "msft_plan_qmap", "msft_plan_grid", "msft_simulate", "msft_simulate_scan", "msft_simulate_contract",
            "msft_simulate_noalloc", "msft_pixel_block",
            "msft_batch_query",
            "msft_simulate_batch", "msft_backward", "msft_render_sh", "msft_render_sh_query",
@@ -269,6 +271,13 @@ def msft_plan_query(plan: int):
     _check(_lib.msft_plan_query(ctypes.c_void_p(plan), ctypes.byref(n), ctypes.byref(w),
                                 ctypes.byref(r), ctypes.byref(q)), "msft_plan_query")
     return n.value, w.value, r.value, q.value
+
+
+def msft_plan_forms(plan: int):
+    """Which of FORMS the plan's forward and adjoint run."""
+    f, a = ctypes.c_int32(), ctypes.c_int32()
+    _check(_lib.msft_plan_forms(ctypes.c_void_p(plan), ctypes.byref(f), ctypes.byref(a)), "msft_plan_forms")
+    return FORMS[f.value], FORMS[a.value]
 
 
 def msft_plan_qmap(plan: int) -> np.ndarray:
