@@ -24,7 +24,7 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-Wno-unused-par
 # copies them to and from the accumulation registers around every loop.
 HIP_EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("ewald.hip", "ewald_adj.hip")}
 
-SOURCES_HOST = ["geometry.cpp", "ewald.cpp", "abi.cpp"]
+SOURCES_HOST = ["geometry.cpp", "ewald.cpp", "forms.cpp", "abi.cpp"]
 SOURCES_HIP = ["kernels.hip", "gauss.hip", "backward.hip", "render.hip", "detector.hip",
                "noalloc.hip", "sepg.hip", "peaks.hip", "ewald.hip", "ewald_adj.hip"]
 

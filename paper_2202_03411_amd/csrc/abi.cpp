@@ -155,20 +155,21 @@ msft_status build_ew_tables(msft_plan_s* p)
         free_device(p);
         return hip_fail(e, "plan tables");
     }
-    p->resident_bytes = total;
+    p->resident_bytes += total;
     return MSFT_OK;
 }
 
-// Resident tables of a plan on its device: FP64 q and coordinates, then the
-// twiddle tables generated from them.
+// Resident tables of a plan's direct form on its device: FP64 q and coordinates, then the
+// twiddle tables generated from them, those of the direction that takes the form.
 msft_status build_device_tables(msft_plan_s* p)
 {
     DeviceScope ds(p->device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
     const Dims& d = p->dims;
     const Geometry& geo = p->geo;
+    const bool fwd = !p->ew_fwd, adj = !p->ew_adj;
     size_t total = 0;
-    hipError_t e;
+    hipError_t e = hipSuccess;
 #define MSFT_TRY(expr, what)                  \
     do {                                      \
         e = (expr);                           \
@@ -188,15 +189,19 @@ msft_status build_device_tables(msft_plan_s* p)
     MSFT_TRY(dev_alloc(&p->zs_dev, sizeof(double) * d.nz, &total), "hipMalloc z");
     if (p->separable) {
         const SepDims& sd = p->sep;
-        MSFT_TRY(dev_alloc(&p->txa, sd.gauss ? sd.txa1g_bytes(d.nxc3) : sd.txa1_bytes(d.nxc), &total),
-                 "hipMalloc Tx");
-        MSFT_TRY(dev_alloc(&p->txa2, sd.gauss ? sd.txa2g_bytes() : sd.txa2_bytes(), &total), "hipMalloc Ty");
         MSFT_TRY(dev_alloc(&p->tz, p->sep.tz_bytes(d.nzb), &total), "hipMalloc Tz");
-        MSFT_TRY(dev_alloc(&p->txT, sd.gauss ? sd.txTg_bytes(d.nx) : sd.txT_bytes(d.nx), &total),
-                 "hipMalloc adjoint Tx");
-        MSFT_TRY(dev_alloc(&p->tyT, sd.gauss ? sd.tyTg_bytes(d.ny) : sd.tyT_bytes(d.ny), &total),
-                 "hipMalloc adjoint Ty");
-    } else {
+        if (fwd) {
+            MSFT_TRY(dev_alloc(&p->txa, sd.gauss ? sd.txa1g_bytes(d.nxc3) : sd.txa1_bytes(d.nxc), &total),
+                     "hipMalloc Tx");
+            MSFT_TRY(dev_alloc(&p->txa2, sd.gauss ? sd.txa2g_bytes() : sd.txa2_bytes(), &total), "hipMalloc Ty");
+        }
+        if (adj) {
+            MSFT_TRY(dev_alloc(&p->txT, sd.gauss ? sd.txTg_bytes(d.nx) : sd.txT_bytes(d.nx), &total),
+                     "hipMalloc adjoint Tx");
+            MSFT_TRY(dev_alloc(&p->tyT, sd.gauss ? sd.tyTg_bytes(d.ny) : sd.tyT_bytes(d.ny), &total),
+                     "hipMalloc adjoint Ty");
+        }
+    } else if (fwd) {
         MSFT_TRY(dev_alloc(&p->txa, d.txa_bytes(), &total), "hipMalloc Tx");
         MSFT_TRY(dev_alloc(&p->ty, d.ty_bytes(), &total), "hipMalloc Ty");
         MSFT_TRY(dev_alloc(&p->tz, d.tz_bytes(), &total), "hipMalloc Tz");
@@ -239,10 +244,10 @@ msft_status build_device_tables(msft_plan_s* p)
                                                 p->xs_dev, p->ys_dev, p->zs_dev,
                                                 sd.gauss ? nullptr : p->txa,
                                                 sd.gauss ? nullptr : p->txa2, p->tz, s);
-        if (e == hipSuccess && sd.gauss)
+        if (e == hipSuccess && sd.gauss && fwd)
             e = (hipError_t)launch_sepg_twiddles(sd, d.nx, d.ny, d.nxc3, dev[3], dev[4], p->xs_dev,
                                                  p->ys_dev, p->txa, p->txa2, s);
-        if (e == hipSuccess)
+        if (e == hipSuccess && adj)
             e = sd.gauss ? (hipError_t)launch_sepg_adj_tables(sd, d.nx, d.ny, p->xs_dev, dev[3], p->ys_dev,
                                                               dev[4], p->txT, p->tyT, s)
                          : (hipError_t)launch_sep_adj_tables(sd, d.nx, d.ny, dev[5], dev[3], dev[6], dev[4],
@@ -251,6 +256,7 @@ msft_status build_device_tables(msft_plan_s* p)
         if (e == hipSuccess) e = e2;
         for (double* t : dev)
             if (t) (void)hipFree(t);
+    } else if (!fwd) {   // the flat adjoint makes its own from q
     } else if (d.g3) {
         e = (hipError_t)launch_twiddles_g3(d, p->q_dev, p->xs_dev, p->ys_dev, p->zs_dev, p->txa,
                                            p->ty, p->tz, s);
@@ -268,7 +274,7 @@ msft_status build_device_tables(msft_plan_s* p)
         return hip_fail(e, "twiddle generation");
     }
 #undef MSFT_TRY
-    p->resident_bytes = total;
+    p->resident_bytes += total;
     return MSFT_OK;
 }
 
@@ -378,12 +384,11 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
             delete p;
             return fail(MSFT_ERR_NOMEM, "host tables");
         }
-        if (p->ew.use && fwd_ws <= MSFT_NOALLOC_MAX_BYTES && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES)
-            p->ew.use = false;
-        if (p->ew.use) {
-            fwd_ws = std::max(fwd_ws, align256(p->ew.workspace));
-            adj_ws = align256(p->ew.adj_workspace);
-        }
+        if (p->ew.use) choose_forms(p, &p->ew_fwd, &p->ew_adj);
+        if (fwd_ws <= MSFT_NOALLOC_MAX_BYTES && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES) p->ew_fwd = false;
+        if (p->ew_fwd) fwd_ws = std::max(fwd_ws, align256(p->ew.workspace));
+        if (p->ew_adj) adj_ws = align256(p->ew.adj_workspace);
+        if (!p->ew_fwd && !p->ew_adj) p->ew = EwHost();
     }
     p->fwd_workspace = fwd_ws;
     p->adj_workspace = adj_ws;
@@ -401,7 +406,8 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
             delete p;
             return fail(MSFT_ERR_DEVICE, "no such HIP device");
         }
-        st = p->ew.use ? build_ew_tables(p) : build_device_tables(p);
+        st = p->ew_fwd || p->ew_adj ? build_ew_tables(p) : MSFT_OK;
+        if (st == MSFT_OK && !(p->ew_fwd && p->ew_adj)) st = build_device_tables(p);
         if (st != MSFT_OK) {
             p->device = -1;
             delete p;
@@ -518,7 +524,7 @@ EwReq ew_request(const msft_plan_s* p, const float* delta, const float* beta, fl
 int launch_contraction(const msft_plan_s* p, const void* workspace, float* intensity,
                        float* amplitude, void* stream)
 {
-    if (p->ew.use) {
+    if (p->ew_fwd) {
         const EwDesc* dims = &p->ew.d;
         EwBatch b;
         b.n = 1;
@@ -563,7 +569,7 @@ ScanArgs scan_args(const msft_plan_s* p, const float* delta, const float* beta, 
 int launch_target_scan(const msft_plan_s* p, const float* delta, const float* beta, void* workspace,
                        void* stream)
 {
-    if (!p->ew.use) return launch_scan(p->geo.g.precision, scan_args(p, delta, beta, workspace), stream);
+    if (!p->ew_fwd) return launch_scan(p->geo.g.precision, scan_args(p, delta, beta, workspace), stream);
     const EwDesc* dims = &p->ew.d;
     EwBatch b;
     b.n = 1;
@@ -800,9 +806,8 @@ msft_status msft_plan_query(msft_plan_t plan, int64_t* npix, size_t* workspace_b
 msft_status msft_plan_forms(msft_plan_t plan, int32_t* forward, int32_t* adjoint)
 {
     if (!plan) return fail(MSFT_ERR_INVALID, "plan is NULL");
-    const int32_t form = plan->ew.use ? MSFT_FORM_SPHERICAL : MSFT_FORM_DIRECT;
-    if (forward) *forward = form;
-    if (adjoint) *adjoint = form;
+    if (forward) *forward = plan->ew_fwd ? MSFT_FORM_SPHERICAL : MSFT_FORM_DIRECT;
+    if (adjoint) *adjoint = plan->ew_adj ? MSFT_FORM_SPHERICAL : MSFT_FORM_DIRECT;
     return ok();
 }
 
@@ -968,7 +973,7 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
         b.n = 0;
         for (; r < n && b.n < EW_MAX_REQ; ++r) {
             const msft_request& q = reqs[r];
-            if (!q.plan->ew.use || b1[r] == b0[r]) continue;
+            if (!q.plan->ew_fwd || b1[r] == b0[r]) continue;
             dims[b.n] = &q.plan->ew.d;
             b.req[b.n++] = ew_request(q.plan, q.delta, q.beta, q.intensity, q.amplitude, ws + offs[r],
                                       (int64_t)b0[r] * BLOCK_PIX, (int64_t)b1[r] * BLOCK_PIX);
@@ -979,7 +984,7 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
         if (e) return hip_fail((hipError_t)e, "batch launch");
     }
     for (int32_t r = 0; r < n; ++r) {
-        if (b1[r] == b0[r] || reqs[r].plan->ew.use) continue;
+        if (b1[r] == b0[r] || reqs[r].plan->ew_fwd) continue;
         const ScanArgs sa = scan_args(reqs[r].plan, reqs[r].delta, reqs[r].beta, ws + offs[r]);
         int e = launch_scan(precision, sa, stream);
         if (e) return hip_fail((hipError_t)e, "scan launch");
@@ -999,7 +1004,7 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
         int32_t nr = 0;
         for (size_t k = k0; k < order.size() && k < k0 + MAX_BATCH; ++k) {
             const int32_t r = order[k];
-            if (b1[r] == b0[r] || reqs[r].plan->ew.use) continue;
+            if (b1[r] == b0[r] || reqs[r].plan->ew_fwd) continue;
             b.req[nr] = forward_args(reqs[r].plan, ws + offs[r], reqs[r].intensity, reqs[r].amplitude);
             b.block_begin[nr] = b0[r];
             b.item_begin[nr] = items;
@@ -1027,7 +1032,7 @@ msft_status msft_backward(msft_plan_t plan, const float* delta, const float* bet
         return fail(MSFT_ERR_INVALID, "NULL argument");
     st = check_workspace(workspace, ws_bytes, plan->adj_workspace);
     if (st != MSFT_OK) return st;
-    if (plan->ew.use) {
+    if (plan->ew_adj) {
         DeviceScope ds(plan->device);
         if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
         const EwAdj a = {plan->ew_dev, delta, beta, amplitude, grad_intensity, grad_delta, grad_beta,

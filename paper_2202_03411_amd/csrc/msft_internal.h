@@ -375,12 +375,19 @@ struct msft_plan_s {
     uint8_t* tyT = nullptr;       // separable detector, adjoint: exp(-i q_y(j) y), rows y
     bool separable = false;
     msft::SepDims sep;
-    msft::EwHost ew;              // the spherical-coordinate form, where ew.use
+    msft::EwHost ew;              // the spherical-coordinate form, where a direction takes it:
+    bool ew_fwd = false, ew_adj = false;
     msft::EwDesc* ew_dev = nullptr;
     void* ew_tables = nullptr;    // the tables it points to
     size_t resident_bytes = 0;
     size_t workspace_bytes = 0;   // max of the two below
-    size_t fwd_workspace = 0;     // msft_simulate: the larger of both forms' (W tiles, H tiles of the separable)
+    size_t fwd_workspace = 0;     // msft_simulate: the larger of both forms (W tiles, H tiles of the separable)
     size_t adj_workspace = 0;     // msft_backward
     size_t per_request = 0;       // one request's own buffers + its share of a batch workspace
 };
+
+namespace msft {
+// Which form the forward and the adjoint of a plan take whose spherical form (p->ew) applies:
+// by estimates of both forms' times (forms.cpp).
+void choose_forms(const msft_plan_s* p, bool* forward, bool* adjoint);
+}  // namespace msft

@@ -24,3 +24,25 @@ def test_a_plan_tells_its_forms():
         assert msft.msft_plan_forms(p.handle) == ("direct", "direct")
     with pytest.raises(msft.MSFTError):
         msft.msft_plan_forms(None)
+
+
+@pytest.mark.parametrize("grid,det,pitch,theta,precision,detector,forms", [
+    # 64 pixels on 256^3 voxels: gradient 749 us in the spherical form, 390 direct; forward 356 / 29 286
+    ((256, 256, 256), 8, (16.0, 16.0, 16.0), 60.0, "fp32", "flat", ("spherical", "direct")),
+    # 28 columns of 1734 slices, split: forward 1102 / 242, gradient 578 / 929
+    ((14, 2, 1734), 109, (3.78, 3.78, 4.567), 75.0, "bf16x3", "flat", ("direct", "spherical")),
+    # many angles on the uniform detector: forward 127 / 103, gradient 278 / 53
+    ((333, 87, 64), 78, (11.25, 11.25, 11.25), 60.0, "fp32", "uniform_q", ("spherical", "direct")),
+    # long columns there: 375 / 58 and 481 / 110 at 171 x 13 x 285 on 126^2, split
+    ((171, 13, 285), 126, (21.0, 21.0, 21.0), 60.0, "bf16x3", "uniform_q", ("direct", "direct")),
+    # columns enough: 721 / 31 295
+    ((76, 150, 1350), 40, (5.0, 5.0, 5.0), 60.0, "fp32", "flat", ("spherical", "spherical")),
+])
+def test_each_direction_takes_the_faster_form(grid, det, pitch, theta, precision, detector, forms):
+    assert _forms(grid, det, pitch, theta, precision, detector) == forms
+
+
+def test_the_fixed_scratch_binds_the_forward_alone():
+    # 140^3 voxels at 13.5 nm: the direct form's tiles fit the 64 MiB of msft_simulate_noalloc,
+    # the spherical form's sums do not; msft_backward has no such variant
+    assert _forms((140, 140, 140), 512, (800 / 140,) * 3, 80.0, lam=13.5) == ("direct", "spherical")

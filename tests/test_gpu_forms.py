@@ -1,0 +1,94 @@
+"""Plans by the form of their sums, against the FP64 oracle.
+
+Tolerances on the norm.  Spherical form: FP64 sums on bases truncated at 3e-11, T to 3e-9
+a step, the FP32 amplitude and result of one rounding (2^-24 = 6e-8) each: 2e-7 for the
+amplitude, twice that for the intensity and the gradients.  Direct form: FP32 sums of up to
+1e4 products in chains of at most some hundreds, 1e-5 as for every FP32 pattern; the split
+leaves out lo * lo and rounds lo, 2^-16 each of a product, 1e-4.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2202_03411_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"spherical": 2e-7, "fp32": 1e-5, "bf16x3": 1e-4}
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2202_03411_amd import msft
+    return torch, msft
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(np.ravel(a) - np.ravel(b)) / np.linalg.norm(np.ravel(b)))
+
+
+def _fields(grid, seed, top=0.05):
+    rng = np.random.default_rng(inputs.SEED_BASE + seed)
+    return (rng.uniform(0.0, top, grid).astype(np.float32) for _ in range(2))
+
+
+def _check(env, grid, det, pitch, theta, precision, detector, forms, lam=45.0, pixels=400):
+    """Forward and adjoint of a plan of these forms against the oracle; returns the plan's
+    intensity and amplitude and its tensors, for what a test adds."""
+    torch, msft = env
+    print(f"[gpu] {detector} {precision} grid={grid} det={det} {forms}", flush=True)
+    d, b = _fields(grid, det)
+    g = np.random.default_rng(det).normal(size=det * det).astype(np.float32)
+    q = oracle.qmap(lam, theta, det) if detector == "flat" else oracle.qmap_uniform(lam, theta, det)
+    ok = np.flatnonzero(~np.isnan(q[:, 2]))
+    pix = ok[:: max(1, ok.size // pixels)]
+    d64, b64 = d.astype(np.float64), b.astype(np.float64)
+    Ao = oracle.amplitude(q[pix], oracle.strength(oracle.MSFT, d64, b64, pitch, lam), pitch, 1)
+    with msft.Plan(lam, theta, det, grid, pitch, precision, detector=detector) as plan:
+        assert msft.msft_plan_forms(plan.handle) == forms
+        dt, bt = torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda()
+        I, A = plan.simulate(dt, bt, amplitude=True)
+        gd, gb = torch.full_like(dt, float("nan")), torch.full_like(bt, float("nan"))
+        msft.msft_backward(plan.handle, dt, bt, torch.view_as_real(A).contiguous(),
+                           torch.from_numpy(g).cuda(), gd, gb, plan.workspace())
+        if plan.workspace_bytes <= msft.MSFT_NOALLOC_MAX_BYTES:
+            In = torch.full_like(I, float("nan"))
+            msft.msft_simulate_noalloc(plan.handle, dt, bt, In, None)
+            assert torch.equal(I, In)
+        if detector == "flat":
+            Ib = torch.full_like(I, float("nan"))
+            reqs = [(plan.handle, dt, bt, Ib, None)]
+            msft.msft_simulate_batch(reqs, msft.workspace_tensor(msft.msft_batch_query(reqs), "cuda"))
+            assert torch.equal(I, Ib)
+        torch.cuda.synchronize()
+        I, A = I.cpu().numpy().astype(np.float64), A.cpu().numpy().astype(np.complex128)
+        gd, gb = (t.cpu().numpy().astype(np.float64).reshape(-1, grid[2]) for t in (gd, gb))
+    rng = np.random.default_rng(det + 1)
+    cols = np.sort(rng.choice(grid[0] * grid[1], size=min(24, grid[0] * grid[1]), replace=False))
+    od, ob = oracle.backward(oracle.MSFT, q[ok], g[ok].astype(np.float64), A[ok], d64, b64, pitch, lam, cols=cols)
+    errs = [_rel(A[pix], Ao), _rel(I[pix], np.abs(Ao) ** 2), _rel(gd[cols], od), _rel(gb[cols], ob)]
+    print("  amplitude %.2e intensity %.2e gradients %.2e %.2e" % tuple(errs), flush=True)
+    fwd = TOL["spherical" if forms[0] == "spherical" else precision]
+    adj = TOL["spherical" if forms[1] == "spherical" else "fp32"]   # the direct adjoint is FP32 in both
+    assert errs[0] <= fwd and errs[1] <= 2 * fwd
+    assert max(errs[2:]) <= 2 * adj
+
+
+@pytest.mark.parametrize("grid,det,pitch,theta,precision,detector,forms", [
+    # few pixels on many angles: the gradient direct
+    ((60, 62, 90), 11, (20.0, 20.0, 20.0), 60.0, "fp32", "flat", ("spherical", "direct")),
+    ((60, 62, 90), 11, (20.0, 20.0, 20.0), 60.0, "bf16x3", "flat", ("spherical", "direct")),
+    ((140, 60, 100), 40, (21.375,) * 3, 60.0, "fp32", "uniform_q", ("spherical", "direct")),
+    ((200, 140, 60), 40, (21.375,) * 3, 60.0, "fp32", "uniform_q", ("spherical", "direct")),
+    ((200, 140, 60), 40, (21.375,) * 3, 60.0, "bf16x3", "uniform_q", ("spherical", "direct")),
+    # few columns of many slices: the pattern direct
+    ((14, 2, 734), 109, (3.78, 3.78, 4.567), 75.0, "fp32", "flat", ("direct", "spherical")),
+    ((14, 2, 734), 109, (3.78, 3.78, 4.567), 75.0, "bf16x3", "flat", ("direct", "spherical")),
+    ((28, 65, 407), 72, (5.31,) * 3, 60.0, "fp32", "uniform_q", ("direct", "spherical")),
+    ((60, 62, 300), 40, (11.25,) * 3, 60.0, "bf16x3", "uniform_q", ("direct", "spherical")),
+])
+def test_forward_and_adjoint_of_different_forms(env, grid, det, pitch, theta, precision, detector, forms):
+    _check(env, grid, det, pitch, theta, precision, detector, forms)
