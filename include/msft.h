@@ -147,9 +147,10 @@ msft_status msft_plan_destroy(msft_plan_t plan);
  * Sizes of a plan (the HBM footprint a scheduler admits requests by):
  *   npix              P, the number of pixels (or q values);
  *   workspace_bytes   device scratch that one msft_simulate or msft_backward call
- *                     of this plan needs (the larger of the two: the sums
- *                     between the stages, or the effective strength w in the
- *                     contraction's tile layout and the backward's partial sums);
+ *                     of this plan needs, the larger of the two, each in the form
+ *                     it runs (spherical: the sums between the stages, which go by
+ *                     the columns, modes and angles; direct: the effective strength
+ *                     w in the contraction's tile layout, the backward's partial sums);
  *   resident_bytes    device memory the plan itself holds (its tables);
  *   per_request_bytes device memory one request of this plan holds while it is
  *                     in flight: its delta and beta (8 bytes per voxel), its
@@ -252,9 +253,9 @@ msft_status msft_simulate_batch(const msft_request* reqs, int32_t n, void* works
  * amplitude.  The call itself allocates nothing.  Every call on one device
  * shares that device's array: calls that overlap on one device (on different
  * streams, or from different threads) race and must not be issued.  A plan
- * whose workspace_bytes-sized forward scratch exceeds MSFT_NOALLOC_MAX_BYTES is
- * refused with MSFT_ERR_UNSUPPORTED (for example 192^3 voxels in FP32); nothing is
- * launched then.
+ * whose forward in the direct form would need more scratch than MSFT_NOALLOC_MAX_BYTES
+ * is refused with MSFT_ERR_UNSUPPORTED, whichever form it runs (for example 192^3 voxels
+ * in FP32); nothing is launched then.
  */
 #define MSFT_NOALLOC_MAX_BYTES (64u << 20)
 msft_status msft_simulate_noalloc(msft_plan_t plan, const float* delta, const float* beta,

@@ -376,20 +376,22 @@ msft_status make_plan(const msft_geometry* g, const double* q_host, int64_t npix
         fwd_ws += align256(p->sep.gauss ? p->sep.hg_bytes(p->dims.nzb) : p->sep.h_bytes(p->dims.nzb));
         adj_ws = sep_adj_layout(p, nullptr, nullptr);
     }
+    // msft_simulate_noalloc takes the plans whose direct form fits its fixed scratch
+    const bool fixed = fwd_ws <= MSFT_NOALLOC_MAX_BYTES;
     if (ew_applies(p)) {
         try {
-            // what the fixed scratch of msft_simulate_noalloc holds in the direct form stays within it
-            ew_plan(*g, fwd_ws <= MSFT_NOALLOC_MAX_BYTES ? (size_t)MSFT_NOALLOC_MAX_BYTES : SIZE_MAX, &p->ew);
+            ew_plan(*g, fixed ? (size_t)MSFT_NOALLOC_MAX_BYTES : SIZE_MAX, &p->ew);
         } catch (const std::bad_alloc&) {
             delete p;
             return fail(MSFT_ERR_NOMEM, "host tables");
         }
         if (p->ew.use) choose_forms(p, &p->ew_fwd, &p->ew_adj);
-        if (fwd_ws <= MSFT_NOALLOC_MAX_BYTES && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES) p->ew_fwd = false;
-        if (p->ew_fwd) fwd_ws = std::max(fwd_ws, align256(p->ew.workspace));
+        if (fixed && p->ew.workspace > MSFT_NOALLOC_MAX_BYTES) p->ew_fwd = false;
+        if (p->ew_fwd) fwd_ws = align256(p->ew.workspace);
         if (p->ew_adj) adj_ws = align256(p->ew.adj_workspace);
         if (!p->ew_fwd && !p->ew_adj) p->ew = EwHost();
     }
+    p->fixed_scratch = fixed;
     p->fwd_workspace = fwd_ws;
     p->adj_workspace = adj_ws;
     p->workspace_bytes = std::max(fwd_ws, adj_ws);
@@ -856,11 +858,11 @@ msft_status msft_simulate_noalloc(msft_plan_t plan, const float* delta, const fl
                                   float* intensity, float* amplitude, void* stream)
 {
     if (!plan) return fail(MSFT_ERR_INVALID, "plan is NULL");
-    if (plan->fwd_workspace > (size_t)MSFT_NOALLOC_MAX_BYTES) {
+    if (!plan->fixed_scratch) {
         char buf[160];
         std::snprintf(buf, sizeof buf,
-                      "the plan's forward scratch is %zu bytes; the fixed scratch holds %zu",
-                      plan->fwd_workspace, (size_t)MSFT_NOALLOC_MAX_BYTES);
+                      "the forward scratch of the plan's direct form passes the fixed scratch's %zu bytes",
+                      (size_t)MSFT_NOALLOC_MAX_BYTES);
         return fail(MSFT_ERR_UNSUPPORTED, buf);
     }
     msft_status st = check_runnable(plan);

@@ -381,8 +381,9 @@ struct msft_plan_s {
     void* ew_tables = nullptr;    // the tables it points to
     size_t resident_bytes = 0;
     size_t workspace_bytes = 0;   // max of the two below
-    size_t fwd_workspace = 0;     // msft_simulate: the larger of both forms (W tiles, H tiles of the separable)
-    size_t adj_workspace = 0;     // msft_backward
+    size_t fwd_workspace = 0;     // msft_simulate, in the form it runs
+    size_t adj_workspace = 0;     // msft_backward, likewise
+    bool fixed_scratch = false;   // msft_simulate_noalloc takes the plan
     size_t per_request = 0;       // one request's own buffers + its share of a batch workspace
 };
 

@@ -46,3 +46,19 @@ def test_the_fixed_scratch_binds_the_forward_alone():
     # 140^3 voxels at 13.5 nm: the direct form's tiles fit the 64 MiB of msft_simulate_noalloc,
     # the spherical form's sums do not; msft_backward has no such variant
     assert _forms((140, 140, 140), 512, (800 / 140,) * 3, 80.0, lam=13.5) == ("direct", "spherical")
+
+
+def test_scratch_is_that_of_the_form_that_runs():
+    # 192^3 voxels on 1024^2 pixels: the direct form's W tiles are 6 x chunks of 32 times 6 z
+    # blocks of 32 times 192 y at 12 KiB (three planes of Re, Im at 64 bytes a row of 32)
+    n, det = 192, 1024
+    direct = 6 * 6 * n * 12288
+    with msft.Plan(45.0, 60.0, det, (n, n, n), (700.0 / n,) * 3, device=-1) as p:
+        assert msft.msft_plan_forms(p.handle) == ("spherical", "spherical")
+        scratch = p.per_request_bytes - 2 * 4 * n ** 3 - 12 * det * det
+        assert 0 < scratch < direct // 2
+        assert scratch % 256 == 0 and p.workspace_bytes >= scratch
+        # and the variant on the fixed scratch refuses what it did, by the direct form's
+        assert direct > msft.MSFT_NOALLOC_MAX_BYTES
+        assert msft._lib.msft_simulate_noalloc(p.handle, None, None, None, None, None) == msft.MSFT_ERR_UNSUPPORTED
+        assert "direct form" in msft.msft_last_error()
