@@ -79,7 +79,8 @@ class Scheduler:
     whose whole cost fits the quantum is cheap: cheap requests are grouped in arrival
     order, up to the quantum and max_batch, and go first.  An expensive request is cut
     into slices of pixel blocks worth about one quantum each (a whole number of device
-    waves of blocks, at least one, so that a slice fills the device), launched one
+    waves of blocks, at least one, so that a slice fills the device; a wave is the whole
+    request where the executor says that its work does not divide by blocks), launched one
     slice per launch, oldest request first; cheap requests that arrive meanwhile start between
     its slices instead of waiting for all of it.  At most max_inflight launches are in
     flight, so the device always has queued work; expensive slices leave one launch
@@ -402,7 +403,10 @@ class GpuExecutor:
             req.ws_bytes = 0           # one stream: the plan's own workspace
         req.blocks = self.plans.blocks(req.key)
         req.block_cost = self.plans.block_cost.get(req.key, 0.0)
-        req.wave_blocks = self.wave_blocks
+        # a slice of a request in the spherical form repeats its scan and all sums but the
+        # pixels' (192^3 on 1024^2: 55 of 69 us): one launch takes it whole
+        whole = self.msft.msft_plan_forms(p.handle)[0] == "spherical"
+        req.wave_blocks = req.blocks if whole else self.wave_blocks
 
     def _render(self, req, p):
         torch, msft = self.torch, self.msft

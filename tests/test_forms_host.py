@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from paper_2202_03411_amd import msft
+from paper_2202_03411_amd import msft, serving
 
 
 def _forms(grid, det, pitch, theta=60.0, precision="fp32", detector="flat", lam=45.0):
@@ -62,3 +62,26 @@ def test_scratch_is_that_of_the_form_that_runs():
         assert direct > msft.MSFT_NOALLOC_MAX_BYTES
         assert msft._lib.msft_simulate_noalloc(p.handle, None, None, None, None, None) == msft.MSFT_ERR_UNSUPPORTED
         assert "direct form" in msft.msft_last_error()
+
+
+@pytest.mark.parametrize("precision,slices", [("fp32", 1), ("bf16", 4)])
+def test_a_request_is_sliced_only_where_its_work_divides_by_pixel_blocks(precision, slices):
+    # the spherical form's scan and sums belong to the request, not to its pixel blocks:
+    # cutting it into slices would repeat them; the direct form's blocks are the work
+    plans = serving.PlanCache(msft, precision, device=-1, calibrate=False)
+    ex = serving.GpuExecutor.__new__(serving.GpuExecutor)
+    ex.plans, ex.msft, ex.batched, ex.wave_blocks = plans, msft, True, 256
+    key = (45.0, 60.0, 360, (24, 24, 24), (9.0, 9.0, 9.0), "msft")
+    launched = []
+    ex.launch = lambda items: launched.extend(items)
+    ex.poll = lambda handle: True
+    ex.finish = lambda handle, items: None
+    ex.complete = lambda req: None
+    plans.get(key)
+    plans.block_cost[key] = 1e-4     # 1013 blocks of 0.1 ms: some 20 quanta
+    s = serving.Scheduler(ex, 1 << 40, max_inflight=2, quantum=0.005)
+    s.submit(serving.Request(0, 0.0, key))
+    while not s.idle():
+        s.step()
+    assert [b1 - b0 for _, b0, b1 in launched] == ([1013] if slices == 1 else [256, 256, 256, 245])
+    plans.close()
