@@ -21,20 +21,34 @@ constexpr double EW_TOL = 3e-11;
 int pad(int n, int m) { return (n + m - 1) / m * m; }
 
 // Eigenvalues below each of four x of the symmetric tridiagonal matrix (d, off-diagonal
-// squared e2), by the signs of its Sturm sequences: four chains of divisions at a time.
+// squared e2), entries of order one: the sign changes of the leading minors, four chains of
+// products at a time (the ratios' chains of divisions took 2.4 times as long).
 void sturm_counts(const std::vector<double>& d, const std::vector<double>& e2, const double* x, int* count)
 {
-    double q[4];
+    constexpr double BIG = 1e150, SMALL = 1e-150;
+    double p0[4], p1[4];
     int c[4];
     for (int j = 0; j < 4; ++j) {
-        q[j] = d[0] - x[j];
-        c[j] = q[j] < 0.0;
+        p0[j] = 1.0;
+        p1[j] = d[0] - x[j];
+        c[j] = p1[j] < 0.0;
     }
-    for (size_t k = 1; k < d.size(); ++k)
+    for (size_t k = 1; k < d.size(); ++k) {
         for (int j = 0; j < 4; ++j) {
-            q[j] = d[k] - x[j] - e2[k - 1] / (q[j] == 0.0 ? 1e-300 : q[j]);
-            c[j] += q[j] < 0.0;
+            double p = (d[k] - x[j]) * p1[j] - e2[k - 1] * p0[j];
+            if (p == 0.0) p = p1[j] * 1e-30;   // no change here, one at the next
+            c[j] += (p < 0.0) != (p1[j] < 0.0);
+            p0[j] = p1[j];
+            p1[j] = p;
         }
+        if ((k & 7) == 0)   // a step grows by 3 at most and falls by 1e-7
+            for (int j = 0; j < 4; ++j) {
+                const double m = std::max(std::fabs(p0[j]), std::fabs(p1[j]));
+                const double f = m > BIG ? SMALL : m < SMALL ? BIG : 1.0;
+                p0[j] *= f;
+                p1[j] *= f;
+            }
+    }
     for (int j = 0; j < 4; ++j) count[j] = c[j];
 }
 
@@ -101,7 +115,7 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
 // the three steps of the inverse iteration then takes six digits.
 struct TriTop {
     const std::vector<double>&d, &e;
-    std::vector<double> e2;
+    std::vector<double> ds, e2;   // over the scale, as lo and top
     double lo, top, scale;
 
     TriTop(const std::vector<double>& d_, const std::vector<double>& e_) : d(d_), e(e_)
@@ -114,9 +128,10 @@ struct TriTop {
             hi = std::max(hi, d[k] + r);
         }
         scale = std::max({std::fabs(lo), std::fabs(hi), 1e-300});
-        top = hi + 1e-14 * scale;
-        lo -= 1e-14 * scale;
-        for (double v : e) e2.push_back(v * v);
+        top = hi / scale + 1e-14;
+        lo = lo / scale - 1e-14;
+        for (double v : d) ds.push_back(v / scale);
+        for (double v : e) e2.push_back(v / scale * (v / scale));
     }
     void next(std::vector<std::vector<double>>* out)
     {
@@ -129,10 +144,12 @@ struct TriTop {
         }
         for (int it = 0; it < 200; ++it) {
             bool open = false;
-            for (int j = 0; j < m; ++j) open |= b[j] - a[j] > 1e-11 * scale;
+            for (int j = 0; j < m; ++j) open |= b[j] - a[j] > 1e-11;
             if (!open) break;
-            for (int j = 0; j < 4; ++j) x[j] = 0.5 * (a[j] + b[j]);
-            sturm_counts(d, e2, x, c);
+            // the middles; of intervals that are still one, points apart
+            const bool one = a[0] == a[3] && b[0] == b[3];
+            for (int j = 0; j < 4; ++j) x[j] = a[j] + (one ? 0.2 * (j + 1) : 0.5) * (b[j] - a[j]);
+            sturm_counts(ds, e2, x, c);
             // every count bounds every one of the eigenvalues n - 1 - first - j
             for (int j = 0; j < m; ++j)
                 for (int i = 0; i < 4; ++i) {
@@ -140,48 +157,66 @@ struct TriTop {
                     else a[j] = std::max(a[j], x[i]);
                 }
         }
-        for (int j = 0; j < m; ++j) out->push_back(tri_vector(d, e, 0.5 * (a[j] + b[j]), scale));
+        for (int j = 0; j < m; ++j) out->push_back(tri_vector(d, e, 0.5 * (a[j] + b[j]) * scale, scale));
         top = b[m - 1];   // above the next one: b only falls on counts that hold it
     }
 };
 
-// Terms after which the Chebyshev series of exp(i k (x sin(w t) + s r cos(w t))) over
-// |t| <= 1 is below EW_TOL, the largest of three shares s of r; 0: more than `most`.
-int series_terms(double kx, double kr, double w, int most)
+// Terms after which the Chebyshev series of exp(i (x sin(w t) + s r cos(w t))) over |t| <= 1,
+// w at most pi / 2, is below EW_TOL, the largest of three shares s of r.  Any count from
+// `enough` on stands for more; 0: more than a plan is planned for.
+int series_terms(double x, double r, double w, int enough)
 {
-    const double c = (kx + kr) * w;
-    const int guess = (int)std::min(c + 14.0 * std::cbrt(c) + 40.0, 4.0e6);
-    if (guess > 3 * most) return 0;
-    const int M = pad(guess, 8) + 64;
-    std::vector<double> cs(4 * M);
-    for (int k = 0; k < 4 * M; ++k) cs[k] = std::cos(kPi * k / (2.0 * M));
-    int worst = 1;
-    std::vector<double> fr(M), fi(M);
-    for (double s : {0.0, 0.5, 1.0}) {
-        for (int j = 0; j < M; ++j) {
-            const double t = cs[2 * j + 1];   // cos((j + 1/2) pi / M)
-            const double ph = kx * std::sin(w * t) + s * kr * std::cos(w * t);
-            fr[j] = std::cos(ph);
-            fi[j] = std::sin(ph);
-        }
-        // coefficients from the highest down, until their sum is too much to leave out
-        double tail = 0.0;
-        int need = M;
-        for (; need > worst; --need) {
-            const int k = need - 1;
-            double re = 0.0, im = 0.0;
-            for (int j = 0, at = k; j < M; ++j) {
-                re += fr[j] * cs[at];
-                im += fi[j] * cs[at];
-                at += 2 * k;
-                if (at >= 4 * M) at -= 4 * M;
-            }
-            tail += 2.0 / M * std::sqrt(re * re + im * im);
-            if (tail >= EW_TOL) break;
-        }
-        worst = std::max(worst, need);
+    const double reach = (x + r) * w;
+    if (reach + 14.0 * std::cbrt(reach) + 40.0 > 6.0 * EW_MAX_NODES + 1.0) return 0;
+    // with t = cos(theta) the terms are a Fourier series, which goes on to the phase's largest
+    // rate in theta and falls off within some cube roots of it
+    double rate = 0.0;
+    for (int k = 0; k < 64; ++k) {
+        const double th = (k + 0.5) * kPi / 128.0, a = w * std::cos(th);
+        rate = std::max(rate, w * (x * std::cos(a) + r * std::sin(a)) * std::sin(th));
     }
-    return worst;
+    if (rate >= enough) return enough;
+    int worst = 1;
+    std::vector<double> cs, er, ei, odr, odi;
+    for (int M = pad((int)(rate + 10.0 * std::cbrt(rate * (1.0 + w * w))) + 16, 8);; M = pad(M + M / 2, 8)) {
+        const int half = M / 2;   // nodes of t > 0; those at -t add the same or nothing
+        cs.resize(4 * M);
+        for (int k = 0; k < 4 * M; ++k) cs[k] = std::cos(kPi * k / (2.0 * M));
+        for (auto* v : {&er, &ei, &odr, &odi}) v->resize(half);
+        bool ended = true;
+        worst = 1;
+        for (double s : {0.0, 0.5, 1.0}) {
+            for (int j = 0; j < half; ++j) {   // the even and the odd part in t
+                const double a = w * cs[2 * j + 1], p = x * std::sin(a), q = s * r * std::cos(a);
+                const double cp = std::cos(p), sp = std::sin(p), cq = std::cos(q), sq = std::sin(q);
+                er[j] = cq * cp;
+                ei[j] = sq * cp;
+                odr[j] = -sq * sp;
+                odi[j] = cq * sp;
+            }
+            // coefficients from the highest down, until their sum is too much to leave out
+            double tail = 0.0;
+            int need = M;
+            for (; need > worst; --need) {
+                const int k = need - 1;
+                const double *fr = (k & 1 ? odr : er).data(), *fi = (k & 1 ? odi : ei).data();
+                double re = 0.0, im = 0.0;
+                for (int j = 0, at = k; j < half; ++j) {
+                    re += fr[j] * cs[at];
+                    im += fi[j] * cs[at];
+                    at += 2 * k;
+                    if (at >= 4 * M) at -= 4 * M;
+                }
+                tail += 4.0 / M * std::sqrt(re * re + im * im);
+                if (tail >= EW_TOL) break;
+                if (need == M - 7) ended &= tail < 1e-2 * EW_TOL;
+            }
+            ended &= need <= M - 8;   // else more nodes: the series goes on past M
+            worst = std::max(worst, need);
+        }
+        if (ended) return worst;
+    }
 }
 
 }  // namespace
@@ -221,15 +256,17 @@ bool ew_basis(int n, double d, double qh, int limit, int* ke, int* ko, std::vect
             res.push_back(r);
         }
         TriTop tri(td, te);
+        const int least = (int)(n * W) - 1;   // half the modes concentrated in the band
         int K = 0;
-        for (;; ++K) {
+        for (; K < size; ++K) {
             double worst = 0.0;
-            for (auto& r : res) {
-                double s = 0.0;
-                for (int h = 0; h < nh; ++h) s += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * r[h];
-                worst = std::max(worst, s);
-            }
-            if (std::sqrt(worst / n) < EW_TOL || K == size) break;
+            if (K >= least)
+                for (auto& r : res) {
+                    double s = 0.0;
+                    for (int h = 0; h < nh; ++h) s += (n % 2 && h == m ? 1.0 : 2.0) * r[h] * r[h];
+                    worst = std::max(worst, s);
+                }
+            if (K >= least && std::sqrt(worst / n) < EW_TOL) break;
             if (K == (int)v.size()) {
                 tri.next(&v);
                 for (size_t j = K; j < v.size(); ++j) {
@@ -299,13 +336,15 @@ void ew_plan(const msft_geometry& g, size_t most_bytes, EwHost* hp)
     // largest M sin b + z cos b of the box over |b| <= w: what exp(-i q r) holds beside N sin a
     const double hN = uni ? hy : hx, hM = uni ? hx : hy, wb = uni ? range : rrange;
     const double top = std::atan2(hM, hz), r = top <= wb ? std::hypot(hM, hz) : hM * std::sin(wb) + hz * std::cos(wb);
-    const int most = 2 * EW_MAX_NODES;
     const double wa = uni ? rrange : range;
-    const int ta = wa > 0.0 ? series_terms(k0 * hN, k0 * r, wa, most) : 1;
-    const int tb = wb > 0.0 ? series_terms(k0 * hM, k0 * hz, wb, most) : 1;
+    // past the limit of the pixels' angle, or as many as the rows, the count does not matter
+    const int enough[] = {2 * half, 2 * EW_MAX_NODES + 1};
+    const int ta = wa > 0.0 ? series_terms(k0 * hN, k0 * r, wa, enough[!uni]) : 1;
+    if (ta == 0 || (!uni && ta > 2 * EW_MAX_NODES)) return;
+    const int tb = wb > 0.0 ? series_terms(k0 * hM, k0 * hz, wb, enough[uni]) : 1;
     const int n = ((uni ? tb : ta) + 1) / 2;
     int nr = ((uni ? ta : tb) + 1) / 2;
-    if (ta == 0 || tb == 0 || n > EW_MAX_NODES) return;
+    if (tb == 0 || n > EW_MAX_NODES) return;
     const bool exact = nr >= half;   // no more rows than nodes: the rows themselves
     if (exact) nr = half;
     if (nr > EW_MAX_NODES) return;
@@ -325,33 +364,40 @@ void ew_plan(const msft_geometry& g, size_t most_bytes, EwHost* hp)
     // Chebyshev points in barycentric form, those of +- a node folded for even and odd parts
     H.wre.assign((size_t)d.nrp * d.rowsp, 0.0);
     H.wro.assign((size_t)d.nrp * d.rowsp, 0.0);
-    std::vector<double> nodes(nr), weights(nr);
+    constexpr int JB = 8;   // rows at a time: their weights are neighbours
+    std::vector<double> nodes(nr), weights(nr), pole(JB * nr);
     for (int k = 0; k < nr; ++k) {
         const double w = (k + 0.5) * kPi / (2.0 * nr);
         nodes[k] = std::cos(w);
-        weights[k] = (k & 1 ? -1.0 : 1.0) * std::sin(w);
+        weights[k] = (k & 1 ? -2.0 : 2.0) * std::sin(w);
     }
-    for (int j = 0; j < half; ++j) {
+    for (int j0 = 0; j0 < half; j0 += JB) {
+        const int rows = std::min(JB, half - j0);
         if (exact) {
-            H.wre[(size_t)j * d.rowsp + j] = H.wro[(size_t)j * d.rowsp + j] = 1.0;
+            for (int j = j0; j < j0 + rows; ++j) H.wre[(size_t)j * d.rowsp + j] = H.wro[(size_t)j * d.rowsp + j] = 1.0;
             continue;
         }
-        const double t = row[j] / rrange;
-        double sum = 0.0;
-        std::vector<double> lp(nr), lm(nr);
-        int hit = -1;
-        for (int k = 0; k < nr; ++k) {
-            const double x = nodes[k], s = weights[k];
-            if (t == x) hit = k;
-            lp[k] = s / (t - x);
-            lm[k] = -s / (t + x);   // point 2 nr - 1 - k, at -x: the other sign
-            sum += lp[k] + lm[k];
+        // s / (t - x) at x and, of the other sign, at -x (point 2 nr - 1 - k): sum and difference
+        double t[JB], scale[JB];
+        int hit[JB];
+        for (int u = 0; u < rows; ++u) {
+            t[u] = row[j0 + u] / rrange;
+            hit[u] = -1;
+            double sum = 0.0;
+            for (int k = 0; k < nr; ++k) {
+                const double x = nodes[k];
+                if (t[u] == x) hit[u] = k;
+                pole[JB * k + u] = weights[k] / ((t[u] - x) * (t[u] + x));
+                sum += pole[JB * k + u] * x;
+            }
+            scale[u] = 1.0 / sum;
         }
-        for (int k = 0; k < nr; ++k) {
-            const double p = hit >= 0 ? (double)(k == hit) : lp[k] / sum, m = hit >= 0 ? 0.0 : lm[k] / sum;
-            H.wre[(size_t)k * d.rowsp + j] = p + m;
-            H.wro[(size_t)k * d.rowsp + j] = p - m;
-        }
+        for (int k = 0; k < nr; ++k)
+            for (int u = 0; u < rows; ++u) {
+                const double p = pole[JB * k + u] * scale[u];
+                H.wre[(size_t)k * d.rowsp + j0 + u] = hit[u] >= 0 ? (double)(k == hit[u]) : p * nodes[k];
+                H.wro[(size_t)k * d.rowsp + j0 + u] = hit[u] >= 0 ? (double)(k == hit[u]) : p * t[u];
+            }
     }
     d.na = (int)H.ang_a.size();
     d.nb = (int)H.ang_b.size();

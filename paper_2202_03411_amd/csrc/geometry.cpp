@@ -56,18 +56,28 @@ void detector_qmap(double wavelength, double theta_max_deg, int32_t n, double* q
 {
     const double k0 = (2.0 * kPi) / wavelength;
     const double t = std::tan((theta_max_deg * kPi) / 180.0);
-    for (int32_t j = 0; j < n; ++j) {
+    // u_{n-1-i} = -u_i to the bit, so a pixel's three mirrors are its value with signs
+    for (int32_t j = 0; j < (n + 1) / 2; ++j) {
         const double v = ((double)(2 * j + 1 - n) * t) / (double)n;
-        for (int32_t i = 0; i < n; ++i) {
+        const double vv = v * v;
+        double* lo = q + 3 * ((int64_t)j * n);
+        double* hi = q + 3 * ((int64_t)(n - 1 - j) * n);
+        for (int32_t i = 0; i < (n + 1) / 2; ++i) {
             const double u = ((double)(2 * i + 1 - n) * t) / (double)n;
             const double uu = u * u;
-            const double vv = v * v;
             const double s = uu + vv;
             const double r = std::sqrt(s + 1.0);
-            double* qp = q + 3 * ((int64_t)j * n + i);
-            qp[0] = (k0 * u) / r;
-            qp[1] = (k0 * v) / r;
-            qp[2] = -((k0 * s) / (r * (r + 1.0)));
+            const double qx = (k0 * u) / r, qy = (k0 * v) / r, qz = -((k0 * s) / (r * (r + 1.0)));
+            auto put = [qz](double* p, double x, double y) {
+                p[0] = x;
+                p[1] = y;
+                p[2] = qz;
+            };
+            const int32_t m = n - 1 - i;   // the mirrors first: a middle one keeps its own signs
+            put(hi + 3 * m, -qx, -qy);
+            put(hi + 3 * i, qx, -qy);
+            put(lo + 3 * m, -qx, qy);
+            put(lo + 3 * i, qx, qy);
         }
     }
 }
@@ -119,7 +129,10 @@ bool sampling_ok(const Geometry& geo, int* bad_axis, double* worst)
     const double pitch[3] = {geo.g.dx, geo.g.dy, geo.g.dz};
     double mx[3] = {0.0, 0.0, 0.0};
     for (int64_t p = 0; p < geo.npix; ++p)
-        for (int k = 0; k < 3; ++k) mx[k] = std::fmax(mx[k], std::fabs(geo.q[3 * p + k]));
+        for (int k = 0; k < 3; ++k) {
+            const double v = std::fabs(geo.q[3 * p + k]);
+            if (v > mx[k]) mx[k] = v;   // never for a NaN (beyond the rim)
+        }
     bool ok = true;
     double w = 0.0;
     for (int k = 0; k < 3; ++k) {

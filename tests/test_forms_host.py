@@ -85,3 +85,20 @@ def test_a_request_is_sliced_only_where_its_work_divides_by_pixel_blocks(precisi
         s.step()
     assert [b1 - b0 for _, b0, b1 in launched] == ([1013] if slices == 1 else [256, 256, 256, 245])
     plans.close()
+
+
+def test_a_plan_the_form_cannot_serve_costs_no_more():
+    # 512^3 voxels of 20 nm need more than 400 angles, which the phase's rate tells at once
+    # (finding it from the series' coefficients took 16 ms); plain BF16 never asks
+    import time
+
+    def fastest(precision):
+        best = 1.0
+        for _ in range(7):
+            t = time.perf_counter()
+            with msft.Plan(45.0, 60.0, 64, (512, 512, 512), (20.0, 20.0, 20.0), precision, device=-1) as p:
+                best = min(best, time.perf_counter() - t)
+                assert msft.msft_plan_forms(p.handle) == ("direct", "direct")
+        return best
+
+    assert fastest("fp32") < fastest("bf16") + 4e-3
