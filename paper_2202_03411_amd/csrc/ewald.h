@@ -49,7 +49,8 @@ inline int ew_rounds(int nz) { return nz > EW_WHOLE_NZ ? 0 : (nz + EW_ZC - 1) / 
 inline int ew_columns(int nz) { return nz > 2 * EW_ZC && nz <= EW_WHOLE_NZ ? 8 : EW_COLS; }
 constexpr int EW_MAX_KZ = 256;    // most modes of z: a scan wave keeps them in registers
 constexpr int EW_MAX_KM = 1024;   // most modes of the M axis
-constexpr int EW_MAX_NODES = 400; // most Chebyshev nodes: 17 doubles each within 64 KB of LDS
+constexpr int EW_MAX_NODES = 400; // most Chebyshev nodes: 17 doubles of LDS each, 54 KB (the adjoint: 79 KB)
+constexpr int EW_LDS = 160 * 1024;   // of one workgroup, at most all of a compute unit's
 
 // One plan's sizes and resident tables, as the kernels see them (device memory).
 // Modes are ordered even, then odd; counts ending in p are padded (tables hold zeros there).

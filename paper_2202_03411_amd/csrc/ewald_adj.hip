@@ -113,11 +113,13 @@ __global__ __launch_bounds__(EA_THREADS) void ew_rows_kernel(EwAdj q)
 // wave to each tile of 16 nodes a.
 // ---------------------------------------------------------------------------
 constexpr int CA_THREADS = 1024;
+constexpr int CA_RED = 3 * 4 * 4 * 64;   // rows' part, tile, its values
+static_assert((EW_MAX_NODES * 17 + CA_RED) * sizeof(double) <= EW_LDS, "one workgroup's LDS at the most nodes");
 
 __global__ __launch_bounds__(CA_THREADS) void ew_coef_adj_kernel(EwAdj q)
 {
     extern __shared__ double lds[];              // [n][17]
-    __shared__ double red[3][4][4 * 64];         // rows' part, tile
+    __shared__ double red[3][4][4 * 64];
     const EwDesc& D = *q.d;
     const int lane = threadIdx.x & 63, wave = wave_index(), li = lane & 15, lk = lane >> 4;
     const int n = D.n, nr = D.nr, rowsp = D.rowsp, np = (n + 15) & ~15;
@@ -382,10 +384,10 @@ __device__ __forceinline__ void store_slices(float* od, float* ob, int z, int nz
         }
 }
 
-// Whole columns (rows of the products: 16 columns, Re and Im apart, or 8 columns' (Re, Im)): even and odd modes on the half axis, E + O and E - O the mirror
-// slices.  A wave takes every fourth (Re or Im and every other) tile of 16 half-axis
-// slices, at most two, both against one operand; 16 modes of each parity at a time, all
-// their loads ahead of the products.
+// Whole columns: even and odd modes on the half axis, E + O and E - O the mirror slices.  The
+// products' rows are 16 columns, Re and Im apart, or 8 columns' (Re, Im).  A wave takes every
+// fourth (Re or Im and every other) tile of 16 half-axis slices, at most two, both against one
+// operand; 16 modes of each parity at a time, all their loads ahead of the products.
 template <bool MSFT, int COLS, int K>
 __global__ __launch_bounds__(EA_THREADS, K == 8 ? 3 : 4) void ew_walk_kernel(EwAdj q)
 {

@@ -92,3 +92,9 @@ def _check(env, grid, det, pitch, theta, precision, detector, forms, lam=45.0, p
 ])
 def test_forward_and_adjoint_of_different_forms(env, grid, det, pitch, theta, precision, detector, forms):
     _check(env, grid, det, pitch, theta, precision, detector, forms)
+
+
+def test_four_hundred_nodes(env):
+    # the most nodes a plan may have: the adjoint's coefficient stage takes 54 400 bytes of
+    # dynamic and 24 576 of static LDS, past 64 KiB
+    _check(env, (324, 30, 4), 100, (22.0, 22.0, 5.0), 80.0, "fp32", "flat", ("spherical", "spherical"))
