@@ -54,10 +54,12 @@ def _check(env, grid, det, pitch, theta, precision, detector, forms, lam=45.0, p
         gd, gb = torch.full_like(dt, float("nan")), torch.full_like(bt, float("nan"))
         msft.msft_backward(plan.handle, dt, bt, torch.view_as_real(A).contiguous(),
                            torch.from_numpy(g).cuda(), gd, gb, plan.workspace())
-        if plan.workspace_bytes <= msft.MSFT_NOALLOC_MAX_BYTES:
-            In = torch.full_like(I, float("nan"))
+        In = torch.full_like(I, float("nan"))
+        try:   # refused where the direct form's scratch passes the fixed one, whichever form runs
             msft.msft_simulate_noalloc(plan.handle, dt, bt, In, None)
             assert torch.equal(I, In)
+        except msft.MSFTError as e:
+            assert e.status == msft.MSFT_ERR_UNSUPPORTED and np.prod(grid) > 5e5
         if detector == "flat":
             Ib = torch.full_like(I, float("nan"))
             reqs = [(plan.handle, dt, bt, Ib, None)]
@@ -164,3 +166,113 @@ def test_uniform_column_groups_of_the_direct_form(env, n, precision):
     print(f"  intensity {err:.2e} on {int(ok.sum())} pixels", flush=True)
     assert err <= 2 * TOL[precision]
     assert np.all(I[~ok] == 0.0)
+
+
+@pytest.mark.parametrize("grid,det,pitch,theta,detector,lam", [
+    # more than 48 modes of a parity: the scan's products make a second pass
+    ((20, 21, 230), 64, (4.0, 4.0, 5.0), 80.0, "flat", 13.5),
+    # columns of more than 256 slices: rounds of 64
+    ((33, 31, 300), 40, (9.0, 9.0, 9.0), 60.0, "flat", 45.0),
+    ((12, 10, 1100), 61, (6.0, 6.0, 3.0), 60.0, "flat", 45.0),
+    ((40, 40, 500), 200, (5.0, 5.0, 5.0), 60.0, "uniform_q", 45.0),
+    # G of 32 of the 232 nodes at a time, the last part short
+    ((130, 130, 130), 512, (6.1538,) * 3, 80.0, "uniform_q", 13.5),
+])
+def test_spherical_kernels_at_their_edges(env, grid, det, pitch, theta, detector, lam):
+    _check(env, grid, det, pitch, theta, "fp32", detector, ("spherical", "spherical"), lam=lam, pixels=150)
+
+
+@pytest.mark.parametrize("detector", ["flat", "uniform_q"])
+def test_aliased_axes(env, detector):
+    # MSFT_ALLOW_ALIAS: pitches past the sampling limit on every axis take the whole basis
+    torch, msft = env
+    grid, det, pitch, lam = (30, 28, 120), 150, (40.0, 41.0, 39.0), 45.0
+    print(f"[gpu] aliased {detector} grid={grid} det={det}", flush=True)
+    d, b = _fields(grid, 11, top=0.01)
+    q = oracle.qmap(lam, 60.0, det) if detector == "flat" else oracle.qmap_uniform(lam, 60.0, det)
+    pix = np.flatnonzero(~np.isnan(q[:, 2]))[::40]
+    w = oracle.strength(oracle.MSFT, d.astype(np.float64), b.astype(np.float64), pitch, lam)
+    Ao = oracle.amplitude(q[pix], w, pitch, 1)
+    with pytest.raises(msft.MSFTError):
+        msft.Plan(lam, 60.0, det, grid, pitch, detector=detector)
+    with msft.Plan(lam, 60.0, det, grid, pitch, detector=detector, allow_alias=True) as plan:
+        assert msft.msft_plan_forms(plan.handle)[0] == "spherical"
+        _, A = plan.simulate(torch.from_numpy(d).cuda(), torch.from_numpy(b).cuda(), amplitude=True)
+        A = A.cpu().numpy().astype(np.complex128)
+    print(f"  amplitude {_rel(A[pix], Ao):.2e}", flush=True)
+    assert _rel(A[pix], Ao) <= TOL["spherical"]
+
+
+def test_batch_equals_each_request_alone(env):
+    # bit for bit, where the batch takes other variants than a request alone: two tiles of b
+    # to a workgroup (12 x 57 x 4 tiles, alone 228), four columns to a lane (9 rows' waves of
+    # 128 past 2048, alone 256), nodes in parts beside whole plans, a direct plan beside them,
+    # and a field of NaN in one request
+    torch, msft = env
+    lam = 45.0
+    with msft.Plan(lam, 60.0, 512, (128, 128, 128), (5.18,) * 3) as star, \
+         msft.Plan(13.5, 80.0, 256, (110, 60, 40), (5.4,) * 3) as wide, \
+         msft.Plan(13.5, 80.0, 90, (116, 115, 114), (5.4,) * 3) as parts, \
+         msft.Plan(lam, 60.0, 16, (8, 8, 8), (9.0,) * 3) as small:
+        assert [msft.msft_plan_forms(p.handle)[0] for p in (star, wide, parts, small)] == \
+            ["spherical"] * 3 + ["direct"]
+        gen = torch.Generator(device="cuda").manual_seed(12)
+
+        def field(p):
+            return [torch.rand(p.grid, generator=gen, device="cuda") * 0.05 for _ in range(2)]
+
+        for plans in ([star] * 12, [wide] * 9 + [parts, small, wide], [parts, star, parts]):
+            print(f"[gpu] batch of {len(plans)}: {plans[0].grid} ...", flush=True)
+            fields = [field(p) for p in plans]
+            fields[1][0][3, 2, 1] = float("nan")
+            out = [(torch.full((p.npix,), -1.0, device="cuda"), torch.full((p.npix, 2), -1.0, device="cuda"))
+                   for p in plans]
+            reqs = [(p.handle, *f, *o) for p, f, o in zip(plans, fields, out)]
+            msft.msft_simulate_batch(reqs, msft.workspace_tensor(msft.msft_batch_query(reqs), "cuda"))
+            for k, (p, f, o) in enumerate(zip(plans, fields, out)):
+                I, A = p.simulate(*f, amplitude=True)
+                if k == 1:
+                    assert bool(o[0].isnan().all()) and bool(I.isnan().all())
+                else:
+                    assert torch.equal(I, o[0]) and torch.equal(torch.view_as_real(A), o[1])
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("detector", ["flat", "uniform_q"])
+@pytest.mark.parametrize("nz", [70, 200, 500])
+def test_a_voxel_that_is_not_finite_reaches_every_pixel(env, detector, nz, value):
+    torch, msft = env
+    with msft.Plan(45.0, 60.0, 200, (40, 40, nz), (5.0, 5.0, 5.0), detector=detector) as plan:
+        assert msft.msft_plan_forms(plan.handle)[0] == "spherical"
+        rim = torch.from_numpy(np.isnan(plan.qmap()[:, 2])).cuda()
+        d = torch.rand(plan.grid, device="cuda") * 0.05
+        for k in range(2):
+            f = [d.clone(), d.clone()]
+            f[k][17, 5, nz // 2] = value
+            I = plan.simulate(*f)
+            assert not bool(I[~rim].isfinite().any())
+            assert bool((I[rim] == 0.0).all())
+
+
+def test_buffers_off_a_16_byte_boundary(env):
+    # the voxel arrays and gradients as views one float into their storage: the same bits
+    torch, msft = env
+    grid, det = (40, 33, 64), 160
+    with msft.Plan(45.0, 60.0, det, grid, (6.0,) * 3) as plan:
+        assert msft.msft_plan_forms(plan.handle) == ("spherical", "spherical")
+        V = int(np.prod(grid))
+
+        def off(t):
+            v = torch.empty(V + 1, device="cuda")[1:].view(grid)
+            v.copy_(t)
+            return v
+        d, b = torch.rand(grid, device="cuda") * 0.05, torch.rand(grid, device="cuda") * 0.05
+        g = torch.randn(plan.npix, device="cuda")
+        I, A = plan.simulate(d, b, amplitude=True)
+        Ar = torch.view_as_real(A).contiguous()
+        gd, gb = torch.empty_like(d), torch.empty_like(b)
+        msft.msft_backward(plan.handle, d, b, Ar, g, gd, gb, plan.workspace())
+        do, bo, god, gob = off(d), off(b), off(d), off(b)
+        assert torch.equal(plan.simulate(do, bo), I)
+        msft.msft_backward(plan.handle, do, bo, Ar, g, god, gob, plan.workspace())
+        assert torch.equal(god, gd) and torch.equal(gob, gb)
