@@ -58,8 +58,8 @@ typedef enum {
 } msft_status;
 
 /* Arithmetic of the sums over the voxels.  In MSFT_FP32 and MSFT_BF16X3 a detector's pattern
- * is summed in FP64 in spherical coordinates where its plan has work enough; what follows
- * then holds for q lists and small plans only. */
+ * is summed in FP64 in spherical coordinates where that is faster (msft_plan_forms); what
+ * follows then holds for the direct form only. */
 typedef enum {
     MSFT_FP32 = 0,   /* FP32 MFMA, FP32 accumulation; the complex x-sum as three real
                         products (Gauss), P1 = Tr Wr, P2 = Ti Wi, P3 = (Tr+Ti)(Wr+Wi) */
@@ -88,14 +88,14 @@ typedef enum {
  * A pixel with q_x^2 + q_y^2 >= k0^2 (a corner beyond the sphere's rim when
  * sin(theta_max) > 1/sqrt(2)) receives no propagating wave: its intensity and
  * amplitude are written as 0 and msft_plan_qmap reports its q_z as NaN.
- * Because q_x depends on i alone and q_y on j alone, msft_simulate runs the
- * separable form: H(i, y, z) = sum_x exp(-i q_x(i) x) w for every column i (one
+ * Because q_x depends on i alone and q_y on j alone, the direct form (msft_plan_forms) is
+ * separable: H(i, y, z) = sum_x exp(-i q_x(i) x) w for every column i (one
  * contraction of N x nx by nx x ny nz), then for every pixel
  * A = sum_z exp(-i q_z z) sum_y exp(-i q_y(j) y) H(i, y, z) (a contraction over y
  * with the z phase behind it): about N (nx + N) ny nz complex products instead of
  * N^2 nx ny nz.  Same pixel order p = j * N + i and the same sum as the flat form
  * for these q.  Not accepted by msft_plan_qlist or msft_simulate_batch.
- * msft_backward runs the same two contractions transposed: with h = g conj(A),
+ * Its msft_backward runs the same two contractions transposed: with h = g conj(A),
  * K(i, y, z) = sum_j exp(-i q_y(j) y) h(i, j) exp(-i q_z(i, j) z), then
  * R = sum_i exp(-i q_x(i) x) K, then the column walk of the general adjoint.
  */
@@ -125,8 +125,8 @@ typedef struct msft_plan_s* msft_plan_t;
  * host (Eq. (3) on the flat detector; bit-reproducible, no FMA contraction),
  * check sampling (pitch * max|q| <= pi per axis, the discrete form of the
  * condition dz << pi / q_z under Eq. (2)), and, for device >= 0, generate the
- * resident twiddle tables exp(-i q_x x), exp(-i q_y y), exp(-i q_z z) on that
- * device from FP64 phase arguments.  device < 0 builds a host-only plan that
+ * resident tables of its forms on that device (direct: exp(-i q_x x), exp(-i q_y y),
+ * exp(-i q_z z)) from FP64 phase arguments.  device < 0 builds a host-only plan that
  * answers the query calls but cannot simulate.  On success *out receives the
  * handle; on failure *out is NULL.  Synchronous.
  */
@@ -171,9 +171,10 @@ typedef enum {
 /*
  * The form that msft_simulate (also its stages, its noalloc variant and batches) and
  * msft_backward run for this plan.  Fixed when the plan is made: MSFT_FORM_SPHERICAL for
- * detector plans in MSFT_FP32 or MSFT_BF16X3 with work enough, at most 400 angles and at
- * most 256 and 1024 modes of its axes, unless the scratch of its forward would pass
- * MSFT_NOALLOC_MAX_BYTES where the direct form's does not (msft_simulate_noalloc runs what
+ * detector plans in MSFT_FP32 or MSFT_BF16X3 from 2e7 pixels times voxels on (uniform-q 8e8)
+ * with at most 400 angles and 256 and 1024 modes of its axes, where by the plan's sizes the
+ * direct form is not clearly faster; and the forward only if its scratch stays within
+ * MSFT_NOALLOC_MAX_BYTES or the direct form's does not (msft_simulate_noalloc runs what
  * msft_simulate runs).  Any output pointer may be NULL.
  */
 msft_status msft_plan_forms(msft_plan_t plan, int32_t* forward, int32_t* adjoint);

@@ -14,8 +14,9 @@ namespace {
 constexpr double kPi = 3.14159265358979323846;
 
 // What the truncated bases and series may leave out, relative to the norm of exp(-i q r)
-// (basis) or to 1 (series).  The sums run in FP64; 3e-11 of the strength's norm is some
-// ten times below the FP32 strength's own rounding in the darkest pixels of a pattern.
+// (basis) or to 1 (series).  All else is FP64 up to the FP32 outputs: 3e-11 is 2000 times below
+// the rounding of a pixel at the peak, and 3e-7 of one whose intensity is 1e-8 of the peak's
+// (the direct form's FP32 sums, good to 1e-7 of the peak's amplitude, leave 1e-3 there).
 constexpr double EW_TOL = 3e-11;
 
 int pad(int n, int m) { return (n + m - 1) / m * m; }
@@ -111,8 +112,9 @@ std::vector<double> tri_vector(const std::vector<double>& d, const std::vector<d
 
 // The eigenvectors of largest eigenvalue, four at a time: appends those of the eigenvalues
 // ranked out->size(), ... (0 the largest); `top` lies above them and is moved down.  An
-// eigenvalue is bracketed to 1e-11 of the scale, the gaps being 1e-5 of it or more: each of
-// the three steps of the inverse iteration then takes six digits.
+// eigenvalue is bracketed to 1e-11 of the scale, the gaps being 5.9e-7 of it or more (4095
+// voxels and a narrow band; 1e-5 up to 1024 voxels): each of the three steps of the inverse
+// iteration then takes nearly five digits.
 struct TriTop {
     const std::vector<double>&d, &e;
     std::vector<double> ds, e2;   // over the scale, as lo and top

@@ -30,7 +30,8 @@
 
 namespace msft {
 
-// Least pixels x voxels.  The form's six launches take 19 us of the host each way, the direct
+// Least pixels x voxels a plan asks for the form with (which direction then takes it: forms.cpp).
+// The form's six launches take 19 us of the host each way, the direct
 // form's two or three 6 to 9.  Flat, a pattern and a gradient: 16^3 voxels on 64^2 pixels
 // (1.7e7) 23 and 162 us against 33 and 145, 32^3 on 64^2 (1.3e8) 24 and 163 against 70 and
 // 171.  Uniform: 32^3 on 128^2 (5.4e8) 26 and 161 against 23 and 150, 64^3 on 64^2 (1.1e9) 30

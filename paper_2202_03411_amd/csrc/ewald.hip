@@ -5,7 +5,7 @@
 // The FP64 matrix instruction runs at the FP64 vector rate (78.6 TFLOP/s), one
 // 16 x 16 x 4 product in 64 cycles of a SIMD, so its operands can come from the L1 cache
 // without staging: one operand of 512 bytes a product.  At the sizes of a pattern
-// (128^3 voxels, 512^2 pixels) a whole call is some 0.3 G multiply-adds, and the five
+// (128^3 voxels, 512^2 pixels) a whole call is some 0.3 G multiply-adds, and the six
 // launches are bound by their own latency and by reading delta and beta once.
 #include <hip/hip_runtime.h>
 

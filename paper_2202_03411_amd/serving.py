@@ -2,7 +2,7 @@
 
 Requests of uneven grid and detector sizes arrive over time (the candidate
 simulations of forward fitting, Sec. 6).  The scheduler keeps one plan per
-geometry resident (q map and twiddle tables), admits queued requests while the
+geometry resident (its tables), admits queued requests while the
 in-flight HBM footprint stays under a budget and a launch slot is free, and
 runs each admitted group as one batched launch
 (``msft_simulate_batch``).  Several launches can be in flight on separate
